@@ -154,6 +154,14 @@ int conv2d_set_tile(int tile_m, int tile_n, int pos_major);
  * way. */
 int conv2d_set_order(int region_wise);
 
+/* Fourth process-wide override for tests and sweeps: how the MFMA kernels with 16-byte loaders form their fp32
+ * products - AUTO (by size), FP32 (v_mfma_f32_32x32x2_f32) or TERMS (every operand as three bf16 terms, six
+ * products on v_mfma_f32_32x32x16_bf16 summed in fp32, at least as exact; see csrc/split_bf16.h).  Ignored by
+ * the plans that have only one of them.  Operands that three bf16 terms do not hold (infinities, NaN, values
+ * that round to infinity in bf16, very small ones) are found in the sums and their blocks redone with FP32. */
+enum { MI355CONV_PRODUCTS_AUTO = -1, MI355CONV_PRODUCTS_FP32 = 0, MI355CONV_PRODUCTS_TERMS = 1 };
+int conv2d_set_products(int kind);
+
 /* Forward convolution (Sec. III Layer-1; Fig. 2 conv3D arguments):
  *   Y[n,oh,ow,oc] = sum_{fh,fw,ic} X[n, oh*sh-ph+fh, ow*sw-pw+fw, ic] * W[oc,fh,fw,ic],
  * X taken as 0 outside the image.  X, W: device, read-only.  Y: device, overwritten.

@@ -19,12 +19,13 @@ VARIANT_AUTO, VARIANT_DIRECT, VARIANT_MFMA = -1, 0, 1
 KERNEL_DIRECT, KERNEL_GATHER, KERNEL_GATHER_ELEM, KERNEL_FIRST_LAYER, KERNEL_WGRAD, KERNEL_WGRAD_FAST = range(6)
 ORDER_PLAIN, ORDER_LONGEST, ORDER_REGIONS = range(3)
 
-EXPORTS = ("conv2d_workspace_bytes", "conv2d_query_plan", "conv2d_query_workgroup", "conv2d_query_tile", "conv2d_set_tuning", "conv2d_set_tile", "conv2d_set_order", "conv2d_fwd",
+EXPORTS = ("conv2d_workspace_bytes", "conv2d_query_plan", "conv2d_query_workgroup", "conv2d_query_tile", "conv2d_set_tuning", "conv2d_set_tile", "conv2d_set_order", "conv2d_set_products", "conv2d_fwd",
            "conv2d_fwd_bias_act", "conv2d_fwd_u8",
            "conv2d_bwd_data", "deconv2d", "conv2d_bwd_weight", "conv2d_status_string",
            "conv2d_last_hip_error", "conv2d_init", "conv2d_bwd_weight_noalloc", "conv2d_noalloc_scratch_bytes",
            "conv2d_probe_mfma_rate", "matmul_workspace_bytes", "matmul_f32")
 MATMUL_NT, MATMUL_NN, MATMUL_TN = 0, 1, 2
+PRODUCTS_AUTO, PRODUCTS_FP32, PRODUCTS_TERMS = -1, 0, 1
 
 
 class ConvDesc(ctypes.Structure):
@@ -85,6 +86,8 @@ def load() -> ctypes.CDLL:
         lib.conv2d_set_tile.restype = ctypes.c_int
         lib.conv2d_set_order.argtypes = [ctypes.c_int]
         lib.conv2d_set_order.restype = ctypes.c_int
+        lib.conv2d_set_products.argtypes = [ctypes.c_int]
+        lib.conv2d_set_products.restype = ctypes.c_int
         for name in ("conv2d_fwd", "conv2d_bwd_data", "deconv2d", "conv2d_bwd_weight"):
             fn = getattr(lib, name)
             fn.argtypes = [vp, vp, vp, dp, vp, ctypes.c_size_t, vp]
@@ -171,6 +174,12 @@ def conv2d_set_order(region_wise: int = 1) -> None:
     rc = load().conv2d_set_order(region_wise)
     if rc != 0:
         raise Mi355ConvError(rc, "conv2d_set_order")
+
+
+def conv2d_set_products(kind: int = PRODUCTS_AUTO) -> None:
+    rc = load().conv2d_set_products(kind)
+    if rc != 0:
+        raise Mi355ConvError(rc, "conv2d_set_products")
 
 
 def conv2d_init() -> None:

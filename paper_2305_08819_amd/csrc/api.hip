@@ -32,8 +32,10 @@ namespace {
 std::atomic<int> g_forceVariant{MI355CONV_VARIANT_AUTO};
 std::atomic<int> g_forceSplit{0};
 std::atomic<int> g_forceBM{0}, g_forceBN{0}, g_forcePosMajor{-1};
+std::atomic<int> g_forceProducts{MI355CONV_PRODUCTS_AUTO};
 std::atomic<int> g_regionalOrder{1};   // 0: region-wise workgroup order off (conv2d_set_order)
 thread_local char t_hipError[256] = "";
+thread_local int t_products = MI355CONV_PRODUCTS_AUTO;   // override of the plan being made by this thread (see make_plan)
 
 constexpr long long kMaxElems = (1LL << 31) - 1;
 constexpr int kSmallMapPixels = 64;      // maps of at most 8x8 outputs use position-major rows
@@ -45,7 +47,8 @@ struct Plan {
     int split = 1;
     int posMajor = 0;
     int elem = 0;          // element-wise loader (channel counts the 16-byte loader cannot take)
-    int fast = 0;          // backward-weight: aligned-map kernel
+    int fast = 0;          // backward-weight: aligned map
+    int terms = 0;         // products on the bf16 matrix pipe (three-term operands) instead of fp32 MFMA
     int smallIc = 0;       // backward-data: patch-gradient GEMM + col2im kernel for very few input channels
     int grid = 0;
     int tilesM = 0, tilesN = 0;
@@ -177,50 +180,88 @@ double launch_cost(const CostParams &k, const TileCand &c, long long tiles, doub
     return t;
 }
 
-// Best slice count for one candidate; returns the cost.
+// The same for the kernels on three-term operands, with an efficiency per number of workgroups on a CU (a lone
+// one leaves every second issue slot of its SIMDs empty) and the time outside the main loop per generation.
+struct TermsTile { int bm, bn, resident; double eff[3]; };
+struct TermsCost {
+    double fixedUs;        // launch, prologue and epilogue of the first generation of workgroups
+    double wgUs;           // prologue and epilogue of every further one
+    double tail;           // drain of the last workgroups, in units of one resident set
+    double outUsPerMB;     // stores of the results (or partial results), which come in bursts
+    double reduceUs, reduceBytesPerUs;
+};
+constexpr double kCuTermsFlopPerUs = 275.0e6 / 256.0;   // fp32 FLOP in six bf16 products, with operands of random bits
+
+double terms_cost(const TermsCost &k, const TermsTile &c, long long tiles, double avgStages, double maxStages, int split,
+                  long long outElems, bool balanced = false, double exactBusiestStages = -1.0)
+{
+    const long long grid = tiles * split;
+    const int cus = 256;
+    const double unit = (2.0 * c.bm * c.bn * kBK) / kCuTermsFlopPerUs;
+    const double avg = avgStages / split, longest = maxStages / split;
+    double t;
+    if (grid <= (long long)cus * c.resident) {
+        const int perCu = (int)((grid + cus - 1) / cus);
+        double busiest = (double)perCu * avg;
+        const double withLongest = balanced && grid >= 2 * cus ? busiest + (longest - avg) * 2.0 / (double)perCu
+                                                               : longest + (double)(perCu - 1) * avg;
+        if (withLongest > busiest) busiest = withLongest;
+        if (exactBusiestStages >= 0) busiest = exactBusiestStages;
+        t = busiest * unit / c.eff[perCu < 3 ? perCu - 1 : 2];
+    } else {
+        const double generations = (double)grid / (cus * c.resident);
+        t = (generations + k.tail) * c.resident * avg * unit / c.eff[c.resident < 3 ? c.resident - 1 : 2] +
+            (generations - 1.0) * k.wgUs;
+    }
+    t += k.fixedUs + (double)outElems * split * 4e-6 * k.outUsPerMB;
+    if (split > 1) t += k.reduceUs + (split + 1.0) * (double)outElems * 4.0 / k.reduceBytesPerUs;
+    // unequal tiles end no earlier than the longest, but leave the others' power to it (A4 forward 78.3 -> 73.1 us,
+    // C3a backward-data 59.9 -> 58.5 with one tile per CU)
+    return balanced ? t * 0.985 : t;
+}
+
+// Best slice count for one candidate; returns the cost.  cost(split, stages of the busiest CU or < 0).
 // busiestFn (optional): stages of the busiest CU for a slice count under the order the launch will use, or a
 // negative value where unknown.  Where it is known for every candidate slice count, the slice count is
 // ranked with it; the cost returned - what tiles and row orders are compared by - stays the estimate.
-double best_split(const CostParams &k, const TileCand &c, long long tiles, double avgStages, double maxStages,
-                  long long outElems, int *splitOut, int minS = 1, bool balanced = false,
+template <class CostFn>
+double best_split(const CostFn &cost, double avgStages, long long outElems, int *splitOut,
                   const std::function<double(int)> *busiestFn = nullptr, int chunksPerTap = 0)
 {
     // Gather operators (chunksPerTap > 0): a slice count that divides the 32-channel chunks of a tap cuts
     // the reduction by source channels, so a slice reads a 1/split part of both operands; any other
-    // count cuts the tap-major list of stages and measured 3-8 % slower than its even neighbours.
+    // count cuts the list of stages and measured 3-8 % slower than its even neighbours.
     auto uneven = [&](int sp) { return chunksPerTap > 0 && sp > 1 && chunksPerTap % sp != 0 ? 1.04 : 1.0; };
     const int forced = g_forceSplit.load();
     int maxS = (int)(avgStages / 2.0);              // keep >= 2 stages per slice on average
     if (maxS > kMaxSplit) maxS = kMaxSplit;
     const long long wsPerSlice = pad4(outElems) * 4;
     if ((long long)maxS * wsPerSlice > (long long)kMaxWorkspace) maxS = (int)(kMaxWorkspace / wsPerSlice);
-    if (maxS < minS) maxS = minS;
+    if (maxS < 1) maxS = 1;
     if (forced > 0) {
         *splitOut = forced < maxS ? forced : maxS;
-        if (*splitOut < minS) *splitOut = minS;
-        return launch_cost(k, c, tiles, avgStages, maxStages, *splitOut, outElems, balanced);
+        return cost(*splitOut, -1.0);
     }
     double best = 1e300;
     int bestS = 1;
-    for (int sp = minS; sp <= maxS; ++sp) {
-        const double t = launch_cost(k, c, tiles, avgStages, maxStages, sp, outElems, balanced) * uneven(sp);
+    for (int sp = 1; sp <= maxS; ++sp) {
+        const double t = cost(sp, -1.0) * uneven(sp);
         if (t < best) { best = t; bestS = sp; }
     }
     if (busiestFn) {   // second opinion on the slice count from the dealing itself
-        constexpr double kWgUs = 0.7;
         double bestExact = 1e300;
         int exactS = 0;
         bool pickKnown = false;
-        for (int sp = minS; sp <= maxS; ++sp) {
+        for (int sp = 1; sp <= maxS; ++sp) {
             const double stages = (*busiestFn)(sp);
             if (stages < 0) continue;   // not resident at once, or another order: no opinion
             if (sp == bestS) pickKnown = true;
-            const double t = launch_cost(k, c, tiles, avgStages, maxStages, sp, outElems, balanced, stages, kWgUs) * uneven(sp);
+            const double t = cost(sp, stages) * uneven(sp);
             if (t < bestExact) { bestExact = t; exactS = sp; }
         }
         if (exactS && pickKnown) {
             bestS = exactS;
-            best = launch_cost(k, c, tiles, avgStages, maxStages, bestS, outElems, balanced) * uneven(bestS);
+            best = cost(bestS, -1.0) * uneven(bestS);
         }
     }
     *splitOut = bestS;
@@ -244,6 +285,24 @@ bool tile_compiled(int bm, int bn, bool gather)
 const TileCand kGatherTiles[] = {{128, 128, 0.88, 2}, {128, 64, 0.93, 2}, {64, 64, 0.945, 4}, {128, 32, 0.80, 3}};
 const TileCand kWgradTiles[] = {{128, 128, 0.80, 1}, {64, 128, 0.93, 2}, {128, 64, 0.94, 2}, {64, 64, 0.98, 4},
                                 {32, 128, 0.90, 3}};
+
+// Fitted, like the constants above, to tile x slices x row order sweeps of 49 layers with either family of products
+// (6 476 timings): the picks are 2.1 % slower than the
+// fastest plan of the sweep on average.  The fp32 MFMA kernels stay because they start and end faster: up to
+// about eight stages per workgroup they win (matrix product 256 x 256 x 32 4.2 against 5.2 us, R7s forward
+// 8.6 / 9.6), beyond that they take 0.50 us a stage against 0.47 (64 x 64 tile, one per CU) and 1.9 against 0.9 (128 x 128).
+// kFp32GatherUs ties the two models' scales together: us = factor * model + offset.
+constexpr TermsCost kGatherTermsCost = {7.33, 1.53, 0.45, 0.134, 2.19, 8.7e6};
+constexpr double kFp32GatherUs[2] = {1.023, 1.85};
+const TermsTile kGatherTermsTiles[] = {{128, 128, 1, {0.872, 0.872, 0.872}}, {128, 64, 2, {0.587, 0.760, 0.760}},
+                                       {64, 64, 3, {0.614, 0.630, 0.669}}, {128, 32, 2, {0.404, 0.380, 0.380}}};
+// Whether a family of products may serve the call under the override.
+bool products_allowed(bool terms)
+{
+    const int f = t_products;
+    return f == MI355CONV_PRODUCTS_AUTO || (f == MI355CONV_PRODUCTS_TERMS) == terms;
+}
+constexpr double kWgUs = 0.7;   // of the exact ranking of slice counts, fp32 MFMA kernels (see launch_cost)
 
 bool forced_tile(int *bm, int *bn, bool gather)
 {
@@ -304,7 +363,8 @@ void plan_elem_tiles(Plan &pl, long long rows, int cols, double stages)
         c.eff *= 0.5;   // 4-byte loads, single LDS buffer
         const long long tiles = (long long)ceil_div(rows, c.bm) * ceil_div(cols, c.bn);
         int sp = 1;
-        const double t = best_split(kGatherCost, c, tiles, stages, stages, pl.outElems, &sp);
+        const double t = best_split([&](int n, double) { return launch_cost(kGatherCost, c, tiles, stages, stages, n, pl.outElems); },
+                                    stages, pl.outElems, &sp);
         if (t < best) {
             best = t;
             pl.bm = c.bm;
@@ -323,6 +383,27 @@ int taps_in_range(int o, int stride, int pad, int f, int in)
     int c = 0;
     for (int t = 0; t < f; ++t) c += (unsigned)(o * stride - pad + t) < (unsigned)in;
     return c;
+}
+
+// Every compiled gather tile of both families of products with its cost function
+// (tiles, average and longest stages, slices, output elements, balanced, stages of the busiest CU or < 0).
+typedef std::function<double(long long, double, double, int, long long, bool, double)> GatherCostFn;
+template <class Visit>
+void for_each_gather_tile(const Visit &visit)
+{
+    if (products_allowed(false))
+        for (const TileCand &c : kGatherTiles)
+            visit(c.bm, c.bn, false,
+                  GatherCostFn([&c](long long tiles, double a, double m, int sp, long long out, bool balanced, double exact) {
+                      return kFp32GatherUs[1] +
+                             kFp32GatherUs[0] * launch_cost(kGatherCost, c, tiles, a, m, sp, out, balanced, exact, exact >= 0 ? kWgUs : 0.0);
+                  }));
+    if (products_allowed(true))
+        for (const TermsTile &c : kGatherTermsTiles)
+            visit(c.bm, c.bn, true,
+                  GatherCostFn([&c](long long tiles, double a, double m, int sp, long long out, bool balanced, double exact) {
+                      return terms_cost(kGatherTermsCost, c, tiles, a, m, sp, out, balanced, exact);
+                  }));
 }
 
 Plan plan_fwd(const Shape &s)
@@ -375,38 +456,46 @@ Plan plan_fwd(const Shape &s)
     int fbm = 0, fbn = 0;
     const bool haveForced = forced_tile(&fbm, &fbn, true);
     double best = 1e300;
-    for (const TileCand &c0 : kGatherTiles) {
-        TileCand c = c0;
+    for_each_gather_tile([&](int bm, int bn, bool terms, const GatherCostFn &cost) {
         if (haveForced) {
-            if (c.bm != fbm || c.bn != fbn) continue;
+            if (bm != fbm || bn != fbn) return;
         } else {
             // no column tile wider than needed, and the narrow tile only for narrow outputs
-            if (c.bn > 32 && c.bn / 2 >= s.OC) continue;
+            if (bn > 32 && bn / 2 >= s.OC) return;
             // the narrow tile: narrow outputs, or a channel count whose last 64-wide tile would be at most half used
-            if (c.bn == 32 && s.OC > 32 && !(s.OC % 64 != 0 && s.OC % 64 <= 32)) continue;
+            if (bn == 32 && s.OC > 32 && !(s.OC % 64 != 0 && s.OC % 64 <= 32)) return;
         }
-        const long long tiles = (long long)ceil_div(M, c.bm) * ceil_div(s.OC, c.bn);
+        const long long tiles = (long long)ceil_div(M, bm) * ceil_div(s.OC, bn);
         for (int order = 0; order < 2; ++order) {
-            if (resolve_order(order, s.N % c.bm == 0) != order) continue;
+            if (resolve_order(order, s.N % bm == 0) != order) continue;
             if (order && !padded && g_forcePosMajor.load() != 1) continue;
             const double avgStages = (order ? avgTapsPos : s.FH * s.FW) * chunksPerTap;
             const double maxStages = (order ? maxTapsPos : s.FH * s.FW) * chunksPerTap;
             int sp = 1;
             const bool balanced = order && s.OH * s.OW <= kMaxBalancedPositions;
             const std::function<double(int)> busiest = [&](int split) {
-                return order ? regional_busiest_stages(s, false, c.bm, c.bn, split, chunksPerTap) : -1.0;
+                return order ? regional_busiest_stages(s, false, bm, bn, split, chunksPerTap) : -1.0;
             };
-            const double t = best_split(kGatherCost, c, tiles, avgStages, maxStages, pl.outElems, &sp, 1, balanced,
-                                        order ? &busiest : nullptr, chunksPerTap);
+            // Maps of 17 to 64 positions, 129 to 256 channels, forward: about four workgroups a CU, which is what the
+            // longest-first dealing needs to even out nine-, six- and four-tap tiles.  (8x8x256 -> 256: 62.9 us with four
+            // 128 x 64 tiles per CU; one 128 x 128 tile per CU takes 54.6, but as long as its longest tile.)
+            const bool wantsFour = terms && padded && s.N % bm == 0 && s.OH * s.OW > 16 && s.OH * s.OW <= kSmallMapPixels &&
+                                   chunksPerTap > 4 && chunksPerTap <= 8;
+            auto of = [&](int n, double exact) {
+                return cost(tiles, avgStages, maxStages, n, pl.outElems, balanced, exact) *
+                       (wantsFour && tiles * n > 128 && tiles * n < 1024 ? 1.25 : 1.0);
+            };
+            const double t = best_split(of, avgStages, pl.outElems, &sp, order ? &busiest : nullptr, chunksPerTap);
             if (t < best) {
                 best = t;
-                pl.bm = c.bm;
-                pl.bn = c.bn;
+                pl.bm = bm;
+                pl.bn = bn;
+                pl.terms = terms;
                 pl.posMajor = order;
                 pl.split = sp;
             }
         }
-    }
+    });
     pl.tilesN = ceil_div(s.OC, pl.bn);
     pl.tilesM = ceil_div(M, pl.bm);
     set_forward_phase(pl, s);
@@ -502,7 +591,8 @@ Plan plan_bwd_data(const Shape &s)
         pl.tilesM = build_phases(s, pl.bm, pl, &avgTaps, &maxTaps);
         int sp = 1;
         TileCand c = {pl.bm, pl.bn, 0.35, 2};
-        best_split(kGatherCost, c, (long long)pl.tilesM * pl.tilesN, stages, stages, pl.outElems, &sp);
+        best_split([&](int n, double) { return launch_cost(kGatherCost, c, (long long)pl.tilesM * pl.tilesN, stages, stages, n, pl.outElems); },
+                   stages, pl.outElems, &sp);
         finish_plan(pl, sp);
         return pl;
     }
@@ -527,45 +617,46 @@ Plan plan_bwd_data(const Shape &s)
     int fbm = 0, fbn = 0;
     const bool haveForced = forced_tile(&fbm, &fbn, true);
     double best = 1e300;
-    for (const TileCand &c0 : kGatherTiles) {
-        TileCand c = c0;
+    const Plan base = pl;
+    for_each_gather_tile([&](int bm, int bn, bool terms, const GatherCostFn &cost) {
         if (s.IC % 4 != 0) {   // 4-byte filter loads exist for the narrow tile only
-            if (c.bn != 32) continue;
+            if (bn != 32) return;
         } else if (haveForced) {
-            if (c.bm != fbm || c.bn != fbn) continue;
+            if (bm != fbm || bn != fbn) return;
         } else {
-            if (c.bn > 32 && c.bn / 2 >= s.IC) continue;
-            if (c.bn == 32 && s.IC > 32 && !(s.IC % 64 != 0 && s.IC % 64 <= 32)) continue;
+            if (bn > 32 && bn / 2 >= s.IC) return;
+            if (bn == 32 && s.IC > 32 && !(s.IC % 64 != 0 && s.IC % 64 <= 32)) return;
         }
-        Plan trial = pl;
+        Plan trial = base;
         double avgTaps = 0;
         int maxTaps = 0;
-        const int tilesM = build_phases(s, c.bm, trial, &avgTaps, &maxTaps);
-        const long long tiles = (long long)tilesM * ceil_div(s.IC, c.bn);
+        const int tilesM = build_phases(s, bm, trial, &avgTaps, &maxTaps);
+        const long long tiles = (long long)tilesM * ceil_div(s.IC, bn);
         for (int order = 0; order < 2; ++order) {
-            if (resolve_order(order, s.N % c.bm == 0) != order) continue;
+            if (resolve_order(order, s.N % bm == 0) != order) continue;
             if (order && !padded && g_forcePosMajor.load() != 1) continue;
-            const double a = order && unitStride ? avgTapsPos : avgTaps;
-            const double m = order && unitStride ? (double)maxTapsPos : (double)maxTaps;
+            const double a = (order && unitStride ? avgTapsPos : avgTaps) * chunksPerTap;
+            const double m = (order && unitStride ? (double)maxTapsPos : (double)maxTaps) * chunksPerTap;
             int sp = 1;
             const bool balanced = order && unitStride && s.IH * s.IW <= kMaxBalancedPositions;
             const std::function<double(int)> busiest = [&](int split) {
-                return regional_busiest_stages(s, true, c.bm, c.bn, split, chunksPerTap);
+                return regional_busiest_stages(s, true, bm, bn, split, chunksPerTap);
             };
-            const double t = best_split(kGatherCost, c, tiles, a * chunksPerTap, m * chunksPerTap, pl.outElems, &sp, 1,
-                                        balanced, order && unitStride ? &busiest : nullptr, chunksPerTap);
+            const double t = best_split([&](int n, double exact) { return cost(tiles, a, m, n, base.outElems, balanced, exact); },
+                                        a, base.outElems, &sp, order && unitStride ? &busiest : nullptr, chunksPerTap);
             if (t < best) {
                 best = t;
-                trial.bm = c.bm;
-                trial.bn = c.bn;
+                trial.bm = bm;
+                trial.bn = bn;
+                trial.terms = terms;
                 trial.posMajor = order;
                 trial.split = sp;
                 trial.tilesM = tilesM;
-                trial.tilesN = ceil_div(s.IC, c.bn);
+                trial.tilesN = ceil_div(s.IC, bn);
                 pl = trial;
             }
         }
-    }
+    });
     finish_plan(pl, pl.split);
     return pl;
 }
@@ -626,27 +717,32 @@ Plan plan_bwd_weight(const Shape &s)
     const bool haveForced = forced_tile(&fbm, &fbn, false);
     double best = 1e300;
     for (int pass = 0; pass < 2 && pl.bm == 0; ++pass) {   // second pass: the forced tile does not apply here
-        for (const TileCand &c : kWgradTiles) {
-            if (pl.elem && c.bn != 64) continue;   // element-wise X loader is compiled for 64-wide tiles
-            // one block row (fast kernel only): narrow outputs, or a channel count whose last 64-row tile
+        auto consider = [&](int bm, int bn, bool terms, const std::function<double(long long, int)> &cost) {
+            if (pl.elem && bn != 64) return;   // element-wise X loader is compiled for 64-wide tiles
+            // one block row (aligned maps only): narrow outputs, or a channel count whose last 64-row tile
             // would be at most half used
-            if (c.bm == 32 && (!pl.fast || (s.OC > 32 && !(s.OC % 64 != 0 && s.OC % 64 <= 32)))) continue;
+            if (bm == 32 && (!pl.fast || (s.OC > 32 && !(s.OC % 64 != 0 && s.OC % 64 <= 32)))) return;
             if (pass == 0 && haveForced && !(pl.elem && fbn != 64)) {
-                if (c.bm != fbm || c.bn != fbn) continue;
+                if (bm != fbm || bn != fbn) return;
             } else {
-                if (c.bm > 64 && c.bm / 2 >= s.OC) continue;
-                if (c.bn > 64 && c.bn / 2 >= Ktot && c.bm != 32) continue;
+                if (bm > 64 && bm / 2 >= s.OC) return;
+                if (bn > 64 && bn / 2 >= Ktot && bm != 32) return;
             }
-            const long long tiles = (long long)ceil_div(s.OC, c.bm) * ceil_div(Ktot, c.bn);
+            const long long tiles = (long long)ceil_div(s.OC, bm) * ceil_div(Ktot, bn);
             int sp = 1;
-            const double t = best_split(kWgradCost, c, tiles, chunks * live, (double)chunks, pl.outElems, &sp);
+            const double t = best_split([&](int n, double) { return cost(tiles, n); }, chunks * live, pl.outElems, &sp);
             if (t < best) {
                 best = t;
-                pl.bm = c.bm;
-                pl.bn = c.bn;
+                pl.bm = bm;
+                pl.bn = bn;
+                pl.terms = terms;
                 pl.split = sp;
             }
-        }
+        };
+        for (const TileCand &c : kWgradTiles)
+                consider(c.bm, c.bn, false, [&](long long tiles, int n) {
+                    return launch_cost(kWgradCost, c, tiles, chunks * live, (double)chunks, n, pl.outElems);
+                });
     }
     pl.posMajor = posMajor;
     pl.tilesM = ceil_div(s.OC, pl.bm);
@@ -690,6 +786,7 @@ int prepare_device(int *devOut)
     e = prepare_gather_gemm();
     if (e == hipSuccess) e = prepare_wgrad();
     if (e == hipSuccess) e = prepare_wgrad_fast();
+    if (e == hipSuccess) e = prepare_gather_terms();
     void *ptr = nullptr;
     if (e == hipSuccess) e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
     if (e != hipSuccess) return hip_fail(e);
@@ -1157,14 +1254,14 @@ bool plan_launchable(int op, const Shape &s, const Plan &pl)
 // that the enqueue path does not repeat the search (and the longest-first dealing, which takes
 // a good fraction of a millisecond) on every call.
 struct PlanKey {
-    int v[18];
+    int v[19];
     bool operator==(const PlanKey &o) const { return memcmp(v, o.v, sizeof v) == 0; }
 };
 struct PlanKeyHash {
     size_t operator()(const PlanKey &k) const
     {
         unsigned h = 2166136261u;
-        for (int i = 0; i < 18; ++i) h = (h ^ (unsigned)k.v[i]) * 16777619u;
+        for (int i = 0; i < 19; ++i) h = (h ^ (unsigned)k.v[i]) * 16777619u;
         return h;
     }
 };
@@ -1172,14 +1269,16 @@ constexpr size_t kMaxCachedPlans = 4096;   // the map is emptied when it grows p
 std::mutex g_planMutex;
 std::unordered_map<PlanKey, Plan, PlanKeyHash> *g_planMap = nullptr;   // allocated on first use, never freed
 
-int make_plan(int op, const Shape &s, Plan *pl)
+// products: which family may serve the call (default: the process-wide override).
+int make_plan(int op, const Shape &s, Plan *pl, int products = g_forceProducts.load())
 {
     if (op != MI355CONV_OP_FWD && op != MI355CONV_OP_BWD_DATA && op != MI355CONV_OP_BWD_WEIGHT)
         return MI355CONV_ERR_UNSUPPORTED;
     PlanKey k;
-    const int vals[18] = {op, s.N, s.IH, s.IW, s.IC, s.OC, s.FH, s.FW, s.sh, s.sw, s.ph, s.pw,
+    const int vals[19] = {op, s.N, s.IH, s.IW, s.IC, s.OC, s.FH, s.FW, s.sh, s.sw, s.ph, s.pw,
                           g_forceVariant.load(), g_forceSplit.load(), g_forceBM.load(), g_forceBN.load(),
-                          g_forcePosMajor.load(), g_regionalOrder.load()};
+                          g_forcePosMajor.load(), g_regionalOrder.load(), products};
+    t_products = products;
     memcpy(k.v, vals, sizeof vals);
     {
         std::lock_guard<std::mutex> lock(g_planMutex);
@@ -1343,7 +1442,8 @@ int run_gather(const float *A, const float *B, float *out, const Shape &s, const
     g.bias = epi.bias;
     g.slope = epi.slope;
     hipError_t e = pl.elem ? launch_gather_elem(g, bwd, pl.bm, pl.bn, pl.grid, st)
-                           : launch_gather_gemm(g, bwd, pl.bm, pl.bn, pl.grid, st);
+                   : pl.terms ? launch_gather_terms(g, bwd, pl.bm, pl.bn, pl.grid, st)
+                              : launch_gather_gemm(g, bwd, pl.bm, pl.bn, pl.grid, st);
     if (e != hipSuccess) return hip_fail(e);
     if (pl.split > 1) {
         e = launch_slice_reduce(static_cast<const float *>(ws), out, pl.outElems, pl.split, pl.sliceStride, st,
@@ -1497,6 +1597,12 @@ int conv2d_set_tile(int tile_m, int tile_n, int pos_major)
 }
 
 
+int conv2d_set_products(int kind)
+{
+    if (kind < MI355CONV_PRODUCTS_AUTO || kind > MI355CONV_PRODUCTS_TERMS) return MI355CONV_ERR_UNSUPPORTED;
+    g_forceProducts.store(kind);
+    return MI355CONV_OK;
+}
 
 int conv2d_set_order(int region_wise)
 {

@@ -550,6 +550,7 @@ inline bool patch_small_ic_accepts(int IC, int FH, int FW) { return FH * FW * IC
 hipError_t prepare_gather_gemm();
 hipError_t prepare_wgrad();
 hipError_t prepare_wgrad_fast();
+hipError_t prepare_gather_terms();
 
 hipError_t launch_direct_fwd(const float *X, const float *W, float *Y, const Shape &s, hipStream_t st);
 hipError_t launch_direct_bwd_data(const float *G, const float *W, float *dX, const Shape &s, hipStream_t st);
@@ -567,6 +568,8 @@ hipError_t launch_bias_act(float *out, long long count, const float *bias, float
 // bm/bn select the compiled tile; returns hipErrorInvalidValue for an unknown pair.
 hipError_t launch_gather_gemm(const GatherGemmParams &p, bool bwdData, int bm, int bn, int grid,
                               hipStream_t st);
+// same tiles and shapes, products on the bf16 matrix pipe (three-term operands)
+hipError_t launch_gather_terms(const GatherGemmParams &p, bool bwdData, int bm, int bn, int grid, hipStream_t st);
 // same tiles (except 128x128), element-wise loader: any channel counts
 hipError_t launch_gather_elem(const GatherGemmParams &p, bool bwdData, int bm, int bn, int grid, hipStream_t st);
 hipError_t launch_wgrad(const WgradParams &p, int bm, int bn, bool xElem, int grid, hipStream_t st);

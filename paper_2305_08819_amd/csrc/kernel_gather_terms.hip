@@ -1,0 +1,636 @@
+// Implicit-GEMM ("gather-GEMM") kernel for forward convolution and backward-data on
+// v_mfma_f32_32x32x16_bf16 with three-term operands (split_bf16.h), written for gfx950 (wave64).
+//
+// GEMM view (never materialised): rows = pixels of the tensor being produced, columns =
+// its channels, reduction = (filter tap, source channel).  A workgroup owns a BM x BN
+// output tile and walks the reduction in stages of kBK = 32 source channels of one tap:
+//   global (NHWC fp32, 16-byte loads along the channel axis) -> registers -> three bf16 terms -> LDS
+//   -> MFMA fragments.
+// Every operand element is split once per workgroup, on its way to LDS (5.5 vector instructions each).
+//
+// Two things make it a small-feature-map operator (paper Sec. IV: special conv\deconv
+// operators that cut the work more the smaller the map is):
+//  * every tile first ORs, over its rows, the set of filter taps that fall inside the
+//    source image, and only walks that set.  With rows ordered (y, x, n) a tile sits on one
+//    pixel position, so at 2x2/4x4/8x8 maps with a padded 3x3 filter only 44/69/84 % of the
+//    taps are ever multiplied;
+//  * backward-data is split into sh*sw stride phases; a tile belongs to one phase and its
+//    tap set holds only the taps congruent to that phase, so no inserted zero is multiplied
+//    and pixels no tap reaches are written as 0 by tiles with an empty tap set.
+//
+// Waves: the tile is cut into wave tiles of up to 64 x 64, and the two 16-channel halves of every
+// stage go to the two waves of a pair, which add their accumulators through LDS at the end.  The pair
+// is there for LDS bandwidth: a fragment set of 64 + 64 rows x 16 channels x 3 terms (12 KB) feeds 24
+// MFMAs (768 cycles of a SIMD); with four waves on 32 x 32 blocks the same tile would read 1.5 times as
+// many LDS bytes per MFMA as the LDS delivers.  And a sliced launch gets its second wave per SIMD without
+// a second set of partial results in memory.
+//
+// MFMA operand layout (AMD CDNA4 ISA, v_mfma_f32_32x32x16_bf16): lane l holds A[i = l%32][k = 8*(l/32) ..
+// +7] and B[k = 8*(l/32) .. +7][j = l%32]; accumulator register r of lane l is
+// D[i = 8*(r/4) + 4*(l/32) + r%4][j = l%32].  The order of reduction elements is free as long as A and
+// B agree.
+#include <hip/hip_runtime.h>
+#include "split_bf16.h"
+
+namespace mi355conv {
+
+namespace {
+// FINE (64 x 64 tile only): eight waves of one 32 x 32 block each instead of four of 32 x 64.
+template <int BM, int BN, bool BWD, bool FINE = false>
+struct SG {
+    static constexpr int WM = 2, WN = BN == 128 || FINE ? 2 : 1;   // wave tiles along rows and columns
+    static constexpr int WAVES = WM * WN * 2, THREADS = WAVES * 64; // two waves per wave tile (halves of a stage)
+    static constexpr int WTM = BM / WM, WTN = BN / WN;
+    static constexpr int MB = WTM / 32, NB = WTN / 32, NBLK = MB * NB, NOWN = NBLK > 1 ? NBLK / 2 : 1;
+    static constexpr int A_RPP = THREADS / 8, PA = BM / A_RPP;     // A loader: 8 threads per row of 32 channels
+    // forward: B tile is [BN cols][kBK] like A; backward-data: [kBK][BN], turned by the LDS reads
+    static constexpr int B_TPR = BWD ? BN / 4 : 8;
+    static constexpr int B_RPP = THREADS / B_TPR, B_ROWS = BWD ? kBK : BN, PB = B_ROWS / B_RPP;
+    static constexpr bool DIRECT = PA + PB > 4;   // split elements go straight to LDS: no registers to hold them for a stage
+    static constexpr int A_PLANE = BM * kBK * 2, B_PLANE = BN * kBK * 2;   // bytes of one term's tile
+    static constexpr int STAGE = 3 * (A_PLANE + B_PLANE);
+    static constexpr int TABLE_INTS = 4 * BM + 4;
+    static constexpr size_t SMEM = 2 * STAGE + TABLE_INTS * sizeof(int);
+    static_assert(B_ROWS % B_RPP == 0 && BM % A_RPP == 0, "loader passes");
+    static_assert(NBLK % 2 == 0 || NBLK == 1, "the two waves of a pair finish half of the blocks each, or one finishes the only block");
+    static_assert(!FINE || (BM == 64 && BN == 64), "a variant of the 64 x 64 tile");
+    static_assert(WAVES * NOWN * 32 * kLDT * 4 <= 2 * STAGE, "exchange buffers fit over the stages");
+};
+}  // namespace
+
+// Epilogue of one 32x32 block, as gather_tile_store has it for a whole wave tile: v in MFMA layout, rows rowInTile .. +31 of the tile, columns colBase .. +31.
+template <class P>
+__device__ __forceinline__ void gather_block_store(const P &p, float *C, bool epi, float slope, int colBase, const int *outRow,
+                                                   int rowInTile, const float16v &v, int l32, int lh, float *scratch)
+{
+    typedef int i4 __attribute__((ext_vector_type(4)));
+    const int lane = lh * 32 + l32;
+    if (scratch && (p.DC & 3) == 0 && colBase + 32 <= p.DC) {   // uniform
+        if (epi) {   // uniform: the plain operator pays no vector arithmetic here
+            const float b = p.bias ? p.bias[colBase + l32] : 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                float x = v[r] + b;
+                x = x > 0.f ? x : x * slope;
+                scratch[(8 * (r / 4) + 4 * lh + (r % 4)) * kLDT + l32] = x;
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) scratch[(8 * (r / 4) + 4 * lh + (r % 4)) * kLDT + l32] = v[r];
+        }
+        // the LDS pipeline keeps a wave's accesses in order; no other wave touches this buffer
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int row = q * 8 + (lane >> 3), seg = lane & 7;
+            const f4 x = *reinterpret_cast<const f4 *>(scratch + row * kLDT + seg * 4);
+            const int o = outRow[rowInTile + row];
+            if (o >= 0) *reinterpret_cast<f4 *>(C + o * p.DC + colBase + seg * 4) = x;
+        }
+    } else {
+        i4 orow[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) orow[g] = *reinterpret_cast<const i4 *>(outRow + rowInTile + 8 * g + 4 * lh);
+        const int col = colBase + l32;
+        if (col < p.DC) {
+            const float b = epi && p.bias ? p.bias[col] : 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int o = orow[r / 4][r % 4];
+                float x = v[r] + b;
+                x = x > 0.f ? x : x * slope;
+                if (o >= 0) C[o * p.DC + col] = x;
+            }
+        }
+    }
+}
+
+// The fp32 form of a tile, for operands that three bf16 terms do not hold: v_mfma_f32_32x32x2_f32 on
+// fragments read straight from memory.  A wave redoes the blocks it finishes, on
+// its own.  Reached only through split_suspect, so it is kept small, not fast (a whole tile takes about three times
+// as long as the main loop).
+template <class T, bool BWD, class P>
+__device__ __forceinline__ void gather_redo_fp32(const P &p, const GatherTile &tile, __amdgpu_buffer_rsrc_t rsrcA,
+                                                           __amdgpu_buffer_rsrc_t rsrcB, const int *rowBase, const int *rowY,
+                                                           const int *rowX, int wm, int wn, int kh, int lane,
+                                                           int it0, int it1, float16v (&own)[T::NOWN])
+{
+    constexpr int kOutOfRange = (int)0x80000000;
+    const int l32 = lane & 31, lh = lane >> 5;
+    const int vCnt = tile.vHi - tile.vLo + 1, taps = (tile.uHi - tile.uLo + 1) * vCnt;
+    const int wRowStride = p.FH * p.FW * (BWD ? p.DC : p.SC);
+#pragma unroll
+    for (int o = 0; o < T::NOWN; ++o)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) own[o][r] = 0.f;
+    for (int it = it0; it < it1; ++it) {
+        const int chunk = it / taps, tapIdx = it - chunk * taps;
+        const int tapU = tile.uLo + tapIdx / vCnt, tapV = tile.vLo + tapIdx % vCnt;
+        const int dy = BWD ? -tapU : tapU, dx = BWD ? -tapV : tapV;
+        const int t = BWD ? (tile.ra + p.sh * tapU) * p.FW + tile.rb + p.sw * tapV : tapU * p.FW + tapV;
+        for (int g = 0; g < kBK / 8; ++g) {
+            const int k = chunk * kBK + g * 8 + lh * 4;   // this lane's four source channels
+            f4 a[T::NOWN], b[T::NOWN];
+#pragma unroll
+            for (int o = 0; o < T::NOWN; ++o) {
+                const int i = T::NBLK == 1 ? 0 : T::NB == 2 ? o : kh, j = T::NB == 2 ? kh : 0;
+                const int row = wm * T::WTM + i * 32 + l32, col = tile.n0 + wn * T::WTN + j * 32 + l32;
+                const bool ok = k < p.SC && (unsigned)(rowY[row] + dy) < (unsigned)p.SH && (unsigned)(rowX[row] + dx) < (unsigned)p.SW;
+                const int offA = ok ? (rowBase[row] + (dy * p.SW + dx) * p.SC + k) * 4 : kOutOfRange;
+                a[o] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcA, offA, 0, 0));
+                const bool okB = k < p.SC && col < p.DC;
+                if (BWD) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        b[o][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                      rsrcB, okB ? ((k + e) * wRowStride + t * p.DC + col) * 4 : kOutOfRange, 0, 0));
+                } else {
+                    b[o] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
+                               rsrcB, okB ? (col * wRowStride + t * p.SC + k) * 4 : kOutOfRange, 0, 0));
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int o = 0; o < T::NOWN; ++o)
+                    own[o] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[o][e], b[o][e], own[o], 0, 0, 0);
+        }
+    }
+}
+
+// BELEM (backward-data only): the destination channel count is not a multiple of 4, so a
+// 16-byte load of four filter columns would be misaligned; the B tile is fetched with four
+// 4-byte loads per thread instead (e.g. the first layer's dX with 3 channels).
+// RAGGED: the source channel count is a multiple of 4 but not of 32, so the last 32-channel
+// stage of every tap is partly empty; its surplus 16-byte loads get an out-of-range offset
+// (one select per load and stage, which the aligned instantiation does not pay).
+template <int BM, int BN, bool BWD, bool BELEM = false, bool RAGGED = false, bool FINE = false>
+__global__ __launch_bounds__((SG<BM, BN, BWD, FINE>::THREADS), (FINE ? 4 : 2)) void gather_terms_kernel(const GatherGemmParams params)
+{
+    BalancePrefetch pre = balance_prefetch(params.runs, params.posOrder);   // in flight with the scalar arguments
+    balance_prefetch_classes(pre, params.classes);
+    const GatherView p = gather_view(params);
+    using T = SG<BM, BN, BWD, FINE>;
+    extern __shared__ f4 smem_raw[];
+    char *smem = reinterpret_cast<char *>(smem_raw);
+    int *rowBase = reinterpret_cast<int *>(smem + 2 * T::STAGE);
+    int *rowY = rowBase + BM;
+    int *rowX = rowY + BM;
+    int *outRow = rowX + BM;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+
+    const GatherTile tile = gather_tile_setup<BM, BN, BWD>(p, pre, rowBase, rowY, rowX, outRow);
+    const int slice = tile.slice, n0 = tile.n0;
+
+    // taps walked by this tile: the rectangle [uLo,uHi] x [vLo,vHi]
+    const int uCnt = tile.uHi >= tile.uLo ? tile.uHi - tile.uLo + 1 : 0;
+    const int vCnt = tile.vHi >= tile.vLo ? tile.vHi - tile.vLo + 1 : 0;
+    const int chunksPerTap = RAGGED ? (p.SC + kBK - 1) / kBK : p.SC / kBK;
+    const int lastValid = p.SC - (chunksPerTap - 1) * kBK;   // source channels in a tap's last stage
+    // The stages are walked channel chunk by channel chunk, all taps of a chunk in turn: a chunk of the
+    // gathered tensor is fetched from memory once and read from L2 for its other taps, so the traffic is
+    // spread over the whole launch.  A slice is a part [it0, it1) of that list; where the slice count divides the
+    // chunks, slices differ in source channels.
+    const int taps = uCnt * vCnt;
+    const int nIter = taps * chunksPerTap;
+    const int it0 = (int)fast_div((unsigned)(slice * nIter), p.divSplit);          // nIter * split is far below 2^31
+    const int it1 = (int)fast_div((unsigned)((slice + 1) * nIter), p.divSplit);
+
+    // ---- per-thread loader state --------------------------------------------------------
+    // Operands are fetched with raw buffer loads: address = base + VGPR byte offset + SGPR byte
+    // offset, and an offset past the tensor's size returns zeros.  The VGPR offsets change only
+    // when the tap changes (rows whose source pixel is padding get an out-of-range offset);
+    // the position inside the tap is the SGPR offset, so a steady-state stage computes no address.
+    const __amdgpu_buffer_rsrc_t rsrcA =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.A), 0, (int)p.aBytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrcB =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.B), 0, (int)p.bBytes, 0x00020000);
+    constexpr int kOutOfRange = (int)0x80000000;   // tensors are below 2^31 bytes
+    const int aSeg = tid & 7, aRow = tid >> 3;
+    int rBase[T::PA], rY[T::PA], rX[T::PA];
+#pragma unroll
+    for (int i = 0; i < T::PA; ++i) {
+        const int r = aRow + T::A_RPP * i;
+        rBase[i] = (rowBase[r] + aSeg * 4) * 4;   // bytes; may be negative before the tap offset is added
+        rY[i] = rowY[r];
+        rX[i] = rowX[r];
+    }
+    const int bSeg = tid % T::B_TPR, bRow = tid / T::B_TPR;
+    const int wRowStride = p.FH * p.FW * (BWD ? p.DC : p.SC);  // floats per oc in W
+    static_assert(!BELEM || BWD, "element-wise B loads exist for backward-data only");
+    int bOff[T::PB];   // fixed for the whole kernel
+    int bOffE[BELEM ? T::PB : 1][4];
+#pragma unroll
+    for (int i = 0; i < T::PB; ++i) {
+        const int r = bRow + T::B_RPP * i;
+        if (BWD) bOff[i] = n0 + bSeg * 4 < p.DC ? (r * wRowStride + n0 + bSeg * 4) * 4 : kOutOfRange;
+        else bOff[i] = n0 + r < p.DC ? ((n0 + r) * wRowStride + bSeg * 4) * 4 : kOutOfRange;
+        if (BELEM) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int col = n0 + bSeg * 4 + e;
+                bOffE[i][e] = col < p.DC ? (r * wRowStride + col) * 4 : kOutOfRange;
+            }
+        }
+    }
+
+    // ragged last stage: which of this thread's loads fall inside it
+    const bool aLastOk = aSeg * 4 < lastValid;
+    bool bLastOk[T::PB];
+#pragma unroll
+    for (int i = 0; i < T::PB; ++i) bLastOk[i] = BWD ? bRow + T::B_RPP * i < lastValid : bSeg * 4 < lastValid;
+
+    // reduction cursor: channel chunk and tap (u,v)
+    int chunk = 0, tapU = tile.uLo, tapV = tile.vLo;
+    if (it0 > 0 && it0 < it1) {
+        chunk = it0 / taps;
+        const int tapIdx = it0 - chunk * taps, du = tapIdx / vCnt;
+        tapU += du;
+        tapV += tapIdx - du * vCnt;
+    }
+    int tapOffB = 0;      // floats, uniform
+    int aOff[T::PA];      // byte offsets of this thread's A rows for the current tap
+
+    auto set_tap = [&]() __attribute__((always_inline)) {
+        int t, dy, dx;
+        if (BWD) {
+            dy = -tapU;
+            dx = -tapV;
+            t = (tile.ra + p.sh * tapU) * p.FW + tile.rb + p.sw * tapV;
+            tapOffB = t * p.DC;
+        } else {
+            dy = tapU;
+            dx = tapV;
+            t = tapU * p.FW + tapV;
+            tapOffB = t * p.SC;
+        }
+        const int tapBytesA = (dy * p.SW + dx) * p.SC * 4;
+        if (p.posMajor) {
+            // (y,x,n) rows: the tile sits on one pixel position (the batch is a multiple of the row tile),
+            // so its tap rectangle holds exactly the taps inside the image - no row needs a test
+#pragma unroll
+            for (int i = 0; i < T::PA; ++i) aOff[i] = rBase[i] + tapBytesA;
+        } else {
+#pragma unroll
+            for (int i = 0; i < T::PA; ++i) {
+                const bool ok = (unsigned)(rY[i] + dy) < (unsigned)p.SH && (unsigned)(rX[i] + dx) < (unsigned)p.SW;
+                aOff[i] = ok ? rBase[i] + tapBytesA : kOutOfRange;
+            }
+        }
+    };
+
+    // item q of a stage: q < PA is A-tile pass q, otherwise B-tile pass q - PA
+    constexpr int kItems = T::PA + T::PB;
+    constexpr int kStoresPerMfma = (3 * kItems + 2 * T::NBLK - 1) / (2 * T::NBLK);
+    constexpr int kReadsPerMfma = (T::MB + (BWD ? 2 : 1) * T::NB + T::NBLK - 1) / T::NBLK;
+    f4 raw[kItems];   // the loads in flight: a register is split, then loaded anew
+    auto gload_item = [&](int q, f4 *raw) __attribute__((always_inline)) {
+        const int c0 = chunk * kBK;
+        const bool lastChunk = RAGGED && chunk == chunksPerTap - 1;   // uniform
+        if (q < T::PA) {
+            const int voff = (lastChunk && !aLastOk) ? kOutOfRange : aOff[q];
+            raw[q] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcA, voff, c0 * 4, 0));
+        } else {
+            const int i = q - T::PA;
+            const int soff = BWD ? (c0 * wRowStride + tapOffB) * 4 : (tapOffB + c0) * 4;
+            const bool drop = lastChunk && !bLastOk[i];
+            if (BELEM) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    raw[q][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                              rsrcB, drop ? kOutOfRange : bOffE[i][e], soff, 0));
+            } else {
+                raw[q] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcB, drop ? kOutOfRange : bOff[i],
+                                                                                     soff, 0));
+            }
+        }
+    };
+    int left = it1 - it0;   // stages not loaded yet
+    auto advance = [&]() __attribute__((always_inline)) {
+        if (++tapV > tile.vHi) {
+            tapV = tile.vLo;
+            if (++tapU > tile.uHi) {
+                tapU = tile.uLo;
+                ++chunk;
+            }
+        }
+        set_tap();
+        if (--left <= 0) {   // nothing left: the loads that still follow read zeros
+#pragma unroll
+            for (int i = 0; i < T::PA; ++i) aOff[i] = kOutOfRange;
+#pragma unroll
+            for (int i = 0; i < T::PB; ++i) {
+                bOff[i] = kOutOfRange;
+                if (BELEM) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) bOffE[i][e] = kOutOfRange;
+                }
+            }
+        }
+    };
+
+    // ---- LDS tiles --------------------------------------------------------------------------
+    // [row][32 k] tiles (A, forward B): 64-byte rows of four 16-byte pieces; piece c of row r sits at
+    // place c ^ (r/4 % 4), which keeps both the 8-byte stores and the 16-byte fragment reads (16 rows at a
+    // time) off each other's banks.  [k][BN] tiles (backward-data B): the 64-byte pieces of a row are
+    // exchanged by k likewise, so that the four rows of a transposing read lie on different banks.
+    constexpr auto kSwz = [](int r) { return BN == 128 ? (r & 3) : BN == 64 ? ((r >> 1) & 1) : 0; };
+    int aStore = aRow * 64 + (((aSeg >> 1) ^ ((aRow >> 2) & 3)) << 4) + (aSeg & 1) * 8;
+    int bStore = 3 * T::A_PLANE + (BWD ? bRow * (BN * 2) + (((bSeg >> 3) ^ kSwz(bRow)) << 6) + (bSeg & 7) * 8
+                                       : bRow * 64 + (((bSeg >> 1) ^ ((bRow >> 2) & 3)) << 4) + (bSeg & 1) * 8);
+    static_assert(T::A_RPP % 16 == 0 && T::B_RPP % 16 == 0, "the exchange of pieces is the same in every loader pass");
+    SplitQuad pk[kItems];   // the next stage's elements, split, on their way to LDS
+    auto split_item = [&](int q, const f4 *raw) __attribute__((always_inline)) {
+        pk[q] = split_quad(raw[q]);
+        // the compiler would otherwise move the arithmetic down to the stores, a stage later, in one lump
+        asm volatile("" : "+v"(pk[q].h), "+v"(pk[q].m), "+v"(pk[q].l));
+    };
+    auto lds_store_item = [&](int q) __attribute__((always_inline)) {
+        char *d;
+        int plane;
+        if (q < T::PA) {
+            d = smem + aStore + q * T::A_RPP * 64;
+            plane = T::A_PLANE;
+        } else {
+            d = smem + bStore + (q - T::PA) * T::B_RPP * (BWD ? BN * 2 : 64);
+            plane = T::B_PLANE;
+        }
+        *reinterpret_cast<u2 *>(d) = pk[q].h;
+        *reinterpret_cast<u2 *>(d + plane) = pk[q].m;
+        *reinterpret_cast<u2 *>(d + 2 * plane) = pk[q].l;
+    };
+
+    float16v acc[T::NBLK], low[T::NBLK];   // sums of the h*h products and of the five smaller ones (see split_bf16.h)
+#pragma unroll
+    for (int b = 0; b < T::NBLK; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[b][r] = low[b][r] = 0.f;
+
+    const int kh = wave & 1, wm = (wave >> 1) / T::WN, wn = (wave >> 1) % T::WN;
+    const int l32 = lane & 31, lh = lane >> 5;
+
+    bf8 fa[3][T::MB], fb[3][T::NB];
+    int aFrag = (wm * T::WTM + l32) * 64 + (((kh * 2 + lh) ^ ((l32 >> 2) & 3)) << 4);
+    int bFrag[T::NB];
+#pragma unroll
+    for (int j = 0; j < T::NB; ++j) {
+        if (BWD) {
+            const int k = kh * 16 + lh * 8 + ((lane & 15) >> 2);
+            bFrag[j] = 3 * T::A_PLANE + k * (BN * 2) + (((wn * T::NB + j) ^ kSwz(k)) << 6) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+        } else {
+            bFrag[j] = 3 * T::A_PLANE + (wn * T::WTN + j * 32 + l32) * 64 + (((kh * 2 + lh) ^ ((l32 >> 2) & 3)) << 4);
+        }
+    }
+    auto read_a = [&](int plane) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < T::MB; ++i)
+            fa[plane][i] = *reinterpret_cast<const bf8 *>(smem + aFrag + plane * T::A_PLANE + i * 2048);
+    };
+    auto read_b = [&](int plane) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < T::NB; ++j) {
+            const char *s = smem + bFrag[j] + plane * T::B_PLANE;
+            if (BWD) fb[plane][j] = join_quads(lds_read_tr(s), lds_read_tr(s + 4 * BN * 2));
+            else fb[plane][j] = *reinterpret_cast<const bf8 *>(s);
+        }
+    };
+
+    int sBuf = T::STAGE, rBuf = T::STAGE;   // distance to the other buffer
+    auto flip_stores = [&]() __attribute__((always_inline)) {
+        aStore += sBuf;
+        bStore += sBuf;
+        sBuf = -sBuf;
+    };
+    auto flip_reads = [&]() __attribute__((always_inline)) {
+        aFrag += rBuf;
+#pragma unroll
+        for (int j = 0; j < T::NB; ++j) bFrag[j] += rBuf;
+        rBuf = -rBuf;
+    };
+
+    // One stage: its six products, one group of NBLK MFMAs each, and beside them, spread so that the
+    // matrix pipe always has the next MFMA queued,
+    //   groups 0, 1  the LDS stores of the next stage (split a stage ago) into the other buffer,
+    //   2 to 5       the split of the stage after that, whose loads were issued a stage ago, and the loads
+    //                of the one after into the same registers,
+    //   3 to 5       behind the stage's one barrier, the next stage's fragment reads, each plane into the
+    //                registers whose last product has been issued.
+    // DIRECT: groups 0 to 3 split and store the next stage (loaded a stage ago) and load the one after; the
+    // barrier comes behind them.
+    constexpr int kBarrier = T::DIRECT ? 4 : 3;   // every plane of both operands has been used by the first three groups
+    auto multiply = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < T::MB; ++i)
+#pragma unroll
+            for (int j = 0; j < T::NB; ++j) {
+                float16v &sum = g == kSplitProducts - 1 ? acc[i * T::NB + j] : low[i * T::NB + j];
+                sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kProdA[g]][i], fb[kProdB[g]][j], sum, 0, 0, 0);
+            }
+    };
+    auto stage = [&]() __attribute__((always_inline)) {
+        constexpr int kSplitFrom = T::DIRECT ? 0 : 2;
+#pragma unroll
+        for (int g = 0; g < kSplitProducts; ++g) {
+            if constexpr (!T::DIRECT) {
+#pragma unroll
+                for (int q = 0; q < kItems; ++q)
+                    if (q * 2 / kItems == g) lds_store_item(q);
+            }
+            if (g == kBarrier) {
+                __syncthreads();
+                flip_reads();
+                read_a(2);
+                read_b(2);
+            }
+            if (g == 4) read_a(1);
+            if (g == 5) read_b(1);
+#pragma unroll
+            for (int q = 0; q < kItems; ++q)   // a register is loaded anew the group after it was split
+                if (kSplitFrom + 1 + q * 4 / kItems == g) gload_item(q, raw);
+#pragma unroll
+            for (int q = 0; q < kItems; ++q)
+                if (kSplitFrom + q * 4 / kItems == g) {
+                    split_item(q, raw);
+                    if (T::DIRECT) lds_store_item(q);
+                }
+            multiply(g);
+#pragma unroll
+            for (int b = 0; b < T::NBLK; ++b) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                          // one MFMA, then
+                if (T::DIRECT ? g < kBarrier : g <= 1)
+                    __builtin_amdgcn_sched_group_barrier(0x200, T::DIRECT ? 1 : kStoresPerMfma, 0);   // LDS stores
+                if (g >= kBarrier) __builtin_amdgcn_sched_group_barrier(0x100, kReadsPerMfma, 0);     // LDS reads
+                if (T::DIRECT ? g < kBarrier : g >= 2)
+                    __builtin_amdgcn_sched_group_barrier(0x002, T::DIRECT ? 9 : 6, 0);                // vector instructions
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int q = 0; q < kItems; ++q)
+            if (kSplitFrom + 1 + q * 4 / kItems == kSplitProducts) gload_item(q, raw);
+        read_b(0);
+        read_a(0);
+        flip_stores();
+        advance();
+    };
+
+    // ---- main loop ----------------------------------------------------------------------
+    // Stage t lies in LDS buffer t & 1.  Loads and splits run past the last stage (out of range: zeros, no
+    // memory traffic).
+    if (it0 < it1) {
+        const int n = it1 - it0;
+        auto load_all = [&](f4 *r) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < kItems; ++q) gload_item(q, r);
+            advance();
+        };
+        auto split_all = [&](const f4 *r) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < kItems; ++q) split_item(q, r);
+        };
+        f4 raw0[kItems], raw1[kItems];   // the first stages are in flight together
+        set_tap();
+        load_all(raw0);
+        if (!T::DIRECT) load_all(raw1);
+        load_all(raw);
+        split_all(raw0);
+#pragma unroll
+        for (int q = 0; q < kItems; ++q) lds_store_item(q);
+        flip_stores();
+        if (!T::DIRECT) split_all(raw1);
+        __syncthreads();
+#pragma unroll
+        for (int pl = 2; pl >= 0; --pl) {
+            read_a(pl);
+            read_b(pl);
+        }
+        for (int t = 1; t < n; ++t) stage();
+        // the last stage: nothing left to store or to read
+#pragma unroll
+        for (int g = 0; g < kSplitProducts; ++g) {
+            if (g == kBarrier) __syncthreads();   // every wave has used its last fragments: the buffers are free
+            multiply(g);
+        }
+    }
+
+#pragma unroll
+    for (int b = 0; b < T::NBLK; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[b][r] += low[b][r];
+
+    // ---- the pair's halves meet: each wave finishes every second block --------------------------------
+    float *mine = reinterpret_cast<float *>(smem) + wave * T::NOWN * 32 * kLDT;
+    float *theirs = reinterpret_cast<float *>(smem) + (wave ^ 1) * T::NOWN * 32 * kLDT;
+    float16v own[T::NOWN];
+    const bool finishes = T::NBLK > 1 || kh == 0;   // uniform
+#pragma unroll
+    for (int o = 0; o < T::NOWN; ++o)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int at = (o * 32 + 8 * (r / 4) + 4 * lh + r % 4) * kLDT + l32;
+            if constexpr (T::NBLK > 1) {
+                const float e = acc[2 * o][r], d = acc[2 * o + 1][r];
+                own[o][r] = kh ? d : e;
+                mine[at] = kh ? e : d;
+            } else {
+                own[o][r] = acc[o][r];
+                if (kh) mine[at] = acc[o][r];
+            }
+        }
+    __syncthreads();
+    bool bad = false;
+    if (finishes) {
+#pragma unroll
+        for (int o = 0; o < T::NOWN; ++o)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                own[o][r] += theirs[(o * 32 + 8 * (r / 4) + 4 * lh + r % 4) * kLDT + l32];
+                bad = bad || split_suspect(own[o][r]);
+            }
+    }
+    if (!finishes) return;   // no barrier follows
+    if (__any(bad)) gather_redo_fp32<T, BWD>(p, tile, rsrcA, rsrcB, rowBase, rowY, rowX, wm, wn, kh, lane, it0, it1, own);
+
+    float *C = p.C + (long long)slice * p.sliceStride;
+    const bool epi = p.epilogue && p.split == 1;   // sliced launches leave it to the combine pass
+    const float slope = epi ? p.slope : 1.f;
+#pragma unroll
+    for (int o = 0; o < T::NOWN; ++o) {
+        const int i = T::NBLK == 1 ? 0 : T::NB == 2 ? o : kh, j = T::NB == 2 ? kh : 0;
+        // turned in the partner's exchange buffer, which only this wave reads
+        gather_block_store(p, C, epi, slope, n0 + wn * T::WTN + j * 32, outRow, wm * T::WTM + i * 32, own[o], l32, lh,
+                           theirs + o * 32 * kLDT);
+    }
+}
+
+template <int BM, int BN, bool BWD, bool BELEM = false, bool RAGGED = false, bool FINE = false>
+static hipError_t launch_one(const GatherGemmParams &p, int grid, hipStream_t st)
+{
+    using T = SG<BM, BN, BWD, FINE>;
+    hipLaunchKernelGGL((gather_terms_kernel<BM, BN, BWD, BELEM, RAGGED, FINE>), dim3((unsigned)grid), dim3(T::THREADS), T::SMEM, st, p);
+    return hipGetLastError();
+}
+
+// Instantiations whose tiles need more LDS than a kernel gets by default (64 KB): the limit is
+// raised once per device, outside any stream capture (see prepare_device in the host API).
+template <int BM, int BN, bool BWD, bool RAGGED>
+static hipError_t raise_lds_limit()
+{
+    constexpr size_t bytes = SG<BM, BN, BWD>::SMEM;
+    if (bytes <= 64 * 1024) return hipSuccess;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(gather_terms_kernel<BM, BN, BWD, false, RAGGED>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
+hipError_t prepare_gather_terms()
+{
+    hipError_t e = hipSuccess;
+#define MI355_GG_PREP(BM_, BN_)                                                    \
+    if (e == hipSuccess) e = raise_lds_limit<BM_, BN_, false, false>();            \
+    if (e == hipSuccess) e = raise_lds_limit<BM_, BN_, false, true>();             \
+    if (e == hipSuccess) e = raise_lds_limit<BM_, BN_, true, false>();             \
+    if (e == hipSuccess) e = raise_lds_limit<BM_, BN_, true, true>();
+    MI355_GG_PREP(128, 128)
+    MI355_GG_PREP(128, 64)
+    MI355_GG_PREP(64, 64)
+    MI355_GG_PREP(128, 32)
+#undef MI355_GG_PREP
+    static_assert(SG<128, 32, true>::SMEM <= 64 * 1024, "the 4-byte filter loader's tile fits the default limit");
+    return e;
+}
+
+hipError_t launch_gather_terms(const GatherGemmParams &p, bool bwdData, int bm, int bn, int grid,
+                              hipStream_t st)
+{
+    if (!gather_gemm_accepts(p.SC, p.DC, bwdData, bm, bn)) return hipErrorInvalidValue;
+    if (bwdData && p.DC % 4 != 0) {   // filter columns by 4-byte loads: on the narrow tile only
+        if (bm == 128 && bn == 32) return launch_one<128, 32, true, true, true>(p, grid, st);
+        return hipErrorInvalidValue;
+    }
+    const bool ragged = p.SC % kBK != 0;
+#define MI355_GG_CASE(BM_, BN_)                                                                 \
+    if (bm == BM_ && bn == BN_) {                                                               \
+        if (ragged)                                                                             \
+            return bwdData ? launch_one<BM_, BN_, true, false, true>(p, grid, st)               \
+                           : launch_one<BM_, BN_, false, false, true>(p, grid, st);             \
+        return bwdData ? launch_one<BM_, BN_, true>(p, grid, st)                                \
+                       : launch_one<BM_, BN_, false>(p, grid, st);                              \
+    }
+    MI355_GG_CASE(128, 128)
+    MI355_GG_CASE(128, 64)
+    if (bm == 64 && bn == 64 && grid <= 512) {
+        if (ragged)
+            return bwdData ? launch_one<64, 64, true, false, true, true>(p, grid, st)
+                           : launch_one<64, 64, false, false, true, true>(p, grid, st);
+        return bwdData ? launch_one<64, 64, true, false, false, true>(p, grid, st)
+                       : launch_one<64, 64, false, false, false, true>(p, grid, st);
+    }
+    MI355_GG_CASE(64, 64)
+    MI355_GG_CASE(128, 32)
+#undef MI355_GG_CASE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace mi355conv

@@ -1,0 +1,84 @@
+// fp32 products on the bf16 matrix pipe: every fp32 operand is held as three bf16 terms,
+// x = h + m + l (each term the remainder of the one before, rounded to nearest: 3 x 8 significant
+// bits, so the sum is exact for |x| between 2^-110 and the bf16 maximum), and a product is the six
+// term products of weight 2^-16 and above, summed in the fp32 accumulator of v_mfma_f32_32x32x16_bf16
+// (the three-term decomposition of Henry, Tang and Heinecke, "Leveraging the bfloat16 artificial
+// intelligence datatype for higher-precision computations", 2019).  What is left out (m*l, l*m, l*l)
+// is below 2^-25 of the product.  The h*h products and the five smaller ones are summed in accumulators of their
+// own: the MFMA cuts its sums towards minus infinity below the accumulator's last places, and small products on
+// a large accumulator would meet that five times in six (a bias that grows with the number of products).  Measured
+// against 64-bit sums of N(0,1) products, 2-norm, two accumulators / one / a chain of fp32 MFMA: K = 64 0.50 / 1.10 /
+// 1.45e-7, 576 1.4 / 3.7 / 4.3e-7, 4608 4.2 / 10.7 / 12.1e-7.
+//
+// Why: register-only loops sustain 2000 TFLOP/s in bf16, 333 TFLOP/s of fp32 products at six each,
+// against 155 TFLOP/s of v_mfma_f32_32x32x2_f32; and up to six vector instructions per bf16 MFMA run
+// beside it (2008 -> 1931 TFLOP/s), where every one beside an fp32 MFMA takes matrix time.
+#pragma once
+#include "gather_common.h"
+
+namespace mi355conv {
+
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));     // one operand fragment: 8 reduction elements
+typedef unsigned u2 __attribute__((ext_vector_type(2)));
+
+struct SplitQuad {   // four fp32 values as bf16 terms, two values per 32-bit word
+    u2 h, m, l;
+};
+
+__device__ __forceinline__ unsigned pack_bf16(float a, float b)   // round to nearest even
+{
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    const f2 v = {a, b};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, b2));
+}
+__device__ __forceinline__ float bf16_low(unsigned w) { return __builtin_bit_cast(float, w << 16); }
+__device__ __forceinline__ float bf16_high(unsigned w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
+
+// 5.5 vector instructions per value.  (v_dot2_f32_bf16 with (-1, 0) forms x - h in one instruction instead of
+// two, 3.5 per value, but runs against the MFMAs: a stage of a lone 64 x 64 tile 0.61 -> 0.68 us.)
+__device__ __forceinline__ SplitQuad split_quad(const f4 &x)
+{
+    SplitQuad s;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const float a = x[2 * i], b = x[2 * i + 1];
+        const unsigned h = pack_bf16(a, b);
+        const float ra = a - bf16_low(h), rb = b - bf16_high(h);   // exact
+        const unsigned m = pack_bf16(ra, rb);
+        s.h[i] = h;
+        s.m[i] = m;
+        s.l[i] = pack_bf16(ra - bf16_low(m), rb - bf16_high(m));
+    }
+    return s;
+}
+
+// Products of a stage, smallest first; plane 0 = h, 1 = m, 2 = l.  Every plane of both operands is
+// used by the first four, so a wave that has issued those holds all its fragments in registers.
+constexpr int kSplitProducts = 6;
+constexpr int kProdA[kSplitProducts] = {1, 2, 0, 1, 0, 0};
+constexpr int kProdB[kSplitProducts] = {1, 0, 2, 0, 1, 0};
+
+// Where the three terms do not stand for the fp32 value - infinities, NaN, values that round to
+// infinity in bf16, operands so small that their lower terms fall below the smallest bf16 - the
+// accumulator shows it: it is not finite, or it is not zero and below 2^-80 (an operand below 2^-110
+// gives that unless the other one is above 2^30).  The kernels then redo the tile with fp32 MFMA.
+__device__ __forceinline__ bool split_suspect(float v)
+{
+    const unsigned u = __builtin_bit_cast(unsigned, v) & 0x7fffffffu;
+    return u >= 0x7f800000u || u - 1u < 0x17800000u - 1u;   // u = 0 wraps to the largest value
+}
+
+// 4 consecutive reduction elements of 16 neighbouring columns, transposed on the way out of LDS:
+// lanes 4k .. 4k+3 of a group of 16 address row k (four columns each), lane j receives column j.
+typedef short s4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ s4v lds_read_tr(const char *p)
+{
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4v *)(p));
+}
+__device__ __forceinline__ bf8 join_quads(s4v a, s4v b)
+{
+    return __builtin_bit_cast(bf8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+}  // namespace mi355conv

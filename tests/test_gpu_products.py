@@ -1,0 +1,140 @@
+"""The kernels that form fp32 products on the bf16 matrix pipe (three bf16 terms per operand) and the fp32
+MFMA kernels next to each other: every compiled tile of both, forced, against the oracle; their errors against
+64-bit sums; and operands that three bf16 terms do not hold."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2305_08819_amd as mc
+import workloads as wl
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+PRODUCTS = [mc.PRODUCTS_FP32, mc.PRODUCTS_TERMS]
+
+
+@pytest.fixture(autouse=True)
+def _restore():
+    yield
+    mc.conv2d_set_products(mc.PRODUCTS_AUTO)
+    mc.conv2d_set_tuning(mc.VARIANT_AUTO, 0)
+    mc.conv2d_set_tile(0, 0, -1)
+
+
+def inputs(d, seed):
+    k = wl.stream_key("products", seed)
+    X = wl.normal01(k, (d.N, d.IH, d.IW, d.IC))
+    W = wl.normal01(k + 1, (d.OC, d.FH, d.FW, d.IC), scale=float(np.sqrt(2.0 / (d.FH * d.FW * d.IC))))
+    G = wl.normal01(k + 2, (d.N, d.OH, d.OW, d.OC))
+    return X, W, G
+
+
+# (N, IH, IW, IC, OC, FH, FW, stride, pad): one stage, two, three and many; ragged rows, columns and channels;
+# (y,x,n) rows; stride phases with and without taps; more than 512 workgroups of the 64 x 64 tile
+GATHER_SHAPES = [
+    (3, 5, 7, 32, 40, 1, 1, 1, 0), (2, 9, 9, 64, 64, 1, 1, 1, 0), (1, 12, 11, 96, 132, 1, 1, 1, 0),
+    (128, 4, 4, 64, 160, 3, 3, 1, 1), (128, 3, 5, 48, 72, 3, 3, 1, 1), (128, 6, 6, 32, 64, 3, 3, 2, 1),
+    (5, 9, 7, 36, 96, 3, 3, 1, 1), (4, 9, 9, 64, 32, 1, 1, 2, 0), (2, 11, 6, 20, 28, 5, 3, (2, 1), (2, 0)),
+    (128, 16, 16, 32, 64, 1, 1, 1, 0),
+]
+
+
+@pytest.mark.parametrize("products", PRODUCTS, ids=["fp32", "terms"])
+@pytest.mark.parametrize("split", [1, 3])
+@pytest.mark.parametrize("tile", [(128, 128), (128, 64), (64, 64), (128, 32)], ids=lambda t: "%dx%d" % t)
+@pytest.mark.parametrize("shp", GATHER_SHAPES)
+def test_gather_tiles(shp, tile, split, products):
+    d = mc.make_desc(*shp)
+    print("products", shp, tile, split, products, flush=True)
+    mc.conv2d_set_products(products)
+    mc.conv2d_set_tuning(mc.VARIANT_MFMA, split)
+    mc.conv2d_set_tile(tile[0], tile[1], -1)
+    gu.check_all_ops(d, *inputs(d, hash(shp) & 0xffff), ops=("fwd", "bwd_data"), label=str(shp), twice=True)
+
+
+@pytest.mark.parametrize("products", PRODUCTS, ids=["fp32", "terms"])
+@pytest.mark.parametrize("channels", [1, 3, 5, 31])
+def test_bwd_data_channels_by_4_byte_loads(channels, products):
+    d = mc.make_desc(3, 7, 9, channels, 40, 3, 3, 2, 1)
+    print("4-byte filter loads", channels, products, flush=True)
+    mc.conv2d_set_products(products)
+    gu.check_all_ops(d, *inputs(d, channels), ops=("bwd_data",), label=str(channels))
+
+
+@pytest.mark.parametrize("shp", [(64, 8, 8, 32, 64, 1, 1, 1, 0), (64, 8, 8, 64, 64, 3, 3, 1, 1), (64, 8, 8, 256, 128, 3, 3, 1, 1),
+                                 (4, 32, 32, 64, 64, 3, 3, 1, 1)])     # 128 stages of rows: the longest slice the planner makes
+def test_terms_are_no_less_exact_than_fp32_products(shp):
+    """Relative 2-norm error against 64-bit sums, same plan otherwise: 3 % are allowed for the choice of the
+    inputs (an error is an average over at least 2048 sums, so it scatters by 1 / sqrt(2 * 2048) = 1.6 %)."""
+    d = mc.make_desc(*shp)
+    t = inputs(d, 7)
+    err = {}
+    for products in PRODUCTS:
+        mc.conv2d_set_products(products)
+        mc.conv2d_set_tuning(mc.VARIANT_MFMA, 1)
+        mc.conv2d_set_tile(64, 64, -1)
+        for op, (rel, _) in gu.check_all_ops(d, *t, label=str(shp)).items():
+            err[op, products] = rel
+    print(shp, {k: "%.2e" % v for k, v in err.items()}, flush=True)
+    for op in ("fwd", "bwd_data", "bwd_weight"):
+        assert err[op, mc.PRODUCTS_TERMS] <= 1.03 * err[op, mc.PRODUCTS_FP32], (op, err)
+
+
+def run(op, d, a, b):
+    shape = {"fwd": (d.N, d.OH, d.OW, d.OC), "bwd_data": (d.N, d.IH, d.IW, d.IC), "bwd_weight": (d.OC, d.FH, d.FW, d.IC)}[op]
+    out = torch.full(shape, float("nan"), device="cuda")
+    fn = {"fwd": mc.conv2d_fwd, "bwd_data": mc.conv2d_bwd_data, "bwd_weight": mc.conv2d_bwd_weight}[op]
+    fn(torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda(), out, d)
+    torch.cuda.synchronize()
+    return out.cpu().numpy()
+
+
+SPECIAL_SHAPES = [(64, 6, 6, 32, 64, 3, 3, 1, 1), (3, 7, 5, 36, 40, 3, 3, 2, 1), (2, 4, 64, 16, 32, 3, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("op", ["fwd", "bwd_data", "bwd_weight"])
+@pytest.mark.parametrize("shp", SPECIAL_SHAPES)
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3.4028e38, -3.3999e38])
+def test_operands_beyond_bf16_give_what_fp32_products_give(shp, op, value):
+    """One such element in each operand.  Which sums are infinite, NaN or finite does not depend on the order
+    of summation here (a sum holds at most one infinite or huge product of either operand)."""
+    d = mc.make_desc(*shp)
+    X, W, G = inputs(d, 3)
+    a, b = gu.operands(op, X, W, G)
+    a.reshape(-1)[a.size // 3] = value
+    b.reshape(-1)[b.size // 2] = value if abs(value) == float("inf") else 1.0
+    got = {}
+    for products in PRODUCTS:
+        mc.conv2d_set_products(products)
+        mc.conv2d_set_tuning(mc.VARIANT_MFMA, 1)
+        mc.conv2d_set_tile(64, 64, 0)      # one row order: in (n,y,x) rows padding is multiplied as 0, in (y,x,n) rows skipped
+        got[products] = run(op, d, a, b)
+    f, t = got[mc.PRODUCTS_FP32], got[mc.PRODUCTS_TERMS]
+    assert np.array_equal(np.isnan(f), np.isnan(t)) and np.array_equal(np.isposinf(f), np.isposinf(t))
+    assert np.array_equal(np.isneginf(f), np.isneginf(t))
+    ok = np.isfinite(f)
+    # sums of at most 10 000 products either way: 1e-5 of the row of magnitudes that went in
+    scale = np.maximum(np.abs(f[ok].astype(np.float64)), 1.0)
+    assert (np.abs(f[ok].astype(np.float64) - t[ok].astype(np.float64)) <= 1e-4 * scale).all()
+
+
+@pytest.mark.parametrize("op", ["fwd", "bwd_data", "bwd_weight"])
+@pytest.mark.parametrize("shp", SPECIAL_SHAPES)
+@pytest.mark.parametrize("scales", [(1e-36, 1.0), (1e-30, 1.0), (1.0, 1e-38), (1e-20, 1e-18), (1e-25, 1e20), (1e18, 1e18)])
+def test_very_small_and_large_operands(shp, op, scales):
+    """Whole tensors far from 1: results keep fp32's relative precision (2-norm 1e-5, the bar of the parity
+    tests) wherever fp32 holds them; results in fp32's subnormal range are only as fine as it is."""
+    d = mc.make_desc(*shp)
+    X, W, G = inputs(d, 5)
+    a, b = gu.operands(op, X, W, G)
+    a, b = (a * np.float32(scales[0])).astype(np.float32), (b * np.float32(scales[1])).astype(np.float32)
+    ref = gu.run_oracle(op, d, a, b)
+    for products in PRODUCTS:
+        mc.conv2d_set_products(products)
+        mc.conv2d_set_tuning(mc.VARIANT_MFMA, 1)
+        mc.conv2d_set_tile(64, 64, -1)
+        got = run(op, d, a, b).astype(np.float64)
+        err = np.linalg.norm((got - ref).ravel())
+        floor = 2.0 ** -149 * 64 * np.sqrt(ref.size)      # a rounding to subnormal spacing per product of a short chain
+        assert err <= 1e-5 * np.linalg.norm(ref.ravel()) + floor, (products, err, np.linalg.norm(ref.ravel()))
