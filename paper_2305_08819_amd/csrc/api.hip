@@ -287,15 +287,20 @@ const TileCand kWgradTiles[] = {{128, 128, 0.80, 1}, {64, 128, 0.93, 2}, {128, 6
                                 {32, 128, 0.90, 3}};
 
 // Fitted, like the constants above, to tile x slices x row order sweeps of 49 layers with either family of products
-// (6 476 timings): the picks are 2.1 % slower than the
+// (6 476 forward / backward-data and 5 394 backward-weight timings): the picks are 2.1 % / 1.8 % slower than the
 // fastest plan of the sweep on average.  The fp32 MFMA kernels stay because they start and end faster: up to
 // about eight stages per workgroup they win (matrix product 256 x 256 x 32 4.2 against 5.2 us, R7s forward
 // 8.6 / 9.6), beyond that they take 0.50 us a stage against 0.47 (64 x 64 tile, one per CU) and 1.9 against 0.9 (128 x 128).
-// kFp32GatherUs ties the two models' scales together: us = factor * model + offset.
+// kFp32GatherUs, kFp32WgradUs tie the two models' scales together: us = factor * model + offset.
 constexpr TermsCost kGatherTermsCost = {7.33, 1.53, 0.45, 0.134, 2.19, 8.7e6};
-constexpr double kFp32GatherUs[2] = {1.023, 1.85};
+constexpr TermsCost kWgradTermsCost = {11.9, 2.88, 0.384, 0.019, 1.5, 4.3e6};
+constexpr double kFp32GatherUs[2] = {1.023, 1.85}, kFp32WgradUs[2] = {0.906, -0.86};
 const TermsTile kGatherTermsTiles[] = {{128, 128, 1, {0.872, 0.872, 0.872}}, {128, 64, 2, {0.587, 0.760, 0.760}},
                                        {64, 64, 3, {0.614, 0.630, 0.669}}, {128, 32, 2, {0.404, 0.380, 0.380}}};
+const TermsTile kWgradTermsTiles[] = {{128, 128, 1, {0.835, 0.835, 0.835}}, {64, 128, 2, {0.570, 0.770, 0.770}},
+                                      {128, 64, 2, {0.600, 0.772, 0.772}}, {64, 64, 3, {0.570, 0.650, 0.719}},
+                                      {32, 128, 2, {0.354, 0.563, 0.563}}};
+
 // Whether a family of products may serve the call under the override.
 bool products_allowed(bool terms)
 {
@@ -716,6 +721,9 @@ Plan plan_bwd_weight(const Shape &s)
     int fbm = 0, fbn = 0;
     const bool haveForced = forced_tile(&fbm, &fbn, false);
     double best = 1e300;
+    // three-term kernel: offsets in 32 bits, and in (oh,ow,n) order the 64-bit mask of positions
+    const bool termsTake = !pl.elem && (long long)s.N * s.IH * s.IW * s.IC * 4 < (1LL << 31) && M * s.OC * 4 < (1LL << 31) &&
+                           (!posMajor || ohow <= 64);
     for (int pass = 0; pass < 2 && pl.bm == 0; ++pass) {   // second pass: the forced tile does not apply here
         auto consider = [&](int bm, int bn, bool terms, const std::function<double(long long, int)> &cost) {
             if (pl.elem && bn != 64) return;   // element-wise X loader is compiled for 64-wide tiles
@@ -739,9 +747,21 @@ Plan plan_bwd_weight(const Shape &s)
                 pl.split = sp;
             }
         };
-        for (const TileCand &c : kWgradTiles)
+        // the general fp32 kernel (maps that are not aligned) lost to the three-term one on every such layer of the sweep
+        if (!termsTake || (products_allowed(false) && (pl.fast || !products_allowed(true))))
+            for (const TileCand &c : kWgradTiles)
                 consider(c.bm, c.bn, false, [&](long long tiles, int n) {
-                    return launch_cost(kWgradCost, c, tiles, chunks * live, (double)chunks, n, pl.outElems);
+                    return kFp32WgradUs[1] + kFp32WgradUs[0] * launch_cost(kWgradCost, c, tiles, chunks * live, (double)chunks, n, pl.outElems);
+                });
+        if (products_allowed(true) && termsTake)
+            for (const TermsTile &c : kWgradTermsTiles)
+                consider(c.bm, c.bn, true, [&](long long tiles, int n) {
+                    // (oh,ow,n) order: a launch of at most one workgroup per CU keeps neither the group-wise order nor the
+                    // dealing (4x4x256 -> 512: 36.9 us on 216 128 x 128 tiles, 34.1 on 576 64 x 64; 8x8x256 -> 256: 61.8 on
+                    // 252, 61.6 on 504 64 x 128).
+                    const double lone = posMajor && tiles * n <= 256 ? 1.15 : 1.0;
+                    if (chunks * live > (double)kTermsMaxStages * n && products_allowed(false)) return 1e290;   // chains too long
+                    return lone * terms_cost(kWgradTermsCost, c, tiles, chunks * live, chunks * live, n, pl.outElems);
                 });
     }
     pl.posMajor = posMajor;
@@ -750,7 +770,7 @@ Plan plan_bwd_weight(const Shape &s)
     // A grid barely above one lap of 256 leaves most CUs with one workgroup and a few with two whole
     // ones; two slices per tile halve the items, and the dealing then fills the CUs to 3 halves at most
     // (measured on 288 tiles: 43 -> 38 us).  The model's whole-number quantisation does not see this.
-    if (posMajor && pl.fast && pl.split == 1 && g_forceSplit.load() == 0 && s.IC % pl.bn == 0) {
+    if (posMajor && pl.fast && !pl.terms && pl.split == 1 && g_forceSplit.load() == 0 && s.IC % pl.bn == 0) {
         const long long tiles = (long long)pl.tilesM * pl.tilesN;
         if (tiles > 256 && tiles < 384 && chunks * live >= 8) pl.split = 2;
     }
@@ -787,6 +807,7 @@ int prepare_device(int *devOut)
     if (e == hipSuccess) e = prepare_wgrad();
     if (e == hipSuccess) e = prepare_wgrad_fast();
     if (e == hipSuccess) e = prepare_gather_terms();
+    if (e == hipSuccess) e = prepare_wgrad_terms();
     void *ptr = nullptr;
     if (e == hipSuccess) e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
     if (e != hipSuccess) return hip_fail(e);
@@ -1162,7 +1183,7 @@ void plan_balance_wgrad(const Shape &s, Plan &pl)
 {
     pl.balance = 0;
     const int nTaps = s.FH * s.FW;
-    if (!pl.posMajor || !pl.fast || s.IC % pl.bn != 0 || nTaps > kMaxBalancedTaps || pl.grid <= 256) return;
+    if (!pl.posMajor || !(pl.fast || pl.terms) || s.IC % pl.bn != 0 || nTaps > kMaxBalancedTaps || pl.grid <= 256) return;
     int live[kMaxBalancedTaps];
     int lo = 1 << 30, hi = 0;
     for (int fh = 0; fh < s.FH; ++fh)
@@ -1239,7 +1260,8 @@ bool plan_launchable(int op, const Shape &s, const Plan &pl)
     if (pl.bm <= 0 || pl.bn <= 0 || pl.split < 1 || pl.grid < 1) return false;
     if (op == MI355CONV_OP_BWD_WEIGHT) {
         if (pl.smallIc) return patch_small_ic_accepts(s.IC, s.FH, s.FW) && pl.bm == 64 && pl.bn == 32;
-        if (pl.fast) return wgrad_fast_accepts(s.N, s.OH, s.OW, s.IC, s.OC, pl.posMajor, pl.bm, pl.bn);
+        if (pl.fast && !pl.terms) return wgrad_fast_accepts(s.N, s.OH, s.OW, s.IC, s.OC, pl.posMajor, pl.bm, pl.bn);
+        if (pl.terms) return wgrad_terms_accepts(s.N, s.OH, s.OW, s.IC, s.OC, pl.posMajor, pl.bm, pl.bn);
         return wgrad_accepts(s.N, s.IC, s.OC, pl.posMajor, pl.elem != 0, pl.bm, pl.bn);
     }
     const bool bwd = op == MI355CONV_OP_BWD_DATA;
@@ -1737,6 +1759,10 @@ static int bwd_weight_impl(const float *X, const float *dY, float *dW, const con
     rc = make_plan(MI355CONV_OP_BWD_WEIGHT, s, &pl);
     if (rc != MI355CONV_OK) return rc;
     if (ownWorkspace) {
+        if (pl.wsBytes > kScratchBytes) {   // the fp32 MFMA plans have fewer slices
+            rc = make_plan(MI355CONV_OP_BWD_WEIGHT, s, &pl, MI355CONV_PRODUCTS_FP32);
+            if (rc != MI355CONV_OK) return rc;
+        }
         if (pl.wsBytes > kScratchBytes) return MI355CONV_ERR_WORKSPACE;   // before any HIP call
         if (!X || !dY || !dW) return MI355CONV_ERR_NULL_PTR;
         if (!aligned16(X) || !aligned16(dY) || !aligned16(dW)) return MI355CONV_ERR_ALIGNMENT;
@@ -1782,7 +1808,8 @@ static int bwd_weight_impl(const float *X, const float *dY, float *dW, const con
     w.X = X;
     w.G = dY;
     w.C = pl.split > 1 ? static_cast<float *>(ws) : dW;
-    hipError_t e = pl.fast ? launch_wgrad_fast(w, pl.bm, pl.bn, pl.grid, st)
+    hipError_t e = pl.terms ? launch_wgrad_terms(w, pl.bm, pl.bn, pl.grid, st)
+                   : pl.fast ? launch_wgrad_fast(w, pl.bm, pl.bn, pl.grid, st)
                            : launch_wgrad(w, pl.bm, pl.bn, pl.elem != 0, pl.grid, st);
     if (e != hipSuccess) return hip_fail(e);
     if (pl.split > 1) {

@@ -539,6 +539,18 @@ inline bool wgrad_fast_accepts(int N, int OH, int OW, int IC, int OC, int posMaj
     if (posMajor && (wide || N % kBK != 0 || ohow > 64)) return false;
     return ((bm == 128 || bm == 64) && (bn == 128 || bn == 64)) || (bm == 32 && bn == 128);
 }
+// Stages of one slice (two waves take 16 of the 32 products of a stage each): chains of 2048 products on the two
+// accumulators of the three-term kernel have the error of 256 products in an fp32 MFMA chain (512 stages measure
+// 5.6e-7 against 64-bit sums, fp32 chains of 512 products 4.1e-7).
+constexpr int kTermsMaxStages = 128;
+// Backward-weight on three-term operands: the maps above plus, where all offsets fit (tensors below 2^31
+// bytes), any other map; (oh,ow,n) order needs only whole stages per position and the 64-bit mask.
+inline bool wgrad_terms_accepts(int N, int OH, int OW, int IC, int OC, int posMajor, int bm, int bn)
+{
+    if (IC % 4 != 0 || OC % 4 != 0) return false;
+    if (posMajor && (N % kBK != 0 || OH * OW > 64)) return false;
+    return ((bm == 128 || bm == 64) && (bn == 128 || bn == 64)) || (bm == 32 && bn == 128);
+}
 inline bool bwd_data_small_ic_accepts(int IC, int OC, int FH, int FW, int sh, int sw)
 {
     return sh == 1 && sw == 1 && IC <= 4 && FH * FW * IC <= 32 && OC % kBK == 0 && (4 + FH - 1) * (32 + FW - 1) <= 224;
@@ -551,6 +563,7 @@ hipError_t prepare_gather_gemm();
 hipError_t prepare_wgrad();
 hipError_t prepare_wgrad_fast();
 hipError_t prepare_gather_terms();
+hipError_t prepare_wgrad_terms();
 
 hipError_t launch_direct_fwd(const float *X, const float *W, float *Y, const Shape &s, hipStream_t st);
 hipError_t launch_direct_bwd_data(const float *G, const float *W, float *dX, const Shape &s, hipStream_t st);
@@ -577,6 +590,8 @@ hipError_t launch_wgrad(const WgradParams &p, int bm, int bn, bool xElem, int gr
 // order only), IC % 4 == 0, OC % 4 == 0,
 // tensors below 2^31 bytes.
 hipError_t launch_wgrad_fast(const WgradParams &p, int bm, int bn, int grid, hipStream_t st);
+// same tiles, any map, products on the bf16 matrix pipe (three-term operands)
+hipError_t launch_wgrad_terms(const WgradParams &p, int bm, int bn, int grid, hipStream_t st);
 // unit stride, FH*FW*IC <= 32, IC <= 4, OC % 32 == 0, (4+FH-1)*(32+FW-1) <= 224, tensors below 2^31 bytes
 hipError_t launch_bwd_data_small_ic(const SmallIcParams &p, hipStream_t st);
 // FH*FW*IC <= 32, any stride; grid = ceil(OC / 64) * split

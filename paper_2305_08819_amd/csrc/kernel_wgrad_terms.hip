@@ -1,0 +1,589 @@
+// Backward-weight on v_mfma_f32_32x32x16_bf16 with three-term operands (split_bf16.h).
+//
+//   dW[oc, col] = sum_m G[m, oc] * Xg[m, col],  m = (n, oh, ow) over N*OH*OW rows,
+//   col = (fh*FW + fw)*IC + ic, Xg the input pixel that tap (fh,fw) reads for output pixel m (zero outside
+//   the image).  The output is small and the reduction long, so the rows are cut into slices unless the
+//   tiles alone fill the chip.
+//
+// A stage is kBK = 32 consecutive rows m.  Both operands have the reduction index as the slow memory index,
+// so both LDS tiles are [k = m][channel], and MFMA fragments (8 rows of one channel per lane) come out of
+// LDS through the transposing reads.  Every element is split into its three terms once per workgroup, on
+// its way to LDS.
+//  * X addresses (template parameter MODE):
+//      kRows  OW divides 32 and OH*OW divides or is a multiple of 32: row r of a stage is always the same
+//             (image offset, row offset, column) relative to the stage's first pixel, so each thread's
+//             part of the address and its column validity are fixed for the whole kernel and a stage costs
+//             one add, two compares and a select per 16-byte load;
+//      kWide  OW is a multiple of 32: a stage is 32 neighbouring pixels of one output row that starts at
+//             column ow0 = 0, 32, 64, ...; column validity is tested per stage as well;
+//      kPos   rows in (oh, ow, n) order, N a multiple of 32, at most 64 positions: a stage sits on one
+//             output position; each thread keeps a 64-bit mask of the positions where its filter tap is
+//             inside the image, and whole stages that are padding for every tap of the tile are skipped
+//             with a find-first-set on the tile's mask (small-feature-map operator, paper Sec. IV);
+//      kAny   any map: every row's pixel is stepped by 32 with at most one carry per digit.
+//  * G rows are consecutive in memory: fixed VGPR offset + a window that moves with the stage, no VALU.
+//  * Loads are raw buffer loads: rows past the end or in the padding get an out-of-range
+//    offset and read zeros, so there is no branch and no zero-select.
+//  * The tile is cut into wave tiles of up to 64 x 64 and the two 16-row halves of a stage go to the two
+//    waves of a pair, which add their accumulators at the end (see kernel_gather_terms.hip for why).
+// Accuracy: a slice is at most kTermsMaxStages stages, 16 products each per wave, so that its two accumulators
+// (see split_bf16.h) stay at least as exact as fp32 chains of 512 products.
+#include <hip/hip_runtime.h>
+#include "split_bf16.h"
+
+namespace mi355conv {
+
+namespace {
+enum { kRows = 0, kPos = 1, kWide = 2, kAny = 3 };
+
+template <int BM, int BN>
+struct SW {
+    static constexpr int WM = BN == 128 && BM < 128 ? 1 : 2, WN = BN == 128 ? 2 : 1;
+    static constexpr int WAVES = WM * WN * 2, THREADS = WAVES * 64;   // two waves per wave tile (halves of a stage)
+    static constexpr int WTM = BM / WM, WTN = BN / WN;
+    static constexpr int MB = WTM / 32, NB = WTN / 32, NBLK = MB * NB, NOWN = NBLK / 2;
+    static constexpr int G_TPR = BM / 4, G_RPP = THREADS / G_TPR, PG = kBK / G_RPP;
+    static constexpr int X_TPR = BN / 4, X_RPP = THREADS / X_TPR, PX = kBK / X_RPP;
+    static constexpr int G_PLANE = kBK * BM * 2, X_PLANE = kBK * BN * 2;   // bytes of one term's tile
+    static constexpr int STAGE = 3 * (G_PLANE + X_PLANE);
+    static constexpr size_t SMEM = 2 * STAGE;
+    static_assert(NB == 2, "the two waves of a pair finish one block column each");
+    static_assert(WAVES * NOWN * 32 * kLDT * 4 <= 2 * STAGE, "exchange buffers fit over the stages");
+};
+
+// 64-byte pieces of a [k][C] tile's rows are exchanged by k, so that the four rows of a transposing
+// read lie on different banks.
+template <int C>
+__device__ __forceinline__ int row_swizzle(int k)
+{
+    return C == 128 ? (k & 3) : C == 64 ? ((k >> 1) & 1) : 0;
+}
+}  // namespace
+
+// Waves per SIMD: the 64 x 64 wave tiles hold 128 accumulator registers (two sums), two waves.
+template <int BM, int BN, int MODE>
+__global__ __launch_bounds__((SW<BM, BN>::THREADS), 2) void wgrad_terms_kernel(const WgradParams params)
+{
+    using T = SW<BM, BN>;
+    constexpr bool PM = MODE == kPos;
+    extern __shared__ f4 smem_raw[];
+    char *smem = reinterpret_cast<char *>(smem_raw);
+
+    const BalancePrefetch pre = balance_prefetch(params.runs, params.tapOrder);   // in flight with the scalar arguments
+    const WgradView p = wgrad_view(params);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int tn, tmo, slice;
+    if (PM && p.regional) {
+        // group-wise order: the XCD fixes the groups of output-channel tiles, input-channel tiles and
+        // slices; the id's place on the XCD gives the tile's rank there (tap by tap, longest taps first)
+        const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
+        const int lr = p.runsN ? balanced_rank_local(q, pre) : q;
+        int tapRank, icTile;
+        group_wise_tile(p, xcd, lr, &tapRank, &icTile, &tmo, &slice);
+        tn = balance_order(pre, tapRank) * p.tilesPerTap + icTile;
+    } else if (PM && p.balance) {   // tiles enumerated tap by tap, taps with the most live positions first
+        const int rank = p.runsN ? balanced_rank(blockIdx.x, p.grid, pre) : (int)blockIdx.x;
+        const int tapRank = (int)fast_div((unsigned)rank, p.divPerTap);
+        const int inner = rank - tapRank * (p.tilesPerTap * p.tilesM * p.split);
+        const int r2 = (int)fast_div((unsigned)inner, p.divTilesPerTap);
+        tn = balance_order(pre, tapRank) * p.tilesPerTap + (inner - r2 * p.tilesPerTap);
+        tmo = (int)fast_div((unsigned)r2, p.divSplit);
+        slice = r2 - tmo * p.split;
+    } else {
+        const int bid = xcd_remap_fast(blockIdx.x, p.xcdWhole, p.xcdUnit, p.divXcdUnit);
+        const int rest = (int)fast_div((unsigned)bid, p.divTilesN);
+        tn = bid - rest * p.tilesN;
+        tmo = (int)fast_div((unsigned)rest, p.divSplit);
+        slice = rest - tmo * p.split;
+    }
+    const int oc0 = tmo * BM, col0 = tn * BN;
+    const int Ktot = p.FH * p.FW * p.IC;
+    const int ohow = p.OH * p.OW;
+
+    const int chunksTotal = (p.M + kBK - 1) / kBK;
+    int ch0 = (int)((long long)slice * chunksTotal / p.split);   // (oh,ow,n) order: replaced below by a cut of the live stages
+    int ch1 = (int)((long long)(slice + 1) * chunksTotal / p.split);
+
+    constexpr int kOutOfRange = (int)0x80000000;
+    const __amdgpu_buffer_rsrc_t rsrcX =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.X), 0, (int)p.xBytes, 0x00020000);
+
+    // ---- per-thread constants ---------------------------------------------------------------
+    const int gSeg = tid % T::G_TPR, gRow = tid / T::G_TPR;
+    const int xSeg = tid % T::X_TPR, xRow = tid / T::X_TPR;
+    const int gOc = oc0 + gSeg * 4;
+    const int xCol = col0 + xSeg * 4;
+    const bool xOk = xCol < Ktot;
+    const int xTap = xOk ? (int)fast_div((unsigned)xCol, p.divIC) : 0;
+    const int xIc = xCol - xTap * p.IC;
+    const int xFh = (int)fast_div((unsigned)xTap, p.divFW), xFw = xTap - xFh * p.FW;
+
+    int gVoff[T::PG];                       // bytes, fixed
+#pragma unroll
+    for (int i = 0; i < T::PG; ++i) {
+        const int r = gRow + T::G_RPP * i;
+        const int pixel = PM ? r * ohow : r;   // (oh,ow,n) order: row r of a stage is image nb + r
+        gVoff[i] = gOc < p.OC ? (pixel * p.OC + gOc) * 4 : kOutOfRange;
+    }
+    // X: element offset of the thread's part of the address; validity inputs.
+    // Rows past the last image need no test: their X addresses lie past the end of X (whole offset
+    // in the VGPR), and G is read through a per-stage window that ends with the tensor.
+    int xPart[T::PX];                       // kAny: the whole element offset, stepped
+    int xH[T::PX];                          // input row of the tap: relative to the stage's first one (kRows, kWide;
+                                            //    far out of range where the thread's column is never inside the image),
+                                            //    of the row itself (kAny)
+    int xW[MODE == kWide || MODE == kAny ? T::PX : 1];   // input column: when the stage starts at ow0 = 0, or of the row itself
+    unsigned long long liveMask = 0ull;     // PM: positions at which this thread's tap is inside the image
+    unsigned long long tileLive = ~0ull;    // PM: positions at which any tap of the tile is (uniform)
+    if constexpr (PM) {
+#pragma unroll
+        for (int i = 0; i < T::PX; ++i) {
+            const int r = xRow + T::X_RPP * i;
+            xPart[i] = (r * p.IH * p.IW + xFh * p.IW + xFw) * p.IC + xIc;
+            xH[i] = 0;
+        }
+        unsigned long long wMask = 0ull;
+        for (int ow = 0; ow < p.OW; ++ow)
+            if ((unsigned)(ow * p.sw - p.pw + xFw) < (unsigned)p.IW) wMask |= 1ull << ow;
+        for (int oh = 0; oh < p.OH; ++oh)
+            if (xOk && (unsigned)(oh * p.sh - p.ph + xFh) < (unsigned)p.IH) liveMask |= wMask << (oh * p.OW);
+        // every wave holds all column segments of the tile in its first X_TPR lanes
+        unsigned lo = 0u, hi = 0u;
+#pragma unroll
+        for (int l = 0; l < T::X_TPR; ++l) {
+            lo |= (unsigned)__builtin_amdgcn_readlane((int)(unsigned)liveMask, l);
+            hi |= (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(liveMask >> 32), l);
+        }
+        tileLive = ((unsigned long long)hi << 32) | lo;
+        // Slices cut the tile's LIVE stages evenly, not its rows: a slice of the first output rows
+        // would otherwise be nearly empty for a tap that reaches up, and the slices of one tile
+        // would differ in length by several times.  Live stage q sits at the (q / cpp)-th live
+        // position, chunk q % cpp of it (cpp = chunks per position).
+        const int cpp = p.N / kBK;
+        const int liveQ = __popcll(tileLive) * cpp;
+        auto chunk_of = [&](int q) __attribute__((always_inline)) -> int {
+            if (q >= liveQ) return chunksTotal;
+            const int idx = q / cpp;
+            unsigned long long m = tileLive;
+            for (int k = 0; k < idx; ++k) m &= m - 1;     // drop the idx lowest live positions
+            return __builtin_ctzll(m) * cpp + (q - idx * cpp);
+        };
+        ch0 = chunk_of((int)((long long)slice * liveQ / p.split));
+        ch1 = chunk_of((int)((long long)(slice + 1) * liveQ / p.split));
+    } else if constexpr (MODE == kAny) {
+#pragma unroll
+        for (int i = 0; i < T::PX; ++i) {
+            const int m = ch0 * kBK + xRow + T::X_RPP * i;
+            const int n = (int)fast_div((unsigned)m, p.divOHOW), rr = m - n * ohow;
+            const int oh = (int)fast_div((unsigned)rr, p.divOW), ow = rr - oh * p.OW;
+            xH[i] = oh * p.sh - p.ph + xFh;
+            xW[i] = ow * p.sw - p.pw + xFw;
+            xPart[i] = ((n * p.IH + xH[i]) * p.IW + xW[i]) * p.IC + xIc;   // may be negative
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < T::PX; ++i) {
+            const int r = xRow + T::X_RPP * i;
+            int dn = 0, rr = r;
+            if (ohow < kBK) {
+                dn = (int)fast_div((unsigned)r, p.divOHOW);
+                rr = r - dn * ohow;
+            }
+            const int doh = (int)fast_div((unsigned)rr, p.divOW), ow = rr - doh * p.OW;
+            const int iw = ow * p.sw - p.pw + xFw;
+            xH[i] = doh * p.sh - p.ph + xFh;
+            xPart[i] = ((dn * p.IH + xH[i]) * p.IW + iw) * p.IC + xIc;   // may be negative
+            if (MODE == kWide) {
+                xW[i] = iw;
+                if (!xOk) xH[i] = kInvalidCoord;
+            } else if (!(xOk && (unsigned)iw < (unsigned)p.IW)) {
+                xH[i] = kInvalidCoord;
+            }
+        }
+    }
+    // kAny: a step of 32 rows is (stepN, stepH, stepW) with at most one carry per digit
+    const int stepN = kBK / ohow, stepRem = kBK - stepN * ohow;
+    const int stepH = stepRem / p.OW, stepW = stepRem - stepH * p.OW;
+
+    // First stage at or after ch that has work for this tile (uniform, branch-free).
+    const int chunksPerPos = p.N / kBK;
+    auto next_live = [&](int ch) __attribute__((always_inline)) -> int {
+        if constexpr (!PM) {
+            return ch < ch1 ? ch : ch1;
+        } else {
+            int pos = (int)fast_div((unsigned)(ch * kBK), p.divN);
+            pos = pos < 63 ? pos : 63;
+            const unsigned long long rem = tileLive >> pos;
+            const int skip = rem ? __builtin_ctzll(rem) : 64;
+            const int nch = skip == 0 ? ch : (pos + skip) * chunksPerPos;
+            return nch < ch1 ? nch : ch1;
+        }
+    };
+
+    // ---- stage cursor for the loads: addresses of stage ch, or out of range past the last one ------------
+    unsigned gSoff = 0;            // bytes
+    int xVoff[T::PX];              // bytes
+    bool first = true;             // kAny: the rows stand at ch0 already
+    auto set_stage = [&](int ch) __attribute__((always_inline)) {
+        if (ch >= ch1) {
+            gSoff = p.gBytes;      // an empty window
+#pragma unroll
+            for (int i = 0; i < T::PX; ++i) xVoff[i] = kOutOfRange;
+            return;
+        }
+        const int m0 = ch * kBK;
+        if constexpr (PM) {
+            const int pos = (int)fast_div((unsigned)m0, p.divN);          // output position
+            const int nb = m0 - pos * p.N;                                 // first image of the stage
+            const int oh = (int)fast_div((unsigned)pos, p.divOW), ow = pos - oh * p.OW;
+            gSoff = (unsigned)((nb * ohow + pos) * p.OC * 4);
+            const int uni = ((nb * p.IH + oh * p.sh - p.ph) * p.IW + ow * p.sw - p.pw) * p.IC;
+            const bool live = ((liveMask >> pos) & 1ull) != 0;
+#pragma unroll
+            for (int i = 0; i < T::PX; ++i) xVoff[i] = live ? (xPart[i] + uni) * 4 : kOutOfRange;
+        } else if constexpr (MODE == kAny) {
+            gSoff = (unsigned)(m0 * p.OC * 4);
+            if (!first) {
+#pragma unroll
+                for (int i = 0; i < T::PX; ++i) {
+                    xW[i] += stepW * p.sw;
+                    xH[i] += stepH * p.sh;
+                    xPart[i] += ((stepN * p.IH + stepH * p.sh) * p.IW + stepW * p.sw) * p.IC;
+                    const bool cw = xW[i] >= p.OW * p.sw - p.pw + xFw;
+                    xW[i] -= cw ? p.OW * p.sw : 0;
+                    xH[i] += cw ? p.sh : 0;
+                    xPart[i] += cw ? (p.sh * p.IW - p.OW * p.sw) * p.IC : 0;
+                    const bool chh = xH[i] >= p.OH * p.sh - p.ph + xFh;
+                    xH[i] -= chh ? p.OH * p.sh : 0;
+                    xPart[i] += chh ? (p.IH - p.OH * p.sh) * p.IW * p.IC : 0;
+                }
+            }
+            first = false;
+#pragma unroll
+            for (int i = 0; i < T::PX; ++i) {
+                const bool ok = xOk && (unsigned)xH[i] < (unsigned)p.IH && (unsigned)xW[i] < (unsigned)p.IW;
+                xVoff[i] = ok ? xPart[i] * 4 : kOutOfRange;
+            }
+        } else {
+            gSoff = (unsigned)(m0 * p.OC * 4);
+            const int n = (int)fast_div((unsigned)m0, p.divOHOW);       // image
+            const int rr = m0 - n * ohow;                                // first output pixel inside it
+            const int oh0 = (int)fast_div((unsigned)rr, p.divOW);
+            const int curW = MODE == kWide ? (rr - oh0 * p.OW) * p.sw : 0;   // ow0 * sw: the stage's column shift
+            const int curH = oh0 * p.sh;
+            const int uni = ((n * p.IH + curH) * p.IW + curW) * p.IC;
+#pragma unroll
+            for (int i = 0; i < T::PX; ++i) {
+                bool ok = (unsigned)(curH + xH[i]) < (unsigned)p.IH;
+                if (MODE == kWide) ok = ok && (unsigned)(curW + xW[i]) < (unsigned)p.IW;
+                xVoff[i] = ok ? (xPart[i] + uni) * 4 : kOutOfRange;
+            }
+        }
+    };
+
+    constexpr int kItems = T::PG + T::PX;
+    auto gload_item = [&](int q, f4 *raw) __attribute__((always_inline)) {
+        // The stage's rows of G are addressed through a descriptor that starts at the stage's first
+        // row and ends with the tensor: the range check of a raw buffer load covers the VGPR
+        // offset only, never the scalar offset, so a window that moves with the stage is what
+        // makes rows past the last one (a partial last stage) read zeros.  Scalar work only.
+        // gSoff is uniform; saying so keeps it in SGPRs instead of a per-lane loop over its values.
+        if (q < T::PG) {
+            const unsigned soff = (unsigned)__builtin_amdgcn_readfirstlane((int)gSoff);
+            const __amdgpu_buffer_rsrc_t rsrcG = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<char *>(reinterpret_cast<const char *>(p.G)) + soff, 0, (int)(p.gBytes - soff), 0x00020000);
+            raw[q] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcG, gVoff[q], 0, 0));
+        } else {
+            raw[q] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcX, xVoff[q - T::PG], 0, 0));
+        }
+    };
+
+    // ---- LDS tiles ------------------------------------------------------------------------------
+    int gStore = gRow * (BM * 2) + (((gSeg >> 3) ^ row_swizzle<BM>(gRow)) << 6) + (gSeg & 7) * 8;
+    int xStore = 3 * T::G_PLANE + xRow * (BN * 2) + (((xSeg >> 3) ^ row_swizzle<BN>(xRow)) << 6) + (xSeg & 7) * 8;
+    static_assert(T::G_RPP % 4 == 0 && T::X_RPP % 4 == 0, "the exchange of pieces is the same in every loader pass");
+    int sBuf = T::STAGE, rBuf = T::STAGE;   // distance to the other buffer
+    auto lds_store_item = [&](int q, const f4 *raw) __attribute__((always_inline)) {
+        const SplitQuad s = split_quad(raw[q]);
+        char *d = q < T::PG ? smem + gStore + q * T::G_RPP * BM * 2 : smem + xStore + (q - T::PG) * T::X_RPP * BN * 2;
+        const int plane = q < T::PG ? T::G_PLANE : T::X_PLANE;
+        *reinterpret_cast<u2 *>(d) = s.h;
+        *reinterpret_cast<u2 *>(d + plane) = s.m;
+        *reinterpret_cast<u2 *>(d + 2 * plane) = s.l;
+    };
+    auto flip_stores = [&]() __attribute__((always_inline)) {
+        gStore += sBuf;
+        xStore += sBuf;
+        sBuf = -sBuf;
+    };
+
+    const int kh = wave & 1, wm = (wave >> 1) / T::WN, wn = (wave >> 1) % T::WN;
+    const int l32 = lane & 31, lh = lane >> 5;
+    const int kLane = kh * 16 + lh * 8 + ((lane & 15) >> 2);   // the row this lane addresses in a transposing read
+    const int inSeg = ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+    int gFrag[T::MB], xFrag[T::NB];
+#pragma unroll
+    for (int i = 0; i < T::MB; ++i)
+        gFrag[i] = kLane * (BM * 2) + (((wm * T::MB + i) ^ row_swizzle<BM>(kLane)) << 6) + inSeg;
+#pragma unroll
+    for (int j = 0; j < T::NB; ++j)
+        xFrag[j] = 3 * T::G_PLANE + kLane * (BN * 2) + (((wn * T::NB + j) ^ row_swizzle<BN>(kLane)) << 6) + inSeg;
+    auto flip_reads = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < T::MB; ++i) gFrag[i] += rBuf;
+#pragma unroll
+        for (int j = 0; j < T::NB; ++j) xFrag[j] += rBuf;
+        rBuf = -rBuf;
+    };
+    bf8 fa[3][T::MB], fb[3][T::NB];
+    auto read_a = [&](int plane) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < T::MB; ++i) {
+            const char *s = smem + gFrag[i] + plane * T::G_PLANE;
+            fa[plane][i] = join_quads(lds_read_tr(s), lds_read_tr(s + 4 * BM * 2));
+        }
+    };
+    auto read_b = [&](int plane) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < T::NB; ++j) {
+            const char *s = smem + xFrag[j] + plane * T::X_PLANE;
+            fb[plane][j] = join_quads(lds_read_tr(s), lds_read_tr(s + 4 * BN * 2));
+        }
+    };
+
+    float16v acc[T::NBLK], low[T::NBLK];   // sums of the h*h products and of the five smaller ones (see split_bf16.h)
+#pragma unroll
+    for (int b = 0; b < T::NBLK; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[b][r] = low[b][r] = 0.f;
+
+    // One stage: the six products of the fragments at hand, one group of NBLK MFMAs each.  Beside the first
+    // four groups the wave splits and stores its share of the next stage (loaded a stage ago) into the other
+    // LDS buffer and issues the loads of the stage after into the same registers.  The one barrier comes
+    // behind the fourth group: by then the wave has used every fragment of this stage; the next stage's
+    // fragments are requested beside the last two groups, into registers whose last product is issued.
+    f4 raw[kItems];
+    constexpr int kMemGroups = 4;
+    auto multiply = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < T::MB; ++i)
+#pragma unroll
+            for (int j = 0; j < T::NB; ++j) {
+                float16v &sum = g == kSplitProducts - 1 ? acc[i * T::NB + j] : low[i * T::NB + j];
+                sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kProdA[g]][i], fb[kProdB[g]][j], sum, 0, 0, 0);
+            }
+    };
+    auto stage = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int g = 0; g < kSplitProducts; ++g) {
+            if (g == kMemGroups) {
+                __syncthreads();
+                flip_reads();
+                read_a(2);
+                read_b(2);
+                read_a(1);
+            }
+            if (g == kMemGroups + 1) read_b(1);
+#pragma unroll
+            for (int q = 0; q < kItems; ++q)
+                if (q * kMemGroups / kItems == g) lds_store_item(q, raw);
+#pragma unroll
+            for (int q = 0; q < kItems; ++q)   // a register is loaded anew the group after it was split
+                if (1 + q * kMemGroups / kItems == g) gload_item(q, raw);
+            multiply(g);
+#pragma unroll
+            for (int b = 0; b < T::NBLK; ++b) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                              // one MFMA, then
+                if (g < kMemGroups) __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);           // vector instructions,
+                if (g < kMemGroups) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);           // an LDS store,
+                if (g >= kMemGroups) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);          // or LDS reads
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        read_a(0);
+        read_b(0);
+        flip_stores();
+    };
+
+    // ---- main loop over the live stages of this slice --------------------------------------------
+    // While one stage is multiplied, c1 sits in registers and c2 is loaded.
+    const int c0 = next_live(ch0);
+    if (c0 < ch1) {
+        f4 raw0[kItems];
+        set_stage(c0);
+#pragma unroll
+        for (int q = 0; q < kItems; ++q) gload_item(q, raw0);
+        int c1 = next_live(c0 + 1);
+        set_stage(c1);
+#pragma unroll
+        for (int q = 0; q < kItems; ++q) gload_item(q, raw);
+        int c2 = next_live(c1 + 1);
+        set_stage(c2);
+#pragma unroll
+        for (int q = 0; q < kItems; ++q) lds_store_item(q, raw0);
+        flip_stores();
+        __syncthreads();
+#pragma unroll
+        for (int pl = 2; pl >= 0; --pl) {
+            read_a(pl);
+            read_b(pl);
+        }
+        while (c1 < ch1) {
+            stage();
+            c1 = c2;
+            c2 = next_live(c2 + 1);
+            set_stage(c2);
+        }
+        // the last stage: nothing left to store or to read
+#pragma unroll
+        for (int g = 0; g < kSplitProducts; ++g) {
+            if (g == kMemGroups) __syncthreads();   // every wave has used its last fragments: the buffers are free
+            multiply(g);
+        }
+    }
+
+    // ---- the pair's halves meet: each wave finishes the block column of its number ---------------------
+    float *mine = reinterpret_cast<float *>(smem) + wave * T::NOWN * 32 * kLDT;
+    const float *theirs = reinterpret_cast<float *>(smem) + (wave ^ 1) * T::NOWN * 32 * kLDT;
+    float16v own[T::NOWN];
+#pragma unroll
+    for (int o = 0; o < T::NOWN; ++o)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float e = acc[2 * o][r] + low[2 * o][r], d = acc[2 * o + 1][r] + low[2 * o + 1][r];
+            own[o][r] = kh ? d : e;
+            mine[(o * 32 + 8 * (r / 4) + 4 * lh + r % 4) * kLDT + l32] = kh ? e : d;
+        }
+    __syncthreads();
+    bool bad = false;
+#pragma unroll
+    for (int o = 0; o < T::NOWN; ++o)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            own[o][r] += theirs[(o * 32 + 8 * (r / 4) + 4 * lh + r % 4) * kLDT + l32];
+            bad = bad || split_suspect(own[o][r]);
+        }
+    const int col = col0 + wn * T::WTN + kh * 32 + l32;   // this lane's column in every block it finishes
+    if (__any(bad)) {
+        // operands that three bf16 terms do not hold: the tile again with v_mfma_f32_32x32x2_f32 on elements read
+        // straight from memory (kept small, not fast), folded as above
+        const __amdgpu_buffer_rsrc_t rsrcG =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.G), 0, (int)p.gBytes, 0x00020000);
+        const int tap = col < Ktot ? (int)fast_div((unsigned)col, p.divIC) : 0, ic = col - tap * p.IC;
+        const int fh = (int)fast_div((unsigned)tap, p.divFW), fw = tap - fh * p.FW;
+        float16v sum[T::NOWN];
+#pragma unroll
+        for (int o = 0; o < T::NOWN; ++o)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) own[o][r] = sum[o][r] = 0.f;
+        int since = 0;
+        for (int c = next_live(ch0); c < ch1; c = next_live(c + 1)) {
+            for (int k = 0; k < kBK; k += 2) {
+                const int m = c * kBK + k + lh;
+                int n, r;
+                if (PM) {
+                    r = (int)fast_div((unsigned)m, p.divN);
+                    n = m - r * p.N;
+                } else {
+                    n = (int)fast_div((unsigned)m, p.divOHOW);
+                    r = m - n * ohow;
+                }
+                const int oh = (int)fast_div((unsigned)r, p.divOW), ow = r - oh * p.OW;
+                const int ih = oh * p.sh - p.ph + fh, iw = ow * p.sw - p.pw + fw;
+                const bool okX = m < p.M && col < Ktot && (unsigned)ih < (unsigned)p.IH && (unsigned)iw < (unsigned)p.IW;
+                const float x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                    rsrcX, okX ? (((n * p.IH + ih) * p.IW + iw) * p.IC + ic) * 4 : kOutOfRange, 0, 0));
+#pragma unroll
+                for (int o = 0; o < T::NOWN; ++o) {
+                    const int oc = oc0 + wm * T::WTM + o * 32 + l32;
+                    const bool okG = m < p.M && oc < p.OC;
+                    const float g = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                        rsrcG, okG ? ((n * ohow + r) * p.OC + oc) * 4 : kOutOfRange, 0, 0));
+                    sum[o] = __builtin_amdgcn_mfma_f32_32x32x2f32(g, x, sum[o], 0, 0, 0);
+                }
+            }
+            if (++since == p.flushChunks) {
+                since = 0;
+#pragma unroll
+                for (int o = 0; o < T::NOWN; ++o)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        own[o][r] += sum[o][r];
+                        sum[o][r] = 0.f;
+                    }
+            }
+        }
+#pragma unroll
+        for (int o = 0; o < T::NOWN; ++o)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) own[o][r] += sum[o][r];
+    }
+
+    float *C = p.C + (long long)slice * p.sliceStride;
+#pragma unroll
+    for (int o = 0; o < T::NOWN; ++o)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int oc = oc0 + wm * T::WTM + o * 32 + 8 * (r / 4) + 4 * lh + (r % 4);
+            if (oc < p.OC && col < Ktot) C[oc * Ktot + col] = own[o][r];
+        }
+}
+
+template <int BM, int BN, int MODE>
+static hipError_t launch_terms_one(const WgradParams &p, int grid, hipStream_t st)
+{
+    using T = SW<BM, BN>;
+    hipLaunchKernelGGL((wgrad_terms_kernel<BM, BN, MODE>), dim3((unsigned)grid), dim3(T::THREADS), T::SMEM, st, p);
+    return hipGetLastError();
+}
+
+// Tiles that need more LDS than a kernel gets by default (64 KB): limit raised once per device,
+// outside any stream capture (see prepare_device in the host API).
+template <int BM, int BN>
+static hipError_t raise_lds_limit()
+{
+    constexpr size_t bytes = SW<BM, BN>::SMEM;
+    if (bytes <= 64 * 1024) return hipSuccess;
+    const void *kerns[4] = {reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kRows>),
+                            reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kPos>),
+                            reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kWide>),
+                            reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kAny>)};
+    for (const void *k : kerns) {
+        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t prepare_wgrad_terms()
+{
+    hipError_t e = raise_lds_limit<128, 128>();
+    if (e == hipSuccess) e = raise_lds_limit<64, 128>();
+    if (e == hipSuccess) e = raise_lds_limit<128, 64>();
+    if (e == hipSuccess) e = raise_lds_limit<64, 64>();
+    if (e == hipSuccess) e = raise_lds_limit<32, 128>();
+    return e;
+}
+
+hipError_t launch_wgrad_terms(const WgradParams &p, int bm, int bn, int grid, hipStream_t st)
+{
+    if (!wgrad_terms_accepts(p.N, p.OH, p.OW, p.IC, p.OC, p.posMajor, bm, bn)) return hipErrorInvalidValue;
+    const bool aligned = wgrad_fast_accepts(p.N, p.OH, p.OW, p.IC, p.OC, 0, bm, bn);
+    const int mode = p.posMajor ? kPos : !aligned ? kAny : p.OW > kBK ? kWide : kRows;
+#define MI355CONV_WF(BM_, BN_)                                                        \
+    if (bm == BM_ && bn == BN_) {                                                     \
+        if (mode == kPos) return launch_terms_one<BM_, BN_, kPos>(p, grid, st);        \
+        if (mode == kRows) return launch_terms_one<BM_, BN_, kRows>(p, grid, st);      \
+        if (mode == kWide) return launch_terms_one<BM_, BN_, kWide>(p, grid, st);      \
+        return launch_terms_one<BM_, BN_, kAny>(p, grid, st);                          \
+    }
+    MI355CONV_WF(128, 128)
+    MI355CONV_WF(64, 128)
+    MI355CONV_WF(64, 64)
+    MI355CONV_WF(128, 64)
+    MI355CONV_WF(32, 128)
+#undef MI355CONV_WF
+    return hipErrorInvalidValue;
+}
+
+}  // namespace mi355conv

@@ -62,6 +62,30 @@ def test_bwd_data_channels_by_4_byte_loads(channels, products):
     gu.check_all_ops(d, *inputs(d, channels), ops=("bwd_data",), label=str(channels))
 
 
+# aligned maps, wide rows, (oh,ow,n) order, and maps on which a step of 32 rows carries through column, row and
+# image in every combination; rows that end inside a stage; one stage and a reduction long enough to be folded
+WGRAD_SHAPES = [
+    (8, 8, 8, 64, 160, 3, 3, 1, 1), (64, 4, 4, 64, 160, 3, 3, 1, 1), (2, 4, 64, 16, 160, 3, 3, 1, 1),
+    (3, 4, 4, 16, 32, 3, 3, 1, 1), (3, 7, 5, 32, 160, 3, 3, 1, 1), (32, 3, 3, 64, 96, 3, 3, 1, 1),
+    (64, 7, 7, 32, 48, 3, 3, 1, 1), (5, 33, 1, 20, 24, 3, 1, 1, (1, 0)), (1, 31, 3, 8, 12, 2, 2, (2, 1), (0, 1)),
+    (2, 1, 45, 24, 16, 1, 3, (1, 2), (0, 1)), (40, 1, 1, 132, 68, 1, 1, 1, 0), (11, 5, 6, 36, 40, 5, 5, 1, 2),
+    (1, 50, 41, 16, 32, 3, 3, 1, 0), (16, 40, 37, 16, 32, 3, 3, 1, 1),
+]
+
+
+@pytest.mark.parametrize("products", PRODUCTS, ids=["fp32", "terms"])
+@pytest.mark.parametrize("split", [1, 3])
+@pytest.mark.parametrize("tile", [(128, 128), (64, 128), (128, 64), (64, 64), (32, 128)], ids=lambda t: "%dx%d" % t)
+@pytest.mark.parametrize("shp", WGRAD_SHAPES)
+def test_wgrad_tiles(shp, tile, split, products):
+    d = mc.make_desc(*shp)
+    print("products wgrad", shp, tile, split, products, flush=True)
+    mc.conv2d_set_products(products)
+    mc.conv2d_set_tuning(mc.VARIANT_MFMA, split)
+    mc.conv2d_set_tile(tile[0], tile[1], -1)
+    gu.check_all_ops(d, *inputs(d, hash(shp) & 0xffff), ops=("bwd_weight",), label=str(shp), twice=True)
+
+
 @pytest.mark.parametrize("shp", [(64, 8, 8, 32, 64, 1, 1, 1, 0), (64, 8, 8, 64, 64, 3, 3, 1, 1), (64, 8, 8, 256, 128, 3, 3, 1, 1),
                                  (4, 32, 32, 64, 64, 3, 3, 1, 1)])     # 128 stages of rows: the longest slice the planner makes
 def test_terms_are_no_less_exact_than_fp32_products(shp):
