@@ -31,6 +31,7 @@ import workloads as wl  # noqa: E402
 
 METRIC = "TFLOP/s and % FP32 MFMA peak per conv op (fwd/dgrad/wgrad), CIFAR shapes"
 PEAK_FP32_MFMA_TFLOPS = 157.3   # 256 CU x 256 FLOP/clk x 2.4 GHz (published dense fp32 matrix peak)
+PEAK_TERMS_TFLOPS = 419.4       # 256 CU x 4096 FLOP/clk x 2.4 GHz dense bf16, six bf16 products to one fp32 product
 PEAK_HBM_GBS = 8000.0
 OPS = ("fwd", "bwd_data", "bwd_weight")
 # HBM bytes per launch of each kernel, written from rocprofv3 FETCH_SIZE / WRITE_SIZE runs of this
@@ -38,7 +39,7 @@ OPS = ("fwd", "bwd_data", "bwd_weight")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "bench_cfg5_hbm_traffic.json")
 
 
-def kernel_name(layer, op, plan, mc):
+def kernel_name(layer, op, plan, desc, mc):
     """Name of the main kernel a plan launches, spelled as rocprofv3 prints it."""
     b = lambda v: "true" if v else "false"   # noqa: E731
     t = (plan.tile_m, plan.tile_n)
@@ -47,6 +48,12 @@ def kernel_name(layer, op, plan, mc):
     if plan.kernel == mc.KERNEL_FIRST_LAYER:
         return {"fwd": "fwd_small_ic_kernel<false>", "bwd_data": "bwd_data_small_ic_kernel",
                 "bwd_weight": "wgrad_small_ic_kernel"}[op]
+    terms = mc.conv2d_query_products(OPS.index(op), desc) == mc.PRODUCTS_TERMS
+    if terms and op == "bwd_weight":
+        aligned = 32 % layer.OW == 0 or layer.OW % 32 == 0
+        aligned = aligned and (32 % (layer.OH * layer.OW) == 0 or layer.OH * layer.OW % 32 == 0)
+        mode = 1 if plan.pos_major else 3 if not aligned else 2 if layer.OW > 32 else 0
+        return "wgrad_terms_kernel<%d, %d, %d>" % (t + (mode,))
     if plan.kernel == mc.KERNEL_WGRAD_FAST:
         return "wgrad_fast_kernel<%d, %d, %s, %s>" % (t + (b(plan.pos_major), b(layer.OW > 32)))
     if plan.kernel == mc.KERNEL_WGRAD:
@@ -57,6 +64,9 @@ def kernel_name(layer, op, plan, mc):
         return "gather_elem_kernel<%d, %d, %d, %s>" % (t + (waves_m, b(bwd)))
     src, dst = (layer.OC, layer.IC) if bwd else (layer.IC, layer.OC)
     belem = bwd and dst % 4 != 0
+    if terms:
+        fine = t == (64, 64) and plan.grid <= 512
+        return "gather_terms_kernel<%d, %d, %s, %s, %s, %s>" % (t + (b(bwd), b(belem), b(belem or src % 32 != 0), b(fine)))
     return "gather_gemm_kernel<%d, %d, %d, %s, %s, %s>" % (t + (waves_m, b(bwd), b(belem), b(belem or src % 32 != 0)))
 
 
@@ -539,7 +549,7 @@ def main():
                         "pct_peak": round(100 * tf / PEAK_FP32_MFMA_TFLOPS, 1),
                         "tflops_effective": round(tfe, 2), "pct_peak_effective": round(100 * tfe / PEAK_FP32_MFMA_TFLOPS, 1),
                         "gbs": round(op_bytes(l, op) / ms / 1e6, 1),
-                        "kernel": kernel_name(l, op, pl, mc), "tile": [pl.tile_m, pl.tile_n], "split": pl.split,
+                        "kernel": kernel_name(l, op, pl, r.desc, mc), "tile": [pl.tile_m, pl.tile_n], "split": pl.split,
                         "pos_major": pl.pos_major, "grid": pl.grid})
         out["per_op"] = per
         out["per_op_sum_ms"] = round(sum(p["ms"] for p in per), 5)
@@ -562,8 +572,9 @@ def workload_text(name, layers, graph):
 
 def roofline(per, layers):
     """The kernel with the largest share of the step: its launches' effective FLOP (in-range taps
-    only; nominal x in-range share) over their event-timed durations, against the fp32 MFMA peak -
-    or, where the step is dominated by an HBM-bound kernel, its algorithmic bytes against 8 TB/s."""
+    only; nominal x in-range share) over their event-timed durations, against the matrix peak of the
+    kernel's products (fp32 MFMA, or six bf16 products to each fp32 product) - or, where the step is
+    dominated by an HBM-bound kernel, its algorithmic bytes against 8 TB/s."""
     by_layer = {l.name: l for l in layers}
     groups = {}
     for p in per:
@@ -573,7 +584,8 @@ def roofline(per, layers):
     nominal = sum(by_layer[p["layer"]].flops for p in rows)
     eff = sum(by_layer[p["layer"]].effective_flops for p in rows)
     nbytes = sum(op_bytes(by_layer[p["layer"]], p["op"]) for p in rows)
-    ridge = PEAK_FP32_MFMA_TFLOPS * 1e3 / PEAK_HBM_GBS
+    peak = PEAK_TERMS_TFLOPS if "_terms_" in kern else PEAK_FP32_MFMA_TFLOPS
+    ridge = peak * 1e3 / PEAK_HBM_GBS
     traffic = None
     if os.path.exists(TRAFFIC_FILE):
         t = json.load(open(TRAFFIC_FILE)).get("kernels", {}).get(kern)
@@ -587,8 +599,8 @@ def roofline(per, layers):
         return dict({"bound": "hbm", "achieved": round(a, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                      "frac": round(a / PEAK_HBM_GBS, 4)}, **common)
     a = eff / ms / 1e9
-    return dict({"bound": "mfma", "achieved": round(a, 2), "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
-                 "frac": round(a / PEAK_FP32_MFMA_TFLOPS, 4),
+    return dict({"bound": "mfma", "achieved": round(a, 2), "peak": peak, "unit": "TFLOP/s",
+                 "frac": round(a / peak, 4),
                  "achieved_nominal": round(nominal / ms / 1e9, 2),
                  "flop_counted": "effective: taps inside the image only (nominal 2*M*OC*K x in-range share)"}, **common)
 

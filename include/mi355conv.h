@@ -162,6 +162,10 @@ int conv2d_set_order(int region_wise);
 enum { MI355CONV_PRODUCTS_AUTO = -1, MI355CONV_PRODUCTS_FP32 = 0, MI355CONV_PRODUCTS_TERMS = 1 };
 int conv2d_set_products(int kind);
 
+/* Which products the call's plan forms (MI355CONV_PRODUCTS_FP32 or _TERMS) into *kind; names the kernel beside
+ * conv2d_query_plan.  Status as conv2d_query_plan. */
+int conv2d_query_products(int op, const conv2d_desc *d, int *kind);
+
 /* Forward convolution (Sec. III Layer-1; Fig. 2 conv3D arguments):
  *   Y[n,oh,ow,oc] = sum_{fh,fw,ic} X[n, oh*sh-ph+fh, ow*sw-pw+fw, ic] * W[oc,fh,fw,ic],
  * X taken as 0 outside the image.  X, W: device, read-only.  Y: device, overwritten.

@@ -19,7 +19,7 @@ VARIANT_AUTO, VARIANT_DIRECT, VARIANT_MFMA = -1, 0, 1
 KERNEL_DIRECT, KERNEL_GATHER, KERNEL_GATHER_ELEM, KERNEL_FIRST_LAYER, KERNEL_WGRAD, KERNEL_WGRAD_FAST = range(6)
 ORDER_PLAIN, ORDER_LONGEST, ORDER_REGIONS = range(3)
 
-EXPORTS = ("conv2d_workspace_bytes", "conv2d_query_plan", "conv2d_query_workgroup", "conv2d_query_tile", "conv2d_set_tuning", "conv2d_set_tile", "conv2d_set_order", "conv2d_set_products", "conv2d_fwd",
+EXPORTS = ("conv2d_workspace_bytes", "conv2d_query_plan", "conv2d_query_workgroup", "conv2d_query_tile", "conv2d_set_tuning", "conv2d_set_tile", "conv2d_set_order", "conv2d_set_products", "conv2d_query_products", "conv2d_fwd",
            "conv2d_fwd_bias_act", "conv2d_fwd_u8",
            "conv2d_bwd_data", "deconv2d", "conv2d_bwd_weight", "conv2d_status_string",
            "conv2d_last_hip_error", "conv2d_init", "conv2d_bwd_weight_noalloc", "conv2d_noalloc_scratch_bytes",
@@ -88,6 +88,8 @@ def load() -> ctypes.CDLL:
         lib.conv2d_set_order.restype = ctypes.c_int
         lib.conv2d_set_products.argtypes = [ctypes.c_int]
         lib.conv2d_set_products.restype = ctypes.c_int
+        lib.conv2d_query_products.argtypes = [ctypes.c_int, dp, ctypes.POINTER(ctypes.c_int)]
+        lib.conv2d_query_products.restype = ctypes.c_int
         for name in ("conv2d_fwd", "conv2d_bwd_data", "deconv2d", "conv2d_bwd_weight"):
             fn = getattr(lib, name)
             fn.argtypes = [vp, vp, vp, dp, vp, ctypes.c_size_t, vp]
@@ -182,6 +184,15 @@ def conv2d_set_products(kind: int = PRODUCTS_AUTO) -> None:
         raise Mi355ConvError(rc, "conv2d_set_products")
 
 
+def conv2d_query_products(op: int, desc: ConvDesc) -> int:
+    """PRODUCTS_FP32 or PRODUCTS_TERMS: which products the call's plan forms."""
+    kind = ctypes.c_int()
+    rc = load().conv2d_query_products(op, ctypes.byref(desc), ctypes.byref(kind))
+    if rc != 0:
+        raise Mi355ConvError(rc, "conv2d_query_products")
+    return kind.value
+
+
 def conv2d_init() -> None:
     """One-time set-up of the current device (needed before stream capture; otherwise optional)."""
     rc = load().conv2d_init()
@@ -193,21 +204,22 @@ def conv2d_noalloc_scratch_bytes() -> int:
     return int(load().conv2d_noalloc_scratch_bytes())
 
 
-def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+def _ptr(t):   # the functions' argtypes turn the integer (None: NULL) into a pointer
+    return t.data_ptr() if t is not None else None
 
 
 def _stream_handle(stream):
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:
+        import torch
+        stream = torch.cuda.current_stream()
+    return stream.cuda_stream
 
 
 def _check(t, shape, name):
     import torch
-    if not (t.is_cuda and t.dtype == torch.float32 and t.is_contiguous()):
+    if not (t.is_cuda and t.dtype is torch.float32 and t.is_contiguous()):
         raise ValueError("%s must be a contiguous fp32 CUDA tensor" % name)
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
 
 

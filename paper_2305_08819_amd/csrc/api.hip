@@ -1511,6 +1511,19 @@ int conv2d_query_plan(int op, const conv2d_desc *d, conv2d_plan_info *info)
     return MI355CONV_OK;
 }
 
+int conv2d_query_products(int op, const conv2d_desc *d, int *kind)
+{
+    if (!kind) return MI355CONV_ERR_NULL_PTR;
+    Shape s;
+    Plan pl;
+    int rc = check_desc(d, &s);
+    if (rc != MI355CONV_OK) return rc;
+    rc = make_plan(op, s, &pl);
+    if (rc != MI355CONV_OK) return rc;
+    *kind = pl.terms && pl.variant != MI355CONV_VARIANT_DIRECT && !pl.smallIc && !pl.elem ? MI355CONV_PRODUCTS_TERMS : MI355CONV_PRODUCTS_FP32;
+    return MI355CONV_OK;
+}
+
 int conv2d_query_workgroup(int op, const conv2d_desc *d, int workgroup, int *rank, int *work)
 {
     if (!rank || !work) return MI355CONV_ERR_NULL_PTR;
