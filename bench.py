@@ -43,6 +43,9 @@ def kernel_name(layer, op, plan, desc, mc):
     """Name of the main kernel a plan launches, spelled as rocprofv3 prints it."""
     b = lambda v: "true" if v else "false"   # noqa: E731
     t = (plan.tile_m, plan.tile_n)
+    if plan.kernel == mc.KERNEL_DIRECT and plan.variant == mc.VARIANT_MFMA:
+        quad = (layer.IC if op == "fwd" else layer.OC) % 4 == 0 and op != "bwd_weight"
+        return "short_kernel<%d, %s>" % (OPS.index(op), b(quad))
     if plan.kernel == mc.KERNEL_DIRECT:
         return "direct_%s_kernel" % op
     if plan.kernel == mc.KERNEL_FIRST_LAYER:

@@ -97,7 +97,8 @@ enum {
 
 /* Kernel families (conv2d_plan_info.kernel); for tests, which force every compiled variant. */
 enum {
-    MI355CONV_KERNEL_DIRECT = 0,
+    MI355CONV_KERNEL_DIRECT = 0,       /* kernels for any shape: one thread per element (variant DIRECT), one
+                                          32 x 32 block per workgroup (variant MFMA, short calls)   */
     MI355CONV_KERNEL_GATHER = 1,       /* gather-GEMM, 16-byte loads along the channel axis     */
     MI355CONV_KERNEL_GATHER_ELEM = 2,  /* gather-GEMM, element-wise loads (any channel count)   */
     MI355CONV_KERNEL_FIRST_LAYER = 3,  /* the kernels for at most 32 patch columns / 4 channels */

@@ -49,6 +49,7 @@ struct Plan {
     int elem = 0;          // element-wise loader (channel counts the 16-byte loader cannot take)
     int fast = 0;          // backward-weight: aligned map
     int terms = 0;         // products on the bf16 matrix pipe (three-term operands) instead of fp32 MFMA
+    int shortCall = 0;     // one launch of short_kernel (variant DIRECT: any shape, no workspace)
     int smallIc = 0;       // backward-data: patch-gradient GEMM + col2im kernel for very few input channels
     int grid = 0;
     int tilesM = 0, tilesN = 0;
@@ -1292,6 +1293,36 @@ std::mutex g_planMutex;
 std::unordered_map<PlanKey, Plan, PlanKeyHash> *g_planMap = nullptr;   // allocated on first use, never freed
 
 // products: which family may serve the call (default: the process-wide override).
+// Calls whose plan takes two launches, or loads element by element, for a few microseconds of work: one launch of
+// short_kernel instead, or of the direct backward-weight kernel.  Replayed graphs, us, before -> after:
+//   forward, sums of at most 512 products (two batches of loads per wave; a batch costs 1.9): 512x256 by 256x512 in 4 slices
+//     9.9 -> 5.3, 4 images 8x8x16 -> 16 10.4 -> 4.7, 7x7x17 -> 24 (element loads) 13.0 -> 7.4; three batches stay: 7.6 against 8.4
+//   backward-data likewise (a batch costs 2.7): 128x512x10 7.9 -> 6.8, 8x8x3 <- 16 10.5 -> 5.6, 512 products 9.9 -> 8.5;
+//     plans of one launch with 16-byte loads stay: 5.6 against 5.7
+//   backward-weight, at most 256 rows (one batch; a batch costs 4.2): 14x14x128 -> 128 11.4 -> 7.4; aligned maps in one
+//     slice stay: 4.9 against 5.8
+//   backward-weight by the direct kernel (3.5 us and 0.4 + 0.0043 rows ns per element): 432 elements over 256 rows 8.3
+//     -> 4.0 against the first-layer kernel and its combine pass; and from it where its elements are many: 10 x 512 over
+//     128 rows 8.1 -> 6.4, 30 x 700 over 300 50.1 -> 10.6.  Not with padding, which the direct kernel leaves out of its sums.
+// At most 256 blocks: one workgroup per CU.
+enum ShortChoice { kKeepPlan, kShortKernel, kDirectKernel };
+ShortChoice short_choice(int op, const Shape &s, const Plan &pl)
+{
+    if (g_forceVariant.load() != MI355CONV_VARIANT_AUTO || g_forceSplit.load() || g_forceBM.load() || g_forceBN.load() ||
+        g_forcePosMajor.load() >= 0 || t_products != MI355CONV_PRODUCTS_AUTO)
+        return kKeepPlan;
+    const ShortExtent x = short_extent(op, s);
+    const bool few = ((x.rows + 31) / 32) * ((x.cols + 31) / 32) <= 256;
+    if (op != MI355CONV_OP_BWD_WEIGHT)
+        return few && pl.variant == MI355CONV_VARIANT_MFMA && !pl.smallIc && (pl.split > 1 || pl.elem) && x.depth <= 512 ? kShortKernel
+                                                                                                                        : kKeepPlan;
+    const long long elems = x.rows * x.cols;
+    if (pl.variant == MI355CONV_VARIANT_DIRECT)
+        return few && !s.ph && !s.pw && elems >= 5120 && x.depth <= 512 ? kShortKernel : kKeepPlan;
+    if (pl.smallIc && pl.split > 1 && (double)elems * (0.4e-3 + 4.3e-6 * (double)x.depth) < 3.0) return kDirectKernel;
+    return few && x.depth <= 256 && (pl.smallIc ? pl.split > 1 : !pl.fast) ? kShortKernel : kKeepPlan;
+}
+
 int make_plan(int op, const Shape &s, Plan *pl, int products = g_forceProducts.load())
 {
     if (op != MI355CONV_OP_FWD && op != MI355CONV_OP_BWD_DATA && op != MI355CONV_OP_BWD_WEIGHT)
@@ -1325,6 +1356,14 @@ int make_plan(int op, const Shape &s, Plan *pl, int products = g_forceProducts.l
         *pl = plan_bwd_weight(s);
         if (pl->variant == MI355CONV_VARIANT_MFMA) plan_balance_wgrad(s, *pl);
         break;
+    }
+    if (const ShortChoice c = short_choice(op, s, *pl)) {
+        *pl = Plan();
+        if (c == kShortKernel) {
+            const ShortExtent x = short_extent(op, s);
+            pl->shortCall = 1;
+            pl->grid = (int)(((x.rows + 31) / 32) * ((x.cols + 31) / 32));
+        }
     }
     if (!plan_launchable(op, s, *pl)) return MI355CONV_ERR_UNSUPPORTED;
     {
@@ -1496,9 +1535,9 @@ int conv2d_query_plan(int op, const conv2d_desc *d, conv2d_plan_info *info)
     if (rc != MI355CONV_OK) return rc;
     rc = make_plan(op, s, &pl);
     if (rc != MI355CONV_OK) return rc;
-    info->variant = pl.variant;
-    info->tile_m = pl.bm;
-    info->tile_n = pl.bn;
+    info->variant = pl.shortCall ? MI355CONV_VARIANT_MFMA : pl.variant;
+    info->tile_m = pl.shortCall ? 32 : pl.bm;
+    info->tile_n = pl.shortCall ? 32 : pl.bn;
     info->split = pl.split;
     info->pos_major = pl.posMajor;
     info->grid = pl.grid;
@@ -1666,6 +1705,10 @@ static int fwd_impl(const float *X, const float *W, float *Y, const conv2d_desc 
     rc = prepare_device(nullptr);
     if (rc != MI355CONV_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (pl.shortCall) {
+        hipError_t e = launch_short(MI355CONV_OP_FWD, X, W, Y, s, epi.on, epi.bias, epi.slope, st);
+        return e == hipSuccess ? MI355CONV_OK : hip_fail(e);
+    }
     if (pl.variant == MI355CONV_VARIANT_DIRECT) {
         hipError_t e = launch_direct_fwd(X, W, Y, s, st);
         if (e == hipSuccess && epi.on)
@@ -1736,6 +1779,10 @@ int conv2d_bwd_data(const float *dY, const float *W, float *dX, const conv2d_des
     rc = prepare_device(nullptr);
     if (rc != MI355CONV_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (pl.shortCall) {
+        hipError_t e = launch_short(MI355CONV_OP_BWD_DATA, dY, W, dX, s, false, nullptr, 1.f, st);
+        return e == hipSuccess ? MI355CONV_OK : hip_fail(e);
+    }
     if (pl.variant == MI355CONV_VARIANT_DIRECT) {
         hipError_t e = launch_direct_bwd_data(dY, W, dX, s, st);
         return e == hipSuccess ? MI355CONV_OK : hip_fail(e);
@@ -1788,6 +1835,10 @@ static int bwd_weight_impl(const float *X, const float *dY, float *dW, const con
     if (rc != MI355CONV_OK) return rc;
     if (ownWorkspace) ws = g_scratchPtr[dev];   // the device's copy of `scratch`, never the array's name
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (pl.shortCall) {
+        hipError_t e = launch_short(MI355CONV_OP_BWD_WEIGHT, dY, X, dW, s, false, nullptr, 1.f, st);
+        return e == hipSuccess ? MI355CONV_OK : hip_fail(e);
+    }
     if (pl.variant == MI355CONV_VARIANT_DIRECT) {
         hipError_t e = launch_direct_bwd_weight(X, dY, dW, s, st);
         return e == hipSuccess ? MI355CONV_OK : hip_fail(e);

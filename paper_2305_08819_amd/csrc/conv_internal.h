@@ -569,6 +569,28 @@ hipError_t launch_direct_fwd(const float *X, const float *W, float *Y, const Sha
 hipError_t launch_direct_bwd_data(const float *G, const float *W, float *dX, const Shape &s, hipStream_t st);
 hipError_t launch_direct_bwd_weight(const float *X, const float *G, float *dW, const Shape &s, hipStream_t st);
 
+// Short calls (kernel_short.hip): rows x columns of the product and the length of its sums.
+struct ShortExtent {
+    long long rows, cols, depth;
+};
+inline ShortExtent short_extent(int op, const Shape &s)   // op: MI355CONV_OP_* (0 forward, 1 backward-data, 2 backward-weight)
+{
+    const long long taps = (long long)s.FH * s.FW, out = (long long)s.N * s.OH * s.OW;
+    if (op == 0) return {out, s.OC, taps * s.IC};
+    if (op == 1) return {(long long)s.N * s.IH * s.IW, s.IC, taps * s.OC};
+    return {s.OC, taps * s.IC, out};
+}
+struct ShortParams {
+    Shape s;
+    const float *A, *B, *bias;
+    float *C;
+    float slope;
+    int epi, rows, cols, depth, steps, ch, pixH, pixW, tilesN;
+    FastDiv divTilesN, divPixH, divPixW, divCh, divFW, divSh, divSw;
+};
+hipError_t launch_short(int op, const float *A, const float *B, float *C, const Shape &s, bool epi, const float *bias,
+                        float slope, hipStream_t st);
+
 // out[i] = sum_{s<split} ws[s*stride + i], combined pairwise in a fixed order.
 // With bias / slope (cols = channel count of the output's last axis, cols > 0):
 // out[i] = act(sum + bias[i % cols]).

@@ -16,6 +16,10 @@ hipError_t prepare_wgrad_terms() { return hipErrorNotSupported; }
 hipError_t launch_direct_fwd(const float *, const float *, float *, const Shape &, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_direct_bwd_data(const float *, const float *, float *, const Shape &, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_direct_bwd_weight(const float *, const float *, float *, const Shape &, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_short(int, const float *, const float *, float *, const Shape &, bool, const float *, float, hipStream_t)
+{
+    return hipErrorNotSupported;
+}
 hipError_t launch_slice_reduce(const float *, float *, long long, int, long long, hipStream_t, const float *, float, int)
 {
     return hipErrorNotSupported;

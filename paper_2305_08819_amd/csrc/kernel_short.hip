@@ -1,0 +1,195 @@
+// Short calls: any operator whose whole output is a few dozen 32 x 32 blocks, as one launch.
+//
+// Such calls are bound by launches and by chains of dependent loads, not by arithmetic or bytes: the tiled
+// kernels walk their stages through LDS with a barrier each and, to have more than a handful of workgroups,
+// cut the reduction into slices that a second kernel adds.  Here a workgroup owns one 32 x 32 block and its
+// eight waves share the reduction: wave w takes the eight-element steps w, w + 8, ..., four of them in
+// flight, straight from global memory into the operand registers of v_mfma_f32_32x32x2_f32 (no LDS, no
+// barrier), and the eight partial blocks meet in LDS once, at the end, and are added in wave order.
+//
+// Views (rows x columns, reduction):  forward  pixels x oc, (tap, ic);  backward-data  pixels x ic, (tap, oc);
+// backward-weight  oc x (tap, ic), pixels.  Every element outside the image or past an end is a zero chosen
+// after a load from element 0, so no lane branches and no access leaves its tensor.  Any channel count, stride
+// and padding; a reduction channel count that is a multiple of 4 (QUAD) is read 16 bytes at a time.
+// Bound by latency: 2.7 us of launch and last addition, then one memory round trip per batch of 256 reduction elements
+// (1.9 us forward, 2.7 backward-data, 4.2 backward-weight, whose loads are 4 bytes).  4 images 8x8x16 -> 16 forward 10.4
+// (four slices and their combine pass) -> 4.7 us, 512x256 by 256x512 9.9 -> 5.3.
+#include <climits>
+#include <type_traits>
+#include "gather_common.h"
+#include "../../include/mi355conv.h"
+
+namespace mi355conv {
+
+namespace {
+constexpr int kShortWaves = 8, kShortSteps = 4, kShortPitch = 33;
+typedef float f4u __attribute__((ext_vector_type(4)));
+
+struct Digits {   // n = hi * d + lo
+    int hi, lo;
+};
+__device__ __forceinline__ Digits digits(int n, int d, const FastDiv &f)
+{
+    Digits q;
+    q.hi = (int)fast_div((unsigned)n, f);
+    q.lo = n - q.hi * d;
+    return q;
+}
+}  // namespace
+
+template <int OP, bool QUAD>
+__global__ __launch_bounds__(kShortWaves * 64) void short_kernel(const ShortParams p)
+{
+    __shared__ float part[kShortWaves][32 * kShortPitch];
+    const Shape &s = p.s;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, lh = lane >> 5;
+    const Digits tile = digits(blockIdx.x, p.tilesN, p.divTilesN);
+    const int row = tile.hi * 32 + l32, col = tile.lo * 32 + l32;
+    const bool rowOk = row < p.rows, colOk = col < p.cols;
+
+    // what a lane keeps of its row (a pixel; an output channel) and its column (a channel; a tap and channel)
+    int img = 0, y0 = 0, x0 = 0, tapY = 0, tapX = 0, colCh = 0;
+    if (OP != MI355CONV_OP_BWD_WEIGHT) {
+        const Digits ny = digits(rowOk ? row : 0, p.pixW, p.divPixW), n = digits(ny.hi, p.pixH, p.divPixH);
+        img = n.hi;
+        y0 = OP == MI355CONV_OP_FWD ? n.lo * s.sh - s.ph : n.lo + s.ph;
+        x0 = OP == MI355CONV_OP_FWD ? ny.lo * s.sw - s.pw : ny.lo + s.pw;
+    } else {
+        const Digits tc = digits(colOk ? col : 0, s.IC, p.divCh), f = digits(tc.hi, s.FW, p.divFW);
+        tapY = f.hi - s.ph;
+        tapX = f.lo - s.pw;
+        colCh = tc.lo;
+    }
+
+    // element offset in A of this lane's row at reduction element k, -1 for a zero
+    auto offA = [&](int k, const Digits &kc) -> int {
+        if (OP == MI355CONV_OP_BWD_WEIGHT) return rowOk && k < p.depth ? k * s.OC + row : -1;
+        const Digits f = digits(kc.hi, s.FW, p.divFW);
+        if (OP == MI355CONV_OP_FWD) {
+            const int y = y0 + f.hi, x = x0 + f.lo;
+            const bool ok = rowOk && k < p.depth && (unsigned)y < (unsigned)s.IH && (unsigned)x < (unsigned)s.IW;
+            return ok ? ((img * s.IH + y) * s.IW + x) * s.IC + kc.lo : -1;
+        }
+        const int ty = y0 - f.hi, tx = x0 - f.lo;
+        const Digits y = digits(ty < 0 ? 0 : ty, s.sh, p.divSh), x = digits(tx < 0 ? 0 : tx, s.sw, p.divSw);
+        const bool ok = rowOk && k < p.depth && ty >= 0 && tx >= 0 && y.lo == 0 && x.lo == 0 && y.hi < s.OH && x.hi < s.OW;
+        return ok ? ((img * s.OH + y.hi) * s.OW + x.hi) * s.OC + kc.lo : -1;
+    };
+    // the same in B for this lane's column
+    auto offB = [&](int k, const Digits &kc) -> int {
+        if (!colOk || k >= p.depth) return -1;
+        if (OP == MI355CONV_OP_FWD) return col * p.depth + k;
+        if (OP == MI355CONV_OP_BWD_DATA) return (kc.lo * s.FH * s.FW + kc.hi) * s.IC + col;
+        const Digits r = digits(k, s.OW, p.divPixW), n = digits(r.hi, s.OH, p.divPixH);
+        const int y = n.lo * s.sh + tapY, x = r.lo * s.sw + tapX;
+        const bool ok = (unsigned)y < (unsigned)s.IH && (unsigned)x < (unsigned)s.IW;
+        return ok ? ((n.hi * s.IH + y) * s.IW + x) * s.IC + colCh : -1;
+    };
+    auto one = [](const float *t, int off) { const float v = t[off < 0 ? 0 : off]; return off < 0 ? 0.f : v; };
+    auto quad = [](const float *t, int off) {
+        const f4u v = *reinterpret_cast<const f4u *>(t + (off < 0 ? 0 : off));
+        const f4u z = {0.f, 0.f, 0.f, 0.f};
+        return off < 0 ? z : v;
+    };
+
+    // Sums: chains of 16 products (two steps) added in fp32, so that no slice of the plans this replaces was shorter than
+    // a chain; backward-weight chains of 8 added in fp64, because the direct kernel adds 256 short chains pairwise.
+    // Error against 64 bits, before -> after: forward K = 512 1.5e-7 -> 0.9e-7, dW of 300 rows 0.81e-7 -> 0.64e-7.  (fp64
+    // throughout costs forward another 1.1 us at 256 products, one chain per wave saves 0.3 and gives dW 1.1e-7.)
+    constexpr int kChain = OP == MI355CONV_OP_BWD_WEIGHT ? 1 : 2;   // steps
+    typename std::conditional<OP == MI355CONV_OP_BWD_WEIGHT, double, float>::type acc[16] = {};
+    for (int step = wave; step < p.steps; step += kShortWaves * kShortSteps) {   // uniform in a wave
+        f4u a[kShortSteps], b[kShortSteps];
+#pragma unroll
+        for (int u = 0; u < kShortSteps; ++u) {
+            const int k = (step + u * kShortWaves) * 8 + lh * 4;   // four elements per half wave; past the end: zeros
+            if (QUAD && OP != MI355CONV_OP_BWD_WEIGHT) {
+                const Digits kc = digits(k, p.ch, p.divCh);        // the four lie in one tap
+                a[u] = quad(p.A, offA(k, kc));
+                if (OP == MI355CONV_OP_FWD) {
+                    b[u] = quad(p.B, offB(k, kc));
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) b[u][i] = one(p.B, offB(k + i, Digits{kc.hi, kc.lo + i}));
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const Digits kc = OP == MI355CONV_OP_BWD_WEIGHT ? Digits{0, 0} : digits(k + i, p.ch, p.divCh);
+                    a[u][i] = one(p.A, offA(k + i, kc));
+                    b[u][i] = one(p.B, offB(k + i, kc));
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kShortSteps; u += kChain) {
+            float16v c = {};
+#pragma unroll
+            for (int i = 0; i < 4 * kChain; ++i)
+                c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u + i / 4][i % 4], b[u + i / 4][i % 4], c, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] += c[r];
+        }
+    }
+
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part[wave][(8 * (r / 4) + 4 * lh + (r % 4)) * kShortPitch + l32] = (float)acc[r];
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 32 * 32 / (kShortWaves * 64); ++h) {
+        const int e = h * kShortWaves * 64 + tid, i = e >> 5, j = e & 31;
+        double sum = 0.;
+#pragma unroll
+        for (int w = 0; w < kShortWaves; ++w) sum += (double)part[w][i * kShortPitch + j];
+        float v = (float)sum;
+        const int r = tile.hi * 32 + i, c = tile.lo * 32 + j;
+        if (r < p.rows && c < p.cols) {
+            if (p.epi) {
+                v += p.bias ? p.bias[c] : 0.f;
+                v = v > 0.f ? v : v * p.slope;
+            }
+            p.C[(long long)r * p.cols + c] = v;
+        }
+    }
+}
+
+hipError_t launch_short(int op, const float *A, const float *B, float *C, const Shape &s, bool epi, const float *bias,
+                        float slope, hipStream_t st)
+{
+    ShortParams p;
+    p.s = s;
+    p.A = A;
+    p.B = B;
+    p.C = C;
+    p.bias = bias;
+    p.slope = slope;
+    p.epi = epi;
+    const bool fwd = op == MI355CONV_OP_FWD, wgt = op == MI355CONV_OP_BWD_WEIGHT;
+    const ShortExtent x = short_extent(op, s);
+    if (x.rows > INT_MAX / 64 || x.cols > INT_MAX / 64 || x.depth > INT_MAX / 64) return hipErrorInvalidValue;
+    p.rows = (int)x.rows;
+    p.cols = (int)x.cols;
+    p.depth = (int)x.depth;
+    p.steps = (p.depth + 7) / 8;
+    p.ch = wgt ? 1 : fwd ? s.IC : s.OC;
+    p.pixH = fwd || wgt ? s.OH : s.IH;
+    p.pixW = fwd || wgt ? s.OW : s.IW;
+    p.tilesN = (p.cols + 31) / 32;
+    p.divTilesN = make_fastdiv((unsigned)p.tilesN);
+    p.divPixH = make_fastdiv((unsigned)p.pixH);
+    p.divPixW = make_fastdiv((unsigned)p.pixW);
+    p.divCh = make_fastdiv((unsigned)(wgt ? s.IC : p.ch));
+    p.divFW = make_fastdiv((unsigned)s.FW);
+    p.divSh = make_fastdiv((unsigned)s.sh);
+    p.divSw = make_fastdiv((unsigned)s.sw);
+    const dim3 grid((unsigned)(p.tilesN * ((p.rows + 31) / 32))), block(kShortWaves * 64);
+    const bool quad = p.ch % 4 == 0;
+    if (wgt) hipLaunchKernelGGL((short_kernel<MI355CONV_OP_BWD_WEIGHT, false>), grid, block, 0, st, p);
+    else if (fwd && quad) hipLaunchKernelGGL((short_kernel<MI355CONV_OP_FWD, true>), grid, block, 0, st, p);
+    else if (fwd) hipLaunchKernelGGL((short_kernel<MI355CONV_OP_FWD, false>), grid, block, 0, st, p);
+    else if (quad) hipLaunchKernelGGL((short_kernel<MI355CONV_OP_BWD_DATA, true>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((short_kernel<MI355CONV_OP_BWD_DATA, false>), grid, block, 0, st, p);
+    return hipGetLastError();
+}
+
+}  // namespace mi355conv

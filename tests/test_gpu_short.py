@@ -1,0 +1,58 @@
+"""Short calls (one 32 x 32 block per workgroup, the reduction shared by its eight waves) against the oracle:
+remainders of blocks, steps and quads, stride phases, taps in the padding, and the fused bias and activation."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2305_08819_amd as mc
+import workloads as wl
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+def is_short(op, d):
+    p = mc.conv2d_query_plan(op, d)
+    return p.variant == mc.VARIANT_MFMA and (p.tile_m, p.tile_n) == (32, 32)
+
+
+def inputs(d, seed):
+    k = wl.stream_key("short", seed)
+    X = wl.normal01(k, (d.N, d.IH, d.IW, d.IC))
+    W = wl.normal01(k + 1, (d.OC, d.FH, d.FW, d.IC), scale=float(np.sqrt(2.0 / (d.FH * d.FW * d.IC))))
+    G = wl.normal01(k + 2, (d.N, d.OH, d.OW, d.OC))
+    return X, W, G
+
+
+# (N, IH, IW, IC, OC, FH, FW, stride, pad): sums of 1 to 512 products; one block and several; the last two also take
+# the direct backward-weight kernel in place of two launches, and short backward-weight in its place
+SHAPES = [
+    (1, 1, 1, 256, 1, 1, 1, 1, 0), (33, 1, 1, 257, 31, 1, 1, 1, 0), (64, 1, 1, 260, 33, 1, 1, 1, 0),
+    (128, 1, 1, 512, 10, 1, 1, 1, 0), (32, 1, 1, 512, 63, 1, 1, 1, 0), (4, 8, 8, 5, 16, 3, 3, 1, 1),
+    (3, 5, 7, 12, 20, 3, 3, 2, 1), (2, 6, 5, 9, 7, 3, 2, (1, 2), (1, 0)), (1, 11, 9, 16, 28, 5, 5, 1, 2),
+    (4, 8, 8, 3, 16, 3, 3, 1, 1), (300, 1, 1, 700, 30, 1, 1, 1, 0),
+]
+
+
+@pytest.mark.parametrize("shp", SHAPES)
+def test_short_calls(shp):
+    d = mc.make_desc(*shp)
+    ops = [op for op in (mc.OP_FWD, mc.OP_BWD_DATA, mc.OP_BWD_WEIGHT) if is_short(op, d)]
+    assert ops, shp
+    print("short", shp, ops, flush=True)
+    gu.check_all_ops(d, *inputs(d, hash(shp) & 0xffff), label=str(shp), twice=True)
+
+
+def test_short_forward_with_bias_and_activation():
+    d = mc.make_desc(40, 1, 1, 300, 37, 1, 1, 1, 0)
+    assert is_short(mc.OP_FWD, d)
+    X, W, _ = inputs(d, 5)
+    bias = wl.normal01(wl.stream_key("short", 6), (d.OC,))
+    Y = torch.empty(40, 1, 1, 37, device="cuda")
+    mc.conv2d_fwd_bias_act(torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda(), torch.from_numpy(bias).cuda(), Y, d, 0.2)
+    ref = X.reshape(40, 300).astype(np.float64) @ W.reshape(37, 300).T.astype(np.float64) + bias
+    ref = np.where(ref > 0, ref, 0.2 * ref)
+    got = Y.cpu().numpy().reshape(40, 37)
+    # fewer than 40 fp32 roundings on the way to a sum (chains of 16, two or three of them added, fp64 from there), each of
+    # a partial sum below four times the largest result
+    assert np.abs(got - ref).max() <= 40 * 2.0 ** -24 * 4 * np.abs(ref).max()
