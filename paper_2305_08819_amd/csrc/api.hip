@@ -288,8 +288,8 @@ const TileCand kWgradTiles[] = {{128, 128, 0.80, 1}, {64, 128, 0.93, 2}, {128, 6
                                 {32, 128, 0.90, 3}};
 
 // Fitted, like the constants above, to tile x slices x row order sweeps of 49 layers with either family of products
-// (6 476 forward / backward-data and 5 394 backward-weight timings): the picks are 2.1 % / 1.8 % slower than the
-// fastest plan of the sweep on average.  The fp32 MFMA kernels stay because they start and end faster: up to
+// (6 476 forward / backward-data and 5 394 backward-weight timings), made while the kernels kept one accumulator per
+// sum: the picks were 2.1 % / 1.8 % slower than the fastest plan of the sweep on average.  The fp32 MFMA kernels stay because they start and end faster: up to
 // about eight stages per workgroup they win (matrix product 256 x 256 x 32 4.2 against 5.2 us, R7s forward
 // 8.6 / 9.6), beyond that they take 0.50 us a stage against 0.47 (64 x 64 tile, one per CU) and 1.9 against 0.9 (128 x 128).
 // kFp32GatherUs, kFp32WgradUs tie the two models' scales together: us = factor * model + offset.
