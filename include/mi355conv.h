@@ -157,9 +157,11 @@ int conv2d_set_order(int region_wise);
 
 /* Fourth process-wide override for tests and sweeps: how the MFMA kernels with 16-byte loaders form their fp32
  * products - AUTO (by size), FP32 (v_mfma_f32_32x32x2_f32) or TERMS (every operand as three bf16 terms, six
- * products on v_mfma_f32_32x32x16_bf16 summed in fp32, at least as exact; see csrc/split_bf16.h).  Ignored by
- * the plans that have only one of them.  Operands that three bf16 terms do not hold (infinities, NaN, values
- * that round to infinity in bf16, very small ones) are found in the sums and their blocks redone with FP32. */
+ * products on v_mfma_f32_32x32x16_bf16 summed in fp32; see csrc/split_bf16.h).  Ignored by the plans that have only
+ * one of them.  Against 64-bit sums TERMS measures a fraction of FP32's error on sums of many products, zero-mean or
+ * one-sided; a sum with a single nonzero product may be one ulp off where FP32 is half a one.  Operands that
+ * three bf16 terms do not hold are found - infinities, NaN and values that round to infinity in bf16 in the sums, nonzero
+ * magnitudes below 2^-102 where they are loaded - and the blocks that read them are redone with FP32, a few times slower. */
 enum { MI355CONV_PRODUCTS_AUTO = -1, MI355CONV_PRODUCTS_FP32 = 0, MI355CONV_PRODUCTS_TERMS = 1 };
 int conv2d_set_products(int kind);
 

@@ -1,14 +1,16 @@
 // fp32 products on the bf16 matrix pipe: every fp32 operand is held as three bf16 terms,
 // x = h + m + l (each term the remainder of the one before, rounded to nearest: 3 x 8 significant
-// bits, so the sum is exact for |x| between 2^-110 and the bf16 maximum), and a product is the six
+// bits, so the sum is exact for |x| between 2^-102 and the bf16 maximum), and a product is the six
 // term products of weight 2^-16 and above, summed in the fp32 accumulator of v_mfma_f32_32x32x16_bf16
 // (the three-term decomposition of Henry, Tang and Heinecke, "Leveraging the bfloat16 artificial
-// intelligence datatype for higher-precision computations", 2019).  What is left out (m*l, l*m, l*l)
-// is below 2^-25 of the product.  The h*h products and the five smaller ones are summed in accumulators of their
+// intelligence datatype for higher-precision computations", 2019).  What is left out (m*l, l*m, l*l) is at most 2^-24
+// of the product (|m| <= 2^-8 and |l| <= 2^-17 of an operand's leading bit), so a sum with one nonzero product is up to one
+// ulp off where fp32 MFMA is half a one (2-norm 2.60e-8 against 2.53e-8).  The h*h products and the five smaller ones are summed in accumulators of their
 // own: the MFMA cuts its sums towards minus infinity below the accumulator's last places, and small products on
 // a large accumulator would meet that five times in six (a bias that grows with the number of products).  Measured
 // against 64-bit sums of N(0,1) products, 2-norm, two accumulators / one / a chain of fp32 MFMA: K = 64 0.50 / 1.10 /
-// 1.45e-7, 576 1.4 / 3.7 / 4.3e-7, 4608 4.2 / 10.7 / 12.1e-7.
+// 1.45e-7, 576 1.4 / 3.7 / 4.3e-7, 4608 4.2 / 10.7 / 12.1e-7.  One-sided sums, where that bias would show (both operands
+// U[0,1), or one U(-1,0]), two accumulators / fp32 MFMA: K = 64 0.42 / 1.15e-7, 4608 1.9 / 10.2e-7, 131072 9.3 / 57e-7.
 //
 // Why: register-only loops sustain 2000 TFLOP/s in bf16, 333 TFLOP/s of fp32 products at six each,
 // against 155 TFLOP/s of v_mfma_f32_32x32x2_f32; and up to six vector instructions per bf16 MFMA run
@@ -59,14 +61,66 @@ constexpr int kSplitProducts = 6;
 constexpr int kProdA[kSplitProducts] = {1, 2, 0, 1, 0, 0};
 constexpr int kProdB[kSplitProducts] = {1, 0, 2, 0, 1, 0};
 
-// Where the three terms do not stand for the fp32 value - infinities, NaN, values that round to
-// infinity in bf16, operands so small that their lower terms fall below the smallest bf16 - the
-// accumulator shows it: it is not finite, or it is not zero and below 2^-80 (an operand below 2^-110
-// gives that unless the other one is above 2^30).  The kernels then redo the tile with fp32 MFMA.
-__device__ __forceinline__ bool split_suspect(float v)
+// Where the three terms do not stand for the fp32 value, the kernels redo the block with fp32 MFMA.  Found in two places:
+//  * infinities, NaN and values that round to infinity in bf16: the sum is not finite;
+//  * nonzero operands below 2^-102, whose lower terms reach below the smallest normal bf16 (2^-126): while they are split.
+//    The sum cannot show it - a lost 2^-135 next to a partner of 2^127 is a lost 0.004, and a sum of lost products is 0.
+//    Every thread keeps the least magnitude it has split, in the order of (bits << 1) - 1, which drops the sign and makes
+//    zero the largest.  1.5 vector instructions per value beside the 5.5 of the split, which costs 2 to 6 % of a call
+//    (128 x 8x8x256 backward-data 57.9 -> 60.1 us, 14x14 5x5 192 -> 48 dW 80.3 -> 85.0); v_cmp_class_f32 on the last remainder
+//    is one instruction less per pair but slower (its scalar results: 66.0 -> 69.1 us where this takes 68.0).
+// Where both operands are small, products or partial sums may fall below the smallest fp32 although every operand keeps
+// its terms: a sum below 2^-80 (zero among them) is redone if the least operands' product is below 2^-100.  Sums of 2^-80
+// and above lose less than their last place to that.
+constexpr unsigned kLeastNone = 0xffffffffu;          // nothing but zeros
+constexpr unsigned kLeastSplit = (25u << 24) - 1u;    // 2^-102
+__device__ __forceinline__ unsigned least_of(unsigned least, const f4 &x)
+{
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const unsigned a = (__builtin_bit_cast(unsigned, (float)x[2 * i]) << 1) - 1u;
+        const unsigned b = (__builtin_bit_cast(unsigned, (float)x[2 * i + 1]) << 1) - 1u;
+        const unsigned ab = a < b ? a : b;
+        least = ab < least ? ab : least;
+    }
+    asm("" : "+v"(least));   // left to itself the compiler keeps a stage's values for a tree of minima: 15 registers more
+    return least;
+}
+
+// Least over the 64 lanes, in every lane.
+__device__ __forceinline__ unsigned wave_least(unsigned v)
+{
+#define MI355_LEAST_STEP(CTRL_)                                                                                     \
+    {                                                                                                               \
+        const unsigned o = (unsigned)__builtin_amdgcn_update_dpp((int)kLeastNone, (int)v, CTRL_, 0xf, 0xf, false);  \
+        v = o < v ? o : v;                                                                                          \
+    }
+    MI355_LEAST_STEP(0x111)   // row_shr:1, 2, 4, 8: lane 15 of a row holds the row's least
+    MI355_LEAST_STEP(0x112)
+    MI355_LEAST_STEP(0x114)
+    MI355_LEAST_STEP(0x118)
+    MI355_LEAST_STEP(0x142)   // row_bcast:15, 31: lane 63 holds the wave's
+    MI355_LEAST_STEP(0x143)
+#undef MI355_LEAST_STEP
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// What the least operands of a workgroup say about its sums (uniform).
+struct SplitCheck {
+    bool lost;         // an operand that its terms do not hold: redo
+    unsigned below;    // magnitudes below this (as bits) are redone
+};
+__device__ __forceinline__ SplitCheck split_check(unsigned leastA, unsigned leastB)
+{
+    SplitCheck c;
+    c.lost = leastA < kLeastSplit || leastB < kLeastSplit;
+    c.below = (leastA >> 24) + (leastB >> 24) < 2 * 127 - 100 ? 0x17800000u : 0u;   // 2^-80
+    return c;
+}
+__device__ __forceinline__ bool split_suspect(float v, const SplitCheck &c)
 {
     const unsigned u = __builtin_bit_cast(unsigned, v) & 0x7fffffffu;
-    return u >= 0x7f800000u || u - 1u < 0x17800000u - 1u;   // u = 0 wraps to the largest value
+    return u >= 0x7f800000u || u < c.below;
 }
 
 // 4 consecutive reduction elements of 16 neighbouring columns, transposed on the way out of LDS:

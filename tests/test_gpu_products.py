@@ -162,3 +162,126 @@ def test_very_small_and_large_operands(shp, op, scales):
         err = np.linalg.norm((got - ref).ravel())
         floor = 2.0 ** -149 * 64 * np.sqrt(ref.size)      # a rounding to subnormal spacing per product of a short chain
         assert err <= 1e-5 * np.linalg.norm(ref.ravel()) + floor, (products, err, np.linalg.norm(ref.ravel()))
+
+
+# One shape per form of a kernel: (y,x,n) rows and (n,y,x) rows, ragged channels, 4-byte filter loads, stride phases;
+# "many" has 1024 workgroups of the 64 x 64 tile (its four-wave form starts above 512)
+GATHER_REDO = [((128, 4, 4, 64, 96, 3, 3, 1, 1), tile, split) for tile in [(128, 128), (128, 64), (64, 64), (128, 32)] for split in (1, 3)]
+GATHER_REDO += [((5, 9, 7, 36, 44, 3, 3, 2, 1), tile, 1) for tile in [(128, 128), (128, 64), (64, 64), (128, 32)]]
+GATHER_REDO += [((128, 16, 16, 32, 128, 1, 1, 1, 0), (64, 64), 1), ((128, 16, 16, 128, 36, 1, 1, 1, 0), (64, 64), 1)]
+WGRAD_REDO = [(shp, tile, split) for tile in [(128, 128), (64, 128), (128, 64), (64, 64), (32, 128)] for split in (1, 3)
+              for shp in [(64, 4, 4, 64, 96, 3, 3, 1, 1), (2, 4, 64, 16, 72, 3, 3, 1, 1), (8, 8, 8, 64, 160, 3, 3, 1, 1)]]
+WGRAD_REDO += [((3, 7, 5, 32, 72, 3, 3, 1, 1), tile, 3) for tile in [(128, 128), (64, 128), (128, 64), (64, 64)]]
+REDO = [(op,) + c for c in GATHER_REDO for op in ("fwd", "bwd_data")] + [("bwd_weight",) + c for c in WGRAD_REDO]
+REDO += [("bwd_data", (3, 7, 9, 3, 40, 3, 3, 2, 1), (128, 32), 1)]
+CODE = {"fwd": mc.OP_FWD, "bwd_data": mc.OP_BWD_DATA, "bwd_weight": mc.OP_BWD_WEIGHT}
+
+
+def force(op, d, tile, split, products, pos_major=-1):
+    mc.conv2d_set_products(products)
+    mc.conv2d_set_tuning(mc.VARIANT_MFMA, split)
+    mc.conv2d_set_tile(tile[0], tile[1], pos_major)
+    p = mc.conv2d_query_plan(CODE[op], d)
+    assert (p.tile_m, p.tile_n) == tile and mc.conv2d_query_products(CODE[op], d) == products
+    return p
+
+
+def far_from_one(op, a, b, kind):
+    """Operands whose products are ordinary numbers although three bf16 terms do not hold one of them.
+    whole: one tensor small, the other large.  hidden: only one element in 32 of the reduction (or one image) is
+    such a pair, so that an ordinary part of every sum covers it."""
+    a, b = a.copy(), b.copy()
+    small, large = {"1e-37": (1e-37, 1e33), "1e-42": (1e-42, 1e36), "hidden": (1e-37, 1e37)}[kind]
+    pick = slice(None) if kind != "hidden" else slice(0, 1)
+    if op == "fwd":            # reduction over the channels of X and W
+        a[..., pick] *= np.float32(small)
+        b[..., pick] *= np.float32(large)
+    elif op == "bwd_data":     # over the channels of G, the filters of W; here the filter is the small one
+        a[..., pick] *= np.float32(large)
+        b[pick] *= np.float32(small)
+    else:                      # over images
+        a[pick] *= np.float32(small)
+        b[pick] *= np.float32(large)
+    return a, b
+
+
+@pytest.mark.parametrize("kind", ["1e-37", "1e-42", "hidden"])
+@pytest.mark.parametrize("op,shp,tile,split", REDO)
+def test_small_operand_with_a_large_partner(op, shp, tile, split, kind):
+    """Against the oracle, at the parity tests' bar."""
+    d = mc.make_desc(*shp)
+    a, b = far_from_one(op, *gu.operands(op, *inputs(d, 11)), kind)
+    force(op, d, tile, split, mc.PRODUCTS_TERMS)
+    print("small with large", op, shp, tile, split, kind, flush=True)
+    ref = gu.run_oracle(op, d, a, b)
+    got = run(op, d, a, b).astype(np.float64)
+    # an operand of 1e-42 is a whole number of 2^-149, exact in both: no allowance beyond the bar
+    assert np.linalg.norm((got - ref).ravel()) <= 1e-5 * np.linalg.norm(ref.ravel())
+
+
+@pytest.mark.parametrize("pos_major", [0, 1])      # (n,y,x) rows multiply padding as 0, (y,x,n) rows skip it
+@pytest.mark.parametrize("op,shp,tile,split", REDO)
+def test_infinite_operands_in_every_tile(op, shp, tile, split, pos_major):
+    """An infinity in one operand and a NaN in the other: the same elements are infinite, NaN and finite as with fp32
+    products on the same tile, slices and row order, and the finite ones agree."""
+    d = mc.make_desc(*shp)
+    a, b = gu.operands(op, *inputs(d, 3))
+    a.reshape(-1)[a.size // 3] = float("inf")
+    b.reshape(-1)[b.size // 2] = float("nan")
+    got = {}
+    for products in PRODUCTS:
+        p = force(op, d, tile, split, products, pos_major)
+        print("infinite", op, shp, tile, split, products, p.pos_major, p.grid, flush=True)
+        got[products] = run(op, d, a, b)
+    f, t = got[mc.PRODUCTS_FP32], got[mc.PRODUCTS_TERMS]
+    assert np.isnan(t).any()
+    same = [np.array_equal(g(f), g(t)) for g in (np.isnan, np.isposinf, np.isneginf)]
+    assert all(same), same
+    ok = np.isfinite(f)
+    assert np.linalg.norm(f[ok].astype(np.float64) - t[ok]) <= 2e-5 * np.linalg.norm(f[ok].astype(np.float64))   # the bar, twice
+
+
+def test_sums_of_small_operands_that_vanish():
+    """Products below the smallest fp32 normal, alone and next to operands of either size: a sum of 0 is not taken for
+    granted where the operands are small, and is where they are not."""
+    d = mc.make_desc(2, 8, 8, 32, 64, 1, 1, 1, 0)
+    X, W, _ = inputs(d, 9)
+    for sx, sw in [(1e-22, 1e-20), (1e-40, 1e-3), (1e-3, 1e-40)]:
+        a, b = X * np.float32(sx), W * np.float32(sw)
+        ref = gu.run_oracle("fwd", d, a, b)
+        force("fwd", d, (64, 64), 1, mc.PRODUCTS_TERMS)
+        got = run("fwd", d, a, b).astype(np.float64)
+        # subnormal results: each of 32 products and sums may be rounded to a multiple of 2^-149
+        assert np.abs(got - ref).max() <= 64 * 2.0 ** -149, (sx, sw)
+
+
+@pytest.mark.parametrize("shp", [(64, 8, 8, 32, 64, 1, 1, 1, 0), (64, 8, 8, 64, 64, 3, 3, 1, 1), (64, 8, 8, 256, 128, 3, 3, 1, 1)])
+def test_one_sided_sums(shp):
+    """Both operands positive: the matrix pipe cuts bf16 sums towards minus infinity, which one-sided sums show most.
+    2-norm error against 64-bit sums no larger than with fp32 products, forward and backward-data (every element is a sum
+    of one sign, so the error has no scatter worth allowing for)."""
+    d = mc.make_desc(*shp)
+    X, W, G = [np.abs(t) for t in inputs(d, 8)]
+    err = {}
+    for products in PRODUCTS:
+        for op in ("fwd", "bwd_data"):
+            force(op, d, (64, 64), 1, products)
+            a, b = gu.operands(op, X, W, G)
+            err[op, products] = gu.errors(run(op, d, a, b), gu.run_oracle(op, d, a, b))[0]
+    print(shp, {k: "%.2e" % v for k, v in err.items()}, flush=True)
+    for op in ("fwd", "bwd_data"):
+        assert err[op, mc.PRODUCTS_TERMS] <= err[op, mc.PRODUCTS_FP32], (op, err)
+
+
+def test_sums_with_one_product():
+    """A filter with one nonzero element per output channel: the six term products leave out at most 2^-24 of a product,
+    each of the five small ones may be cut by 2^-30 of it, and the last addition rounds by 2^-24."""
+    d = mc.make_desc(8, 8, 8, 64, 64, 1, 1, 1, 0)
+    X, W, _ = inputs(d, 4)
+    keep = np.zeros(W.shape, bool)
+    keep[np.arange(64), 0, 0, (np.arange(64) * 7) % 64] = True
+    W = np.where(keep, W, np.float32(0))
+    ref = gu.run_oracle("fwd", d, X, W)
+    for products, bound in [(mc.PRODUCTS_FP32, 2.0 ** -24), (mc.PRODUCTS_TERMS, 2.0 ** -23 + 5 * 2.0 ** -30)]:
+        force("fwd", d, (64, 64), 1, products)
+        assert (np.abs(run("fwd", d, X, W) - ref) <= bound * np.abs(ref)).all(), products
