@@ -221,6 +221,8 @@ double terms_cost(const TermsCost &k, const TermsTile &c, long long tiles, doubl
     return balanced ? t * 0.985 : t;
 }
 
+constexpr double kNoPlan = 1e300;   // the cost of a plan that must not be taken
+
 // Best slice count for one candidate; returns the cost.  cost(split, stages of the busiest CU or < 0).
 // busiestFn (optional): stages of the busiest CU for a slice count under the order the launch will use, or a
 // negative value where unknown.  Where it is known for every candidate slice count, the slice count is
@@ -243,7 +245,7 @@ double best_split(const CostFn &cost, double avgStages, long long outElems, int 
         *splitOut = forced < maxS ? forced : maxS;
         return cost(*splitOut, -1.0);
     }
-    double best = 1e300;
+    double best = kNoPlan;
     int bestS = 1;
     for (int sp = 1; sp <= maxS; ++sp) {
         const double t = cost(sp, -1.0) * uneven(sp);
@@ -721,7 +723,7 @@ Plan plan_bwd_weight(const Shape &s)
     }
     int fbm = 0, fbn = 0;
     const bool haveForced = forced_tile(&fbm, &fbn, false);
-    double best = 1e300;
+    double best = kNoPlan;
     // three-term kernel: offsets in 32 bits, and in (oh,ow,n) order the 64-bit mask of positions
     const bool termsTake = !pl.elem && (long long)s.N * s.IH * s.IW * s.IC * 4 < (1LL << 31) && M * s.OC * 4 < (1LL << 31) &&
                            (!posMajor || ohow <= 64);
@@ -748,12 +750,14 @@ Plan plan_bwd_weight(const Shape &s)
                 pl.split = sp;
             }
         };
-        // the general fp32 kernel (maps that are not aligned) lost to the three-term one on every such layer of the sweep
-        if (!termsTake || (products_allowed(false) && (pl.fast || !products_allowed(true))))
+        auto consider_fp32 = [&]() {
             for (const TileCand &c : kWgradTiles)
                 consider(c.bm, c.bn, false, [&](long long tiles, int n) {
                     return kFp32WgradUs[1] + kFp32WgradUs[0] * launch_cost(kWgradCost, c, tiles, chunks * live, (double)chunks, n, pl.outElems);
                 });
+        };
+        // the general fp32 kernel (maps that are not aligned) lost to the three-term one on every such layer of the sweep
+        if (!termsTake || (products_allowed(false) && (pl.fast || !products_allowed(true)))) consider_fp32();
         if (products_allowed(true) && termsTake)
             for (const TermsTile &c : kWgradTermsTiles)
                 consider(c.bm, c.bn, true, [&](long long tiles, int n) {
@@ -761,9 +765,10 @@ Plan plan_bwd_weight(const Shape &s)
                     // dealing (4x4x256 -> 512: 36.9 us on 216 128 x 128 tiles, 34.1 on 576 64 x 64; 8x8x256 -> 256: 61.8 on
                     // 252, 61.6 on 504 64 x 128).
                     const double lone = posMajor && tiles * n <= 256 ? 1.15 : 1.0;
-                    if (chunks * live > (double)kTermsMaxStages * n && products_allowed(false)) return 1e290;   // chains too long
+                    if (chunks > (long long)kTermsMaxStages * n && products_allowed(false)) return kNoPlan;   // chains too long (a tile may keep all stages)
                     return lone * terms_cost(kWgradTermsCost, c, tiles, chunks * live, chunks * live, n, pl.outElems);
                 });
+        if (pl.bm == 0 && products_allowed(false)) consider_fp32();   // no slice count keeps the chains short: the kernels that fold
     }
     pl.posMajor = posMajor;
     pl.tilesM = ceil_div(s.OC, pl.bm);

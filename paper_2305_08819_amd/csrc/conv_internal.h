@@ -539,9 +539,9 @@ inline bool wgrad_fast_accepts(int N, int OH, int OW, int IC, int OC, int posMaj
     if (posMajor && (wide || N % kBK != 0 || ohow > 64)) return false;
     return ((bm == 128 || bm == 64) && (bn == 128 || bn == 64)) || (bm == 32 && bn == 128);
 }
-// Stages of one slice (two waves take 16 of the 32 products of a stage each): chains of 2048 products on the two
-// accumulators of the three-term kernel have the error of 256 products in an fp32 MFMA chain (512 stages measure
-// 5.6e-7 against 64-bit sums, fp32 chains of 512 products 4.1e-7).
+// Stages of one slice at most (two waves take 16 of the 32 products of a stage each).  At 128 stages, 4096 products in two
+// halves, the two accumulators of the three-term kernel measure 2.7e-7 against 64-bit sums where fp32 chains folded every
+// 512 products measure 4.1e-7; sums of products of one sign 1.6e-7 against 1.2e-7.  512 stages: 5.6e-7.
 constexpr int kTermsMaxStages = 128;
 // Backward-weight on three-term operands: the maps above plus, where all offsets fit (tensors below 2^31
 // bytes), any other map; (oh,ow,n) order needs only whole stages per position and the 64-bit mask.

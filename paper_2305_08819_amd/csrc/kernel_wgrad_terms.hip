@@ -29,8 +29,8 @@
 // Bound like the forward kernel: the bf16 pipe inside, about 12 us of launch, first loads, exchange and tail around it.
 // Against the fp32 kernels: 4x4x512 -> 512 at N = 128 59.7 -> 48.3 us, the 14x14 5x5 layer's three operators 351 -> 231
 // (its dW came from the general fp32 kernel, 148 us).
-// Accuracy: a slice is at most kTermsMaxStages stages, 16 products each per wave, so that its two accumulators
-// (see split_bf16.h) stay at least as exact as fp32 chains of 512 products.
+// Accuracy: a slice is at most kTermsMaxStages stages (unless these products are forced), 16 products each per wave, so that
+// its two accumulators (see split_bf16.h) stay about as exact as fp32 chains of 512 products; nothing is folded.
 #include <hip/hip_runtime.h>
 #include "split_bf16.h"
 

@@ -362,3 +362,37 @@ def test_plan_queries_from_many_threads(lib):
     assert not errors, errors
     for t in range(8):
         assert got[t] == want, t
+
+
+def test_three_term_slices_keep_their_length(lib):
+    """Backward-weight on three-term operands does not fold its accumulators, so the planner gives it at most 128 stages
+    of 32 rows a slice and takes an fp32 kernel, which folds, where no slice count within the limits allows that:
+    many rows with a large output (the workspace bounds the slices), more rows than 1024 slices hold, forced counts."""
+    q, products = mc.conv2d_query_plan, lambda d: mc.conv2d_query_products(mc.OP_BWD_WEIGHT, d)
+    large = [mc.make_desc(512, 31, 31, 512, 512, 3, 3, 1, 1), mc.make_desc(128, 45, 45, 512, 512, 5, 5, 1, 2),
+             mc.make_desc(66, 255, 257, 64, 64, 3, 3, 1, 1), mc.make_desc(66, 256, 256, 64, 64, 3, 3, 1, 1)]
+    for d in large:
+        p = q(mc.OP_BWD_WEIGHT, d)
+        mc.conv2d_set_products(mc.PRODUCTS_FP32)
+        try:
+            f = q(mc.OP_BWD_WEIGHT, d)
+        finally:
+            mc.conv2d_set_products(mc.PRODUCTS_AUTO)
+        assert products(d) == mc.PRODUCTS_FP32, (d.N, d.IH, d.IW, p.split, p.grid)
+        assert (p.tile_m, p.tile_n, p.split, p.grid) == (f.tile_m, f.tile_n, f.split, f.grid)
+    taken = 0
+    try:
+        for N in (32, 100, 512, 2048):
+            for hw in (1, 2, 3, 4, 7, 8, 14, 16, 31, 32):
+                for C, F in ((16, 1), (64, 3), (512, 3), (512, 5)):
+                    for split in (0, 1, 5):
+                        mc.conv2d_set_tuning(mc.VARIANT_AUTO, split)
+                        d = mc.make_desc(N, hw, hw, C, C, F, F, 1, F // 2)
+                        if products(d) != mc.PRODUCTS_TERMS:
+                            continue
+                        p, stages = q(mc.OP_BWD_WEIGHT, d), (N * hw * hw + 31) // 32
+                        assert -(-stages // p.split) <= 128, (N, hw, C, F, split, p.split)   # the longest tile keeps all of them
+                        taken += 1
+    finally:
+        mc.conv2d_set_tuning(mc.VARIANT_AUTO, 0)
+    assert taken > 100
