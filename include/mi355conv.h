@@ -215,12 +215,14 @@ int conv2d_bwd_weight(const float *X, const float *dY, float *dW, const conv2d_d
                       void *ws, size_t ws_bytes, void *stream);
 
 /* Backward-weight for callers that cannot allocate device memory or bring a workspace: code
- * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same operator,
- * same plan and same kernels as conv2d_bwd_weight; the slice partials go to a device array that is
+ * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same operator
+ * as conv2d_bwd_weight; the slice partials go to a device array that is
  * part of the library (conv2d_noalloc_scratch_bytes() bytes, 32 MiB, held by every GPU the library
  * runs on until the process ends) instead of a caller workspace.  The call allocates nothing and
- * frees nothing.  Returns MI355CONV_ERR_WORKSPACE, before any HIP call, when the shape needs more
- * than that (conv2d_workspace_bytes(MI355CONV_OP_BWD_WEIGHT, d) tells).  All calls on one GPU share
+ * frees nothing.  Where conv2d_bwd_weight's workspace (conv2d_workspace_bytes(MI355CONV_OP_BWD_WEIGHT, d))
+ * fits the array, plan, kernels and result are its own, bit for bit; where it does not, the plan is the one under
+ * MI355CONV_PRODUCTS_FP32, which has fewer slices, and the result is that plan's.  Returns MI355CONV_ERR_WORKSPACE,
+ * before any HIP call, when the shape needs more than the array under both.  All calls on one GPU share
  * that GPU's array: two such calls that may run at the same time on one GPU (different streams)
  * race; calls on one stream are ordered and safe.  Nothing in the array needs clearing between
  * calls (every partial that is read was written by the same call).  As with every operator, the

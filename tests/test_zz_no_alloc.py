@@ -64,6 +64,28 @@ def test_noalloc_matches_workspace_entry_point_twice_in_a_row():
     assert needs[1] < needs[0]
 
 
+def test_noalloc_takes_the_fp32_plan_where_only_that_fits():
+    """A layer whose automatic plan needs more than the array and whose plan with fp32 products does not: the result
+    is that plan's, bit for bit."""
+    d = mc.make_desc(128, 14, 14, 192, 96, 5, 5, 1, 2)
+    assert mc.conv2d_workspace_bytes(mc.OP_BWD_WEIGHT, d) > mc.conv2d_noalloc_scratch_bytes()
+    X, G = _inputs(d, 7)
+    buf, out = gu.guarded((d.OC, d.FH, d.FW, d.IC))
+    mc.conv2d_bwd_weight_noalloc(gu.nan_fenced(X), gu.nan_fenced(G), out, d)
+    torch.cuda.synchronize()
+    assert gu.guards_intact(buf)
+    got = out.cpu().numpy()
+    mc.conv2d_set_products(mc.PRODUCTS_FP32)
+    try:
+        assert mc.conv2d_workspace_bytes(mc.OP_BWD_WEIGHT, d) <= mc.conv2d_noalloc_scratch_bytes()
+        ref_gpu = gu.run_gpu("bwd_weight", d, X, G)
+    finally:
+        mc.conv2d_set_products(mc.PRODUCTS_AUTO)
+    assert np.array_equal(got, ref_gpu)
+    rel, mx = gu.errors(got, gu.run_oracle("bwd_weight", d, X, G))
+    assert rel <= gu.REL_L2_TOL and mx <= gu.MAX_ABS_TOL, (rel, mx)
+
+
 def test_noalloc_rejects_shapes_beyond_its_array():
     lib = mc.load()
     mc.conv2d_set_tuning(mc.VARIANT_MFMA, 64)      # many slices of a 9.4 MB result: far beyond 32 MiB
