@@ -37,6 +37,49 @@ __device__ __forceinline__ Digits digits(int n, int d, const FastDiv &f)
 }
 }  // namespace
 
+// One element from its definition: the products of taps inside the image only.  The matrix form multiplies what lies outside by
+// 0, and 0 times an infinite or NaN partner is NaN, so elements that come out not finite are formed again here (fp32
+// chains of 16 products added in fp64, like the others; kept small, not fast).
+template <int OP>
+__device__ __forceinline__ float short_element(const ShortParams &p, int r, int c)
+{
+    const Shape &s = p.s;
+    const int tapC = OP == MI355CONV_OP_BWD_WEIGHT ? c / s.IC : 0, ic = c - tapC * s.IC;
+    const int pw = r % p.pixW, ph = r / p.pixW % p.pixH, n = r / p.pixW / p.pixH;
+    double sum = 0.;
+    float chain = 0.f;
+    int held = 0;
+    for (int k = 0; k < p.depth; ++k) {
+        const int tap = k / p.ch, ch = k - tap * p.ch;   // forward, backward-data
+        const int fh = (OP == MI355CONV_OP_BWD_WEIGHT ? tapC : tap) / s.FW, fw = (OP == MI355CONV_OP_BWD_WEIGHT ? tapC : tap) % s.FW;
+        int a, b;
+        if (OP == MI355CONV_OP_FWD) {
+            const int y = ph * s.sh - s.ph + fh, x = pw * s.sw - s.pw + fw;
+            if (y < 0 || x < 0 || y >= s.IH || x >= s.IW) continue;
+            a = ((n * s.IH + y) * s.IW + x) * s.IC + ch;
+            b = c * p.depth + k;
+        } else if (OP == MI355CONV_OP_BWD_DATA) {
+            const int ty = ph + s.ph - fh, tx = pw + s.pw - fw;
+            if (ty < 0 || tx < 0 || ty % s.sh || tx % s.sw || ty / s.sh >= s.OH || tx / s.sw >= s.OW) continue;
+            a = ((n * s.OH + ty / s.sh) * s.OW + tx / s.sw) * s.OC + ch;
+            b = (ch * s.FH * s.FW + tap) * s.IC + c;
+        } else {
+            const int ow = k % s.OW, oh = k / s.OW % s.OH, img = k / s.OW / s.OH;
+            const int y = oh * s.sh - s.ph + fh, x = ow * s.sw - s.pw + fw;
+            if (y < 0 || x < 0 || y >= s.IH || x >= s.IW) continue;
+            a = k * s.OC + r;
+            b = ((img * s.IH + y) * s.IW + x) * s.IC + ic;
+        }
+        chain = fmaf(p.A[a], p.B[b], chain);
+        if (++held == 16) {
+            sum += (double)chain;
+            chain = 0.f;
+            held = 0;
+        }
+    }
+    return (float)(sum + (double)chain);
+}
+
 template <int OP, bool QUAD>
 __global__ __launch_bounds__(kShortWaves * 64) void short_kernel(const ShortParams p)
 {
@@ -144,6 +187,7 @@ __global__ __launch_bounds__(kShortWaves * 64) void short_kernel(const ShortPara
         float v = (float)sum;
         const int r = tile.hi * 32 + i, c = tile.lo * 32 + j;
         if (r < p.rows && c < p.cols) {
+            if ((__builtin_bit_cast(unsigned, v) & 0x7f800000u) == 0x7f800000u) v = short_element<OP>(p, r, c);
             if (p.epi) {
                 v += p.bias ? p.bias[c] : 0.f;
                 v = v > 0.f ? v : v * p.slope;

@@ -56,3 +56,52 @@ def test_short_forward_with_bias_and_activation():
     # fewer than 40 fp32 roundings on the way to a sum (chains of 16, two or three of them added, fp64 from there), each of
     # a partial sum below four times the largest result
     assert np.abs(got - ref).max() <= 40 * 2.0 ** -24 * 4 * np.abs(ref).max()
+
+
+NONFINITE = [(1, 4, 4, 16, 56, 3, 3, 2, 1), (3, 5, 7, 12, 20, 3, 3, 2, 1), (2, 6, 5, 9, 7, 3, 2, (1, 2), (1, 0)),
+             (4, 8, 8, 5, 16, 3, 3, 1, 1), (128, 2, 2, 32, 32, 3, 3, 1, 1), (1, 11, 9, 16, 28, 5, 5, 1, 2), (64, 1, 1, 260, 33, 1, 1, 1, 0),
+             (300, 1, 1, 700, 30, 1, 1, 1, 0)]
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+@pytest.mark.parametrize("shp", NONFINITE)
+def test_non_finite_operands_reach_what_their_taps_reach(shp, value):
+    """One such element in either operand: infinite and NaN results are the definition's.  Taps outside the image, and taps
+    of another stride phase, are not products: 0 times infinity must not be formed for them."""
+    d = mc.make_desc(*shp)
+    X, W, G = inputs(d, 3)
+    short = [op for op in (mc.OP_FWD, mc.OP_BWD_DATA, mc.OP_BWD_WEIGHT) if is_short(op, d)]
+    assert short, shp
+    for code in short:
+        op = ("fwd", "bwd_data", "bwd_weight")[code]
+        for which in (0, 1):
+            ab = [t.copy() for t in gu.operands(op, X, W, G)]
+            ab[which].reshape(-1)[ab[which].size // 3] = value
+            shape = {"fwd": (d.N, d.OH, d.OW, d.OC), "bwd_data": (d.N, d.IH, d.IW, d.IC), "bwd_weight": (d.OC, d.FH, d.FW, d.IC)}[op]
+            out = torch.empty(shape, device="cuda")
+            fn = {"fwd": mc.conv2d_fwd, "bwd_data": mc.conv2d_bwd_data, "bwd_weight": mc.conv2d_bwd_weight}[op]
+            print("non-finite", shp, op, which, value, flush=True)
+            fn(torch.from_numpy(ab[0]).cuda(), torch.from_numpy(ab[1]).cuda(), out, d)
+            got, ref = out.cpu().numpy().astype(np.float64), np.asarray(gu.run_oracle(op, d, *ab))
+            for kind in (np.isnan, np.isposinf, np.isneginf):
+                assert np.array_equal(kind(got), kind(ref)), (op, which, kind.__name__)
+            ok = np.isfinite(ref)
+            assert np.linalg.norm(got[ok] - ref[ok]) <= gu.REL_L2_TOL * np.linalg.norm(ref[ok])
+
+
+def test_non_finite_before_bias_and_activation():
+    """The element formed again takes bias and slope like the others."""
+    d = mc.make_desc(3, 6, 5, 5, 12, 3, 3, 1, 1)
+    assert is_short(mc.OP_FWD, d)
+    X, W, _ = inputs(d, 5)
+    W[1, 0, 0, 2], W[2, 2, 2, 1] = float("inf"), float("nan")
+    bias = wl.normal01(wl.stream_key("short", 6), (d.OC,))
+    Y = torch.empty(3, 6, 5, 12, device="cuda")
+    mc.conv2d_fwd_bias_act(torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda(), torch.from_numpy(bias).cuda(), Y, d, 0.25)
+    ref = np.asarray(gu.run_oracle("fwd", d, X, W)) + bias
+    ref = np.where(ref > 0, ref, 0.25 * ref)
+    got = Y.cpu().numpy().astype(np.float64)
+    for kind in (np.isnan, np.isposinf, np.isneginf):
+        assert np.array_equal(kind(got), kind(ref)), kind.__name__
+    ok = np.isfinite(ref)
+    assert np.isnan(ref).any() and ok[0, 0, :, 1].all() and np.linalg.norm(got[ok] - ref[ok]) <= gu.REL_L2_TOL * np.linalg.norm(ref[ok])
