@@ -484,15 +484,7 @@ Plan plan_fwd(const Shape &s)
             const std::function<double(int)> busiest = [&](int split) {
                 return order ? regional_busiest_stages(s, false, bm, bn, split, chunksPerTap) : -1.0;
             };
-            // Maps of 17 to 64 positions, 129 to 256 channels, forward: about four workgroups a CU, which is what the
-            // longest-first dealing needs to even out nine-, six- and four-tap tiles.  (8x8x256 -> 256: 62.9 us with four
-            // 128 x 64 tiles per CU; one 128 x 128 tile per CU takes 54.6, but as long as its longest tile.)
-            const bool wantsFour = terms && padded && s.N % bm == 0 && s.OH * s.OW > 16 && s.OH * s.OW <= kSmallMapPixels &&
-                                   chunksPerTap > 4 && chunksPerTap <= 8;
-            auto of = [&](int n, double exact) {
-                return cost(tiles, avgStages, maxStages, n, pl.outElems, balanced, exact) *
-                       (wantsFour && tiles * n > 128 && tiles * n < 1024 ? 1.25 : 1.0);
-            };
+            auto of = [&](int n, double exact) { return cost(tiles, avgStages, maxStages, n, pl.outElems, balanced, exact); };
             const double t = best_split(of, avgStages, pl.outElems, &sp, order ? &busiest : nullptr, chunksPerTap);
             if (t < best) {
                 best = t;

@@ -137,6 +137,9 @@ def test_longest_first_dealing_is_a_permutation_and_balances(lib):
     for op, d, region_wise in [c + (1,) for c in cases] + [c + (0,) for c in cases]:
         mc.conv2d_set_tuning(mc.VARIANT_AUTO, 1 if op == mc.OP_BWD_WEIGHT else 0)   # backward-weight: one slice
         mc.conv2d_set_order(region_wise)
+        if d.IH == 8:      # four slices of 128 x 64 tiles: the planner's own pick is one 128 x 128 tile per CU, which is not dealt
+            mc.conv2d_set_tuning(mc.VARIANT_AUTO, 4)
+        mc.conv2d_set_tile(*((128, 64) if d.IH == 8 else (0, 0)), -1)
         pl = mc.conv2d_query_plan(op, d)
         assert pl.pos_major == 1 and pl.grid > 256
         # every XCD owns a group of the tiles unless that is switched off
@@ -151,6 +154,7 @@ def test_longest_first_dealing_is_a_permutation_and_balances(lib):
         mean = sum(load) / 256.0
         if pl.grid <= 1024:     # resident at once (64x64 tiles: four per CU); larger grids refill as workgroups finish
             assert max(load) <= 1.5 * mean if pl.grid < 512 else max(load) <= 1.1 * mean, (op, pl.grid, max(load), mean)
+    mc.conv2d_set_tile(0, 0, -1)
     mc.conv2d_set_tuning(mc.VARIANT_AUTO, 0)
     mc.conv2d_set_order(1)
     with pytest.raises(mc.Mi355ConvError):
@@ -396,3 +400,13 @@ def test_three_term_slices_keep_their_length(lib):
     finally:
         mc.conv2d_set_tuning(mc.VARIANT_AUTO, 0)
     assert taken > 100
+
+
+def test_forward_and_backward_data_of_a_square_layer_get_alike_plans(lib):
+    """Forward and unit-stride backward-data of a layer with as many input as output channels multiply the same tiles, so
+    one model that ranks both by their cost alone picks the same tile, slices and products for both."""
+    for N, hw, C in [(128, 4, 512), (128, 8, 256), (128, 8, 160), (256, 8, 192), (128, 7, 256), (128, 16, 128), (64, 8, 224)]:
+        d = mc.make_desc(N, hw, hw, C, C, 3, 3, 1, 1)
+        f, b = [(lambda p: (p.tile_m, p.tile_n, p.split, p.pos_major, p.grid))(mc.conv2d_query_plan(op, d)) + (mc.conv2d_query_products(op, d),)
+                for op in (mc.OP_FWD, mc.OP_BWD_DATA)]
+        assert f == b, (N, hw, C, f, b)
