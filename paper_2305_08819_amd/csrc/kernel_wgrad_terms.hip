@@ -562,14 +562,15 @@ template <int BM, int BN>
 static hipError_t raise_lds_limit()
 {
     constexpr size_t bytes = SW<BM, BN>::SMEM;
-    if (bytes <= 64 * 1024) return hipSuccess;
-    const void *kerns[4] = {reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kRows>),
-                            reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kPos>),
-                            reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kWide>),
-                            reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kAny>)};
-    for (const void *k : kerns) {
-        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        if (e != hipSuccess) return e;
+    if constexpr (bytes > 64 * 1024) {
+        const void *kerns[4] = {reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kRows>),
+                                reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kPos>),
+                                reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kWide>),
+                                reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kAny>)};
+        for (const void *k : kerns) {
+            const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+            if (e != hipSuccess) return e;
+        }
     }
     return hipSuccess;
 }
@@ -580,7 +581,7 @@ hipError_t prepare_wgrad_terms()
     if (e == hipSuccess) e = raise_lds_limit<64, 128>();
     if (e == hipSuccess) e = raise_lds_limit<128, 64>();
     if (e == hipSuccess) e = raise_lds_limit<64, 64>();
-    if (e == hipSuccess) e = raise_lds_limit<32, 128>();
+    static_assert(SW<32, 128>::SMEM <= 64 * 1024, "the 32 x 128 tile fits the default limit");
     return e;
 }
 
@@ -594,7 +595,7 @@ hipError_t launch_wgrad_terms(const WgradParams &p, int bm, int bn, int grid, hi
         if (mode == kPos) return launch_terms_one<BM_, BN_, kPos>(p, grid, st);        \
         if (mode == kRows) return launch_terms_one<BM_, BN_, kRows>(p, grid, st);      \
         if (mode == kWide) return launch_terms_one<BM_, BN_, kWide>(p, grid, st);      \
-        return launch_terms_one<BM_, BN_, kAny>(p, grid, st);                          \
+        if constexpr (BM_ != 32) return launch_terms_one<BM_, BN_, kAny>(p, grid, st); \
     }
     MI355CONV_WF(128, 128)
     MI355CONV_WF(64, 128)

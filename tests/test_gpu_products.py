@@ -31,12 +31,12 @@ def inputs(d, seed):
 
 
 # (N, IH, IW, IC, OC, FH, FW, stride, pad): one stage, two, three and many; ragged rows, columns and channels;
-# (y,x,n) rows; stride phases with and without taps; more than 512 workgroups of the 64 x 64 tile
+# (y,x,n) rows; stride phases with and without taps; 512 workgroups of the 64 x 64 tile (eight waves each) and 1024 (four)
 GATHER_SHAPES = [
     (3, 5, 7, 32, 40, 1, 1, 1, 0), (2, 9, 9, 64, 64, 1, 1, 1, 0), (1, 12, 11, 96, 132, 1, 1, 1, 0),
     (128, 4, 4, 64, 160, 3, 3, 1, 1), (128, 3, 5, 48, 72, 3, 3, 1, 1), (128, 6, 6, 32, 64, 3, 3, 2, 1),
     (5, 9, 7, 36, 96, 3, 3, 1, 1), (4, 9, 9, 64, 32, 1, 1, 2, 0), (2, 11, 6, 20, 28, 5, 3, (2, 1), (2, 0)),
-    (128, 16, 16, 32, 64, 1, 1, 1, 0),
+    (128, 16, 16, 32, 64, 1, 1, 1, 0), (128, 16, 16, 72, 72, 1, 1, 1, 0),
 ]
 
 
@@ -83,6 +83,10 @@ def test_wgrad_tiles(shp, tile, split, products):
     mc.conv2d_set_products(products)
     mc.conv2d_set_tuning(mc.VARIANT_MFMA, split)
     mc.conv2d_set_tile(tile[0], tile[1], -1)
+    p = mc.conv2d_query_plan(mc.OP_BWD_WEIGHT, d)
+    if (p.tile_m, p.tile_n) != tile:    # the planner's pick instead: only the 32-row tile, which is for aligned maps
+        aligned = (32 % d.OW == 0 and (d.OH * d.OW % 32 == 0 or 32 % (d.OH * d.OW) == 0)) or d.OW % 32 == 0
+        assert tile == (32, 128) and not aligned, (p.tile_m, p.tile_n)
     gu.check_all_ops(d, *inputs(d, hash(shp) & 0xffff), ops=("bwd_weight",), label=str(shp), twice=True)
 
 
