@@ -72,7 +72,7 @@ typedef struct conv2d_desc {
 enum {
     MI355CONV_VARIANT_AUTO = -1,
     MI355CONV_VARIANT_DIRECT = 0,  /* one thread per output element; any shape             */
-    MI355CONV_VARIANT_MFMA = 1     /* implicit GEMM on v_mfma_f32_32x32x2_f32, LDS-staged  */
+    MI355CONV_VARIANT_MFMA = 1     /* implicit GEMM on the matrix cores                     */
 };
 
 /* What the host-side selection picked for a problem (the paper's "operators selected by a
@@ -95,7 +95,8 @@ enum {
     MI355CONV_ORDER_REGIONS = 2    /* every XCD owns a part of the tiles that shares operands          */
 };
 
-/* Kernel families (conv2d_plan_info.kernel); for tests, which force every compiled variant. */
+/* Kernel families (conv2d_plan_info.kernel); for tests, which force every compiled variant.  GATHER, WGRAD and
+ * WGRAD_FAST name the loader and map, whichever way the products are formed: conv2d_query_products tells that. */
 enum {
     MI355CONV_KERNEL_DIRECT = 0,       /* kernels for any shape: one thread per element (variant DIRECT), one
                                           32 x 32 block per workgroup (variant MFMA, short calls)   */

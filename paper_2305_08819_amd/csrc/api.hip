@@ -290,10 +290,13 @@ const TileCand kWgradTiles[] = {{128, 128, 0.80, 1}, {64, 128, 0.93, 2}, {128, 6
                                 {32, 128, 0.90, 3}};
 
 // Fitted, like the constants above, to tile x slices x row order sweeps of 49 layers with either family of products
-// (6 476 forward / backward-data and 5 394 backward-weight timings), made while the kernels kept one accumulator per
-// sum: the picks were 2.1 % / 1.8 % slower than the fastest plan of the sweep on average.  The fp32 MFMA kernels stay because they start and end faster: up to
-// about eight stages per workgroup they win (matrix product 256 x 256 x 32 4.2 against 5.2 us, R7s forward
-// 8.6 / 9.6), beyond that they take 0.50 us a stage against 0.47 (64 x 64 tile, one per CU) and 1.9 against 0.9 (128 x 128).
+// (6 476 forward / backward-data and 5 394 backward-weight timings).  The kernels of that sweep kept one accumulator per sum and
+// did not look at their operands' magnitudes; the ones below take 2 to 6 % longer, and the constants have not been fitted
+// again (charging all three-term plans 4 % more made worse picks: 4x4x512 -> 512 dW would go from 53 to 59 us).  Over 500 drawn
+// calls with today's kernels the three-term pick is slower than the best fp32 pick by more than 2 % in 9 (by up to 23 %).
+// The fp32 MFMA kernels stay because they start and end faster: they win small launches with few stages per
+// workgroup (matrix product 256 x 256 x 32 4.2 against 5.2 us, R7s forward 8.6 / 9.6), and up to some 16 where a launch is one
+// workgroup per CU (2x2x512 -> 512); beyond that they take 0.50 us a stage against 0.47 (64 x 64 tile, one per CU) and 1.9 against 0.9 (128 x 128).
 // kFp32GatherUs, kFp32WgradUs tie the two models' scales together: us = factor * model + offset.
 constexpr TermsCost kGatherTermsCost = {7.33, 1.53, 0.45, 0.134, 2.19, 8.7e6};
 constexpr TermsCost kWgradTermsCost = {11.9, 2.88, 0.384, 0.019, 1.5, 4.3e6};
@@ -1024,6 +1027,8 @@ void plan_balance_gather(const Shape &s, Plan &pl, bool bwd)
         pl.unitWork[i] = (unsigned char)(work[i] < 255 ? work[i] : 255);
     }
     pl.itemsPerClassUnit = (s.N / pl.bm) * pl.tilesN * pl.split;
+    // workgroups a CU holds of the fp32 MFMA kernels; of the three-term kernels three 64 x 64 (two with eight waves) and one 128 x 128,
+    // so larger launches of those are dealt as if resident and the later laps start as CUs come free
     const int resident = pl.bm * pl.bn <= 64 * 64 ? 4 : 2;
     build_balance_runs(work, nPos, pl.itemsPerClassUnit, pl.grid, resident, &pl.runs);
     pl.balance = 1;
@@ -1126,6 +1131,7 @@ bool plan_regional_gather(const Shape &s, Plan &pl, bool bwd)
     pl.regPerPos = pl.regRowTiles * pl.regCsPer;
     pl.regW = rw;
     pl.itemsPerClassUnit = pl.regPerPos;
+    // as in plan_balance_gather: the fp32 MFMA kernels' residency
     const int resident = pl.bm * pl.bn <= 64 * 64 ? 4 : 2;
     pl.regSnake = pl.grid / 8 <= 32 * resident;
     pl.regional = 1;
@@ -1204,6 +1210,7 @@ void plan_balance_wgrad(const Shape &s, Plan &pl)
         work[i] = live[order[i]];
         pl.unitWork[i] = (unsigned char)(work[i] < 255 ? work[i] : 255);
     }
+    // workgroups a CU holds of the fp32 MFMA kernels; of the three-term kernel three 64 x 64, the others alike
     const int resident = pl.bm * pl.bn <= 64 * 64 ? 4 : pl.bm * pl.bn >= 128 * 128 ? 1 : 2;
     pl.balance = 1;
     // Group-wise order: the 8 XCDs (workgroup id % 8, one L2 each) divide the tiles as (A groups of
@@ -1289,7 +1296,6 @@ constexpr size_t kMaxCachedPlans = 4096;   // the map is emptied when it grows p
 std::mutex g_planMutex;
 std::unordered_map<PlanKey, Plan, PlanKeyHash> *g_planMap = nullptr;   // allocated on first use, never freed
 
-// products: which family may serve the call (default: the process-wide override).
 // Calls whose plan takes two launches, or loads element by element, for a few microseconds of work: one launch of
 // short_kernel instead, or of the direct backward-weight kernel.  Replayed graphs, us, before -> after:
 //   forward, sums of at most 512 products (two batches of loads per wave; a batch costs 1.9): 512x256 by 256x512 in 4 slices
@@ -1320,6 +1326,7 @@ ShortChoice short_choice(int op, const Shape &s, const Plan &pl)
     return few && x.depth <= 256 && (pl.smallIc ? pl.split > 1 : !pl.fast) ? kShortKernel : kKeepPlan;
 }
 
+// products: which family may serve the call (default: the process-wide override).
 int make_plan(int op, const Shape &s, Plan *pl, int products = g_forceProducts.load())
 {
     if (op != MI355CONV_OP_FWD && op != MI355CONV_OP_BWD_DATA && op != MI355CONV_OP_BWD_WEIGHT)

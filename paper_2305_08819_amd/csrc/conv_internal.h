@@ -12,7 +12,7 @@ struct Shape {
     int OH, OW;
 };
 
-constexpr int kThreads = 256;     // every MFMA kernel runs 4 wavefronts per workgroup
+constexpr int kThreads = 256;     // the fp32 MFMA kernels run 4 wavefronts per workgroup
 constexpr int kBK = 32;           // reduction elements staged per LDS stage
 constexpr int kMaxPhases = 16;    // sh*sw limit of the MFMA backward-data variant
 constexpr int kMaxBalancedPositions = 256;
