@@ -6,7 +6,7 @@
 // output tile and walks the reduction in stages of kBK = 32 source channels of one tap:
 //   global (NHWC fp32, 16-byte loads along the channel axis) -> registers -> three bf16 terms -> LDS
 //   -> MFMA fragments.
-// Every operand element is split and looked at once per workgroup, on its way to LDS (7 vector instructions each).
+// Every operand element is split and looked at once per workgroup, on its way to LDS (6 vector instructions each).
 //
 // Two things make it a small-feature-map operator (paper Sec. IV: special conv\deconv
 // operators that cut the work more the smaller the map is):
@@ -54,7 +54,7 @@ struct SG {
     static constexpr bool DIRECT = PA + PB > 4;   // split elements go straight to LDS: no registers to hold them for a stage
     static constexpr int A_PLANE = BM * kBK * 2, B_PLANE = BN * kBK * 2;   // bytes of one term's tile
     static constexpr int STAGE = 3 * (A_PLANE + B_PLANE);
-    static constexpr int TABLE_INTS = 4 * BM + 2 * WAVES;   // row tables, and the waves' least operands
+    static constexpr int TABLE_INTS = 4 * BM + WAVES;   // row tables, and what each wave has seen of its operands
     static constexpr size_t SMEM = 2 * STAGE + TABLE_INTS * sizeof(int);
     static_assert(B_ROWS % B_RPP == 0 && BM % A_RPP == 0, "loader passes");
     static_assert(NBLK % 2 == 0 || NBLK == 1, "the two waves of a pair finish half of the blocks each, or one finishes the only block");
@@ -111,7 +111,7 @@ __device__ __forceinline__ void gather_block_store(const P &p, float *C, bool ep
 
 // The fp32 form of a tile, for operands that three bf16 terms do not hold: v_mfma_f32_32x32x2_f32 on
 // fragments read straight from memory.  A wave redoes the blocks it finishes, on
-// its own.  Reached only through split_check and split_suspect, so it is kept small, not fast (a launch that redoes every
+// its own.  Reached only through split_lost and split_suspect, so it is kept small, not fast (a launch that redoes every
 // tile takes two to three times as long).
 template <class T, bool BWD, class P>
 __device__ __forceinline__ void gather_redo_fp32(const P &p, const GatherTile &tile, __amdgpu_buffer_rsrc_t rsrcA,
@@ -182,7 +182,7 @@ __global__ __launch_bounds__((SG<BM, BN, BWD, FINE>::THREADS), (FINE ? 4 : BM * 
     int *rowY = rowBase + BM;
     int *rowX = rowY + BM;
     int *outRow = rowX + BM;
-    unsigned *leasts = reinterpret_cast<unsigned *>(outRow + BM);
+    int *lost = outRow + BM;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -348,12 +348,10 @@ __global__ __launch_bounds__((SG<BM, BN, BWD, FINE>::THREADS), (FINE ? 4 : BM * 
     int bStore = 3 * T::A_PLANE + (BWD ? bRow * (BN * 2) + (((bSeg >> 3) ^ kSwz(bRow)) << 6) + (bSeg & 7) * 8
                                        : bRow * 64 + (((bSeg >> 1) ^ ((bRow >> 2) & 3)) << 4) + (bSeg & 1) * 8);
     static_assert(T::A_RPP % 16 == 0 && T::B_RPP % 16 == 0, "the exchange of pieces is the same in every loader pass");
-    unsigned leastA = kLeastNone, leastB = kLeastNone;   // least magnitudes split so far (see split_bf16.h)
+    unsigned rest = 0u;     // what the terms left of the elements split so far (see split_bf16.h)
     SplitQuad pk[kItems];   // the next stage's elements, split, on their way to LDS
     auto split_item = [&](int q, const f4 *raw) __attribute__((always_inline)) {
-        pk[q] = split_quad(raw[q]);
-        if (q < T::PA) leastA = least_of(leastA, raw[q]);
-        else leastB = least_of(leastB, raw[q]);
+        pk[q] = split_quad(raw[q], rest);
         // the compiler would otherwise move the arithmetic down to the stores, a stage later, in one lump
         asm volatile("" : "+v"(pk[q].h), "+v"(pk[q].m), "+v"(pk[q].l));
     };
@@ -549,27 +547,19 @@ __global__ __launch_bounds__((SG<BM, BN, BWD, FINE>::THREADS), (FINE ? 4 : BM * 
                 if (kh) mine[at] = acc[o][r];
             }
         }
-    leastA = wave_least(leastA);
-    leastB = wave_least(leastB);
-    if (lane == 0) {
-        leasts[wave] = leastA;
-        leasts[T::WAVES + wave] = leastB;
-    }
+    const int mineLost = split_lost(rest);
+    if (lane == 0) lost[wave] = mineLost;
     __syncthreads();
+    bool bad = false;
 #pragma unroll
-    for (int w = 0; w < T::WAVES; ++w) {
-        leastA = min(leastA, leasts[w]);
-        leastB = min(leastB, leasts[T::WAVES + w]);
-    }
-    const SplitCheck check = split_check(leastA, leastB);
-    bool bad = check.lost;
+    for (int w = 0; w < T::WAVES; ++w) bad = bad || lost[w] != 0;
     if (finishes) {
 #pragma unroll
         for (int o = 0; o < T::NOWN; ++o)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 own[o][r] += theirs[(o * 32 + 8 * (r / 4) + 4 * lh + r % 4) * kLDT + l32];
-                bad = bad || split_suspect(own[o][r], check);
+                bad = bad || split_suspect(own[o][r]);
             }
     }
     if (!finishes) return;   // no barrier follows

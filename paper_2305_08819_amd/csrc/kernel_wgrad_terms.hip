@@ -51,7 +51,7 @@ struct SW {
     static constexpr int X_TPR = BN / 4, X_RPP = THREADS / X_TPR, PX = kBK / X_RPP;
     static constexpr int G_PLANE = kBK * BM * 2, X_PLANE = kBK * BN * 2;   // bytes of one term's tile
     static constexpr int STAGE = 3 * (G_PLANE + X_PLANE);
-    static constexpr size_t SMEM = 2 * STAGE + 2 * WAVES * sizeof(unsigned);   // stages, and the waves' least operands
+    static constexpr size_t SMEM = 2 * STAGE + WAVES * sizeof(int);   // stages, and what each wave has seen of its operands
     static_assert(NB == 2, "the two waves of a pair finish one block column each");
     static_assert(WAVES * NOWN * 32 * kLDT * 4 <= 2 * STAGE, "exchange buffers fit over the stages");
 };
@@ -73,7 +73,7 @@ __global__ __launch_bounds__((SW<BM, BN>::THREADS), 2) void wgrad_terms_kernel(c
     constexpr bool PM = MODE == kPos;
     extern __shared__ f4 smem_raw[];
     char *smem = reinterpret_cast<char *>(smem_raw);
-    unsigned *leasts = reinterpret_cast<unsigned *>(smem + 2 * T::STAGE);
+    int *lost = reinterpret_cast<int *>(smem + 2 * T::STAGE);
 
     const BalancePrefetch pre = balance_prefetch(params.runs, params.tapOrder);   // in flight with the scalar arguments
     const WgradView p = wgrad_view(params);
@@ -309,11 +309,9 @@ __global__ __launch_bounds__((SW<BM, BN>::THREADS), 2) void wgrad_terms_kernel(c
     int xStore = 3 * T::G_PLANE + xRow * (BN * 2) + (((xSeg >> 3) ^ row_swizzle<BN>(xRow)) << 6) + (xSeg & 7) * 8;
     static_assert(T::G_RPP % 4 == 0 && T::X_RPP % 4 == 0, "the exchange of pieces is the same in every loader pass");
     int sBuf = T::STAGE, rBuf = T::STAGE;   // distance to the other buffer
-    unsigned leastG = kLeastNone, leastX = kLeastNone;   // least magnitudes split so far (see split_bf16.h)
+    unsigned rest = 0u;     // what the terms left of the elements split so far (see split_bf16.h)
     auto lds_store_item = [&](int q, const f4 *raw) __attribute__((always_inline)) {
-        const SplitQuad s = split_quad(raw[q]);
-        if (q < T::PG) leastG = least_of(leastG, raw[q]);
-        else leastX = least_of(leastX, raw[q]);
+        const SplitQuad s = split_quad(raw[q], rest);
         char *d = q < T::PG ? smem + gStore + q * T::G_RPP * BM * 2 : smem + xStore + (q - T::PG) * T::X_RPP * BN * 2;
         const int plane = q < T::PG ? T::G_PLANE : T::X_PLANE;
         *reinterpret_cast<u2 *>(d) = s.h;
@@ -463,26 +461,18 @@ __global__ __launch_bounds__((SW<BM, BN>::THREADS), 2) void wgrad_terms_kernel(c
             own[o][r] = kh ? d : e;
             mine[(o * 32 + 8 * (r / 4) + 4 * lh + r % 4) * kLDT + l32] = kh ? e : d;
         }
-    leastG = wave_least(leastG);
-    leastX = wave_least(leastX);
-    if (lane == 0) {
-        leasts[wave] = leastG;
-        leasts[T::WAVES + wave] = leastX;
-    }
+    const int mineLost = split_lost(rest);
+    if (lane == 0) lost[wave] = mineLost;
     __syncthreads();
+    bool bad = false;
 #pragma unroll
-    for (int w = 0; w < T::WAVES; ++w) {
-        leastG = min(leastG, leasts[w]);
-        leastX = min(leastX, leasts[T::WAVES + w]);
-    }
-    const SplitCheck check = split_check(leastG, leastX);
-    bool bad = check.lost;
+    for (int w = 0; w < T::WAVES; ++w) bad = bad || lost[w] != 0;
 #pragma unroll
     for (int o = 0; o < T::NOWN; ++o)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             own[o][r] += theirs[(o * 32 + 8 * (r / 4) + 4 * lh + r % 4) * kLDT + l32];
-            bad = bad || split_suspect(own[o][r], check);
+            bad = bad || split_suspect(own[o][r]);
         }
     const int col = col0 + wn * T::WTN + kh * 32 + l32;   // this lane's column in every block it finishes
     if (__any(bad)) {

@@ -1,6 +1,6 @@
 // fp32 products on the bf16 matrix pipe: every fp32 operand is held as three bf16 terms,
 // x = h + m + l (each term the remainder of the one before, rounded to nearest: 3 x 8 significant
-// bits, so the sum is exact for |x| between 2^-102 and the bf16 maximum), and a product is the six
+// bits, so the sum is exact for |x| between 2^-110 and the bf16 maximum), and a product is the six
 // term products of weight 2^-16 and above, summed in the fp32 accumulator of v_mfma_f32_32x32x16_bf16
 // (the three-term decomposition of Henry, Tang and Heinecke, "Leveraging the bfloat16 artificial
 // intelligence datatype for higher-precision computations", 2019).  What is left out (m*l, l*m, l*l) is at most 2^-24
@@ -37,9 +37,12 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b)   // round to ne
 __device__ __forceinline__ float bf16_low(unsigned w) { return __builtin_bit_cast(float, w << 16); }
 __device__ __forceinline__ float bf16_high(unsigned w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
 
-// 5.5 vector instructions per value.  (v_dot2_f32_bf16 with (-1, 0) forms x - h in one instruction instead of
-// two, 3.5 per value, but runs against the MFMAs: a stage of a lone 64 x 64 tile 0.61 -> 0.68 us.)
-__device__ __forceinline__ SplitQuad split_quad(const f4 &x)
+// 5.5 vector instructions per value, and half a one for `rest`.  (v_dot2_f32_bf16 with (-1, 0) forms x - h in one instruction
+// instead of two, 3.5 per value, but runs against the MFMAs: a stage of a lone 64 x 64 tile 0.61 -> 0.68 us.)
+// rest collects the bits of the last remainders.  The third term is such a remainder's upper half, so it is exact if and
+// only if the lower half is zero: for every finite x of at least 2^-110 (24 bits reach down to 2^-133, bf16's last place), and
+// for smaller ones that happen to end there.
+__device__ __forceinline__ SplitQuad split_quad(const f4 &x, unsigned &rest)
 {
     SplitQuad s;
 #pragma unroll
@@ -48,10 +51,13 @@ __device__ __forceinline__ SplitQuad split_quad(const f4 &x)
         const unsigned h = pack_bf16(a, b);
         const float ra = a - bf16_low(h), rb = b - bf16_high(h);   // exact
         const unsigned m = pack_bf16(ra, rb);
+        const float qa = ra - bf16_low(m), qb = rb - bf16_high(m);
         s.h[i] = h;
         s.m[i] = m;
-        s.l[i] = pack_bf16(ra - bf16_low(m), rb - bf16_high(m));
+        s.l[i] = pack_bf16(qa, qb);
+        rest |= __builtin_bit_cast(unsigned, qa) | __builtin_bit_cast(unsigned, qb);
     }
+    asm("" : "+v"(rest));   // left to itself the compiler keeps a stage's remainders for a tree: 15 registers more
     return s;
 }
 
@@ -61,66 +67,20 @@ constexpr int kSplitProducts = 6;
 constexpr int kProdA[kSplitProducts] = {1, 2, 0, 1, 0, 0};
 constexpr int kProdB[kSplitProducts] = {1, 0, 2, 0, 1, 0};
 
-// Where the three terms do not stand for the fp32 value, the kernels redo the block with fp32 MFMA.  Found in two places:
+// Where the three terms do not stand for the fp32 value, the kernels redo the block with fp32 MFMA:
 //  * infinities, NaN and values that round to infinity in bf16: the sum is not finite;
-//  * nonzero operands below 2^-102, whose lower terms reach below the smallest normal bf16 (2^-126): while they are split.
-//    The sum cannot show it - a lost 2^-135 next to a partner of 2^127 is a lost 0.004, and a sum of lost products is 0.
-//    Every thread keeps the least magnitude it has split, in the order of (bits << 1) - 1, which drops the sign and makes
-//    zero the largest.  1.5 vector instructions per value beside the 5.5 of the split, which costs 2 to 6 % of a call
-//    (128 x 8x8x256 backward-data 57.9 -> 60.1 us, 14x14 5x5 192 -> 48 dW 80.3 -> 85.0); v_cmp_class_f32 on the last remainder
-//    is one instruction less per pair but slower (its scalar results: 66.0 -> 69.1 us where this takes 68.0).
-// Where both operands are small, products or partial sums may fall below the smallest fp32 although every operand keeps
-// its terms: a sum below 2^-80 (zero among them) is redone if the least operands' product is below 2^-100.  Sums of 2^-80
-// and above lose less than their last place to that.
-constexpr unsigned kLeastNone = 0xffffffffu;          // nothing but zeros
-constexpr unsigned kLeastSplit = (25u << 24) - 1u;    // 2^-102
-__device__ __forceinline__ unsigned least_of(unsigned least, const f4 &x)
-{
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const unsigned a = (__builtin_bit_cast(unsigned, (float)x[2 * i]) << 1) - 1u;
-        const unsigned b = (__builtin_bit_cast(unsigned, (float)x[2 * i + 1]) << 1) - 1u;
-        const unsigned ab = a < b ? a : b;
-        least = ab < least ? ab : least;
-    }
-    asm("" : "+v"(least));   // left to itself the compiler keeps a stage's values for a tree of minima: 15 registers more
-    return least;
-}
-
-// Least over the 64 lanes, in every lane.
-__device__ __forceinline__ unsigned wave_least(unsigned v)
-{
-#define MI355_LEAST_STEP(CTRL_)                                                                                     \
-    {                                                                                                               \
-        const unsigned o = (unsigned)__builtin_amdgcn_update_dpp((int)kLeastNone, (int)v, CTRL_, 0xf, 0xf, false);  \
-        v = o < v ? o : v;                                                                                          \
-    }
-    MI355_LEAST_STEP(0x111)   // row_shr:1, 2, 4, 8: lane 15 of a row holds the row's least
-    MI355_LEAST_STEP(0x112)
-    MI355_LEAST_STEP(0x114)
-    MI355_LEAST_STEP(0x118)
-    MI355_LEAST_STEP(0x142)   // row_bcast:15, 31: lane 63 holds the wave's
-    MI355_LEAST_STEP(0x143)
-#undef MI355_LEAST_STEP
-    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
-}
-
-// What the least operands of a workgroup say about its sums (uniform).
-struct SplitCheck {
-    bool lost;         // an operand that its terms do not hold: redo
-    unsigned below;    // magnitudes below this (as bits) are redone
-};
-__device__ __forceinline__ SplitCheck split_check(unsigned leastA, unsigned leastB)
-{
-    SplitCheck c;
-    c.lost = leastA < kLeastSplit || leastB < kLeastSplit;
-    c.below = (leastA >> 24) + (leastB >> 24) < 2 * 127 - 100 ? 0x17800000u : 0u;   // 2^-80
-    return c;
-}
-__device__ __forceinline__ bool split_suspect(float v, const SplitCheck &c)
+//  * operands with bits below 2^-133: `rest` shows them while they are split.  The sum cannot: a lost 2^-135 next to a
+//    partner of 2^127 is a lost 0.004, and a sum of lost products is 0.  The workgroup joins what its threads have seen;
+//  * sums that are not zero and below 2^-80, where products of exact terms may have lost places below the smallest fp32.
+// The MFMA takes subnormal bf16 operands and gives subnormal sums as they are (gfx942 and later do not flush them).
+// The look at the operands costs 1 to 3 % of a call (128 x 8x8x256 backward-data 55.5 -> 56.7 us, 14x14 5x5 192 -> 48 dW 77.9 -> 79.2).
+// Looking at their magnitudes instead - the minimum of (bits << 1) - 1, 1.5 instructions per value - cost 2 to 6 %, and
+// v_cmp_class_f32 on the remainders more (its results go through scalar registers).
+__device__ __forceinline__ bool split_lost(unsigned rest) { return __builtin_amdgcn_ballot_w64((rest & 0xffffu) != 0u) != 0ull; }
+__device__ __forceinline__ bool split_suspect(float v)
 {
     const unsigned u = __builtin_bit_cast(unsigned, v) & 0x7fffffffu;
-    return u >= 0x7f800000u || u < c.below;
+    return u >= 0x7f800000u || u - 1u < 0x17800000u - 1u;   // u = 0 wraps to the largest value
 }
 
 // 4 consecutive reduction elements of 16 neighbouring columns, transposed on the way out of LDS:

@@ -195,7 +195,7 @@ def far_from_one(op, a, b, kind):
     whole: one tensor small, the other large.  hidden: only one element in 32 of the reduction (or one image) is
     such a pair, so that an ordinary part of every sum covers it."""
     a, b = a.copy(), b.copy()
-    small, large = {"1e-37": (1e-37, 1e33), "1e-42": (1e-42, 1e36), "hidden": (1e-37, 1e37)}[kind]
+    small, large = {"1e-37": (1e-37, 1e33), "1e-42": (1e-42, 1e36), "hidden": (1e-37, 1e37), "2^-133": (1.0, 1e37)}[kind]
     pick = slice(None) if kind != "hidden" else slice(0, 1)
     if op == "fwd":            # reduction over the channels of X and W
         a[..., pick] *= np.float32(small)
@@ -206,10 +206,14 @@ def far_from_one(op, a, b, kind):
     else:                      # over images
         a[pick] *= np.float32(small)
         b[pick] *= np.float32(large)
+    if kind == "2^-133":                # what bf16 holds below its smallest normal: the terms are exact, and subnormal
+        i = 1 if op == "bwd_data" else 0
+        t = (a, b)[i]
+        t[...] = np.clip(np.rint(t * 64), -255, 255) * np.float32(2.0 ** -133)
     return a, b
 
 
-@pytest.mark.parametrize("kind", ["1e-37", "1e-42", "hidden"])
+@pytest.mark.parametrize("kind", ["1e-37", "1e-42", "hidden", "2^-133"])
 @pytest.mark.parametrize("op,shp,tile,split", REDO)
 def test_small_operand_with_a_large_partner(op, shp, tile, split, kind):
     """Against the oracle, at the parity tests' bar."""
