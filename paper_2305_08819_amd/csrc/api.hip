@@ -306,7 +306,8 @@ constexpr double kFp32GatherUs[2] = {1.023, 1.85}, kFp32WgradUs[2] = {0.906, -0.
 const TermsTile kGatherTermsTiles[] = {{128, 128, 1, {0.872, 0.872, 0.872}}, {128, 64, 2, {0.587, 0.760, 0.760}},
                                        {64, 64, 3, {0.614, 0.630, 0.669}}, {128, 32, 2, {0.404, 0.380, 0.380}}};
 const TermsTile kWgradTermsTiles[] = {{128, 128, 1, {0.835, 0.835, 0.835}}, {64, 128, 2, {0.570, 0.770, 0.770}},
-                                      {128, 64, 2, {0.600, 0.772, 0.772}}, {64, 64, 3, {0.570, 0.650, 0.719}}};
+                                      {128, 64, 2, {0.600, 0.772, 0.772}}, {64, 64, 3, {0.570, 0.650, 0.719}},
+                                      {32, 128, 2, {0.354, 0.563, 0.563}}};
 
 // Whether a family of products may serve the call under the override.
 bool products_allowed(bool terms)
@@ -726,7 +727,7 @@ Plan plan_bwd_weight(const Shape &s)
     for (int pass = 0; pass < 2 && pl.bm == 0; ++pass) {   // second pass: the forced tile does not apply here
         auto consider = [&](int bm, int bn, bool terms, const std::function<double(long long, int)> &cost) {
             if (pl.elem && bn != 64) return;   // element-wise X loader is compiled for 64-wide tiles
-            // one block row (fp32 kernel for aligned maps only): narrow outputs, or a channel count whose last 64-row tile
+            // one block row (aligned maps only): narrow outputs, or a channel count whose last 64-row tile
             // would be at most half used
             if (bm == 32 && (!pl.fast || (s.OC > 32 && !(s.OC % 64 != 0 && s.OC % 64 <= 32)))) return;
             if (pass == 0 && haveForced && !(pl.elem && fbn != 64)) {

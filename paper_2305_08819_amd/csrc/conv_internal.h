@@ -544,11 +544,12 @@ inline bool wgrad_fast_accepts(int N, int OH, int OW, int IC, int OC, int posMaj
 // 512 products measure 4.1e-7; sums of products of one sign 1.6e-7 against 1.2e-7.  512 stages: 5.6e-7.
 constexpr int kTermsMaxStages = 128;
 // Backward-weight on three-term operands: the maps above plus, where all offsets fit (tensors below 2^31
-// bytes), any other map; (oh,ow,n) order needs only whole stages per position and the 64-bit mask.
+// bytes), any other map on the tiles of 64 and 128 rows; (oh,ow,n) order needs only whole stages per position and the 64-bit mask.
 inline bool wgrad_terms_accepts(int N, int OH, int OW, int IC, int OC, int posMajor, int bm, int bn)
 {
     if (IC % 4 != 0 || OC % 4 != 0) return false;
     if (posMajor && (N % kBK != 0 || OH * OW > 64)) return false;
+    if (bm == 32) return wgrad_fast_accepts(N, OH, OW, IC, OC, posMajor, bm, bn);   // aligned maps only
     return (bm == 128 || bm == 64) && (bn == 128 || bn == 64);
 }
 inline bool bwd_data_small_ic_accepts(int IC, int OC, int FH, int FW, int sh, int sw)
@@ -612,7 +613,7 @@ hipError_t launch_wgrad(const WgradParams &p, int bm, int bn, bool xElem, int gr
 // order only), IC % 4 == 0, OC % 4 == 0,
 // tensors below 2^31 bytes.
 hipError_t launch_wgrad_fast(const WgradParams &p, int bm, int bn, int grid, hipStream_t st);
-// same tiles (except 32x128), any map, products on the bf16 matrix pipe (three-term operands)
+// same tiles, any map, products on the bf16 matrix pipe (three-term operands)
 hipError_t launch_wgrad_terms(const WgradParams &p, int bm, int bn, int grid, hipStream_t st);
 // unit stride, FH*FW*IC <= 32, IC <= 4, OC % 32 == 0, (4+FH-1)*(32+FW-1) <= 224, tensors below 2^31 bytes
 hipError_t launch_bwd_data_small_ic(const SmallIcParams &p, hipStream_t st);

@@ -26,8 +26,6 @@
 //    offset and read zeros, so there is no branch and no zero-select.
 //  * The tile is cut into wave tiles of up to 64 x 64 and the two 16-row halves of a stage go to the two
 //    waves of a pair, which add their accumulators at the end (see kernel_gather_terms.hip for why).
-// No tile of 32 rows: its 64-wide wave tiles split twice as many values per MFMA, and it lost to the fp32 kernel's on 17 of 17
-// calls (16x16 256 -> 32 5x5 122.1 against 117.7 us, 128 x 30x32 224 -> 32 140 against 130, 384 x 4x4 240 -> 32 5x5 29.8 against 24.8).
 // Bound like the forward kernel: the bf16 pipe inside, about 12 us of launch, first loads, exchange and tail around it.
 // Against the fp32 kernels: 4x4x512 -> 512 at N = 128 59.7 -> 48.3 us, the 14x14 5x5 layer's three operators 351 -> 231
 // (its dW came from the general fp32 kernel, 148 us).
@@ -554,14 +552,15 @@ template <int BM, int BN>
 static hipError_t raise_lds_limit()
 {
     constexpr size_t bytes = SW<BM, BN>::SMEM;
-    if (bytes <= 64 * 1024) return hipSuccess;
-    const void *kerns[4] = {reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kRows>),
-                            reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kPos>),
-                            reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kWide>),
-                            reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kAny>)};
-    for (const void *k : kerns) {
-        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-        if (e != hipSuccess) return e;
+    if constexpr (bytes > 64 * 1024) {
+        const void *kerns[4] = {reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kRows>),
+                                reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kPos>),
+                                reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kWide>),
+                                reinterpret_cast<const void *>(wgrad_terms_kernel<BM, BN, kAny>)};
+        for (const void *k : kerns) {
+            const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+            if (e != hipSuccess) return e;
+        }
     }
     return hipSuccess;
 }
@@ -572,6 +571,7 @@ hipError_t prepare_wgrad_terms()
     if (e == hipSuccess) e = raise_lds_limit<64, 128>();
     if (e == hipSuccess) e = raise_lds_limit<128, 64>();
     if (e == hipSuccess) e = raise_lds_limit<64, 64>();
+    static_assert(SW<32, 128>::SMEM <= 64 * 1024, "the 32 x 128 tile fits the default limit");
     return e;
 }
 
@@ -585,12 +585,13 @@ hipError_t launch_wgrad_terms(const WgradParams &p, int bm, int bn, int grid, hi
         if (mode == kPos) return launch_terms_one<BM_, BN_, kPos>(p, grid, st);        \
         if (mode == kRows) return launch_terms_one<BM_, BN_, kRows>(p, grid, st);      \
         if (mode == kWide) return launch_terms_one<BM_, BN_, kWide>(p, grid, st);      \
-        return launch_terms_one<BM_, BN_, kAny>(p, grid, st);                          \
+        if constexpr (BM_ != 32) return launch_terms_one<BM_, BN_, kAny>(p, grid, st); \
     }
     MI355CONV_WF(128, 128)
     MI355CONV_WF(64, 128)
     MI355CONV_WF(64, 64)
     MI355CONV_WF(128, 64)
+    MI355CONV_WF(32, 128)
 #undef MI355CONV_WF
     return hipErrorInvalidValue;
 }

@@ -84,9 +84,9 @@ def test_wgrad_tiles(shp, tile, split, products):
     mc.conv2d_set_tuning(mc.VARIANT_MFMA, split)
     mc.conv2d_set_tile(tile[0], tile[1], -1)
     p = mc.conv2d_query_plan(mc.OP_BWD_WEIGHT, d)
-    if (p.tile_m, p.tile_n) != tile:    # the planner's pick instead: only the 32-row tile, which the fp32 kernel for aligned maps has
+    if (p.tile_m, p.tile_n) != tile:    # the planner's pick instead: only the 32-row tile, which is for aligned maps
         aligned = (32 % d.OW == 0 and (d.OH * d.OW % 32 == 0 or 32 % (d.OH * d.OW) == 0)) or d.OW % 32 == 0
-        assert tile == (32, 128) and not (aligned and products == mc.PRODUCTS_FP32), (p.tile_m, p.tile_n)
+        assert tile == (32, 128) and not aligned, (p.tile_m, p.tile_n)
     gu.check_all_ops(d, *inputs(d, hash(shp) & 0xffff), ops=("bwd_weight",), label=str(shp), twice=True)
 
 
@@ -173,7 +173,7 @@ def test_very_small_and_large_operands(shp, op, scales):
 GATHER_REDO = [((128, 4, 4, 64, 96, 3, 3, 1, 1), tile, split) for tile in [(128, 128), (128, 64), (64, 64), (128, 32)] for split in (1, 3)]
 GATHER_REDO += [((5, 9, 7, 36, 44, 3, 3, 2, 1), tile, 1) for tile in [(128, 128), (128, 64), (64, 64), (128, 32)]]
 GATHER_REDO += [((128, 16, 16, 32, 128, 1, 1, 1, 0), (64, 64), 1), ((128, 16, 16, 128, 36, 1, 1, 1, 0), (64, 64), 1)]
-WGRAD_REDO = [(shp, tile, split) for tile in [(128, 128), (64, 128), (128, 64), (64, 64)] for split in (1, 3)
+WGRAD_REDO = [(shp, tile, split) for tile in [(128, 128), (64, 128), (128, 64), (64, 64), (32, 128)] for split in (1, 3)
               for shp in [(64, 4, 4, 64, 96, 3, 3, 1, 1), (2, 4, 64, 16, 72, 3, 3, 1, 1), (8, 8, 8, 64, 160, 3, 3, 1, 1)]]
 WGRAD_REDO += [((3, 7, 5, 32, 72, 3, 3, 1, 1), tile, 3) for tile in [(128, 128), (64, 128), (128, 64), (64, 64)]]
 REDO = [(op,) + c for c in GATHER_REDO for op in ("fwd", "bwd_data")] + [("bwd_weight",) + c for c in WGRAD_REDO]
