@@ -39,6 +39,10 @@ OPS = ("fwd", "bwd_data", "bwd_weight")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "bench_cfg5_hbm_traffic.json")
 
 
+def products_name(op, desc, mc):
+    return "terms" if mc.conv2d_query_products(OPS.index(op), desc) == mc.PRODUCTS_TERMS else "fp32"
+
+
 def kernel_name(layer, op, plan, desc, mc):
     """Name of the main kernel a plan launches, spelled as rocprofv3 prints it."""
     b = lambda v: "true" if v else "false"   # noqa: E731
@@ -51,7 +55,7 @@ def kernel_name(layer, op, plan, desc, mc):
     if plan.kernel == mc.KERNEL_FIRST_LAYER:
         return {"fwd": "fwd_small_ic_kernel<false>", "bwd_data": "bwd_data_small_ic_kernel",
                 "bwd_weight": "wgrad_small_ic_kernel"}[op]
-    terms = mc.conv2d_query_products(OPS.index(op), desc) == mc.PRODUCTS_TERMS
+    terms = products_name(op, desc, mc) == "terms"
     if terms and op == "bwd_weight":
         aligned = 32 % layer.OW == 0 or layer.OW % 32 == 0
         aligned = aligned and (32 % (layer.OH * layer.OW) == 0 or layer.OH * layer.OW % 32 == 0)
@@ -227,8 +231,8 @@ def table(mc, torch, cfg_names, with_oracle=False, with_epilogue=False):
                     cold = r.event_ms(rotate)
                 tf, tfe = layer.flops / ms / 1e9, layer.effective_flops / ms / 1e9
                 pl = r.plans[op]
-                plan = "v%d %dx%d s%d pm%d o%d g%d" % (pl.variant, pl.tile_m, pl.tile_n, pl.split,
-                                                       pl.pos_major, pl.order, pl.grid)
+                plan = "v%d %dx%d s%d pm%d o%d g%d %s" % (pl.variant, pl.tile_m, pl.tile_n, pl.split, pl.pos_major, pl.order,
+                                                          pl.grid, products_name(op, r.desc, mc))
                 gbs = op_bytes(layer, op) / ms / 1e6
                 rows.append({"layer": layer.name, "op": op, "ms": round(ms, 5), "tflops": round(tf, 2),
                              "pct_peak": round(100 * tf / PEAK_FP32_MFMA_TFLOPS, 1),
@@ -331,8 +335,8 @@ def streams_report(mc, torch):
 
 
 def regret_report(mc, torch, names):
-    """Planner pick against an exhaustive sweep of compiled tiles x row orders x slice counts, per
-    layer and operator (the overrides conv2d_set_tile / conv2d_set_tuning drive the sweep)."""
+    """Planner pick against an exhaustive sweep of products x compiled tiles x row orders x slice counts, per layer and
+    operator (the overrides conv2d_set_products / conv2d_set_tile / conv2d_set_tuning drive the sweep)."""
     import itertools
     layers = {l.name: l for l in wl.all_layers()}
     gather_tiles = [(128, 128), (128, 64), (64, 64), (128, 32)]
@@ -345,19 +349,22 @@ def regret_report(mc, torch, names):
             r = LayerRunner(layers[name], mc, torch, random_fill=True)
             r.spin_up()
             for op in OPS:
+                mc.conv2d_set_products(mc.PRODUCTS_AUTO)
                 mc.conv2d_set_tile(0, 0, -1)
                 mc.conv2d_set_tuning(mc.VARIANT_AUTO, 0)
-                pl0 = mc.conv2d_query_plan(opcodes[op], r.desc)
+                pl0, products0 = mc.conv2d_query_plan(opcodes[op], r.desc), products_name(op, r.desc, mc)
                 if pl0.workspace_bytes > r.ws.numel():
                     r.ws = torch.empty(pl0.workspace_bytes, dtype=torch.uint8, device="cuda")
                 base = r.event_ms(lambda: r.run(op), 50, 10, 3)
                 best, best_plan, seen = base, "planner", set()
-                for (bm, bn), pm in itertools.product(wgrad_tiles if op == "bwd_weight" else gather_tiles, (0, 1)):
+                for products, (bm, bn), pm in itertools.product((mc.PRODUCTS_FP32, mc.PRODUCTS_TERMS),
+                                                                wgrad_tiles if op == "bwd_weight" else gather_tiles, (0, 1)):
                     for sp in splits:
+                        mc.conv2d_set_products(products)
                         mc.conv2d_set_tile(bm, bn, pm)
                         mc.conv2d_set_tuning(mc.VARIANT_AUTO, sp)
                         pl = mc.conv2d_query_plan(opcodes[op], r.desc)
-                        key = (pl.tile_m, pl.tile_n, pl.pos_major, pl.split)
+                        key = (pl.tile_m, pl.tile_n, pl.pos_major, pl.split, products_name(op, r.desc, mc))
                         if key in seen or pl.variant != mc.VARIANT_MFMA or not 128 <= pl.grid <= 8192:
                             continue
                         seen.add(key)
@@ -367,16 +374,17 @@ def regret_report(mc, torch, names):
                             r.ws = torch.empty(pl.workspace_bytes, dtype=torch.uint8, device="cuda")
                         ms = r.event_ms(lambda: r.run(op), 30, 5, 3)
                         if ms < best:
-                            best, best_plan = ms, "%dx%d pm%d s%d g%d" % (key + (pl.grid,))
+                            best, best_plan = ms, "%dx%d pm%d s%d %s g%d" % (key + (pl.grid,))
                 rows.append({"layer": name, "op": op, "planner_ms": round(base, 5), "best_ms": round(best, 5),
                              "best_plan": best_plan, "regret_pct": round(100 * (base / best - 1), 1),
-                             "planner_plan": "%dx%d pm%d s%d g%d" % (pl0.tile_m, pl0.tile_n, pl0.pos_major,
-                                                                    pl0.split, pl0.grid)})
-                log("%-4s %-10s planner %-24s %.4f ms | best %.4f ms %-24s | regret %.1f%%"
+                             "planner_plan": "%dx%d pm%d s%d %s g%d" % (pl0.tile_m, pl0.tile_n, pl0.pos_major,
+                                                                       pl0.split, products0, pl0.grid)})
+                log("%-4s %-10s planner %-30s %.4f ms | best %.4f ms %-30s | regret %.1f%%"
                     % (name, op, rows[-1]["planner_plan"], base, best, best_plan, rows[-1]["regret_pct"]))
             del r
             torch.cuda.empty_cache()
     finally:
+        mc.conv2d_set_products(mc.PRODUCTS_AUTO)
         mc.conv2d_set_tile(0, 0, -1)
         mc.conv2d_set_tuning(mc.VARIANT_AUTO, 0)
     return rows
@@ -552,6 +560,9 @@ def main():
                         "pct_peak": round(100 * tf / PEAK_FP32_MFMA_TFLOPS, 1),
                         "tflops_effective": round(tfe, 2), "pct_peak_effective": round(100 * tfe / PEAK_FP32_MFMA_TFLOPS, 1),
                         "gbs": round(op_bytes(l, op) / ms / 1e6, 1),
+                        "products": products_name(op, r.desc, mc),   # pct_peak is of the fp32 MFMA peak for either kind
+                        "pct_products_peak_effective": round(100 * tfe / (PEAK_TERMS_TFLOPS if products_name(op, r.desc, mc) == "terms"
+                                                                          else PEAK_FP32_MFMA_TFLOPS), 1),
                         "kernel": kernel_name(l, op, pl, r.desc, mc), "tile": [pl.tile_m, pl.tile_n], "split": pl.split,
                         "pos_major": pl.pos_major, "grid": pl.grid})
         out["per_op"] = per

@@ -291,11 +291,11 @@ const TileCand kWgradTiles[] = {{128, 128, 0.80, 1}, {64, 128, 0.93, 2}, {128, 6
 
 // Fitted, like the constants above, to tile x slices x row order sweeps of 49 layers with either family of products
 // (6 476 forward / backward-data and 5 394 backward-weight timings).  The kernels of that sweep kept one accumulator per sum and
-// did not look at their operands' magnitudes; the ones below take 2 to 6 % longer, and the constants have not been fitted
+// did not look at their operands' magnitudes; today's take longer by a few per cent, and the constants have not been fitted
 // again (charging all three-term plans 4 % more made worse picks: 4x4x512 -> 512 dW would go from 53 to 59 us).  Of 1517 drawn
-// calls that take three-term kernels today 75 are slower than the planner's fp32 pick by more than 2 % (forward and backward-data by up to
-// 30 %, most of them 128 x 128 tiles with a mostly empty column tile or a second lap of few workgroups; dW by up to 7 %), the
-// rest 1.2 to 1.6 times as fast.  A lap overhead of 5 to 6 us in place of 1.53 made as many other picks worse.
+// calls that take three-term kernels today 79 are slower than the planner's fp32 pick by more than 2 % (forward and backward-data by up to
+// 32 %, most of them 128 x 128 tiles with a mostly empty column tile or a second lap of few workgroups; dW by up to 15 %); all
+// together they are 1.17 (dW 1.37) times as fast.  A lap overhead of 5 to 6 us in place of 1.53 made as many other picks worse.
 // The fp32 MFMA kernels stay because they start and end faster: they win small launches with few stages per
 // workgroup (matrix product 256 x 256 x 32 4.2 against 5.2 us, R7s forward 8.6 / 9.6), and up to some 16 where a launch is one
 // workgroup per CU (2x2x512 -> 512); beyond that they take 0.50 us a stage against 0.47 (64 x 64 tile, one per CU) and 1.9 against 0.9 (128 x 128).
