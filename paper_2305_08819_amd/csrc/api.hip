@@ -298,7 +298,7 @@ const TileCand kWgradTiles[] = {{128, 128, 0.80, 1}, {64, 128, 0.93, 2}, {128, 6
 // together they are 1.17 (dW 1.37) times as fast.  A lap overhead of 5 to 6 us in place of 1.53 made as many other picks worse.
 // The fp32 MFMA kernels stay because they start and end faster: they win small launches with few stages per
 // workgroup (matrix product 256 x 256 x 32 4.2 against 5.2 us, R7s forward 8.6 / 9.6), and up to some 16 where a launch is one
-// workgroup per CU (2x2x512 -> 512); beyond that they take 0.50 us a stage against 0.47 (64 x 64 tile, one per CU) and 1.9 against 0.9 (128 x 128).
+// workgroup per CU (2x2x512 -> 512); beyond that they take 0.50 us a stage against 0.48 (64 x 64 tile, one per CU) and 1.9 against 1.2 (128 x 128).
 // kFp32GatherUs, kFp32WgradUs tie the two models' scales together: us = factor * model + offset.
 constexpr TermsCost kGatherTermsCost = {7.33, 1.53, 0.45, 0.134, 2.19, 8.7e6};
 constexpr TermsCost kWgradTermsCost = {11.9, 2.88, 0.384, 0.019, 1.5, 4.3e6};

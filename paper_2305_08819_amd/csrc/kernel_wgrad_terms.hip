@@ -27,7 +27,7 @@
 //  * The tile is cut into wave tiles of up to 64 x 64 and the two 16-row halves of a stage go to the two
 //    waves of a pair, which add their accumulators at the end (see kernel_gather_terms.hip for why).
 // Bound like the forward kernel: the bf16 pipe inside, about 12 us of launch, first loads, exchange and tail around it.
-// Against the fp32 kernels: 4x4x512 -> 512 at N = 128 59.7 -> 48.3 us, the 14x14 5x5 layer's three operators 351 -> 231
+// Against the fp32 kernels: 4x4x512 -> 512 at N = 128 59.6 -> 49.2 us, the 14x14 5x5 layer's three operators 351 -> 237
 // (its dW came from the general fp32 kernel, 148 us).
 // Accuracy: a slice is at most kTermsMaxStages stages (unless these products are forced), 16 products each per wave, so that
 // its two accumulators (see split_bf16.h) stay about as exact as fp32 chains of 512 products; nothing is folded.
