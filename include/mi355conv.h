@@ -92,7 +92,10 @@ typedef struct conv2d_plan_info {
 enum {
     MI355CONV_ORDER_PLAIN = 0,     /* tiles in id order (ids regrouped so that neighbours share an XCD) */
     MI355CONV_ORDER_LONGEST = 1,   /* unequal tiles dealt longest first to the 256 CUs                 */
-    MI355CONV_ORDER_REGIONS = 2    /* every XCD owns a part of the tiles that shares operands          */
+    MI355CONV_ORDER_REGIONS = 2,   /* every XCD owns a part of the tiles that shares operands          */
+    MI355CONV_ORDER_CONTIGUOUS = 3 /* every XCD owns consecutive row tiles: the forward / backward-data kernel of unit-stride
+                                      layers with equal maps, which gathers a tile's pixels once for all taps; its 64-column
+                                      workgroups take two neighbouring 128 x 64 tiles and are reported as such */
 };
 
 /* Kernel families (conv2d_plan_info.kernel); for tests, which force every compiled variant.  GATHER, WGRAD and

@@ -17,7 +17,7 @@ LIB_PATH = os.environ.get("MI355CONV_LIB") or os.path.join(_PKG, "libmi355conv.s
 OP_FWD, OP_BWD_DATA, OP_BWD_WEIGHT = 0, 1, 2
 VARIANT_AUTO, VARIANT_DIRECT, VARIANT_MFMA = -1, 0, 1
 KERNEL_DIRECT, KERNEL_GATHER, KERNEL_GATHER_ELEM, KERNEL_FIRST_LAYER, KERNEL_WGRAD, KERNEL_WGRAD_FAST = range(6)
-ORDER_PLAIN, ORDER_LONGEST, ORDER_REGIONS = range(3)
+ORDER_PLAIN, ORDER_LONGEST, ORDER_REGIONS, ORDER_CONTIGUOUS = range(4)
 
 EXPORTS = ("conv2d_workspace_bytes", "conv2d_query_plan", "conv2d_query_workgroup", "conv2d_query_tile", "conv2d_set_tuning", "conv2d_set_tile", "conv2d_set_order", "conv2d_set_products", "conv2d_query_products", "conv2d_fwd",
            "conv2d_fwd_bias_act", "conv2d_fwd_u8",

@@ -49,6 +49,7 @@ struct Plan {
     int elem = 0;          // element-wise loader (channel counts the 16-byte loader cannot take)
     int fast = 0;          // backward-weight: aligned map
     int terms = 0;         // products on the bf16 matrix pipe (three-term operands) instead of fp32 MFMA
+    int halo = 0;          // forward / backward-data: the kernel that splits the gathered tensor once for all taps (with terms)
     int shortCall = 0;     // one launch of short_kernel (variant DIRECT: any shape, no workspace)
     int smallIc = 0;       // backward-data: patch-gradient GEMM + col2im kernel for very few input channels
     int grid = 0;
@@ -419,6 +420,57 @@ void for_each_gather_tile(const Visit &visit)
                   }));
 }
 
+// The kernel that splits the gathered tensor once for all taps (halo_terms_kernel), one workgroup a CU.  Constants fitted to 1 470 timings
+// of 146 layers (tile x slices, forward and backward-data; rms 4.5 %): us per stage of one tap when the chip is full (its clock falls to 1.7
+// GHz then) and when few CUs have work, launch, workgroup, results stored, combine pass.
+struct HaloCost { double stageFull, stageFew, fixedUs, wgUs, unevenUs, outUsPerMB, reduceUs, reduceUsPerMB, wide; };
+constexpr HaloCost kHaloCost = {0.927, 0.764, 4.16, 1.04, 0.742, 0.320, 3.05, 0.141, 1.031};
+
+// The share of the other plan's cost that it has to undercut.  2 % for the errors of the two models: with that, one of 122 changed picks of
+// 400 drawn calls is slower (4 %), all together are 1.23 times as fast.  (y,x,n) rows that skip more than a quarter of the taps make
+// both kernels about equal (4x4x512 -> 512 47.6 and 46.3 us), so there the older one stays unless the model sees 8 %.
+double halo_margin(int posMajor, double avgTaps, int taps) { return posMajor && avgTaps < 0.75 * taps ? 0.92 : 0.98; }
+
+double halo_cost(const HaloCost &k, long long tiles, int chunks, int taps, int split, long long outElems, bool wide)
+{
+    const long long grid = tiles * split, laps = grid / 256;
+    const double left = (double)(grid % 256) / 256.0, scale = wide ? k.wide : 1.0;
+    const double avg = (double)chunks / split * taps, longest = (double)ceil_div(chunks, split) * taps;
+    double t = k.fixedUs + (double)laps * (k.wgUs + avg * k.stageFull * scale) + (longest - avg) * k.unevenUs;
+    if (left > 0) t += k.wgUs + avg * (k.stageFew + (k.stageFull - k.stageFew) * left * left * left * left) * scale;
+    const double mb = (double)outElems * 4e-6;
+    t += mb * split * k.outUsPerMB;
+    if (split > 1) t += k.reduceUs + (split + 1.0) * mb * k.reduceUsPerMB;
+    return t;
+}
+
+// Its tile and slice count for the call; the cost, or kNoPlan.  A forced tile or row order names one of the other kernels.
+double halo_plan(const Shape &s, bool bwd, long long outElems, int *bmOut, int *bnOut, int *splitOut)
+{
+    double best = kNoPlan;
+    if (!products_allowed(true) || g_forceBM.load() || g_forcePosMajor.load() >= 0) return best;
+    const int cols = bwd ? s.IC : s.OC, chunks = ceil_div(bwd ? s.OC : s.IC, kBK);
+    const long long rows = (long long)s.N * s.IH * s.IW, wsPerSlice = pad4(outElems) * 4;
+    const int forced = g_forceSplit.load(), tiles[2][2] = {{256, 64}, {128, 128}};
+    for (int k = 0; k < 2; ++k) {
+        const int bm = tiles[k][0], bn = tiles[k][1];
+        int lo, span, items;
+        if (!halo_span(s, bm, &lo, &span, &items)) continue;
+        const long long tilesMN = (long long)ceil_div(rows, bm) * ceil_div(cols, bn);
+        for (int sp = 1; sp <= chunks && sp * wsPerSlice <= (long long)kMaxWorkspace; ++sp) {
+            if (forced && sp != std::min(forced, chunks)) continue;
+            const double t = halo_cost(kHaloCost, tilesMN, chunks, s.FH * s.FW, sp, outElems, bn == 128);
+            if (t < best) {
+                best = t;
+                *bmOut = bm;
+                *bnOut = bn;
+                *splitOut = sp;
+            }
+        }
+    }
+    return best;
+}
+
 Plan plan_fwd(const Shape &s)
 {
     Plan pl;
@@ -501,6 +553,14 @@ Plan plan_fwd(const Shape &s)
             }
         }
     });
+    int hbm, hbn, hsp;
+    if (halo_plan(s, false, pl.outElems, &hbm, &hbn, &hsp) < halo_margin(pl.posMajor, avgTapsPos, s.FH * s.FW) * best) {
+        pl.halo = pl.terms = 1;
+        pl.bm = hbm;
+        pl.bn = hbn;
+        pl.posMajor = 0;
+        pl.split = hsp;
+    }
     pl.tilesN = ceil_div(s.OC, pl.bn);
     pl.tilesM = ceil_div(M, pl.bm);
     set_forward_phase(pl, s);
@@ -662,6 +722,16 @@ Plan plan_bwd_data(const Shape &s)
             }
         }
     });
+    int hbm, hbn, hsp;
+    if (s.IC % 4 == 0 && halo_plan(s, true, base.outElems, &hbm, &hbn, &hsp) < halo_margin(pl.posMajor, avgTapsPos, s.FH * s.FW) * best) {
+        pl = base;
+        pl.halo = pl.terms = 1;
+        pl.bm = hbm;
+        pl.bn = hbn;
+        pl.split = hsp;
+        pl.tilesM = ceil_div((long long)s.N * s.IH * s.IW, hbm);
+        pl.tilesN = ceil_div(s.IC, hbn);
+    }
     finish_plan(pl, pl.split);
     return pl;
 }
@@ -811,6 +881,7 @@ int prepare_device(int *devOut)
     if (e == hipSuccess) e = prepare_wgrad_fast();
     if (e == hipSuccess) e = prepare_gather_terms();
     if (e == hipSuccess) e = prepare_wgrad_terms();
+    if (e == hipSuccess) e = prepare_halo_terms();
     void *ptr = nullptr;
     if (e == hipSuccess) e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
     if (e != hipSuccess) return hip_fail(e);
@@ -1176,7 +1247,7 @@ void plan_order_gather(const Shape &s, Plan &pl, bool bwd)
     pl.balance = 0;
     pl.regional = 0;
     pl.chunksPerSlice = 0;
-    if (pl.smallIc) return;
+    if (pl.smallIc || pl.halo) return;
     const int chunks = ceil_div(bwd ? s.OC : s.IC, kBK);
     if (!pl.elem && pl.split > 1 && chunks % pl.split == 0) pl.chunksPerSlice = chunks / pl.split;
     if (g_regionalOrder.load() && plan_regional_gather(s, pl, bwd)) return;
@@ -1274,6 +1345,11 @@ bool plan_launchable(int op, const Shape &s, const Plan &pl)
     const bool bwd = op == MI355CONV_OP_BWD_DATA;
     if (pl.smallIc)
         return bwd ? bwd_data_small_ic_accepts(s.IC, s.OC, s.FH, s.FW, s.sh, s.sw) : patch_small_ic_accepts(s.IC, s.FH, s.FW);
+    if (pl.halo) {
+        int lo, span, items;
+        return ((pl.bm == 128 && pl.bn == 128) || (pl.bm == 256 && pl.bn == 64)) && halo_span(s, pl.bm, &lo, &span, &items) &&
+               pl.split <= ceil_div(bwd ? s.OC : s.IC, kBK);
+    }
     if (pl.posMajor && s.N % pl.bm != 0) return false;   // a row tile sits on one pixel position
     if (pl.elem) return gather_elem_accepts(pl.bm, pl.bn);
     return gather_gemm_accepts(bwd ? s.OC : s.IC, bwd ? s.IC : s.OC, bwd, pl.bm, pl.bn);
@@ -1497,9 +1573,54 @@ void fill_wgrad_geometry(WgradParams &w, const Shape &s, const Plan &pl)
     }
 }
 
+// Arguments of a launch that splits the gathered tensor once for all taps (no pointers, no epilogue).
+void fill_halo_geometry(HaloParams &h, const Shape &s, const Plan &pl, bool bwd)
+{
+    memset(&h, 0, sizeof h);
+    h.M = s.N * s.IH * s.IW;
+    h.H = s.IH;
+    h.W = s.IW;
+    h.SC = bwd ? s.OC : s.IC;
+    h.DC = bwd ? s.IC : s.OC;
+    h.FH = s.FH; h.FW = s.FW; h.ph = s.ph; h.pw = s.pw;
+    h.taps = s.FH * s.FW;
+    h.chunks = ceil_div(h.SC, kBK);
+    h.split = pl.split;
+    h.tilesN = pl.tilesN;
+    halo_span(s, pl.bm, &h.haloLo, &h.span, &h.items);
+    const int sign = bwd ? -1 : 1;   // forward reads row y - ph + u under filter row u, backward-data row y + ph - u
+    h.shift0 = -sign * (s.ph * s.IW + s.pw);
+    h.shiftStep = sign;
+    h.shiftWrap = sign * (s.IW - s.FW);
+    h.shiftChunk = -sign * s.FH * s.IW;
+    h.aBytes = (unsigned)((long long)h.M * h.SC * 4);
+    h.bBytes = (unsigned)((long long)s.OC * h.taps * s.IC * 4);
+    h.sliceStride = pl.sliceStride;
+    // neighbouring row tiles, which share their halo, and the column tiles and slices of one stay on one XCD
+    h.xcdUnit = pl.grid >= 8 ? pl.grid / 8 : 1;
+    h.xcdWhole = pl.grid / (8 * h.xcdUnit) * (8 * h.xcdUnit);
+    h.divXcdUnit = make_fastdiv((unsigned)h.xcdUnit);
+    h.divTilesN = make_fastdiv((unsigned)pl.tilesN);
+    h.divSplit = make_fastdiv((unsigned)pl.split);
+    h.divHW = make_fastdiv((unsigned)(s.IH * s.IW));
+    h.divW = make_fastdiv((unsigned)s.IW);
+}
+
 int run_gather(const float *A, const float *B, float *out, const Shape &s, const Plan &pl, bool bwd,
                void *ws, hipStream_t st, const Epilogue &epi = Epilogue())
 {
+    hipError_t e;
+    if (pl.halo) {
+        HaloParams h;
+        fill_halo_geometry(h, s, pl, bwd);
+        h.A = A;
+        h.B = B;
+        h.C = pl.split > 1 ? static_cast<float *>(ws) : out;
+        h.epilogue = epi.on ? 1 : 0;
+        h.bias = epi.bias;
+        h.slope = epi.slope;
+        e = launch_halo_terms(h, bwd, pl.bm, pl.bn, pl.grid, st);
+    } else {
     GatherGemmParams g;
     fill_gather_geometry(g, s, pl, bwd);
     g.A = A;
@@ -1508,13 +1629,14 @@ int run_gather(const float *A, const float *B, float *out, const Shape &s, const
     g.epilogue = epi.on ? 1 : 0;
     g.bias = epi.bias;
     g.slope = epi.slope;
-    hipError_t e = pl.elem ? launch_gather_elem(g, bwd, pl.bm, pl.bn, pl.grid, st)
+    e = pl.elem ? launch_gather_elem(g, bwd, pl.bm, pl.bn, pl.grid, st)
                    : pl.terms ? launch_gather_terms(g, bwd, pl.bm, pl.bn, pl.grid, st)
                               : launch_gather_gemm(g, bwd, pl.bm, pl.bn, pl.grid, st);
+    }
     if (e != hipSuccess) return hip_fail(e);
     if (pl.split > 1) {
         e = launch_slice_reduce(static_cast<const float *>(ws), out, pl.outElems, pl.split, pl.sliceStride, st,
-                                epi.bias, epi.slope, epi.on ? g.DC : 0);
+                                epi.bias, epi.slope, epi.on ? s.OC : 0);
         if (e != hipSuccess) return hip_fail(e);
     }
     return MI355CONV_OK;
@@ -1542,7 +1664,7 @@ int conv2d_query_plan(int op, const conv2d_desc *d, conv2d_plan_info *info)
     rc = make_plan(op, s, &pl);
     if (rc != MI355CONV_OK) return rc;
     info->variant = pl.shortCall ? MI355CONV_VARIANT_MFMA : pl.variant;
-    info->tile_m = pl.shortCall ? 32 : pl.bm;
+    info->tile_m = pl.shortCall ? 32 : pl.bm == 256 ? 128 : pl.bm;   // 256 rows: two 128 x 64 tiles a workgroup
     info->tile_n = pl.shortCall ? 32 : pl.bn;
     info->split = pl.split;
     info->pos_major = pl.posMajor;
@@ -1552,7 +1674,7 @@ int conv2d_query_plan(int op, const conv2d_desc *d, conv2d_plan_info *info)
     else if (pl.smallIc) info->kernel = MI355CONV_KERNEL_FIRST_LAYER;
     else if (op == MI355CONV_OP_BWD_WEIGHT) info->kernel = pl.fast ? MI355CONV_KERNEL_WGRAD_FAST : MI355CONV_KERNEL_WGRAD;
     else info->kernel = pl.elem ? MI355CONV_KERNEL_GATHER_ELEM : MI355CONV_KERNEL_GATHER;
-    info->order = pl.regional ? MI355CONV_ORDER_REGIONS : pl.balance ? MI355CONV_ORDER_LONGEST : MI355CONV_ORDER_PLAIN;
+    info->order = pl.halo ? MI355CONV_ORDER_CONTIGUOUS : pl.regional ? MI355CONV_ORDER_REGIONS : pl.balance ? MI355CONV_ORDER_LONGEST : MI355CONV_ORDER_PLAIN;
     return MI355CONV_OK;
 }
 

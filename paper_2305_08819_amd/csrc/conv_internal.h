@@ -214,6 +214,41 @@ __device__ __forceinline__ GatherView gather_view(const GatherGemmParams &p)
 }
 #endif
 
+// ---- forward and backward-data of unit-stride layers with equal maps (kernel_halo_terms.hip) ------------
+// Row m of the result is pixel m; under tap t it reads pixel m + shift(t) of the gathered tensor where bit t of its mask is set.
+struct HaloParams {
+    const float *A;       // gathered tensor [M pixels, SC]
+    const float *B;       // filter
+    float *C;             // result [M pixels, DC], or workspace base when split > 1
+    const float *bias;    // may be null
+    unsigned aBytes, bBytes;
+    int M, H, W, SC, DC, FH, FW, ph, pw, taps;
+    int chunks, split;    // 32-channel chunks of SC, cut into split slices
+    int tilesN, xcdUnit, xcdWhole;
+    int haloLo, span, items;   // a tile reads pixels m0 - haloLo .. + span-1, in `items` passes of 64
+    // tap (0,0) reads pixel m + shift0; the next tap is shiftStep further, a new filter row shiftWrap more, a new chunk shiftChunk more
+    int shift0, shiftStep, shiftWrap, shiftChunk;
+    int epilogue;
+    float slope;
+    long long sliceStride;
+    FastDiv divTilesN, divSplit, divXcdUnit, divHW, divW;
+};
+// gathered pixels that the LDS tile of a row tile holds
+constexpr int halo_rows(int bm) { return bm == 256 ? 320 : 256; }
+// The run of pixels that a row tile needs for all taps together: its own where it is whole images, whole rows above and below where it is whole
+// rows, any pixel that a tap reaches otherwise.  False where the kernel does not take the layer.
+inline bool halo_span(const Shape &s, int bm, int *lo, int *span, int *items)
+{
+    if (s.sh != 1 || s.sw != 1 || s.OH != s.IH || s.OW != s.IW || s.IC % 4 != 0 || s.OC % 4 != 0) return false;
+    const long long hw = (long long)s.IH * s.IW, rows = (long long)s.ph * s.IW;
+    if (rows + s.pw > halo_rows(bm) || s.FH > 32 || s.FW > 32) return false;
+    *lo = (int)(bm % hw == 0 ? 0 : bm % s.IW == 0 ? rows : rows + s.pw);
+    *span = bm + 2 * *lo;
+    *items = (*span + 63) / 64;
+    const int taps = s.FH * s.FW;
+    return *items * 64 <= halo_rows(bm) && taps <= 32 && taps >= *items + 2;
+}
+
 // ---- backward-weight ---------------------------------------------------------------------
 // dW[oc, col] = sum over rows m=(n,oh,ow): G[m, oc] * X[n, oh*sh-ph+fh(col), ow*sw-pw+fw(col), ic(col)]
 // with col = (fh*FW + fw)*IC + ic.  The row range is cut into `split` slices.
@@ -565,6 +600,7 @@ hipError_t prepare_wgrad();
 hipError_t prepare_wgrad_fast();
 hipError_t prepare_gather_terms();
 hipError_t prepare_wgrad_terms();
+hipError_t prepare_halo_terms();
 
 hipError_t launch_direct_fwd(const float *X, const float *W, float *Y, const Shape &s, hipStream_t st);
 hipError_t launch_direct_bwd_data(const float *G, const float *W, float *dX, const Shape &s, hipStream_t st);
@@ -606,6 +642,8 @@ hipError_t launch_gather_gemm(const GatherGemmParams &p, bool bwdData, int bm, i
                               hipStream_t st);
 // same tiles and shapes, products on the bf16 matrix pipe (three-term operands)
 hipError_t launch_gather_terms(const GatherGemmParams &p, bool bwdData, int bm, int bn, int grid, hipStream_t st);
+// unit stride, equal maps (halo_span); tiles 128x128 and 256x64
+hipError_t launch_halo_terms(const HaloParams &p, bool bwdData, int bm, int bn, int grid, hipStream_t st);
 // same tiles (except 128x128), element-wise loader: any channel counts
 hipError_t launch_gather_elem(const GatherGemmParams &p, bool bwdData, int bm, int bn, int grid, hipStream_t st);
 hipError_t launch_wgrad(const WgradParams &p, int bm, int bn, bool xElem, int grid, hipStream_t st);

@@ -22,7 +22,9 @@
 // N(0,1) activations, operands in cache: a 128 x 128 stage 1.20 us (224 TFLOP/s of fp32 products; 1.17 before the operands were
 // looked at), three 64 x 64 workgroups 1.28 us for a stage of each (158), a lone eight-wave one 0.48 (140; a CU for itself).
 // The rest is 6 (eight waves) to 12 us of launch, first loads, accumulator exchange and tail.  Against the fp32 MFMA kernel: 32x32x64 -> 64 at
-// N = 128 with bias and activation 76.0 -> 62.3 us, 8x8x256 backward-data 68.3 -> 55.0.
+// N = 128 with bias and activation 76.0 -> 62.3 us, 8x8x256 backward-data 68.3 -> 55.0.  Both of those are faster still where the pixels are
+// split once for all taps (kernel_halo_terms.hip: unit stride, equal maps); this kernel is for the other layers, and for maps of a few
+// pixels, where (y,x,n) rows skip more taps than that saves.
 //
 // Waves: the tile is cut into wave tiles of up to 64 x 64, and the two 16-channel halves of every
 // stage go to the two waves of a pair, which add their accumulators through LDS at the end.  The pair

@@ -1,0 +1,523 @@
+// Forward convolution and backward-data of unit-stride layers whose two maps have the same size (3x3 with padding 1, 5x5 with
+// padding 2, ...), on v_mfma_f32_32x32x16_bf16 with three-term operands (split_bf16.h): the gathered tensor is split once per
+// channel chunk, not once per tap.
+//
+// GEMM view as in kernel_gather_terms.hip: rows = pixels of the tensor being produced in (n, y, x) order, columns = its channels,
+// reduction = (channel chunk of 32, filter tap).  With equal maps the source pixel of row m under a tap (dy, dx) is pixel
+// m + dy*W + dx of the gathered tensor, so the rows of a tile need, for all taps together, one run of consecutive source pixels:
+// the tile's own and a halo of dy*W + dx on either side (none where a tile is whole images, whole rows above and below where it
+// is whole rows).  A chunk of that run is loaded, split and stored to LDS once and serves every tap; a tap only shifts
+// the row index of the fragment reads, and a row whose source pixel lies outside the image (one bit per row and tap) reads a row
+// of zeros.  The filter, which differs from tap to tap, is loaded and split stage by stage as before.
+//
+// Why: a wave issues at most one vector instruction every eight cycles, two waves on a SIMD one every four, so beside the 64 cycles
+// that two waves' MFMAs take there is room for fewer than seven other instructions per MFMA of each wave.  The per-tap split alone
+// took four to six (128 x 128 and 128 x 64 tiles); here it takes two or one, and the loads and LDS stores shrink likewise.
+//
+// Bound by the chip's power: a 256 x 64 stage takes 1870 cycles of the 1536 that its MFMAs need, at 1.7 to 1.8 GHz while all CUs run it
+// (0.97 us; 0.74 with half of them, at 2.3 GHz).  Around the stages of a workgroup are 0.7 us of decode, 1.3 of first loads, 1.1 of the
+// last stage and 2.4 of exchange and stores, and 2 to 3 us of launch.  Both sides in turn, us, gather_terms_kernel and here: 128 x
+// 32x32x64 -> 64 with bias and activation 62.6 and 54.1, 8x8x256 backward-data (two slices) 55.3 and 49.5, 100 x 14x14 5x5 192 -> 48
+// forward and backward-data 160 and 108.  The whole VGG-shaped step stays at 1.56 ms: it runs against the power limit, and its clock falls as its
+// kernels get denser (2.14 to 2.03 GHz).
+//
+// Waves, LDS use of the pair, accumulators and the redo of blocks that the terms do not hold: see kernel_gather_terms.hip.
+// The operands of the MFMA are exchanged against that kernel (filter first), so that a lane of the result holds sixteen channels of one
+// pixel, four neighbouring ones at a time, and puts them into LDS 16 bytes at a time.
+#include <hip/hip_runtime.h>
+#include "split_bf16.h"
+
+#include <type_traits>
+
+namespace mi355conv {
+
+namespace {
+template <int BM, int BN, bool BWD>
+struct SH {
+    static constexpr int WM = BM / 64, WN = BN / 64;               // wave tiles of 64 x 64
+    static constexpr int WAVES = WM * WN * 2, THREADS = WAVES * 64;   // two waves per wave tile (halves of a stage)
+    static constexpr int MB = 2, NB = 2, NBLK = 4, NOWN = 2;
+    static constexpr int ROWS = halo_rows(BM), A_RPP = THREADS / 8, PA = ROWS / A_RPP;   // gathered pixels: 8 threads per row of 32 channels
+    // forward: B tile is [BN cols][kBK]; backward-data: [kBK][BN], turned by the LDS reads
+    static constexpr int B_TPR = BWD ? BN / 4 : 8;
+    static constexpr int B_RPP = THREADS / B_TPR, B_ROWS = BWD ? kBK : BN, PB = B_ROWS / B_RPP;
+    // gathered pixels: four columns (8 channels each) of 16 bytes per row; row ROWS is the row of zeros.  A column's bytes are 64 modulo 256,
+    // so that the 8-byte stores of four rows at a time fall on different banks; the fragment reads are 512 consecutive bytes.
+    static constexpr int A_COL = ((ROWS + 1) * 16 + 191) / 256 * 256 + 64;
+    static constexpr int A_PLANE = 4 * A_COL, A_BUF = 3 * A_PLANE;
+    static constexpr int B_PLANE = BN * kBK * 2, B_BUF = 3 * B_PLANE;
+    static constexpr int B_BASE = 2 * A_BUF, LOST = B_BASE + 2 * B_BUF;
+    static constexpr size_t SMEM = LOST + WAVES * sizeof(int);
+    static_assert(A_COL >= (ROWS + 1) * 16 && A_COL % 256 == 64, "columns of the gathered tile");
+    static_assert(ROWS % A_RPP == 0 && B_ROWS % B_RPP == 0, "loader passes");
+    static_assert(2 * A_PLANE + 3 * A_COL < 65536, "planes by immediate offsets");
+    static_assert(WAVES == 8 && WAVES * NBLK * 32 * kLDT * 4 <= LOST, "exchange buffers fit over the tiles");
+    static_assert(SMEM <= 160 * 1024, "LDS of a CU");
+};
+
+enum { kPlain = -1, kLoadChunk = -2 };   // what a stage does beside its products; 0 .. PA-1: split and store item q of the next chunk
+}  // namespace
+
+// The fp32 form of a tile (see kernel_gather_terms.hip): v_mfma_f32_32x32x2_f32 on elements read straight from memory, every tap summed by
+// itself and added only to the rows it is inside the image for, so that infinities and NaN reach no further than their taps do.
+template <class T, bool BWD>
+__device__ __forceinline__ void halo_redo_fp32(const HaloParams &p, __amdgpu_buffer_rsrc_t rsrcA, __amdgpu_buffer_rsrc_t rsrcB,
+                                               const int (&pixel)[2], const unsigned (&mask)[2], int col, int lane, int c0, int c1,
+                                               float16v (&own)[2])
+{
+    constexpr int kOutOfRange = (int)0x80000000;
+    const int lh = lane >> 5, wRowStride = p.taps * (BWD ? p.DC : p.SC);
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) own[o][r] = 0.f;
+    int shift = p.shift0, v = 0;
+    for (int t = 0; t < p.taps; ++t) {
+        float16v sum[2];
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum[o][r] = 0.f;
+        for (int k0 = c0 * kBK; k0 < c1 * kBK; k0 += 8) {
+            const int k = k0 + lh * 4;   // this lane's four source channels
+            f4 a[2], b;
+#pragma unroll
+            for (int o = 0; o < 2; ++o) {
+                const bool ok = k < p.SC && ((mask[o] >> t) & 1u);
+                a[o] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                  rsrcA, ok ? ((pixel[o] + shift) * p.SC + k) * 4 : kOutOfRange, 0, 0));
+            }
+            const bool okB = k < p.SC && col < p.DC;
+            if (BWD) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    b[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                               rsrcB, okB ? ((k + e) * wRowStride + t * p.DC + col) * 4 : kOutOfRange, 0, 0));
+            } else {
+                b = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
+                        rsrcB, okB ? (col * wRowStride + t * p.SC + k) * 4 : kOutOfRange, 0, 0));
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int o = 0; o < 2; ++o) sum[o] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[e], a[o][e], sum[o], 0, 0, 0);
+        }
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) own[o][r] += (mask[o] >> t) & 1u ? sum[o][r] : 0.f;
+        shift += p.shiftStep;
+        if (++v == p.FW) {
+            v = 0;
+            shift += p.shiftWrap;
+        }
+    }
+}
+
+// RAGGED: the source channel count is a multiple of 4 but not of 32, so the last chunk is partly empty (its surplus loads read zeros).
+template <int BM, int BN, bool BWD, bool RAGGED>
+__global__ __launch_bounds__((SH<BM, BN, BWD>::THREADS), 2) void halo_terms_kernel(const HaloParams p)
+{
+    using T = SH<BM, BN, BWD>;
+    extern __shared__ f4 smem_raw[];
+    char *smem = reinterpret_cast<char *>(smem_raw);
+    int *lost = reinterpret_cast<int *>(smem + T::LOST);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+
+    const int bid = xcd_remap_fast(blockIdx.x, p.xcdWhole, p.xcdUnit, p.divXcdUnit);
+    const int rest0 = (int)fast_div((unsigned)bid, p.divTilesN);
+    const int n0 = (bid - rest0 * p.tilesN) * BN;
+    const int tm = (int)fast_div((unsigned)rest0, p.divSplit);
+    const int slice = rest0 - tm * p.split;
+    const int m0 = tm * BM;
+    const int c0 = (int)fast_div((unsigned)(slice * p.chunks), p.divSplit);
+    const int c1 = (int)fast_div((unsigned)((slice + 1) * p.chunks), p.divSplit);
+
+    const __amdgpu_buffer_rsrc_t rsrcA =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.A), 0, (int)p.aBytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrcB =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.B), 0, (int)p.bBytes, 0x00020000);
+    constexpr int kOutOfRange = (int)0x80000000;   // tensors are below 2^31 bytes
+    const int lastValid = p.SC - (p.chunks - 1) * kBK;   // source channels of the last chunk
+
+    // ---- loader state ----------------------------------------------------------------------------
+    const int aSeg = tid & 7, aRow = tid >> 3;
+    int aOff[T::PA];
+#pragma unroll
+    for (int q = 0; q < T::PA; ++q) {
+        const int row = aRow + T::A_RPP * q, pix = m0 - p.haloLo + row;
+        aOff[q] = row < p.span && (unsigned)pix < (unsigned)p.M ? (pix * p.SC + aSeg * 4) * 4 : kOutOfRange;
+    }
+    const int bSeg = tid % T::B_TPR, bRow = tid / T::B_TPR;
+    const int wRowStride = p.taps * (BWD ? p.DC : p.SC);   // floats per oc in W
+    int bOff[T::PB];
+#pragma unroll
+    for (int i = 0; i < T::PB; ++i) {
+        const int r = bRow + T::B_RPP * i;
+        if (BWD) bOff[i] = n0 + bSeg * 4 < p.DC ? (r * wRowStride + n0 + bSeg * 4) * 4 : kOutOfRange;
+        else bOff[i] = n0 + r < p.DC ? ((n0 + r) * wRowStride + bSeg * 4) * 4 : kOutOfRange;
+    }
+    const bool aLastOk = aSeg * 4 < lastValid;
+    bool bLastOk[T::PB];
+#pragma unroll
+    for (int i = 0; i < T::PB; ++i) bLastOk[i] = BWD ? bRow + T::B_RPP * i < lastValid : bSeg * 4 < lastValid;
+
+    f4 rawA[T::PA], rawB[T::PB];   // loads in flight
+    auto load_a = [&](int q, int chunk) __attribute__((always_inline)) {
+        const bool drop = RAGGED && chunk == p.chunks - 1 && !aLastOk;
+        rawA[q] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcA, drop ? kOutOfRange : aOff[q], chunk * (kBK * 4), 0));
+    };
+    // cursor of the filter loads, two stages ahead: past the slice it stays where it is (the loads are repeated and not used)
+    const int bTap = (BWD ? p.DC : p.SC) * 4, bChunk = (BWD ? kBK * wRowStride : kBK) * 4 - p.taps * bTap;   // bytes
+    int lChunk = c0, lTap = 0, lLeft = (c1 - c0) * p.taps - 1, lOff = c0 * (bChunk + p.taps * bTap);
+    auto load_b = [&](int i) __attribute__((always_inline)) {
+        const bool drop = RAGGED && lChunk == p.chunks - 1 && !bLastOk[i];
+        rawB[i] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcB, drop ? kOutOfRange : bOff[i], lOff, 0));
+    };
+    auto advance_b = [&]() __attribute__((always_inline)) {
+        const bool wrap = ++lTap == p.taps;
+        const int step = wrap ? bTap + bChunk : bTap;
+        lTap = wrap ? 0 : lTap;
+        lOff += lLeft > 0 ? step : 0;
+        if (RAGGED) lChunk += wrap && lLeft > 0 ? 1 : 0;
+        --lLeft;
+    };
+
+    // ---- LDS tiles ----------------------------------------------------------------------------------
+    // Filter tiles as in kernel_gather_terms.hip: forward [col][32 k] with 16-byte pieces exchanged by row, backward-data [k][BN] with
+    // 64-byte pieces exchanged by k.
+    constexpr auto kSwz = [](int r) { return BN == 128 ? (r & 3) : ((r >> 1) & 1); };
+    int aStore = (aSeg >> 1) * T::A_COL + aRow * 16 + (aSeg & 1) * 8;
+    int bStore = T::B_BASE + (BWD ? bRow * (BN * 2) + (((bSeg >> 3) ^ kSwz(bRow)) << 6) + (bSeg & 7) * 8
+                                  : bRow * 64 + (((bSeg >> 1) ^ ((bRow >> 2) & 3)) << 4) + (bSeg & 1) * 8);
+    static_assert(T::B_RPP % 16 == 0, "the exchange of pieces is the same in every loader pass");
+    unsigned rest = 0u;   // what the terms left of the elements split so far (see split_bf16.h)
+    auto store = [&](char *d, int plane, const SplitQuad &s) __attribute__((always_inline)) {
+        *reinterpret_cast<u2 *>(d) = s.h;
+        *reinterpret_cast<u2 *>(d + plane) = s.m;
+        *reinterpret_cast<u2 *>(d + 2 * plane) = s.l;
+    };
+    auto store_a = [&](int q, const SplitQuad &s) __attribute__((always_inline)) { store(smem + aStore + q * T::A_RPP * 16, T::A_PLANE, s); };
+    auto store_b = [&](int i, const SplitQuad &s) __attribute__((always_inline)) {
+        store(smem + bStore + i * T::B_RPP * (BWD ? BN * 2 : 64), T::B_PLANE, s);
+    };
+
+    // the rows of zeros (one per buffer would not be needed: invalid rows read the first buffer's)
+    if (tid < 12) *reinterpret_cast<f4 *>(smem + (tid >> 2) * T::A_PLANE + (tid & 3) * T::A_COL + T::ROWS * 16) = f4{0.f, 0.f, 0.f, 0.f};
+
+    const int kh = wave & 1, wm = (wave >> 1) / T::WN, wn = (wave >> 1) % T::WN;
+    const int l32 = lane & 31, lh = lane >> 5;
+
+    // ---- rows of this lane: their pixel and the taps inside the image ---------------------------------
+    int pixel[2], aBase[2];
+    unsigned mask[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int r = wm * 64 + i * 32 + l32, m = m0 + r;
+        pixel[i] = m;
+        aBase[i] = (kh * 2 + lh) * T::A_COL + (r + p.haloLo) * 16;
+        const int q = m - (int)fast_div((unsigned)m, p.divHW) * (p.H * p.W);
+        const int y = (int)fast_div((unsigned)q, p.divW), x = q - y * p.W;
+        unsigned xs = 0u;   // taps along x inside the image
+        for (int v = 0; v < p.FW; ++v) xs |= ((unsigned)(x + (BWD ? p.pw - v : v - p.pw)) < (unsigned)p.W ? 1u : 0u) << v;
+        mask[i] = 0u;
+        for (int u = 0; u < p.FH; ++u)
+            mask[i] |= (m < p.M && (unsigned)(y + (BWD ? p.ph - u : u - p.ph)) < (unsigned)p.H ? xs : 0u) << (u * p.FW);
+    }
+    const int aZero = (kh * 2 + lh) * T::A_COL + T::ROWS * 16;
+
+    float16v acc[T::NBLK], low[T::NBLK];   // sums of the h*h products and of the five smaller ones (see split_bf16.h)
+#pragma unroll
+    for (int b = 0; b < T::NBLK; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[b][r] = low[b][r] = 0.f;
+
+    bf8 fa[3][T::MB], fb[3][T::NB];
+    int aFrag[T::MB], bFrag[T::NB];
+#pragma unroll
+    for (int j = 0; j < T::NB; ++j) {
+        if (BWD) {
+            const int k = kh * 16 + lh * 8 + ((lane & 15) >> 2);
+            bFrag[j] = T::B_BASE + k * (BN * 2) + (((wn * T::NB + j) ^ kSwz(k)) << 6) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+        } else {
+            bFrag[j] = T::B_BASE + (wn * 64 + j * 32 + l32) * 64 + (((kh * 2 + lh) ^ ((l32 >> 2) & 3)) << 4);
+        }
+    }
+    auto read_a = [&](int plane) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < T::MB; ++i) fa[plane][i] = *reinterpret_cast<const bf8 *>(smem + aFrag[i] + plane * T::A_PLANE);
+    };
+    auto read_b = [&](int plane) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < T::NB; ++j) {
+            const char *s = smem + bFrag[j] + plane * T::B_PLANE;
+            if (BWD) fb[plane][j] = join_quads(lds_read_tr(s), lds_read_tr(s + 4 * BN * 2));
+            else fb[plane][j] = *reinterpret_cast<const bf8 *>(s);
+        }
+    };
+    // cursor of the fragment reads, one stage ahead: tap, its shift (in bytes of a column, with the chunk's buffer), and the step to the next
+    int fTap = 0, fV = 0, fShift = p.shift0 * 16, fBuf = T::A_BUF;
+    auto place_a = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < T::MB; ++i) {
+            const int in = aBase[i] + fShift, sel = __builtin_amdgcn_sbfe((int)mask[i], fTap, 1);   // -1: inside the image
+            aFrag[i] = (sel & in) | (~sel & aZero);
+        }
+        const bool wrapV = fV + 1 == p.FW, wrap = fTap + 1 == p.taps;
+        fTap = wrap ? 0 : fTap + 1;
+        fV = wrapV ? 0 : fV + 1;
+        fShift += (p.shiftStep + (wrapV ? p.shiftWrap : 0)) * 16;
+        fShift += wrap ? p.shiftChunk * 16 + fBuf : 0;
+        fBuf = wrap ? -fBuf : fBuf;
+    };
+    int bStep = T::B_BUF, bRead = T::B_BUF;   // distance to the other filter buffer
+    auto flip_reads = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < T::NB; ++j) bFrag[j] += bRead;
+        bRead = -bRead;
+    };
+
+    // One stage (a tap of a chunk): its six products, one group of four MFMAs each.  Beside the first four groups the wave splits and
+    // stores its share of the next stage's filter tile (loaded a stage ago) and loads the one after into the same registers.  KIND: the
+    // first stage of a chunk also loads the gathered pixels of the next chunk, the last PA ones split and store them one item a stage.  The one
+    // barrier comes behind the fourth group; the next stage's fragments are requested beside the last two groups.
+    auto multiply = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < T::MB; ++i)
+#pragma unroll
+            for (int j = 0; j < T::NB; ++j) {
+                float16v &sum = g == kSplitProducts - 1 ? acc[i * T::NB + j] : low[i * T::NB + j];
+                sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kProdB[g]][j], fa[kProdA[g]][i], sum, 0, 0, 0);
+            }
+    };
+    constexpr int kBarrier = 3;   // every plane of both operands has been used by the first three groups
+    auto stage = [&](auto kindTag, int nextChunk) __attribute__((always_inline)) {
+        constexpr int KIND = decltype(kindTag)::value;
+        f4 cur[T::PB];
+        SplitQuad sb, sa;
+#pragma unroll
+        for (int g = 0; g < kSplitProducts; ++g) {
+            if (g == 0) {   // the loads of the next stage go out before this stage's elements are split
+#pragma unroll
+                for (int i = 0; i < T::PB; ++i) {
+                    cur[i] = rawB[i];
+                    asm volatile("" : "+v"(cur[i]));
+                }
+#pragma unroll
+                for (int i = 0; i < T::PB; ++i) load_b(i);
+            }
+            if (g == kBarrier) {
+                __syncthreads();
+                read_a(2);
+                read_b(2);
+            }
+            if (g == kBarrier + 1) read_a(1);
+            if (g == kBarrier + 2) read_b(1);
+            if constexpr (T::PB == 1) {
+                if (g < 2) split_pair(cur[0], g, rest, sb);
+                if (g == 1) store_b(0, sb);
+            } else {
+                if (g < 2) {
+                    split_pair(cur[g], 0, rest, sb);
+                    split_pair(cur[g], 1, rest, sb);
+                    store_b(g, sb);
+                }
+            }
+            if (g == 1) advance_b();
+            if (g == 2) {
+                if constexpr (KIND >= 0) {
+                    split_pair(rawA[KIND], 0, rest, sa);
+                    split_pair(rawA[KIND], 1, rest, sa);
+                    store_a(KIND, sa);
+                }
+                place_a();
+                flip_reads();
+                bStore += bStep;
+                bStep = -bStep;
+            }
+            if constexpr (KIND == kLoadChunk) {
+                if (g == kBarrier)
+#pragma unroll
+                    for (int q = 0; q < T::PA; ++q) load_a(q, nextChunk);
+            }
+            asm volatile("" : "+v"(rest));
+            multiply(g);
+#pragma unroll
+            for (int b = 0; b < T::NBLK; ++b) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                              // one MFMA, then
+                if (g >= kBarrier) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);           // LDS reads,
+                __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);                              // vector instructions,
+                if (g < kBarrier) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);            // an LDS store,
+                __builtin_amdgcn_sched_group_barrier(0x004, 4, 0);                              // scalar instructions
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        read_b(0);
+        read_a(0);
+    };
+
+    // ---- main loop ------------------------------------------------------------------------------------
+#pragma unroll
+    for (int i = 0; i < T::PB; ++i) load_b(i);
+#pragma unroll
+    for (int q = 0; q < T::PA; ++q) load_a(q, c0);
+#pragma unroll
+    for (int i = 0; i < T::PB; ++i) store_b(i, split_quad(rawB[i], rest));
+    bStore += bStep;
+    bStep = -bStep;
+    advance_b();
+#pragma unroll
+    for (int i = 0; i < T::PB; ++i) load_b(i);
+    advance_b();
+#pragma unroll
+    for (int q = 0; q < T::PA; ++q) store_a(q, split_quad(rawA[q], rest));
+    place_a();
+    __syncthreads();
+#pragma unroll
+    for (int pl = 2; pl >= 0; --pl) {
+        read_a(pl);
+        read_b(pl);
+    }
+    int aStep = T::A_BUF;
+    for (int c = c0; c + 1 < c1; ++c) {
+        aStore += aStep;
+        aStep = -aStep;
+        stage(std::integral_constant<int, kLoadChunk>(), c + 1);
+        stage(std::integral_constant<int, kPlain>(), 0);
+        for (int t = 2 + p.items; t < p.taps; ++t) stage(std::integral_constant<int, kPlain>(), 0);
+        if constexpr (T::PA > 4) {
+            if (p.items > 4) stage(std::integral_constant<int, 4>(), 0);
+        }
+        if (p.items > 3) stage(std::integral_constant<int, 3>(), 0);
+        if (p.items > 2) stage(std::integral_constant<int, 2>(), 0);
+        stage(std::integral_constant<int, 1>(), 0);
+        stage(std::integral_constant<int, 0>(), 0);
+    }
+    for (int t = 1; t < p.taps; ++t) stage(std::integral_constant<int, kPlain>(), 0);
+    // the last stage: nothing left to store or to read
+#pragma unroll
+    for (int g = 0; g < kSplitProducts; ++g) {
+        if (g == kBarrier) __syncthreads();   // every wave has used its last fragments: the buffers are free
+        multiply(g);
+    }
+
+    // ---- the pair's halves meet: each wave finishes the two blocks of its column --------------------------
+    // Every wave puts its four blocks into LDS, [pixel][channel]; behind the barrier it reads its own and its partner's half of the
+    // blocks it finishes as rows of 32 channels, eight lanes a pixel, adds them and stores 128 bytes a pixel.
+    float *mine = reinterpret_cast<float *>(smem) + wave * T::NBLK * 32 * kLDT;
+    const float *theirs = reinterpret_cast<const float *>(smem) + (wave ^ 1) * T::NBLK * 32 * kLDT;
+#pragma unroll
+    for (int b = 0; b < T::NBLK; ++b)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            f4 x;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = acc[b][g * 4 + e] + low[b][g * 4 + e];
+            *reinterpret_cast<f4 *>(mine + (b * 32 + l32) * kLDT + g * 8 + lh * 4) = x;
+        }
+    const int mineLost = split_lost(rest);
+    if (lane == 0) lost[wave] = mineLost;
+    __syncthreads();
+    bool bad = false;
+#pragma unroll
+    for (int w = 0; w < T::WAVES; ++w) bad = bad || lost[w] != 0;
+    const int sRow = lane >> 3, seg = lane & 7;   // this lane's pixel (8q + sRow of a block) and channels (4*seg .. +3)
+    f4 own[T::NOWN][4];
+    SplitCheck check;
+#pragma unroll
+    for (int o = 0; o < T::NOWN; ++o)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int at = ((2 * o + kh) * 32 + q * 8 + sRow) * kLDT + seg * 4;
+            own[o][q] = *reinterpret_cast<const f4 *>(mine + at) + *reinterpret_cast<const f4 *>(theirs + at);
+            check.look(own[o][q]);
+        }
+    bad = bad || check.bad();
+    const int colBase = n0 + wn * 64 + kh * 32;   // the columns this wave finishes
+    if (__any(bad)) {
+        float16v redo[T::NOWN];
+        halo_redo_fp32<T, BWD>(p, rsrcA, rsrcB, pixel, mask, colBase + l32, lane, c0, c1, redo);
+#pragma unroll
+        for (int o = 0; o < T::NOWN; ++o) {   // turned in the wave's own buffer of the block, which its partner does not read
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mine[((2 * o + kh) * 32 + l32) * kLDT + 8 * (r / 4) + 4 * lh + r % 4] = redo[o][r];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                own[o][q] = *reinterpret_cast<const f4 *>(mine + ((2 * o + kh) * 32 + q * 8 + sRow) * kLDT + seg * 4);
+        }
+    }
+
+    float *C = p.C + (long long)slice * p.sliceStride;
+    const int col = colBase + seg * 4, m1 = m0 + wm * 64 + sRow;
+    if (col >= p.DC) return;   // no barrier follows
+    if (p.epilogue && p.split == 1) {   // uniform; sliced launches leave it to the combine pass
+        f4 b = f4{0.f, 0.f, 0.f, 0.f};
+        if (p.bias) {   // 4-byte loads: the bias may be aligned to 4 bytes only
+#pragma unroll
+            for (int e = 0; e < 4; ++e) b[e] = p.bias[col + e];
+        }
+#pragma unroll
+        for (int o = 0; o < T::NOWN; ++o)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float v = own[o][q][e] + b[e];
+                    own[o][q][e] = v > 0.f ? v : v * p.slope;
+                }
+    }
+#pragma unroll
+    for (int o = 0; o < T::NOWN; ++o)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int m = m1 + o * 32 + q * 8;
+            if (m < p.M) *reinterpret_cast<f4 *>(C + (long long)m * p.DC + col) = own[o][q];
+        }
+}
+
+template <int BM, int BN, bool BWD, bool RAGGED>
+static hipError_t launch_halo_one(const HaloParams &p, int grid, hipStream_t st)
+{
+    using T = SH<BM, BN, BWD>;
+    hipLaunchKernelGGL((halo_terms_kernel<BM, BN, BWD, RAGGED>), dim3((unsigned)grid), dim3(T::THREADS), T::SMEM, st, p);
+    return hipGetLastError();
+}
+
+// The tiles need more LDS than a kernel gets by default (64 KB): limit raised once per device, outside any stream capture.
+hipError_t prepare_halo_terms()
+{
+    hipError_t e = hipSuccess;
+#define MI355_HALO_PREP(BM_, BN_, BWD_, RAGGED_)                                                                            \
+    if (e == hipSuccess)                                                                                                    \
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(halo_terms_kernel<BM_, BN_, BWD_, RAGGED_>),                  \
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)SH<BM_, BN_, BWD_>::SMEM);
+    MI355_HALO_PREP(128, 128, false, false)
+    MI355_HALO_PREP(128, 128, false, true)
+    MI355_HALO_PREP(128, 128, true, false)
+    MI355_HALO_PREP(128, 128, true, true)
+    MI355_HALO_PREP(256, 64, false, false)
+    MI355_HALO_PREP(256, 64, false, true)
+    MI355_HALO_PREP(256, 64, true, false)
+    MI355_HALO_PREP(256, 64, true, true)
+#undef MI355_HALO_PREP
+    return e;
+}
+
+hipError_t launch_halo_terms(const HaloParams &p, bool bwdData, int bm, int bn, int grid, hipStream_t st)
+{
+    if (p.span > halo_rows(bm) || p.items * 64 > halo_rows(bm) || p.items * 64 < p.span || p.taps < p.items + 2 || p.taps > 32 ||
+        p.SC % 4 != 0 || p.DC % 4 != 0 || p.split < 1 || p.split > p.chunks)
+        return hipErrorInvalidValue;
+    const bool ragged = p.SC % kBK != 0;
+#define MI355_HALO_CASE(BM_, BN_)                                                                                            \
+    if (bm == BM_ && bn == BN_) {                                                                                           \
+        if (ragged) return bwdData ? launch_halo_one<BM_, BN_, true, true>(p, grid, st) : launch_halo_one<BM_, BN_, false, true>(p, grid, st); \
+        return bwdData ? launch_halo_one<BM_, BN_, true, false>(p, grid, st) : launch_halo_one<BM_, BN_, false, false>(p, grid, st);          \
+    }
+    MI355_HALO_CASE(128, 128)
+    MI355_HALO_CASE(256, 64)
+#undef MI355_HALO_CASE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace mi355conv
