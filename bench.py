@@ -53,8 +53,8 @@ def kernel_name(layer, op, plan, desc, mc):
     if plan.kernel == mc.KERNEL_DIRECT:
         return "direct_%s_kernel" % op
     if plan.kernel == mc.KERNEL_FIRST_LAYER:
-        return {"fwd": "fwd_small_ic_kernel<false>", "bwd_data": "bwd_data_small_ic_kernel",
-                "bwd_weight": "wgrad_small_ic_kernel"}[op]
+        return {"fwd": "fwd_small_ic_kernel<false, false, %s>" % b(layer.OC % 4 == 0), "bwd_data": "bwd_data_small_ic_kernel",
+                "bwd_weight": "wgrad_small_ic_kernel<%s>" % b(layer.OW % 8 == 0)}[op]
     terms = products_name(op, desc, mc) == "terms"
     if terms and op == "bwd_weight":
         aligned = 32 % layer.OW == 0 or layer.OW % 32 == 0

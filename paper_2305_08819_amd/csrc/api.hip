@@ -639,7 +639,7 @@ Plan plan_bwd_data(const Shape &s)
         (4 + s.FH - 1) * (32 + s.FW - 1) <= 224 && g_forceSplit.load() == 0 && !forced_tile(&ftm, &ftn, true) &&
         (long long)s.N * s.OH * s.OW * s.OC * 4 < (1LL << 31) && pl.outElems * 4 < (1LL << 31)) {
         pl.smallIc = 1;
-        pl.bm = 128;     // 4 x 32 pixels of dX per workgroup
+        pl.bm = 128;     // tiles of 4 x 32 pixels of dX; a workgroup takes small_ic_tile_rows() rows, two tiles but for very wide filters
         pl.bn = 32;
         pl.tilesM = s.N * ceil_div(s.IH, 4) * ceil_div(s.IW, 32);
         pl.tilesN = 1;
@@ -756,8 +756,8 @@ Plan plan_bwd_weight(const Shape &s)
         pl.tilesN = 1;
         const int chunks = ceil_div(M, kBK);
         int sp = g_forceSplit.load();
-        if (sp <= 0) {   // about two workgroups per CU, at least 4 stages each
-            sp = 512 / pl.tilesM;
+        if (sp <= 0) {   // about one workgroup of eight waves per CU, at least one step of 16 rows a wave
+            sp = 256 / pl.tilesM;
             if (sp > chunks / 4) sp = chunks / 4;
         }
         if (sp > chunks) sp = chunks;
@@ -1923,6 +1923,7 @@ int conv2d_bwd_data(const float *dY, const float *W, float *dX, const conv2d_des
         q.wBytes = (unsigned)((long long)s.OC * s.FH * s.FW * s.IC * 4);
         q.N = s.N; q.IH = s.IH; q.IW = s.IW; q.IC = s.IC; q.OC = s.OC; q.OH = s.OH; q.OW = s.OW;
         q.FH = s.FH; q.FW = s.FW; q.ph = s.ph; q.pw = s.pw;
+        q.rows = small_ic_tile_rows(s.FH, s.FW);
         hipError_t e = launch_bwd_data_small_ic(q, st);
         return e == hipSuccess ? MI355CONV_OK : hip_fail(e);
     }

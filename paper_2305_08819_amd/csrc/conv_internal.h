@@ -351,6 +351,7 @@ struct SmallIcParams {
     float *dX;            // [N, IH, IW, IC]; the forward kernel writes Y [N, OH, OW, OC] through it
     unsigned gBytes, wBytes;
     int N, IH, IW, IC, OC, OH, OW, FH, FW, ph, pw;
+    int rows;             // backward-data only: small_ic_tile_rows()
     // backward-weight only
     const float *X;       // [N, IH, IW, IC]
     float *C;             // dW, or workspace base when split > 1
@@ -587,6 +588,9 @@ inline bool wgrad_terms_accepts(int N, int OH, int OW, int IC, int OC, int posMa
     if (bm == 32) return wgrad_fast_accepts(N, OH, OW, IC, OC, posMajor, bm, bn);   // aligned maps only
     return (bm == 128 || bm == 64) && (bn == 128 || bn == 64);
 }
+// Rows of a 32-pixel-wide tile of dX whose halo of dY pixels fits the LDS of bwd_data_small_ic_kernel.  What it accepts fits with 4 rows.
+constexpr int kSmallIcRows = 384;
+inline int small_ic_tile_rows(int FH, int FW) { return (8 + FH - 1) * (32 + FW - 1) <= kSmallIcRows ? 8 : 4; }
 inline bool bwd_data_small_ic_accepts(int IC, int OC, int FH, int FW, int sh, int sw)
 {
     return sh == 1 && sw == 1 && IC <= 4 && FH * FW * IC <= 32 && OC % kBK == 0 && (4 + FH - 1) * (32 + FW - 1) <= 224;

@@ -7,37 +7,44 @@
 //   P[pixel of dY][(fh,fw,ic)] = sum_oc dY[pixel, oc] * W[oc, fh, fw, ic]        (a dense GEMM with
 //                                 K = OC and N = FH*FW*IC <= 32: 27 of 32 columns real for 3x3x3)
 //   dX[n, ih, iw, ic]          = sum_{fh,fw} P[(ih+ph-fh, iw+pw-fw)][(fh,fw,ic)]  (col2im gather)
-// which is the same sum in another order and 9x fewer MFMAs.  A workgroup owns kTR x 32 pixels of
-// one image of dX; it computes P for those pixels' halo ((kTR+FH-1) x (32+FW-1) dY pixels, at most
-// 224) with v_mfma_f32_32x32x2_f32 into LDS and then gathers.  dY pixels outside the map get an
-// out-of-range buffer offset, read zeros and give zero rows of P, so the gather needs no test.
+// which is the same sum in another order and 9x fewer MFMAs.  A workgroup owns `rows` (8, or 4 for very wide filters) x 32 pixels of
+// one image of dX; it computes P for those pixels' halo ((rows+FH-1) x (32+FW-1) dY pixels, at most 384) into LDS and then gathers.
+// dY pixels outside the map get an out-of-range buffer offset, read zeros and give zero rows of P, so the gather needs no test.
+//
+// P on v_mfma_f32_32x32x16_bf16 with three-term operands (split_bf16.h).  Bound by reading dY once and by latency: a wave loads its dY
+// pixels straight into the MFMA's operand layout (lane l: pixel l%32, channels 8*(l/32) .. +7 of a step, 32 bytes), the next
+// block of 32 pixels while one is multiplied; only the filter's terms go through LDS, 64 channels at a time.  128 x 32x32x3 -> 64: with
+// fp32 MFMA, 4-row tiles (1.6 times the pixels, 1.3 here) and both operands staged through LDS 16.6 us, now 13.0 (first pass over dY
+// each; reading its 34 MB alone takes 7).
 #include <hip/hip_runtime.h>
-#include "gather_common.h"
+#include "split_bf16.h"
 
 namespace mi355conv {
 
 namespace {
-constexpr int kTR = 4, kTC = 32;          // dX tile: rows x columns of one image
-constexpr int kPRows = 224;               // P rows held (7 MFMA row blocks)
-constexpr int kLDP = 33;                  // P row pitch (floats): odd, so the gather's strided reads spread over banks
+constexpr int kTC = 32;                            // columns of a dX tile
+constexpr int kPRows = kSmallIcRows;               // P rows held
+constexpr int kPBlocks = kPRows / 32 / 4;          // blocks of 32 of a wave
+constexpr int kLDP = 33;                           // P row pitch (floats): odd, so the gather's strided reads spread over banks
+constexpr int kPChunk = 64;                        // channels of dY whose filter terms lie in LDS
 }  // namespace
 
 __global__ __launch_bounds__(kThreads, 2) void bwd_data_small_ic_kernel(const SmallIcParams p)
 {
-    extern __shared__ f4 smem_raw[];
-    float *As = reinterpret_cast<float *>(smem_raw);          // [kPRows][LDA], later P as [kPRows][kLDP]
-    float *Bs = As + kPRows * LDA;                            // [32 columns (fh,fw,ic)][LDA] (k = oc contiguous)
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    __shared__ u4 filter[3][kPChunk / 8][32];      // term, 8 channels, column (fh,fw,ic)
+    __shared__ float Ps[kPRows * kLDP];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, lh = lane >> 5;
-    const int tilesW = (p.IW + kTC - 1) / kTC, tilesH = (p.IH + kTR - 1) / kTR;
+    const int tilesW = (p.IW + kTC - 1) / kTC, tilesH = (p.IH + p.rows - 1) / p.rows;
     int bid = blockIdx.x;
     const int tw = bid % tilesW;
     bid /= tilesW;
     const int th = bid % tilesH;
     const int n = bid / tilesH;
-    const int ih0 = th * kTR, iw0 = tw * kTC;
-    const int PR = kTR + p.FH - 1, PC = kTC + p.FW - 1;       // halo of dY pixels; PR * PC <= kPRows (host checks)
+    const int ih0 = th * p.rows, iw0 = tw * kTC;
+    const int PR = p.rows + p.FH - 1, PC = kTC + p.FW - 1;    // halo of dY pixels; PR * PC <= kPRows (host checks)
     const int ohBase = ih0 + p.ph - (p.FH - 1), owBase = iw0 + p.pw - (p.FW - 1);
     const int Kp = p.FH * p.FW * p.IC;                        // real columns of P (<= 32)
 
@@ -47,91 +54,113 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_data_small_ic_kernel(const Sm
     const __amdgpu_buffer_rsrc_t rsrcW =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.W), 0, (int)p.wBytes, 0x00020000);
 
-    // A loader: 224 rows x 8 segments of 16 bytes per 32-channel chunk = 7 loads per thread
-    constexpr int kPA = kPRows * 8 / kThreads;
-    const int aSeg = tid & 7, aRow = tid >> 3;
-    int aOff[kPA];
+    // wave w owns P row blocks w, w + 4, w + 8; this lane's pixel of each (byte offset of its channels 8*lh)
+    int gOff[kPBlocks];
 #pragma unroll
-    for (int i = 0; i < kPA; ++i) {
-        const int q = aRow + 32 * i;
-        const int pr = q / PC, pc = q - pr * PC;
+    for (int b = 0; b < kPBlocks; ++b) {
+        const int q = (wave + 4 * b) * 32 + l32, pr = q / PC, pc = q - pr * PC;
         const int oh = ohBase + pr, ow = owBase + pc;
         const bool ok = q < PR * PC && (unsigned)oh < (unsigned)p.OH && (unsigned)ow < (unsigned)p.OW;
-        aOff[i] = ok ? (((n * p.OH + oh) * p.OW + ow) * p.OC + aSeg * 4) * 4 : kOutOfRange;
+        gOff[b] = ok ? (((n * p.OH + oh) * p.OW + ow) * p.OC + 8 * lh) * 4 : kOutOfRange;
     }
-    // B loader: Bs[col][k] = W[oc = c0 + k][col], 32 x 32 elements, 4 per thread
-    int bOff[4];
+    f4 raw[2][8];   // two blocks' loads in flight: steps of 16 channels, two quads of a lane's eight
+    auto load = [&](int set, int b, int c0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int idx = tid + kThreads * i;
-        const int col = idx >> 5, k = idx & 31;
-        bOff[i] = col < Kp ? (k * Kp + col) * 4 : kOutOfRange;
-    }
-
-    f4 ga[kPA];
-    float gb[4];
-    auto gload = [&](int chunk) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < kPA; ++i)
-            ga[i] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcG, aOff[i], chunk * kBK * 4, 0));
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            gb[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrcW, bOff[i], chunk * kBK * Kp * 4, 0));
-    };
-    auto lds_store = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < kPA; ++i) *reinterpret_cast<f4 *>(As + (aRow + 32 * i) * LDA + aSeg * 4) = ga[i];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int idx = tid + kThreads * i;
-            Bs[(idx >> 5) * LDA + (idx & 31)] = gb[i];
+        for (int q = 0; q < 8; ++q) {
+            const int ch = c0 + 16 * (q >> 1);   // uniform; a lane's 8 channels lie in the same half of 32
+            raw[set][q] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcG, ch < p.OC ? gOff[b] : kOutOfRange,
+                                                                                       (ch < p.OC ? ch : 0) * 4 + (q & 1) * 16, 0));
         }
     };
-
-    // wave w owns P row blocks w and w + 4 (block 7 does not exist)
-    float16v acc[2];
+    unsigned rest = 0u;   // what the terms left of the elements split so far (see split_bf16.h)
+    float16v acc[kPBlocks], low[kPBlocks];
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < kPBlocks; ++b)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
-    const bool second = wave + 4 < kPRows / 32;
+        for (int r = 0; r < 16; ++r) acc[b][r] = low[b][r] = 0.f;
 
-    const int chunks = p.OC / kBK;
-    gload(0);
-    for (int c = 0; c < chunks; ++c) {
-        lds_store();
+    load(0, 0, 0);
+    for (int c0 = 0; c0 < p.OC; c0 += kPChunk) {
+        {   // the filter's terms: thread t takes column t%32, channels c0 + 8*(t/32) .. +7
+            const int col = tid & 31, g = tid >> 5;
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int oc = c0 + 8 * g + e;
+                v[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                     rsrcW, col < Kp && oc < p.OC ? (oc * Kp + col) * 4 : kOutOfRange, 0, 0));
+            }
+            const SplitQuad a = split_quad(f4{v[0], v[1], v[2], v[3]}, rest), b = split_quad(f4{v[4], v[5], v[6], v[7]}, rest);
+            if (c0) __syncthreads();   // every wave has read the terms before these
+            filter[0][g][col] = u4{a.h[0], a.h[1], b.h[0], b.h[1]};
+            filter[1][g][col] = u4{a.m[0], a.m[1], b.m[0], b.m[1]};
+            filter[2][g][col] = u4{a.l[0], a.l[1], b.l[0], b.l[1]};
+        }
         __syncthreads();
-        if (c + 1 < chunks) gload(c + 1);
 #pragma unroll
-        for (int g = 0; g < kBK / 8; ++g) {
-            const f4 fb = *reinterpret_cast<const f4 *>(Bs + l32 * LDA + g * 8 + lh * 4);
-            const f4 fa0 = *reinterpret_cast<const f4 *>(As + (wave * 32 + l32) * LDA + g * 8 + lh * 4);
-            f4 fa1 = f4{0.f, 0.f, 0.f, 0.f};
-            if (second) fa1 = *reinterpret_cast<const f4 *>(As + ((wave + 4) * 32 + l32) * LDA + g * 8 + lh * 4);
+        for (int b = 0; b < kPBlocks; ++b) {
+            if (b + 1 < kPBlocks) load((b + 1) & 1, b + 1, c0);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa0[t], fb[t], acc[0], 0, 0, 0);
-                if (second) acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa1[t], fb[t], acc[1], 0, 0, 0);
+            for (int s = 0; s < kPChunk / 16; ++s) {
+                bf8 fw[3], fg[3];
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) fw[pl] = __builtin_bit_cast(bf8, filter[pl][2 * s + lh][l32]);
+                const SplitQuad x = split_quad(raw[b & 1][2 * s], rest), y = split_quad(raw[b & 1][2 * s + 1], rest);
+                fg[0] = __builtin_bit_cast(bf8, u4{x.h[0], x.h[1], y.h[0], y.h[1]});
+                fg[1] = __builtin_bit_cast(bf8, u4{x.m[0], x.m[1], y.m[0], y.m[1]});
+                fg[2] = __builtin_bit_cast(bf8, u4{x.l[0], x.l[1], y.l[0], y.l[1]});
+#pragma unroll
+                for (int g = 0; g < kSplitProducts; ++g) {
+                    float16v &sum = g == kSplitProducts - 1 ? acc[b] : low[b];
+                    sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[kProdB[g]], fg[kProdA[g]], sum, 0, 0, 0);
+                }
             }
         }
-        __syncthreads();   // everyone is done reading this chunk's tiles
+        if (c0 + kPChunk < p.OC) load(0, 0, c0 + kPChunk);
     }
+    static_assert(kPBlocks == 3, "the first block of a chunk and its third share a set of registers");
 
-    // P into LDS (over the A tile): accumulator register r of lane l is row 8*(r/4)+4*(l/32)+r%4, column l%32
-    float *Ps = As;
+    // register r of lane l is column 8*(r/4) + 4*lh + r%4 of pixel l32.  A wave whose operands or sums the terms do not stand for forms its
+    // blocks again with v_mfma_f32_32x32x2_f32 (the filter elements that a wave split are not those that it multiplies: all waves join in).
+    SplitCheck check;
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-        if (b == 0 || second) {
+    for (int b = 0; b < kPBlocks; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = (wave + 4 * b) * 32 + 8 * (r / 4) + 4 * lh + (r % 4);
-                Ps[row * kLDP + l32] = acc[b][r];
+        for (int g = 0; g < 4; ++g) {
+            f4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                acc[b][4 * g + e] += low[b][4 * g + e];
+                v[e] = acc[b][4 * g + e];
             }
+            check.look(v);
         }
+    if (__syncthreads_or(split_lost(rest) || check.bad())) {
+        for (int b = 0; b < kPBlocks; ++b) {
+            const int off = b == 0 ? gOff[0] : b == 1 ? gOff[1] : gOff[2];
+            float16v sum;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum[r] = 0.f;
+            for (int oc = lh; oc < p.OC; oc += 2) {
+                const float w = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                              rsrcW, l32 < Kp ? (oc * Kp + l32) * 4 : kOutOfRange, 0, 0));
+                const float g = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                              rsrcG, off == kOutOfRange ? kOutOfRange : off + (oc - 8 * lh) * 4, 0, 0));
+                sum = __builtin_amdgcn_mfma_f32_32x32x2f32(w, g, sum, 0, 0, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) Ps[((wave + 4 * b) * 32 + l32) * kLDP + 8 * (r / 4) + 4 * lh + r % 4] = sum[r];
+        }
+    } else {
+#pragma unroll
+        for (int b = 0; b < kPBlocks; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) Ps[((wave + 4 * b) * 32 + l32) * kLDP + 8 * (r / 4) + 4 * lh + r % 4] = acc[b][r];
+    }
     __syncthreads();
 
     // col2im: one thread per dX pixel of the tile
-    if (tid < kTR * kTC) {
+    if (tid < p.rows * kTC) {
         const int r = tid / kTC, cc = tid - r * kTC;
         const int ih = ih0 + r, iw = iw0 + cc;
         if (ih < p.IH && iw < p.IW) {
@@ -153,296 +182,478 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_data_small_ic_kernel(const Sm
 
 hipError_t launch_bwd_data_small_ic(const SmallIcParams &p, hipStream_t st)
 {
-    const int PR = kTR + p.FH - 1, PC = kTC + p.FW - 1;
-    static_assert(kTR == 4 && kTC == 32 && kPRows == 224, "bwd_data_small_ic_accepts() states these tile sizes");
-    if (PR * PC > kPRows || !bwd_data_small_ic_accepts(p.IC, p.OC, p.FH, p.FW, 1, 1)) return hipErrorInvalidValue;
-    const size_t smem = (size_t)(kPRows * LDA + 32 * LDA) * sizeof(float);
-    static_assert(kPRows * kLDP <= kPRows * LDA, "P fits over the A tile");
-    static_assert((size_t)(kPRows * LDA + 32 * LDA) * sizeof(float) <= 64 * 1024, "within the default dynamic LDS limit");
-    const int grid = p.N * ((p.IH + kTR - 1) / kTR) * ((p.IW + kTC - 1) / kTC);
-    hipLaunchKernelGGL(bwd_data_small_ic_kernel, dim3((unsigned)grid), dim3(kThreads), smem, st, p);
+    if (!bwd_data_small_ic_accepts(p.IC, p.OC, p.FH, p.FW, 1, 1) || p.rows != small_ic_tile_rows(p.FH, p.FW)) return hipErrorInvalidValue;
+    static_assert(kTC == 32 && kThreads == 8 * kTC, "small_ic_tile_rows() states these tile sizes");
+    static_assert(sizeof(float) * kPRows * kLDP + 3 * kPChunk * 32 * 2 <= 64 * 1024, "within the LDS a kernel gets");
+    const int grid = p.N * ((p.IH + p.rows - 1) / p.rows) * ((p.IW + kTC - 1) / kTC);
+    hipLaunchKernelGGL(bwd_data_small_ic_kernel, dim3((unsigned)grid), dim3(kThreads), 0, st, p);
     return hipGetLastError();
 }
 
 // ---- forward for very few input channels -------------------------------------------------------
-// Y[m, oc] = sum_k patch[m, k] * W[oc, k] with k = (fh,fw,ic) and at most 32 patch columns: the
-// whole reduction is one MFMA stage.  A workgroup gathers the patch rows of 128 output pixels
-// element by element (a thread owns one row; the tap of column k is uniform, so its address
-// part is a scalar), 64 filter rows, multiplies once and stores.  Bound by writing Y.
-// U8: X holds unsigned bytes (pixels); each is converted on load, x = (float)byte * p.scale.
-template <bool U8>
-__global__ __launch_bounds__(kThreads, 2) void fwd_small_ic_kernel(const SmallIcParams p)
+// Y[m, oc] = sum_k patch[m, k] * W[oc, k] with k = (fh,fw,ic) and at most 32 patch columns, on v_mfma_f32_32x32x16_bf16 with
+// three-term operands (split_bf16.h).  Bound by writing Y, so everything else has to stay out of the way: a wave keeps the terms of
+// its 64 filter rows in registers and walks over tiles of 32 output pixels on its own - no barrier, no LDS but for turning the
+// results.  Lane l gathers 16 columns of pixel l%32 (the half l/32 of the columns), which are its MFMA fragments as they come: slot
+// 16s + 8*(l/32) + j of the reduction is column 16*(l/32) + 8s + j, for pixels and filter alike.  The next tile's elements are
+// loaded before this tile is multiplied.
+// U8: X holds unsigned bytes (pixels), each x = (float)byte * p.scale.  A byte is exact in one bf16 term, so three products do,
+// and the scale is applied to the sum; scales outside 2^-100 .. 2^100 take the fp32 form.
+// The sums are short (12 MFMAs, small products first), so one accumulator is as exact as two.  Sums that the terms may not stand for
+// (see split_bf16.h) are formed again with v_mfma_f32_32x32x2_f32, a tile at a time.
+// EPI: bias and activation.  QUAD: OC is a multiple of 4, results leave 16 bytes at a time.
+// 512 x 32x32x3 bytes -> 64 40.3 -> 31.7 us against fp32 MFMA, LDS tiles and one tile a workgroup (a fill of those 134 MB takes 21),
+// 128 fp32 images 14.3 -> 12.0 (7).
+namespace {
+constexpr int kPatchTile = 32, kPatchWaves = 4;
+}
+template <bool U8, bool EPI, bool QUAD>
+__global__ __launch_bounds__(kPatchWaves * 64, U8 ? 3 : 2) void fwd_small_ic_kernel(const SmallIcParams p)
 {
-    constexpr int BMf = 128, BNf = 64, LDf = 33;      // odd pitch: both the stores (lane = row) and the
-                                                      // fragment reads (lane = row, 4 bytes) spread over banks
-    __shared__ __attribute__((aligned(16))) float sm[BMf * LDf + BNf * LDf];
-    float *As = sm, *Bs = sm + BMf * LDf;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int l32 = lane & 31, lh = lane >> 5;
-    const int tilesN = (p.OC + BNf - 1) / BNf;
-    const int tn = blockIdx.x % tilesN, tm = blockIdx.x / tilesN;
-    const int m0 = tm * BMf, oc0 = tn * BNf;
+    __shared__ __attribute__((aligned(16))) float turn[kPatchWaves][32 * kLDT];
+    __shared__ unsigned __attribute__((ext_vector_type(4))) filter[3][4][64];   // term, 8 columns, row
+    __shared__ int lostFilter[kPatchWaves];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, lh = lane >> 5;
+    const int tilesN = (p.OC + 63) / 64, tiles = (p.M + kPatchTile - 1) / kPatchTile;
+    const int tn = blockIdx.x % tilesN, oc0 = tn * 64;
+    const int stride = (int)(gridDim.x / tilesN) * kPatchWaves;
     const int Kp = p.FH * p.FW * p.IC, ohow = p.OH * p.OW;
-
     constexpr int kOutOfRange = (int)0x80000000;
+    constexpr int kElem = U8 ? 1 : 4;   // bytes per element of X
     const __amdgpu_buffer_rsrc_t rsrcX =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.X), 0, (int)p.xBytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rsrcW =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.W), 0, (int)p.wBytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrcY = __builtin_amdgcn_make_buffer_rsrc(p.dX, 0, (int)((unsigned)p.M * (unsigned)p.OC * 4u), 0x00020000);
+    typedef unsigned i4s __attribute__((ext_vector_type(4)));
+    float *scratch = turn[wave];
 
-    // filter tile: Bs[oc][k], 64 x 32 elements, 8 per thread (k fastest: coalesced rows of W)
-    float wv[8];
+    // this lane's columns: offset of column 16*lh + e from the pixel's first one (bytes)
+    int kOff[16];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int idx = tid + kThreads * i;
-        const int oc = idx >> 5, k = idx & 31;
-        const int off = (k < Kp && oc0 + oc < p.OC) ? ((oc0 + oc) * Kp + k) * 4 : kOutOfRange;
-        wv[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrcW, off, 0, 0));
+    for (int e = 0; e < 16; ++e) {
+        const int k = 16 * lh + e, tap = (int)fast_div((unsigned)k, p.divIC), fh = (int)fast_div((unsigned)tap, p.divFW);
+        kOff[e] = ((fh * p.IW + tap - fh * p.FW) * p.IC + k - tap * p.IC) * kElem;
     }
-    // patch tile: thread owns row (tid & 127) and the columns of one half (16 each)
-    const int row = tid & (BMf - 1), khalf = tid >> 7;
-    const int m = m0 + row;
-    const int n = (int)fast_div((unsigned)m, p.divOHOW);
-    const int r = m - n * ohow;
-    const int oh = (int)fast_div((unsigned)r, p.divOW), ow = r - oh * p.OW;
-    const int ihBase = oh * p.sh - p.ph, iwBase = ow * p.sw - p.pw;
-    constexpr int kElem = U8 ? 1 : 4;                                       // bytes per element of X
-    const int pixBase = ((n * p.IH + ihBase) * p.IW + iwBase) * p.IC * kElem;   // bytes; may be negative
-    float xv[16];
+    const unsigned pixelBits = 0xffffffffu >> (32 - p.IC);   // columns of one tap
+
+    auto load_x = [&](int off) __attribute__((always_inline)) -> unsigned {
+        return U8 ? __builtin_amdgcn_raw_buffer_load_b8(rsrcX, off, 0, 0) : __builtin_amdgcn_raw_buffer_load_b32(rsrcX, off, 0, 0);
+    };
+    // pixel m: byte offset of its first column (may be negative) and the columns inside the image
+    auto place = [&](int tile, int &base, unsigned &inside) __attribute__((always_inline)) {
+        const int m = tile * kPatchTile + l32;
+        const int n = (int)fast_div((unsigned)m, p.divOHOW), r = m - n * ohow;
+        const int oh = (int)fast_div((unsigned)r, p.divOW), ow = r - oh * p.OW;
+        const int ih = oh * p.sh - p.ph, iw = ow * p.sw - p.pw;
+        base = ((n * p.IH + ih) * p.IW + iw) * p.IC * kElem;
+        unsigned row = 0u;
+        for (int fw = 0; fw < p.FW; ++fw) row |= ((unsigned)(iw + fw) < (unsigned)p.IW ? pixelBits : 0u) << (fw * p.IC);
+        inside = 0u;
+        for (int fh = 0; fh < p.FH; ++fh) inside |= ((unsigned)(ih + fh) < (unsigned)p.IH ? row : 0u) << (fh * p.FW * p.IC);
+        inside = m < p.M ? inside >> (16 * lh) : 0u;
+    };
+    unsigned x[16];   // the loads in flight: bytes or fp32 bits
+    auto gather = [&](int tile) __attribute__((always_inline)) {
+        int base;
+        unsigned inside;
+        place(tile, base, inside);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int k = khalf * 16 + i;                                     // uniform per instruction
-        const int tap = (int)fast_div((unsigned)k, p.divIC), ic = k - tap * p.IC;
-        const int fh = (int)fast_div((unsigned)tap, p.divFW), fw = tap - fh * p.FW;
-        const bool ok = k < Kp && m < p.M && (unsigned)(ihBase + fh) < (unsigned)p.IH &&
-                        (unsigned)(iwBase + fw) < (unsigned)p.IW;
-        const int off = ok ? pixBase + ((fh * p.IW + fw) * p.IC + ic) * kElem : kOutOfRange;
-        if (U8) xv[i] = (float)__builtin_amdgcn_raw_buffer_load_b8(rsrcX, off, 0, 0) * p.scale;
-        else xv[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrcX, off, 0, 0));
+        for (int e = 0; e < 16; ++e) {
+            const int off = base + kOff[e], ok = __builtin_amdgcn_sbfe((int)inside, e, 1);
+            x[e] = load_x((ok & off) | (~ok & kOutOfRange));
+        }
+    };
+    const int t0 = (int)(blockIdx.x / tilesN) * kPatchWaves + wave;
+    gather(t0);   // past the last tile: nothing inside
+
+    // 64 filter rows, split once per workgroup: thread t takes columns 8*(t%4) .. +7 of row t/4
+    auto terms = [&](const float *v, SplitQuad (&q)[2], unsigned &rest) __attribute__((always_inline)) {
+        q[0] = split_quad(f4{v[0], v[1], v[2], v[3]}, rest);
+        q[1] = split_quad(f4{v[4], v[5], v[6], v[7]}, rest);
+    };
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    unsigned restW = 0u;
+    {
+        const int row = threadIdx.x >> 2, g = threadIdx.x & 3, oc = oc0 + row;
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int k = 8 * g + e;
+            v[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                 rsrcW, k < Kp && oc < p.OC ? (oc * Kp + k) * 4 : kOutOfRange, 0, 0));
+        }
+        SplitQuad q[2];
+        terms(v, q, restW);
+        filter[0][g][row] = u4{q[0].h[0], q[0].h[1], q[1].h[0], q[1].h[1]};
+        filter[1][g][row] = u4{q[0].m[0], q[0].m[1], q[1].m[0], q[1].m[1]};
+        filter[2][g][row] = u4{q[0].l[0], q[0].l[1], q[1].l[0], q[1].l[1]};
     }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int idx = tid + kThreads * i;
-        Bs[(idx >> 5) * LDf + (idx & 31)] = wv[i];
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) As[row * LDf + khalf * 16 + i] = xv[i];
+    const int lostHere = split_lost(restW);
+    if (lane == 0) lostFilter[wave] = lostHere;
     __syncthreads();
-
-    // wave w: rows 32w .. 32w+31, all 64 columns
-    float16v acc[2];
+    if (t0 >= tiles) return;   // no barrier follows
+    bf8 fw[2][3][2];   // block of 32 rows, term, step of 16 columns
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int q = 0; q < 16; ++q) acc[j][q] = 0.f;
-    const float *a = As + (wave * 32 + l32) * LDf + lh;
-    const float *b = Bs + l32 * LDf + lh;
+        for (int pl = 0; pl < 3; ++pl)
 #pragma unroll
-    for (int step = 0; step < 16; ++step) {
-        const float fa = a[2 * step];
+            for (int s = 0; s < 2; ++s) fw[b][pl][s] = __builtin_bit_cast(bf8, filter[pl][2 * lh + s][b * 32 + l32]);
+    int lostAny = 0;
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-            acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa, b[j * 32 * LDf + 2 * step], acc[j], 0, 0, 0);
+    for (int w = 0; w < kPatchWaves; ++w) lostAny |= lostFilter[w];
+    const bool scaleOk = !U8 || (__builtin_fabsf(p.scale) >= 0x1p-100f && __builtin_fabsf(p.scale) <= 0x1p100f);
+    const bool lostW = lostAny != 0 || !scaleOk;
+    const int sRow = lane >> 3, seg = lane & 7;   // of the stores: pixel 8q + sRow of the tile, channels 4*seg .. +3 of a block
+    f4 bias[2];
+    if (EPI) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int oc = oc0 + b * 32 + seg * 4 + e;
+                bias[b][e] = p.bias && oc < p.OC ? p.bias[oc] : 0.f;
+            }
     }
-    // accumulator register q of lane l is row 8*(q/4)+4*(l/32)+q%4, column l%32
-    if (p.epilogue) {   // uniform: bias add and leaky-ReLU in the accumulator registers
+
+    bf8 fx[3][2];
+    unsigned rest;
+    auto take = [&]() __attribute__((always_inline)) {   // the gathered elements as fragments
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int col = oc0 + j * 32 + l32;
-            const float b = p.bias && col < p.OC ? p.bias[col] : 0.f;
+        for (int e = 0; e < 16; ++e) asm volatile("" : "+v"(x[e]));   // waited for here, not where they are loaded
+        rest = 0u;
+        if (U8) {
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const float v = acc[j][q] + b;
-                acc[j][q] = v > 0.f ? v : v * p.slope;
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) fx[0][s][e] = (__bf16)(float)x[8 * s + e];
+        } else {
+            float v[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = __builtin_bit_cast(float, x[e]);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                SplitQuad q[2];
+                terms(v + 8 * s, q, rest);
+                fx[0][s] = __builtin_bit_cast(bf8, u4{q[0].h[0], q[0].h[1], q[1].h[0], q[1].h[1]});
+                fx[1][s] = __builtin_bit_cast(bf8, u4{q[0].m[0], q[0].m[1], q[1].m[0], q[1].m[1]});
+                fx[2][s] = __builtin_bit_cast(bf8, u4{q[0].l[0], q[0].l[1], q[1].l[0], q[1].l[1]});
             }
         }
-    }
-    if ((p.OC & 3) == 0) {
-        // the kernel is bound by writing Y: turn each 32x32 block through LDS (the tiles are done
-        // with) so that a lane stores 16 bytes and a store instruction covers eight 128-byte runs
-        static_assert(4 * 32 * kLDT <= BMf * LDf + BNf * LDf, "four turning buffers fit over the tiles");
-        __syncthreads();                       // every wave has read its last fragments
-        float *scratch = sm + wave * 32 * kLDT;
+    };
+    take();
+    for (int tile = t0; tile < tiles; tile += stride) {
+        const int next = tile + stride;
+        const bool lostX = !U8 && split_lost(rest);
+        if (next < tiles) gather(next);   // uniform
+
+        float16v acc[2];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int colBase = oc0 + j * 32;
-            if (colBase < p.OC) {              // uniform; OC % 4 == 0, so 16-byte groups are in or out as a whole
+        for (int b = 0; b < 2; ++b)
 #pragma unroll
-                for (int q = 0; q < 16; ++q) scratch[(8 * (q / 4) + 4 * lh + (q % 4)) * kLDT + l32] = acc[j][q];
+            for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
+        if (U8) {
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int rowT = t * 8 + (lane >> 3), seg = lane & 7;
-                    const f4 v = *reinterpret_cast<const f4 *>(scratch + rowT * kLDT + seg * 4);
-                    const int mm = m0 + wave * 32 + rowT;
-                    if (mm < p.M && colBase + seg * 4 < p.OC)
-                        *reinterpret_cast<f4 *>(p.dX + (long long)mm * p.OC + colBase + seg * 4) = v;
+            for (int pl = 2; pl >= 0; --pl)
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[b][pl][s], fx[0][s], acc[b], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int g = 0; g < kSplitProducts; ++g)
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[b][kProdB[g]][s], fx[kProdA[g]][s], acc[b], 0, 0, 0);
+        }
+        SplitCheck check;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) check.look(f4{acc[b][4 * g], acc[b][4 * g + 1], acc[b][4 * g + 2], acc[b][4 * g + 3]});
+        const bool redo = lostW || lostX || __any(check.bad());
+        if (redo) {   // uniform
+            int base;
+            unsigned inside;
+            place(tile, base, inside);
+            if (lh) inside <<= 16;   // back to the pixel's columns; a lane takes columns 2t + lh here
+            inside |= (unsigned)__shfl_xor((int)inside, 32);
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
+            for (int t = 0; t < 16; ++t) {
+                const int k = 2 * t + lh, tap = (int)fast_div((unsigned)k, p.divIC), fh = (int)fast_div((unsigned)tap, p.divFW);
+                const int off = base + ((fh * p.IW + tap - fh * p.FW) * p.IC + k - tap * p.IC) * kElem;
+                const unsigned bits = load_x((inside >> k) & 1u ? off : kOutOfRange);
+                const float v = U8 ? (float)bits * p.scale : __builtin_bit_cast(float, bits);
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    const int oc = oc0 + b * 32 + l32;
+                    const float w = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                                  rsrcW, k < Kp && oc < p.OC ? (oc * Kp + k) * 4 : kOutOfRange, 0, 0));
+                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(w, v, acc[b], 0, 0, 0);
                 }
             }
         }
-        return;
-    }
+        // register r of lane l is channel 8*(r/4) + 4*lh + r%4 of pixel l32; the LDS pipeline keeps the wave's accesses in order
+        const float factor = U8 && !redo ? p.scale : 1.f;
+        f4 out[2][4];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int col = oc0 + j * 32 + l32;
-        if (col < p.OC) {
+        for (int b = 0; b < 2; ++b) {
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int mm = m0 + wave * 32 + 8 * (q / 4) + 4 * lh + (q % 4);
-                if (mm < p.M) p.dX[(long long)mm * p.OC + col] = acc[j][q];
+            for (int g = 0; g < 4; ++g) {
+                f4 v = f4{acc[b][4 * g], acc[b][4 * g + 1], acc[b][4 * g + 2], acc[b][4 * g + 3]};
+                if (U8) v *= factor;
+                *reinterpret_cast<f4 *>(scratch + l32 * kLDT + g * 8 + lh * 4) = v;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                f4 v = *reinterpret_cast<const f4 *>(scratch + (q * 8 + sRow) * kLDT + seg * 4);
+                if (EPI) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float y = v[e] + bias[b][e];
+                        v[e] = y > 0.f ? y : y * p.slope;
+                    }
+                }
+                out[b][q] = v;
             }
         }
+        // Loads and stores complete in any order among each other, so a wait for loads is one for all stores before it: the next tile's
+        // elements are taken before this tile's results leave, which then have a whole tile's time to complete.
+        if (next < tiles) take();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int m = tile * kPatchTile + q * 8 + sRow, col = oc0 + b * 32 + seg * 4, off = (m * p.OC + col) * 4;
+                if (QUAD) {
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i4s, out[b][q]), rsrcY,
+                                                           m < p.M && col < p.OC ? off : kOutOfRange, 0, 0);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, (float)out[b][q][e]), rsrcY,
+                                                              m < p.M && col + e < p.OC ? off + 4 * e : kOutOfRange, 0, 0);
+                }
+            }
     }
 }
 
 hipError_t launch_fwd_small_ic(const SmallIcParams &p, hipStream_t st)
 {
     if (!patch_small_ic_accepts(p.IC, p.FH, p.FW)) return hipErrorInvalidValue;
-    const int grid = ((p.M + 127) / 128) * ((p.OC + 63) / 64);
-    if (p.u8) hipLaunchKernelGGL(fwd_small_ic_kernel<true>, dim3((unsigned)grid), dim3(kThreads), 0, st, p);
-    else hipLaunchKernelGGL(fwd_small_ic_kernel<false>, dim3((unsigned)grid), dim3(kThreads), 0, st, p);
+    // at most three (bytes) or two waves a SIMD, each as many tiles as the others; whole laps of the 256 CUs where there are several
+    const int tilesN = (p.OC + 63) / 64, tiles = (p.M + kPatchTile - 1) / kPatchTile;
+    const int waves = p.u8 ? 3 : 2, most = 256 * waves / tilesN > 0 ? 256 * waves / tilesN : 1;
+    const int laps = (tiles + most * kPatchWaves - 1) / (most * kPatchWaves);
+    int rows = (tiles + laps * kPatchWaves - 1) / (laps * kPatchWaves);
+    if (laps > 1 && tilesN == 1) rows = (rows + 255) / 256 * 256;
+    const unsigned grid = (unsigned)(rows * tilesN);
+    const dim3 threads(kPatchWaves * 64);
+    if (p.u8 && p.epilogue) return hipErrorInvalidValue;
+    if (p.OC % 4 == 0) {
+        if (p.u8) hipLaunchKernelGGL((fwd_small_ic_kernel<true, false, true>), dim3(grid), threads, 0, st, p);
+        else if (p.epilogue) hipLaunchKernelGGL((fwd_small_ic_kernel<false, true, true>), dim3(grid), threads, 0, st, p);
+        else hipLaunchKernelGGL((fwd_small_ic_kernel<false, false, true>), dim3(grid), threads, 0, st, p);
+    } else {
+        if (p.u8) hipLaunchKernelGGL((fwd_small_ic_kernel<true, false, false>), dim3(grid), threads, 0, st, p);
+        else if (p.epilogue) hipLaunchKernelGGL((fwd_small_ic_kernel<false, true, false>), dim3(grid), threads, 0, st, p);
+        else hipLaunchKernelGGL((fwd_small_ic_kernel<false, false, false>), dim3(grid), threads, 0, st, p);
+    }
     return hipGetLastError();
 }
 
 // ---- backward-weight for very few input channels ----------------------------------------------
-// dW[oc, (fh,fw,ic)] = sum_m dY[m, oc] * patch[m, (fh,fw,ic)] with at most 32 columns: one 64 x 32
-// output tile per 64 output channels, the rows m = (n, oh, ow) cut into `split` slices.  The
-// kernel is bound by reading dY once, so it moves in macro-stages of 4 x 32 rows: all loads of a
-// macro-stage are in flight together (dY with 16-byte loads, the patch matrix element by element
-// - each thread owns one column, so its filter tap is fixed), and the next macro-stage is
-// requested before the current one is multiplied.  The four waves are 2 (oc halves) x 2 (halves
-// of a 32-row stage's 16 MFMA steps); the two step halves are added through LDS at the end.
+// dW[oc, (fh,fw,ic)] = sum_m dY[m, oc] * patch[m, (fh,fw,ic)] with at most 32 columns: one 64 x 32 tile per 64 output channels, the rows
+// m = (n, oh, ow) cut into `split` slices, on v_mfma_f32_32x32x16_bf16 with three-term operands (split_bf16.h).  Bound by reading dY
+// once and by the latency of doing so: a slice is a few dozen steps of 16 rows, dealt to the workgroup's eight waves, and every wave loads
+// the elements of its steps straight into the MFMA's operand layout (lane l: dY channel l%32 and patch column l%32, rows 8*(l/32) .. +7 of
+// the step), two steps ahead, without LDS or barriers.  The eight partial tiles are added through LDS in wave order.
+// ALIGNED: OW is a multiple of 8, so a lane's eight rows lie in one row of the image.
+// Accumulators as in kernel_wgrad_terms.hip, folded into LDS every 128 steps; a wave whose operands or sums the terms do not stand for forms its
+// part again with v_mfma_f32_32x32x2_f32.
+// 128 x 32x32x3 -> 64: with fp32 MFMA and 512 slices staged through LDS 14.5 us, now 12.0 on 256 slices; their combine pass 3.9 either way.
 namespace {
-constexpr int kSub = 4;                                   // 32-row stages per macro-stage
-constexpr int kWsLDG = 64 + 8, kWsLDX = 32 + 8;
-constexpr int kWsGStage = kBK * kWsLDG, kWsXStage = kBK * kWsLDX;
-}  // namespace
-
-__global__ __launch_bounds__(kThreads, 2) void wgrad_small_ic_kernel(const SmallIcParams p)
+constexpr int kWsWaves = 8, kWsStep = 16, kWsFold = 128;
+}
+template <bool ALIGNED>
+__global__ __launch_bounds__(kWsWaves * 64, 2) void wgrad_small_ic_kernel(const SmallIcParams p)
 {
-    constexpr int LDG = kWsLDG, LDX = kWsLDX, G_STAGE = kWsGStage, X_STAGE = kWsXStage;
-    extern __shared__ f4 smem_raw[];
-    float *Gs = reinterpret_cast<float *>(smem_raw);       // [kSub][32 rows][LDG]
-    float *Xs = Gs + kSub * G_STAGE;                       // [kSub][32 rows][LDX]
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int l32 = lane & 31, lh = lane >> 5;
-    const int slice = blockIdx.x % p.split, tmo = blockIdx.x / p.split;
-    const int oc0 = tmo * 64;
+    __shared__ f4 part[kWsWaves][8][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, lh = lane >> 5;
+    const int slice = blockIdx.x % p.split, oc0 = (int)(blockIdx.x / p.split) * 64;
     const int Kp = p.FH * p.FW * p.IC, ohow = p.OH * p.OW;
-    const int chunksTotal = (p.M + kBK - 1) / kBK;
-    const int ch0 = (int)((long long)slice * chunksTotal / p.split), ch1 = (int)((long long)(slice + 1) * chunksTotal / p.split);
-
+    const int chunks = (p.M + kBK - 1) / kBK;
+    const int s0 = __builtin_amdgcn_readfirstlane((int)((long long)slice * chunks / p.split) * (kBK / kWsStep));
+    const int s1 = __builtin_amdgcn_readfirstlane((int)((long long)(slice + 1) * chunks / p.split) * (kBK / kWsStep));
     constexpr int kOutOfRange = (int)0x80000000;
     const __amdgpu_buffer_rsrc_t rsrcX =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.X), 0, (int)p.xBytes, 0x00020000);
 
-    // dY loader: 32 rows x 16 segments per stage, 2 per thread; rows past M read zeros (see gload)
-    const int gSeg = tid & 15, gRow = tid >> 4;
-    int gOff[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-        gOff[i] = oc0 + gSeg * 4 < p.OC ? ((gRow + 16 * i) * p.OC + oc0 + gSeg * 4) * 4 : kOutOfRange;
-    // patch loader: thread owns column xCol (its tap is fixed) and rows xRow + 8*i of every stage
-    const int xCol = tid & 31, xRow = tid >> 5;
-    const bool colOk = xCol < Kp;
-    const int tap = colOk ? (int)fast_div((unsigned)xCol, p.divIC) : 0;
-    const int ic = xCol - tap * p.IC;
+    // this lane's patch column
+    const int tap = (int)fast_div((unsigned)l32, p.divIC), ic = l32 - tap * p.IC;
     const int fh = (int)fast_div((unsigned)tap, p.divFW), fw = tap - fh * p.FW;
+    const bool colOk = l32 < Kp;
 
-    f4 gg[kSub][2];
-    float gx[kSub][4];
-    auto gload = [&](int chBase) __attribute__((always_inline)) {
+    // byte offset of patch element (m, this lane's column), out of range outside the image; rows past the last one lie past the end of X
+    auto patch = [&](int m) __attribute__((always_inline)) -> int {
+        const int n = (int)fast_div((unsigned)m, p.divOHOW), r = m - n * ohow;
+        const int oh = (int)fast_div((unsigned)r, p.divOW), ow = r - oh * p.OW;
+        const int ih = oh * p.sh - p.ph + fh, iw = ow * p.sw - p.pw + fw;
+        const bool ok = colOk && m < p.M && (unsigned)ih < (unsigned)p.IH && (unsigned)iw < (unsigned)p.IW;
+        return ok ? (((n * p.IH + ih) * p.IW + iw) * p.IC + ic) * 4 : kOutOfRange;
+    };
+    int gOff[2][8];   // bytes from the step's first row
 #pragma unroll
-        for (int s = 0; s < kSub; ++s) {
-            const int ch = chBase + s;
-            const bool live = ch < ch1;      // uniform; stages past the slice load zeros
-            const int m0 = ch * kBK;
-            // dY through a window that starts at the stage's first row and ends with the tensor (empty
-            // for stages past the slice): the range check of a raw buffer load covers the VGPR offset
-            // only, so this is what makes the rows past M of a partial last stage read zeros
-            const unsigned gStart = live ? (unsigned)m0 * (unsigned)p.OC * 4u : p.gBytes;
-            const __amdgpu_buffer_rsrc_t rsrcG = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<char *>(reinterpret_cast<const char *>(p.G)) + gStart, 0, (int)(p.gBytes - gStart), 0x00020000);
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-                gg[s][i] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcG, gOff[i], 0, 0));
+        for (int e = 0; e < 8; ++e)
+            gOff[b][e] = oc0 + b * 32 + l32 < p.OC ? ((8 * lh + e) * p.OC + oc0 + b * 32 + l32) * 4 : kOutOfRange;
+    struct Raw {
+        float g[2][8], x[8];
+    };
+    auto load = [&](int step, Raw &raw) __attribute__((always_inline)) {
+        const int m0 = step * kWsStep + 8 * lh;
+        const bool live = step < s1;   // uniform
+        // dY through a window that starts at the step's first row and ends with the tensor (empty past the slice): the
+        // range check of a raw buffer load covers the VGPR offset only, so this is what makes the rows past M read zeros
+        const unsigned first = (unsigned)(step * kWsStep) * (unsigned)p.OC * 4u;
+        const unsigned start = (unsigned)__builtin_amdgcn_readfirstlane((int)(live && first < p.gBytes ? first : p.gBytes));
+        const __amdgpu_buffer_rsrc_t rsrcG = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char *>(reinterpret_cast<const char *>(p.G)) + start, 0, (int)(p.gBytes - start), 0x00020000);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int m = m0 + xRow + 8 * i;
-                const int n = (int)fast_div((unsigned)m, p.divOHOW);
-                const int r = m - n * ohow;
-                const int oh = (int)fast_div((unsigned)r, p.divOW), ow = r - oh * p.OW;
-                const int ih = oh * p.sh - p.ph + fh, iw = ow * p.sw - p.pw + fw;
-                const bool ok = live && colOk && m < p.M && (unsigned)ih < (unsigned)p.IH && (unsigned)iw < (unsigned)p.IW;
-                const int off = ok ? (((n * p.IH + ih) * p.IW + iw) * p.IC + ic) * 4 : kOutOfRange;
-                gx[s][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrcX, off, 0, 0));
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                raw.g[b][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrcG, gOff[b][e], 0, 0));
+        if constexpr (ALIGNED) {
+            const int n = (int)fast_div((unsigned)m0, p.divOHOW), r = m0 - n * ohow;
+            const int oh = (int)fast_div((unsigned)r, p.divOW), ow = r - oh * p.OW;
+            const int ih = oh * p.sh - p.ph + fh, iw = ow * p.sw - p.pw + fw;
+            const bool rowOk = live && colOk && m0 < p.M && (unsigned)ih < (unsigned)p.IH;
+            const int off = (((n * p.IH + ih) * p.IW + iw) * p.IC + ic) * 4;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const bool ok = rowOk && (unsigned)(iw + e * p.sw) < (unsigned)p.IW;
+                raw.x[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                         rsrcX, ok ? off + e * p.sw * p.IC * 4 : kOutOfRange, 0, 0));
             }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                raw.x[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrcX, live ? patch(m0 + e) : kOutOfRange, 0, 0));
         }
     };
-    auto lds_store = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int s = 0; s < kSub; ++s) {
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-                *reinterpret_cast<f4 *>(Gs + s * G_STAGE + (gRow + 16 * i) * LDG + gSeg * 4) = gg[s][i];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) Xs[s * X_STAGE + (xRow + 8 * i) * LDX + xCol] = gx[s][i];
-        }
+    unsigned rest = 0u;   // what the terms left of the elements split so far (see split_bf16.h)
+    auto terms = [&](const float *v, bf8 (&f)[3]) __attribute__((always_inline)) {
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        const SplitQuad a = split_quad(f4{v[0], v[1], v[2], v[3]}, rest), b = split_quad(f4{v[4], v[5], v[6], v[7]}, rest);
+        f[0] = __builtin_bit_cast(bf8, u4{a.h[0], a.h[1], b.h[0], b.h[1]});
+        f[1] = __builtin_bit_cast(bf8, u4{a.m[0], a.m[1], b.m[0], b.m[1]});
+        f[2] = __builtin_bit_cast(bf8, u4{a.l[0], a.l[1], b.l[0], b.l[1]});
     };
 
-    float16v acc;
+    float16v acc[2], low[2];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    const int wo = wave >> 1, wk = wave & 1;   // oc half, half of a stage's MFMA steps
-
-    if (ch0 < ch1) {
-        gload(ch0);
-        for (int ch = ch0; ch < ch1; ch += kSub) {
-            lds_store();
-            __syncthreads();
-            if (ch + kSub < ch1) gload(ch + kSub);
-            // lane (l32, lh) supplies row k = 2*step + lh of a stage: G^T as A, patch as B
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int s = 0; s < kSub; ++s) {
-                const float *g = Gs + s * G_STAGE + lh * LDG + wo * 32 + l32;
-                const float *x = Xs + s * X_STAGE + lh * LDX + l32;
+        for (int r = 0; r < 16; ++r) acc[b][r] = low[b][r] = 0.f;
+    int since = 0;
+    bool folded = false;
+    // the wave's sums into its part of LDS, added to what was folded before
+    auto fold = [&]() __attribute__((always_inline)) {
 #pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const int step = wk * 8 + t;
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(g[2 * step * LDG], x[2 * step * LDX], acc, 0, 0, 0);
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                f4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = 4 * g + e;
+                    v[e] = acc[b][r] + low[b][r];
+                    acc[b][r] = low[b][r] = 0.f;
+                }
+                f4 &held = part[wave][b * 4 + g][lane];
+                held = folded ? held + v : v;
+            }
+        folded = true;
+        since = 0;
+    };
+    auto multiply = [&](Raw &raw) __attribute__((always_inline)) {
+        bf8 fg[2][3], fx[3];
+        terms(raw.x, fx);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) terms(raw.g[b], fg[b]);
+#pragma unroll
+        for (int g = 0; g < kSplitProducts; ++g)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                float16v &sum = g == kSplitProducts - 1 ? acc[b] : low[b];
+                sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fg[b][kProdA[g]], fx[kProdB[g]], sum, 0, 0, 0);
+            }
+        if (++since == kWsFold) fold();   // uniform
+    };
+    Raw ra, rb;
+    load(s0 + wave, ra);
+    load(s0 + wave + kWsWaves, rb);
+    for (int s = s0 + wave; s < s1; s += 2 * kWsWaves) {   // steps past the slice load and add zeros
+        multiply(ra);
+        load(s + 2 * kWsWaves, ra);
+        multiply(rb);
+        load(s + 3 * kWsWaves, rb);
+    }
+    fold();
+    SplitCheck check;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) check.look(part[wave][q][lane]);
+    if (split_lost(rest) || __any(check.bad())) {   // uniform
+        const __amdgpu_buffer_rsrc_t rsrcG =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.G), 0, (int)p.gBytes, 0x00020000);
+        folded = false;
+        since = 0;
+        for (int s = s0 + wave; s < s1; s += kWsWaves) {
+            for (int t = 0; t < kWsStep / 2; ++t) {
+                const int m = s * kWsStep + 2 * t + lh;
+                const float x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrcX, patch(m), 0, 0));
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    const int oc = oc0 + b * 32 + l32;
+                    const float g = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                                  rsrcG, m < p.M && oc < p.OC ? (m * p.OC + oc) * 4 : kOutOfRange, 0, 0));
+                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(g, x, acc[b], 0, 0, 0);
                 }
             }
-            __syncthreads();   // all waves are done with this macro-stage's tiles
+            if (++since == 32) fold();   // chains of 512 products
         }
+        fold();
     }
 
-    // add the two step halves: waves with wk = 1 hand their block to the wave with the same oc half
-    float *red = Gs;   // 64 x 33 floats, the stage buffers are free now
-    if (wk == 1) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) red[(wo * 32 + 8 * (r / 4) + 4 * lh + (r % 4)) * 33 + l32] = acc[r];
-    }
+    // wave w adds registers 4*(w%4) .. +3 of block w/4 of all eight: rows 8*(w%4) + 4*lh .. +3 of the block, column l32
     __syncthreads();
-    if (wk == 0) {
-        float *C = p.C + (long long)slice * p.sliceStride;
+    f4 sum = part[0][wave][lane];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = 8 * (r / 4) + 4 * lh + (r % 4);
-            const int oc = oc0 + wo * 32 + row;
-            if (oc < p.OC && l32 < Kp) C[oc * Kp + l32] = acc[r] + red[(wo * 32 + row) * 33 + l32];
-        }
+    for (int w = 1; w < kWsWaves; ++w) sum += part[w][wave][lane];
+    float *C = p.C + (long long)slice * p.sliceStride;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int oc = oc0 + (wave >> 2) * 32 + 8 * (wave & 3) + 4 * lh + e;
+        if (oc < p.OC && colOk) C[oc * Kp + l32] = sum[e];
     }
 }
 
 hipError_t launch_wgrad_small_ic(const SmallIcParams &p, hipStream_t st)
 {
     if (!patch_small_ic_accepts(p.IC, p.FH, p.FW) || p.split < 1) return hipErrorInvalidValue;
-    constexpr size_t smem = (size_t)kSub * (kWsGStage + kWsXStage) * sizeof(float);
-    static_assert(64 * 33 <= kSub * kWsGStage, "the reduction buffer fits over the dY stages");
-    static_assert(smem <= 64 * 1024, "within the default dynamic LDS limit");
-    const int grid = ((p.OC + 63) / 64) * p.split;
-    hipLaunchKernelGGL(wgrad_small_ic_kernel, dim3((unsigned)grid), dim3(kThreads), smem, st, p);
+    const dim3 grid((unsigned)((p.OC + 63) / 64 * p.split)), threads(kWsWaves * 64);
+    if (p.OW % 8 == 0) hipLaunchKernelGGL(wgrad_small_ic_kernel<true>, grid, threads, 0, st, p);
+    else hipLaunchKernelGGL(wgrad_small_ic_kernel<false>, grid, threads, 0, st, p);
     return hipGetLastError();
 }
 

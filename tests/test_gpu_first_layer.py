@@ -1,0 +1,135 @@
+"""The first-layer kernels (at most 32 patch columns; backward-data at most 4 input channels) at the edges of their tiles, laps, steps and
+chunks, and on operands that three bf16 terms do not hold, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2305_08819_amd as mc
+from tests import gpu_util as gu
+from tests.test_gpu_products import far_from_one, inputs, run
+
+pytestmark = pytest.mark.gpu
+CODE = {"fwd": mc.OP_FWD, "bwd_data": mc.OP_BWD_DATA, "bwd_weight": mc.OP_BWD_WEIGHT}
+
+
+@pytest.fixture(autouse=True)
+def _restore():
+    yield
+    mc.conv2d_set_tuning(mc.VARIANT_AUTO, 0)
+
+
+def check_kernel(op, d):
+    assert mc.conv2d_query_plan(CODE[op], d).kernel == mc.KERNEL_FIRST_LAYER, op
+
+
+# (N, H, W, IC, OC, FH, FW, stride, pad), forced slices of backward-weight, operators
+FWD, DATA, WEIGHT = ("fwd",), ("bwd_data",), ("bwd_weight",)
+CASES = [
+    ((1, 3, 3, 3, 4, 3, 3, 1, 1), 0, FWD),                        # one partial tile of pixels, one of channels
+    ((3, 11, 13, 3, 66, 3, 3, 1, 1), 0, FWD),                     # channels not a multiple of 4, a second group of two
+    ((2, 9, 7, 2, 61, 4, 4, (2, 1), (1, 2)), 0, FWD),      # 32 patch columns exactly
+    ((80, 33, 33, 3, 64, 3, 3, 1, 1), 0, FWD),                    # two laps, the second one partial
+    ((200, 32, 32, 1, 160, 5, 5, 1, 2), 0, FWD),                  # several groups of channels, many laps
+    ((3, 8, 16, 3, 64, 3, 3, 1, 1), 1, WEIGHT),                   # rows of 8 pixels: eight rows of a lane in one image row
+    ((3, 9, 11, 3, 68, 3, 3, 1, 1), 1, WEIGHT),                   # and not; a last step that is partly empty
+    ((3, 9, 11, 3, 68, 3, 3, 1, 1), 9, WEIGHT),
+    ((2, 17, 16, 2, 132, 4, 4, 2, 1), 2, WEIGHT),
+    ((20, 33, 32, 3, 64, 3, 3, 1, 1), 1, WEIGHT),                 # 165 steps a wave: sums folded once
+    ((34, 31, 33, 1, 8, 3, 3, 1, 1), 1, WEIGHT),                  # twice, rows that end anywhere
+    ((2, 17, 33, 3, 32, 3, 3, 1, 1), 0, DATA),                    # half a chunk of channels; tiles cut on both sides
+    ((3, 7, 5, 4, 96, 2, 4, 1, 1), 0, DATA),                      # a chunk and a half
+    ((2, 9, 40, 1, 64, 1, 24, 1, (0, 3)), 0, DATA),               # a filter so wide that tiles have 4 rows
+    ((2, 12, 40, 2, 64, 3, 5, 1, (1, 2)), 0, DATA),               # 10 x 36 pixels of halo
+]
+IDS = dict(ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+
+
+@pytest.mark.parametrize("shp,split,ops", CASES, **IDS)
+def test_tiles(shp, split, ops):
+    d = mc.make_desc(*shp)
+    mc.conv2d_set_tuning(mc.VARIANT_MFMA if "bwd_weight" in ops else mc.VARIANT_AUTO, split)
+    for op in ops:
+        check_kernel(op, d)
+    print("first layer", shp, split, ops, flush=True)
+    gu.check_all_ops(d, *inputs(d, 31), ops=ops, label=str(shp), twice=True)
+
+
+REDO = [((3, 9, 11, 3, 68, 3, 3, 1, 0), 2, ("fwd", "bwd_weight")), ((20, 33, 32, 3, 64, 3, 3, 1, 0), 1, ("fwd", "bwd_weight")),
+        ((3, 20, 5, 4, 96, 2, 4, 1, 1), 0, DATA)]
+
+
+@pytest.mark.parametrize("shp,split,ops", REDO, **IDS)
+@pytest.mark.parametrize("kind", ["1e-37", "1e-42", "hidden", "2^-133"])
+def test_small_operand_with_a_large_partner(shp, split, ops, kind):
+    d = mc.make_desc(*shp)
+    for op in ops:
+        mc.conv2d_set_tuning(mc.VARIANT_MFMA if op == "bwd_weight" else mc.VARIANT_AUTO, split if op == "bwd_weight" else 0)
+        check_kernel(op, d)
+        print("first layer small", shp, op, kind, flush=True)
+        a, b = far_from_one(op, *gu.operands(op, *inputs(d, 11)), kind)
+        ref = gu.run_oracle(op, d, a, b)
+        got = run(op, d, a, b).astype(np.float64)
+        assert np.linalg.norm((got - ref).ravel()) <= 1e-5 * np.linalg.norm(ref.ravel()), op
+
+
+@pytest.mark.parametrize("shp,split,ops", REDO[:2], **IDS)
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 3.4028e38])
+def test_operands_beyond_bf16(shp, split, ops, value):
+    """One such element in the first operand, no padding: the elements it reaches are what the definition gives, the others are not touched."""
+    d = mc.make_desc(*shp)
+    for op in ops:
+        mc.conv2d_set_tuning(mc.VARIANT_MFMA if op == "bwd_weight" else mc.VARIANT_AUTO, split if op == "bwd_weight" else 0)
+        check_kernel(op, d)
+        print("first layer non-finite", shp, op, value, flush=True)
+        a, b = gu.operands(op, *inputs(d, 3))
+        b = np.clip(b, -0.5, 0.5)                      # products with the largest fp32 value stay finite
+        a.reshape(-1)[a.size // 3] = value
+        with np.errstate(over="ignore"):
+            ref = gu.run_oracle(op, d, a, b).astype(np.float32)
+        got = run(op, d, a, b)
+        for f in (np.isnan, np.isposinf, np.isneginf):
+            assert np.array_equal(f(got), f(ref)), op
+        ok = np.isfinite(ref)
+        assert ok.any()
+        scale = np.maximum(np.abs(ref[ok].astype(np.float64)), 1.0)      # sums of ordinary products, or one huge one
+        assert (np.abs(got[ok].astype(np.float64) - ref[ok]) <= 1e-4 * scale).all()
+
+
+@pytest.mark.parametrize("scale", [1.0 / 255, -2.0, 2.0 ** -100, 2.0 ** -101, 2.0 ** 100, 1e-38, 0.0])
+@pytest.mark.parametrize("shp", [(3, 11, 13, 3, 66, 3, 3, 1, 1), (600, 8, 8, 1, 64, 3, 3, 1, 1)], ids=str)
+def test_bytes(shp, scale):
+    """Scales inside and outside the range in which they are applied to the sums; filters of a size that keeps results in fp32's range."""
+    d = mc.make_desc(*shp)
+    rng = np.random.default_rng(5)
+    X8 = rng.integers(0, 256, (d.N, d.IH, d.IW, d.IC), dtype=np.uint8)
+    W = inputs(d, 2)[1]
+    if 0 < abs(scale) < 1e-20:
+        W = (W * np.float32(2.0 ** 90)).astype(np.float32)
+    elif abs(scale) > 1e20:
+        W = (W * np.float32(2.0 ** -90)).astype(np.float32)
+    scale = float(np.float32(scale))
+    buf, Y = gu.guarded((d.N, d.OH, d.OW, d.OC))
+    mc.conv2d_fwd_u8(torch.from_numpy(X8).cuda(), scale, gu.nan_fenced(W), Y, d)
+    torch.cuda.synchronize()
+    assert gu.guards_intact(buf)
+    ref = gu.oracle.conv2d_fwd_u8(X8, scale, W, (d.sh, d.sw), (d.ph, d.pw))
+    got = Y.cpu().numpy().astype(np.float64)
+    # byte * scale is rounded to fp32 before it is multiplied in the oracle: 2^-24 of each product, or a subnormal's spacing
+    floor = 2.0 ** -149 * 32 * np.abs(W).max() * np.sqrt(ref.size)
+    assert np.linalg.norm((got - ref).ravel()) <= 1e-6 * np.linalg.norm(ref.ravel()) + floor
+
+
+def test_bias_and_activation():
+    for shp in [(3, 11, 13, 3, 66, 3, 3, 1, 1), (80, 33, 33, 3, 64, 3, 3, 1, 1)]:
+        d = mc.make_desc(*shp)
+        check_kernel("fwd", d)
+        X, W, _ = inputs(d, 5)
+        bias = np.linspace(-1, 1, d.OC + 1).astype(np.float32)
+        ref = gu.run_oracle("fwd", d, X, W) + bias[1:]
+        ref = np.where(ref > 0, ref, ref * np.float32(0.125))
+        buf, Y = gu.guarded((d.N, d.OH, d.OW, d.OC))
+        mc.conv2d_fwd_bias_act(gu.nan_fenced(X), gu.nan_fenced(W), torch.from_numpy(bias).cuda()[1:], Y, d, 0.125)
+        torch.cuda.synchronize()
+        assert gu.guards_intact(buf)
+        rel, mx = gu.errors(Y.cpu().numpy(), ref)
+        assert rel <= gu.REL_L2_TOL and mx <= gu.MAX_ABS_TOL, (shp, rel, mx)
