@@ -1,8 +1,9 @@
 """MI355X-native fp32 NHWC convolution (forward, deconvolution/backward-data, backward-weight).
 
-Thin ctypes binding over ``libmi355conv.so`` (C ABI in ``include/mi355conv.h``).  The binding
+Thin binding over ``libmi355conv.so`` (C ABI in ``include/mi355conv.h``).  The binding
 only marshals arguments: shapes into a ``conv2d_desc``, torch CUDA tensors into raw device
-pointers, the current torch stream into a ``hipStream_t``.  All arithmetic runs in the HIP
+pointers, the current torch stream into a ``hipStream_t``.  The common operator calls are checked and
+converted in native code (``_binding``); what that declines, and everything else, goes through ctypes.  All arithmetic runs in the HIP
 kernels; there is no fallback, and importing the library fails loudly if it was not built.
 """
 from __future__ import annotations
@@ -59,6 +60,24 @@ class Mi355ConvError(RuntimeError):
 
 
 _lib = None
+_native = None       # the fast path of the operator calls, bound to the loaded library
+
+
+def _bind(lib):
+    global _native
+    import torch
+    try:
+        from . import _binding
+    except ImportError as e:
+        raise ImportError("%s: run `python -m paper_2305_08819_amd.build`" % e) from e
+    addresses = tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in
+                      ("conv2d_workspace_bytes", "conv2d_fwd", "conv2d_bwd_data", "conv2d_bwd_weight", "conv2d_fwd_bias_act",
+                       "conv2d_fwd_u8", "matmul_workspace_bytes", "matmul_f32"))
+    _binding.bind(addresses, torch.Tensor, torch.nn.Parameter, torch.float32, torch.uint8, ConvDesc,
+                  torch._C._cuda_getDevice if hasattr(torch._C, "_cuda_getDevice") else torch.cuda.current_device,
+                  torch._C._cuda_getCurrentRawStream if hasattr(torch._C, "_cuda_getCurrentRawStream") else
+                  lambda device: torch.cuda.current_stream(device).cuda_stream)
+    _native = _binding
 
 
 def load() -> ctypes.CDLL:
@@ -114,6 +133,7 @@ def load() -> ctypes.CDLL:
         lib.conv2d_status_string.restype = ctypes.c_char_p
         lib.conv2d_last_hip_error.argtypes = []
         lib.conv2d_last_hip_error.restype = ctypes.c_char_p
+        _bind(lib)
         _lib = lib
     return _lib
 
@@ -204,6 +224,20 @@ def conv2d_noalloc_scratch_bytes() -> int:
     return int(load().conv2d_noalloc_scratch_bytes())
 
 
+def _load_native():
+    load()
+    return _native
+
+
+def _done(rc, where):
+    """Whether the fast path made the call (rc None: not one for it)."""
+    if rc == 0:
+        return True
+    if rc is not None:
+        raise Mi355ConvError(rc, where)
+    return False
+
+
 def _ptr(t):   # the functions' argtypes turn the integer (None: NULL) into a pointer
     return t.data_ptr() if t is not None else None
 
@@ -250,6 +284,8 @@ def _call(name, op, a, b, out, desc, ws, stream):
 
 def conv2d_fwd(X, W, Y, desc: ConvDesc, ws=None, stream=None):
     """Y[N,OH,OW,OC] <- conv(X[N,IH,IW,IC], W[OC,FH,FW,IC]); enqueue only."""
+    if _done((_native or _load_native()).conv(OP_FWD, X, W, Y, desc, ws, stream), "conv2d_fwd"):
+        return Y
     _check(X, (desc.N, desc.IH, desc.IW, desc.IC), "X")
     _check(W, (desc.OC, desc.FH, desc.FW, desc.IC), "W")
     _check(Y, (desc.N, desc.OH, desc.OW, desc.OC), "Y")
@@ -258,6 +294,8 @@ def conv2d_fwd(X, W, Y, desc: ConvDesc, ws=None, stream=None):
 
 def conv2d_fwd_bias_act(X, W, bias, Y, desc: ConvDesc, negative_slope=1.0, ws=None, stream=None):
     """Y <- act(conv(X, W) + bias[oc]), act(v) = v if v > 0 else negative_slope * v; bias may be None."""
+    if _done((_native or _load_native()).bias_act(X, W, bias, Y, desc, negative_slope, ws, stream), "conv2d_fwd_bias_act"):
+        return Y
     _check(X, (desc.N, desc.IH, desc.IW, desc.IC), "X")
     _check(W, (desc.OC, desc.FH, desc.FW, desc.IC), "W")
     _check(Y, (desc.N, desc.OH, desc.OW, desc.OC), "Y")
@@ -276,6 +314,8 @@ def conv2d_fwd_bias_act(X, W, bias, Y, desc: ConvDesc, negative_slope=1.0, ws=No
 
 def conv2d_fwd_u8(X8, scale, W, Y, desc: ConvDesc, stream=None):
     """Y <- conv(float(X8) * scale, W) for uint8 pixels X8[N,IH,IW,IC]; first-layer shapes only."""
+    if _done((_native or _load_native()).fwd_u8(X8, scale, W, Y, desc, stream), "conv2d_fwd_u8"):
+        return Y
     import torch
     if not (X8.is_cuda and X8.dtype == torch.uint8 and X8.is_contiguous()):
         raise ValueError("X8 must be a contiguous uint8 CUDA tensor")
@@ -292,6 +332,8 @@ def conv2d_fwd_u8(X8, scale, W, Y, desc: ConvDesc, stream=None):
 
 def conv2d_bwd_data(dY, W, dX, desc: ConvDesc, ws=None, stream=None):
     """dX[N,IH,IW,IC] <- deconv(dY[N,OH,OW,OC], W[OC,FH,FW,IC]); enqueue only."""
+    if _done((_native or _load_native()).conv(OP_BWD_DATA, dY, W, dX, desc, ws, stream), "conv2d_bwd_data"):
+        return dX
     _check(dY, (desc.N, desc.OH, desc.OW, desc.OC), "dY")
     _check(W, (desc.OC, desc.FH, desc.FW, desc.IC), "W")
     _check(dX, (desc.N, desc.IH, desc.IW, desc.IC), "dX")
@@ -308,6 +350,8 @@ def deconv2d(dY, W, dX, desc: ConvDesc, ws=None, stream=None):
 
 def conv2d_bwd_weight(X, dY, dW, desc: ConvDesc, ws=None, stream=None):
     """dW[OC,FH,FW,IC] <- sum over pixels of dY x X; enqueue only."""
+    if _done((_native or _load_native()).conv(OP_BWD_WEIGHT, X, dY, dW, desc, ws, stream), "conv2d_bwd_weight"):
+        return dW
     _check(X, (desc.N, desc.IH, desc.IW, desc.IC), "X")
     _check(dY, (desc.N, desc.OH, desc.OW, desc.OC), "dY")
     _check(dW, (desc.OC, desc.FH, desc.FW, desc.IC), "dW")
@@ -341,6 +385,8 @@ def matmul_workspace_bytes(kind: int, M: int, N: int, K: int) -> int:
 def matmul_f32(kind, A, B, C, ws=None, stream=None):
     """C[M,N] <- A B^T (MATMUL_NT), A B (MATMUL_NN) or A^T B (MATMUL_TN): the fully-connected layer's
     forward, input gradient and weight gradient; enqueue only."""
+    if _done((_native or _load_native()).matmul(kind, A, B, C, ws, stream), "matmul_f32"):
+        return C
     M, N = C.shape
     K = A.shape[0] if kind == MATMUL_TN else A.shape[1]
     _check(A, (K, M) if kind == MATMUL_TN else (M, K), "A")

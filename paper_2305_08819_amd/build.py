@@ -7,12 +7,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libmi355conv.so")
+BINDING = os.path.join(PKG, "_binding.so")      # the Python binding's fast path (host code only)
 SOURCES = ["api.hip", "kernels_direct.hip", "kernel_gather_gemm.hip", "kernel_gather_elem.hip",
            "kernel_wgrad.hip", "kernel_wgrad_fast.hip", "kernel_gather_terms.hip", "kernel_wgrad_terms.hip", "kernel_halo_terms.hip",
            "kernel_short.hip",
@@ -64,6 +66,15 @@ def build_host_sanitized(out_dir: str) -> str:
     return lib
 
 
+def build_binding(force: bool = False) -> str:
+    if force or not os.path.exists(BINDING) or os.path.getmtime(BINDING) < _deps_mtime():
+        tmp = BINDING + ".tmp%d" % os.getpid()
+        subprocess.check_call(["g++", "-std=c++17", "-O2", "-Wall", "-fPIC", "-shared", "-I" + sysconfig.get_paths()["include"],
+                               os.path.join(CSRC, "binding.cpp"), "-o", tmp])
+        os.replace(tmp, BINDING)
+    return BINDING
+
+
 def build(force: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=4) as ex:
@@ -72,6 +83,7 @@ def build(force: bool = False) -> str:
         tmp = LIB + ".tmp%d" % os.getpid()
         subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs)
         os.replace(tmp, LIB)
+    build_binding(force)
     return LIB
 
 

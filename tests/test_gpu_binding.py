@@ -1,0 +1,86 @@
+"""The native fast path of the binding and the interpreted one behind it: the same results, the same refusals."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2305_08819_amd as mc
+
+pytestmark = pytest.mark.gpu
+
+
+class Sub(torch.Tensor):
+    pass
+
+
+def operands(d):
+    g = torch.Generator(device="cuda").manual_seed(3)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda")   # noqa: E731
+    return r(d.N, d.IH, d.IW, d.IC), r(d.OC, d.FH, d.FW, d.IC), r(d.N, d.OH, d.OW, d.OC), r(d.OC)
+
+
+def calls(d, X, W, G, b, ws, stream=None, slope=0.25):
+    """Every operator into fresh outputs."""
+    Y, Y2, dX, dW = torch.empty_like(G), torch.empty_like(G), torch.empty_like(X), torch.empty_like(W)
+    mc.conv2d_fwd(X, W, Y, d, ws=ws, stream=stream)
+    mc.conv2d_fwd_bias_act(X, W, b, Y2, d, slope, ws=ws, stream=stream)
+    mc.conv2d_bwd_data(G, W, dX, d, ws=ws, stream=stream)
+    mc.conv2d_bwd_weight(X, G, dW, d, ws=ws, stream=stream)
+    A, B = X.reshape(-1, d.IC), W.reshape(-1, d.IC)
+    C = torch.empty(A.shape[0], B.shape[0], device="cuda")
+    mc.matmul_f32(mc.MATMUL_NT, A.as_subclass(type(X)), B, C, ws=ws, stream=stream)
+    torch.cuda.synchronize()
+    return [t.detach().cpu().numpy() for t in (Y, Y2, dX, dW, C)]
+
+
+@pytest.mark.parametrize("shp", [(2, 5, 7, 36, 40, 3, 2, (2, 1), (1, 0)), (64, 4, 4, 64, 96, 3, 3, 1, 1)], ids=str)
+def test_same_results_either_way(shp):
+    """Forms that the native path takes (tensors, parameters, another stream, no workspace needed) and forms that it leaves to the
+    interpreted one (subclasses, a workspace to be allocated, an integer slope)."""
+    d = mc.make_desc(*shp)
+    X, W, G, b = operands(d)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    ref = calls(d, X, W, G, b, ws)
+    assert mc._native is not None and mc._native.conv(mc.OP_FWD, X, W, torch.empty_like(G), d, ws, None) == 0
+    sub = X.as_subclass(Sub)
+    assert mc._native.conv(mc.OP_FWD, sub, W, torch.empty_like(G), d, ws, None) is None
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    for got in (calls(d, X, torch.nn.Parameter(W), G, b, ws), calls(d, sub, W, G, b, ws), calls(d, X, W, G, b, None),
+                calls(d, X, W, G, b, ws, stream=s), calls(d, X, W, G, b, ws.view(torch.float32))):
+        for a, r in zip(got, ref):
+            assert np.array_equal(a, r)
+    one = calls(d, X, W, G, b, ws, slope=1)
+    assert np.array_equal(one[1], calls(d, X, W, G, b, ws, slope=1.0)[1])
+    with torch.cuda.stream(s):
+        for a, r in zip(calls(d, X, W, G, b, ws), ref):
+            assert np.array_equal(a, r)
+
+
+def test_same_refusals():
+    d = mc.make_desc(2, 8, 8, 64, 64, 3, 3, 1, 1)
+    X, W, G, b = operands(d)
+    Y = torch.empty_like(G)
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    for bad in (X.cpu(), X.double(), X.transpose(1, 2), X[:1], X.reshape(-1), None):
+        with pytest.raises((ValueError, AttributeError)):
+            mc.conv2d_fwd(bad, W, Y, d, ws=ws)
+    with pytest.raises(ValueError):
+        mc.conv2d_fwd_bias_act(X, W, b[:-1], Y, d, 0.5, ws=ws)
+    with pytest.raises(mc.Mi355ConvError):
+        mc.conv2d_fwd_bias_act(X, W, b, Y, d, float("nan"), ws=ws)
+    mc.conv2d_set_tuning(mc.VARIANT_MFMA, 2)
+    try:
+        with pytest.raises(mc.Mi355ConvError):       # a workspace that is too small is the library's to refuse
+            mc.conv2d_fwd(X, W, Y, d, ws=ws[:16])
+    finally:
+        mc.conv2d_set_tuning(mc.VARIANT_AUTO, 0)
+    off = torch.empty(X.numel() + 1, device="cuda")[1:].view(X.shape)
+    with pytest.raises(mc.Mi355ConvError):           # aligned to 4 bytes only
+        mc.conv2d_fwd(off, W, Y, d, ws=ws)
+    broken = mc.make_desc(2, 8, 8, 64, 64, 3, 3, 0, 1)
+    with pytest.raises((mc.Mi355ConvError, ZeroDivisionError)):
+        mc.conv2d_fwd(X, W, Y, broken, ws=ws)
+    with pytest.raises(ValueError):
+        mc.conv2d_fwd_u8(X, 1.0, W, Y, d)
+    with pytest.raises(ValueError):
+        mc.matmul_f32(mc.MATMUL_NT, X.reshape(-1, 64), W.reshape(-1, 32), torch.empty(128, 1152, device="cuda"))
