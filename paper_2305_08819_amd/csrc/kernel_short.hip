@@ -3,7 +3,7 @@
 // Such calls are bound by launches and by chains of dependent loads, not by arithmetic or bytes: the tiled
 // kernels walk their stages through LDS with a barrier each and, to have more than a handful of workgroups,
 // cut the reduction into slices that a second kernel adds.  Here a workgroup owns one 32 x 32 block and its
-// eight waves share the reduction: wave w takes the eight-element steps w, w + 8, ..., four of them in
+// eight waves share the reduction: wave w takes the eight-element steps w, w + 8, ..., up to eight of them in
 // flight, straight from global memory into the operand registers of v_mfma_f32_32x32x2_f32 (no LDS, no
 // barrier), and the eight partial blocks meet in LDS once, at the end, and are added in wave order.
 //
@@ -11,9 +11,11 @@
 // backward-weight  oc x (tap, ic), pixels.  Every element outside the image or past an end is a zero chosen
 // after a load from element 0, so no lane branches and no access leaves its tensor.  Any channel count, stride
 // and padding; a reduction channel count that is a multiple of 4 (QUAD) is read 16 bytes at a time.
-// Bound by latency: 2.7 us of launch and last addition, then one memory round trip per batch of 256 reduction elements
-// (1.9 us forward, 2.7 backward-data, 4.2 backward-weight, whose loads are 4 bytes).  4 images 8x8x16 -> 16 forward 10.4
-// (four slices and their combine pass) -> 4.7 us, 512x256 by 256x512 9.9 -> 5.3.
+// Bound by latency: 2.7 us of launch and last addition, then the addresses (some 25 instructions for every 4-byte load) and one memory round
+// trip per batch of 8 * 8 * STEPS reduction elements.  STEPS is the number of steps that a wave has, up to eight: a shorter sum computes no
+// addresses for steps past its end, a longer one waits once for twice as many loads.  Four steps always and this, us: backward-data 128 x 512 x 10
+// 7.0 and 4.0, backward-weight 10 x 512 over 128 rows 6.4 and 5.0, forward of 512 products 6.0 and 6.0; the three matrix products of that layer
+// 18.5 and 14.2.  Against the sliced plans: 4 images 8x8x16 -> 16 forward 10.4 (four slices and their combine pass) -> 4.7 us.
 #include <climits>
 #include <type_traits>
 #include "gather_common.h"
@@ -22,7 +24,7 @@
 namespace mi355conv {
 
 namespace {
-constexpr int kShortWaves = 8, kShortSteps = 4, kShortPitch = 33;
+constexpr int kShortWaves = 8, kShortPitch = 33;
 typedef float f4u __attribute__((ext_vector_type(4)));
 
 struct Digits {   // n = hi * d + lo
@@ -80,7 +82,7 @@ __device__ __forceinline__ float short_element(const ShortParams &p, int r, int 
     return (float)(sum + (double)chain);
 }
 
-template <int OP, bool QUAD>
+template <int OP, bool QUAD, int STEPS>
 __global__ __launch_bounds__(kShortWaves * 64) void short_kernel(const ShortParams p)
 {
     __shared__ float part[kShortWaves][32 * kShortPitch];
@@ -139,12 +141,12 @@ __global__ __launch_bounds__(kShortWaves * 64) void short_kernel(const ShortPara
     // a chain; backward-weight chains of 8 added in fp64, because the direct kernel adds 256 short chains pairwise.
     // Error against 64 bits, before -> after: forward K = 512 1.5e-7 -> 0.9e-7, dW of 300 rows 0.81e-7 -> 0.64e-7.  (fp64
     // throughout costs forward another 1.1 us at 256 products, one chain per wave saves 0.3 and gives dW 1.1e-7.)
-    constexpr int kChain = OP == MI355CONV_OP_BWD_WEIGHT ? 1 : 2;   // steps
+    constexpr int kChain = OP == MI355CONV_OP_BWD_WEIGHT || STEPS == 1 ? 1 : 2;   // steps
     typename std::conditional<OP == MI355CONV_OP_BWD_WEIGHT, double, float>::type acc[16] = {};
-    for (int step = wave; step < p.steps; step += kShortWaves * kShortSteps) {   // uniform in a wave
-        f4u a[kShortSteps], b[kShortSteps];
+    for (int step = wave; step < p.steps; step += kShortWaves * STEPS) {   // uniform in a wave
+        f4u a[STEPS], b[STEPS];
 #pragma unroll
-        for (int u = 0; u < kShortSteps; ++u) {
+        for (int u = 0; u < STEPS; ++u) {
             const int k = (step + u * kShortWaves) * 8 + lh * 4;   // four elements per half wave; past the end: zeros
             if (QUAD && OP != MI355CONV_OP_BWD_WEIGHT) {
                 const Digits kc = digits(k, p.ch, p.divCh);        // the four lie in one tap
@@ -165,7 +167,7 @@ __global__ __launch_bounds__(kShortWaves * 64) void short_kernel(const ShortPara
             }
         }
 #pragma unroll
-        for (int u = 0; u < kShortSteps; u += kChain) {
+        for (int u = 0; u < STEPS; u += kChain) {
             float16v c = {};
 #pragma unroll
             for (int i = 0; i < 4 * kChain; ++i)
@@ -197,6 +199,17 @@ __global__ __launch_bounds__(kShortWaves * 64) void short_kernel(const ShortPara
     }
 }
 
+template <int OP, bool QUAD>
+static void launch_steps(const ShortParams &p, dim3 grid, hipStream_t st)
+{
+    const dim3 block(kShortWaves * 64);
+    const int steps = (p.steps + kShortWaves - 1) / kShortWaves;   // of a wave
+    if (steps <= 1) hipLaunchKernelGGL((short_kernel<OP, QUAD, 1>), grid, block, 0, st, p);
+    else if (steps <= 2) hipLaunchKernelGGL((short_kernel<OP, QUAD, 2>), grid, block, 0, st, p);
+    else if (steps <= 4) hipLaunchKernelGGL((short_kernel<OP, QUAD, 4>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((short_kernel<OP, QUAD, 8>), grid, block, 0, st, p);
+}
+
 hipError_t launch_short(int op, const float *A, const float *B, float *C, const Shape &s, bool epi, const float *bias,
                         float slope, hipStream_t st)
 {
@@ -226,13 +239,13 @@ hipError_t launch_short(int op, const float *A, const float *B, float *C, const 
     p.divFW = make_fastdiv((unsigned)s.FW);
     p.divSh = make_fastdiv((unsigned)s.sh);
     p.divSw = make_fastdiv((unsigned)s.sw);
-    const dim3 grid((unsigned)(p.tilesN * ((p.rows + 31) / 32))), block(kShortWaves * 64);
+    const dim3 grid((unsigned)(p.tilesN * ((p.rows + 31) / 32)));
     const bool quad = p.ch % 4 == 0;
-    if (wgt) hipLaunchKernelGGL((short_kernel<MI355CONV_OP_BWD_WEIGHT, false>), grid, block, 0, st, p);
-    else if (fwd && quad) hipLaunchKernelGGL((short_kernel<MI355CONV_OP_FWD, true>), grid, block, 0, st, p);
-    else if (fwd) hipLaunchKernelGGL((short_kernel<MI355CONV_OP_FWD, false>), grid, block, 0, st, p);
-    else if (quad) hipLaunchKernelGGL((short_kernel<MI355CONV_OP_BWD_DATA, true>), grid, block, 0, st, p);
-    else hipLaunchKernelGGL((short_kernel<MI355CONV_OP_BWD_DATA, false>), grid, block, 0, st, p);
+    if (wgt) launch_steps<MI355CONV_OP_BWD_WEIGHT, false>(p, grid, st);
+    else if (fwd && quad) launch_steps<MI355CONV_OP_FWD, true>(p, grid, st);
+    else if (fwd) launch_steps<MI355CONV_OP_FWD, false>(p, grid, st);
+    else if (quad) launch_steps<MI355CONV_OP_BWD_DATA, true>(p, grid, st);
+    else launch_steps<MI355CONV_OP_BWD_DATA, false>(p, grid, st);
     return hipGetLastError();
 }
 
