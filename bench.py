@@ -71,6 +71,8 @@ def kernel_name(layer, op, plan, desc, mc):
         return "gather_elem_kernel<%d, %d, %d, %s>" % (t + (waves_m, b(bwd)))
     src, dst = (layer.OC, layer.IC) if bwd else (layer.IC, layer.OC)
     belem = bwd and dst % 4 != 0
+    if terms and plan.order == mc.ORDER_CONTIGUOUS and layer.FH * layer.FW == 1:
+        return "pointwise_terms_kernel<%d, %s>" % ((src + 31) // 32 * 2, b(bwd))
     if terms and plan.order == mc.ORDER_CONTIGUOUS:
         return "halo_terms_kernel<%d, %d, %s, %s>" % ((128 if t[1] == 128 else 256, t[1]) + (b(bwd), b(src % 32 != 0)))
     if terms:

@@ -95,7 +95,9 @@ enum {
     MI355CONV_ORDER_REGIONS = 2,   /* every XCD owns a part of the tiles that shares operands          */
     MI355CONV_ORDER_CONTIGUOUS = 3 /* every XCD owns consecutive row tiles: the forward / backward-data kernel of unit-stride
                                       layers with equal maps, which gathers a tile's pixels once for all taps; its 64-column
-                                      workgroups take two neighbouring 128 x 64 tiles and are reported as such */
+                                      workgroups take two neighbouring 128 x 64 tiles and are reported as such.  With a 1x1
+                                      filter: the kernel that keeps a panel of the filter in LDS; its workgroups walk row tiles
+                                      (grid counts workgroups, the tile is 128 rows by a block pair of 64 columns)          */
 };
 
 /* Kernel families (conv2d_plan_info.kernel); for tests, which force every compiled variant.  GATHER, WGRAD and

@@ -50,6 +50,7 @@ struct Plan {
     int fast = 0;          // backward-weight: aligned map
     int terms = 0;         // products on the bf16 matrix pipe (three-term operands) instead of fp32 MFMA
     int halo = 0;          // forward / backward-data: the kernel that splits the gathered tensor once for all taps (with terms)
+    int pointwise = 0;     // forward / backward-data of a 1x1 filter: columns of a panel (tilesM: 128-row tiles, tilesN: panels; with terms)
     int shortCall = 0;     // one launch of short_kernel (variant DIRECT: any shape, no workspace)
     int smallIc = 0;       // backward-data: patch-gradient GEMM + col2im kernel for very few input channels
     int grid = 0;
@@ -471,6 +472,43 @@ double halo_plan(const Shape &s, bool bwd, long long outElems, int *bmOut, int *
     return best;
 }
 
+// The 1x1 kernel that keeps a filter panel in LDS (pointwise_terms_kernel), one workgroup a CU.  Taken where the result has at least 768 Ki
+// elements, 2048 rows and more than 32 columns.  110 drawn calls (16 to 128 reduction channels), forward and backward-data, us, the other
+// kernels and this one: the 104 timings in that range 1.37 times as fast together, none slower by more than 2 % (32768 x 64 -> 256 18.5
+// and 16.0, 100352 x 128 -> 512 137 and 102, 2383 x 56 -> 540 8.9 and 6.5); below it either may win (8192 x 96 -> 64 6.5 and 8.1, 1024 x 128 ->
+// 512 6.5 and 9.9, 6666 x 56 -> 136 7.6 and 4.9), and with 32 columns one wave of each pair has no block (158745 x 64 -> 32 17.7 and 20.0).
+// The width of a panel - wide ones read the pixels less often, narrow ones use more CUs - by a cost in us fitted to those timings (rms 8 %, its
+// picks 0.03 % above the best width): prologue, laps over the row tiles, result, pixels once a panel.
+void pointwise_take(const Shape &s, bool bwd, Plan &pl)
+{
+    const int K = bwd ? s.OC : s.IC, N = bwd ? s.IC : s.OC, ks = pointwise_steps(K);
+    const long long M = (long long)s.N * s.IH * s.IW;
+    if (!pointwise_accepts(s, bwd) || M < 2048 || N <= 32 || M * N < 768 * 1024 || !products_allowed(true) || g_forceBM.load() ||
+        g_forcePosMajor.load() >= 0 || g_forceSplit.load())
+        return;
+    const int tiles = ceil_div(M, 128), blocksN = ceil_div(N, 64);
+    double best = 1e300;
+    for (int panels = 1; panels <= blocksN; ++panels) {
+        const int blocks = ceil_div(blocksN, panels);
+        if (blocks * 64 > pointwise_columns(ks) || ceil_div(blocksN, blocks) != panels) continue;
+        const int groups = std::min(std::max(1, 32 / panels), ceil_div(tiles, 8));
+        const double laps = ceil_div(tiles, 8 * groups), mb = 4e-6 * (double)M;
+        const double t = 3.2 + 0.24 * ks * blocks + laps * (0.27 + 0.18 * ks * blocks) + 0.094 * mb * N + 0.16 * mb * K * panels;
+        if (t >= best) continue;
+        best = t;
+        pl.pointwise = blocks * 64;
+        pl.tilesN = panels;
+        pl.grid = 8 * groups * panels;
+    }
+    pl.terms = 1;
+    pl.posMajor = 0;
+    pl.bm = 128;
+    pl.bn = 64;
+    pl.split = 1;
+    pl.tilesM = tiles;
+    pl.wsBytes = 0;
+}
+
 Plan plan_fwd(const Shape &s)
 {
     Plan pl;
@@ -565,6 +603,7 @@ Plan plan_fwd(const Shape &s)
     pl.tilesM = ceil_div(M, pl.bm);
     set_forward_phase(pl, s);
     finish_plan(pl, pl.split);
+    pointwise_take(s, false, pl);
     return pl;
 }
 
@@ -733,6 +772,7 @@ Plan plan_bwd_data(const Shape &s)
         pl.tilesN = ceil_div(s.IC, hbn);
     }
     finish_plan(pl, pl.split);
+    pointwise_take(s, true, pl);
     return pl;
 }
 
@@ -882,6 +922,7 @@ int prepare_device(int *devOut)
     if (e == hipSuccess) e = prepare_gather_terms();
     if (e == hipSuccess) e = prepare_wgrad_terms();
     if (e == hipSuccess) e = prepare_halo_terms();
+    if (e == hipSuccess) e = prepare_pointwise_terms();
     void *ptr = nullptr;
     if (e == hipSuccess) e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
     if (e != hipSuccess) return hip_fail(e);
@@ -1247,7 +1288,7 @@ void plan_order_gather(const Shape &s, Plan &pl, bool bwd)
     pl.balance = 0;
     pl.regional = 0;
     pl.chunksPerSlice = 0;
-    if (pl.smallIc || pl.halo) return;
+    if (pl.smallIc || pl.halo || pl.pointwise) return;
     const int chunks = ceil_div(bwd ? s.OC : s.IC, kBK);
     if (!pl.elem && pl.split > 1 && chunks % pl.split == 0) pl.chunksPerSlice = chunks / pl.split;
     if (g_regionalOrder.load() && plan_regional_gather(s, pl, bwd)) return;
@@ -1349,6 +1390,10 @@ bool plan_launchable(int op, const Shape &s, const Plan &pl)
         int lo, span, items;
         return ((pl.bm == 128 && pl.bn == 128) || (pl.bm == 256 && pl.bn == 64)) && halo_span(s, pl.bm, &lo, &span, &items) &&
                pl.split <= ceil_div(bwd ? s.OC : s.IC, kBK);
+    }
+    if (pl.pointwise) {
+        const int ks = pointwise_steps(bwd ? s.OC : s.IC);
+        return pointwise_accepts(s, bwd) && pl.pointwise % 64 == 0 && pl.pointwise <= pointwise_columns(ks) && pl.split == 1;
     }
     if (pl.posMajor && s.N % pl.bm != 0) return false;   // a row tile sits on one pixel position
     if (pl.elem) return gather_elem_accepts(pl.bm, pl.bn);
@@ -1620,6 +1665,26 @@ int run_gather(const float *A, const float *B, float *out, const Shape &s, const
         h.bias = epi.bias;
         h.slope = epi.slope;
         e = launch_halo_terms(h, bwd, pl.bm, pl.bn, pl.grid, st);
+    } else if (pl.pointwise) {
+        PointwiseParams q;
+        memset(&q, 0, sizeof q);
+        q.A = A;
+        q.B = B;
+        q.C = out;
+        q.bias = epi.on ? epi.bias : nullptr;
+        q.epilogue = epi.on ? 1 : 0;
+        q.slope = epi.slope;
+        q.M = s.N * s.IH * s.IW;
+        q.K = bwd ? s.OC : s.IC;
+        q.N = bwd ? s.IC : s.OC;
+        q.aBytes = (unsigned)((long long)q.M * q.K * 4);
+        q.bBytes = (unsigned)((long long)q.K * q.N * 4);
+        q.rowTiles = pl.tilesM;
+        q.panels = pl.tilesN;
+        q.cols = pl.pointwise;
+        q.groups = pl.grid / (8 * pl.tilesN);
+        q.divPanels = make_fastdiv((unsigned)pl.tilesN);
+        e = launch_pointwise_terms(q, bwd, pl.grid, st);
     } else {
     GatherGemmParams g;
     fill_gather_geometry(g, s, pl, bwd);
@@ -1674,7 +1739,7 @@ int conv2d_query_plan(int op, const conv2d_desc *d, conv2d_plan_info *info)
     else if (pl.smallIc) info->kernel = MI355CONV_KERNEL_FIRST_LAYER;
     else if (op == MI355CONV_OP_BWD_WEIGHT) info->kernel = pl.fast ? MI355CONV_KERNEL_WGRAD_FAST : MI355CONV_KERNEL_WGRAD;
     else info->kernel = pl.elem ? MI355CONV_KERNEL_GATHER_ELEM : MI355CONV_KERNEL_GATHER;
-    info->order = pl.halo ? MI355CONV_ORDER_CONTIGUOUS : pl.regional ? MI355CONV_ORDER_REGIONS : pl.balance ? MI355CONV_ORDER_LONGEST : MI355CONV_ORDER_PLAIN;
+    info->order = pl.halo || pl.pointwise ? MI355CONV_ORDER_CONTIGUOUS : pl.regional ? MI355CONV_ORDER_REGIONS : pl.balance ? MI355CONV_ORDER_LONGEST : MI355CONV_ORDER_PLAIN;
     return MI355CONV_OK;
 }
 

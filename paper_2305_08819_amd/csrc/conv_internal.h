@@ -249,6 +249,28 @@ inline bool halo_span(const Shape &s, int bm, int *lo, int *span, int *items)
     return *items * 64 <= halo_rows(bm) && taps <= 32 && taps >= *items + 2;
 }
 
+// ---- 1x1 layers of unit stride without padding, few reduction channels (kernel_pointwise_terms.hip) -----
+// C[M, N] = A[M, K] x filter; the filter's columns in panels, a workgroup takes one and walks 128-row tiles.
+struct PointwiseParams {
+    const float *A, *B;
+    float *C;
+    const float *bias;    // may be null
+    unsigned aBytes, bBytes;
+    int M, K, N;
+    int rowTiles, panels, cols, groups;   // panels of `cols` columns; 8 * groups workgroups a panel
+    int epilogue;
+    float slope;
+    FastDiv divPanels;
+};
+// 16-channel steps of the compiled kernel that holds K channels (0: none), and columns of a panel that its LDS holds
+constexpr int pointwise_steps(int K) { return K <= 32 ? 2 : K <= 64 ? 4 : K <= 96 ? 6 : K <= 128 ? 8 : 0; }
+constexpr int pointwise_columns(int steps) { return steps == 2 ? 512 : steps == 4 ? 256 : 128; }
+inline bool pointwise_accepts(const Shape &s, bool bwd)
+{
+    return s.FH == 1 && s.FW == 1 && s.sh == 1 && s.sw == 1 && s.ph == 0 && s.pw == 0 && s.IC % 4 == 0 && s.OC % 4 == 0 &&
+           pointwise_steps(bwd ? s.OC : s.IC) != 0;
+}
+
 // ---- backward-weight ---------------------------------------------------------------------
 // dW[oc, col] = sum over rows m=(n,oh,ow): G[m, oc] * X[n, oh*sh-ph+fh(col), ow*sw-pw+fw(col), ic(col)]
 // with col = (fh*FW + fw)*IC + ic.  The row range is cut into `split` slices.
@@ -605,6 +627,7 @@ hipError_t prepare_wgrad_fast();
 hipError_t prepare_gather_terms();
 hipError_t prepare_wgrad_terms();
 hipError_t prepare_halo_terms();
+hipError_t prepare_pointwise_terms();
 
 hipError_t launch_direct_fwd(const float *X, const float *W, float *Y, const Shape &s, hipStream_t st);
 hipError_t launch_direct_bwd_data(const float *G, const float *W, float *dX, const Shape &s, hipStream_t st);
@@ -648,6 +671,8 @@ hipError_t launch_gather_gemm(const GatherGemmParams &p, bool bwdData, int bm, i
 hipError_t launch_gather_terms(const GatherGemmParams &p, bool bwdData, int bm, int bn, int grid, hipStream_t st);
 // unit stride, equal maps (halo_span); tiles 128x128 and 256x64
 hipError_t launch_halo_terms(const HaloParams &p, bool bwdData, int bm, int bn, int grid, hipStream_t st);
+// 1x1 filters (pointwise_accepts)
+hipError_t launch_pointwise_terms(const PointwiseParams &p, bool bwdData, int grid, hipStream_t st);
 // same tiles (except 128x128), element-wise loader: any channel counts
 hipError_t launch_gather_elem(const GatherGemmParams &p, bool bwdData, int bm, int bn, int grid, hipStream_t st);
 hipError_t launch_wgrad(const WgradParams &p, int bm, int bn, bool xElem, int grid, hipStream_t st);

@@ -14,6 +14,7 @@ hipError_t prepare_wgrad_fast() { return hipErrorNotSupported; }
 hipError_t prepare_gather_terms() { return hipErrorNotSupported; }
 hipError_t prepare_wgrad_terms() { return hipErrorNotSupported; }
 hipError_t prepare_halo_terms() { return hipErrorNotSupported; }
+hipError_t prepare_pointwise_terms() { return hipErrorNotSupported; }
 hipError_t launch_direct_fwd(const float *, const float *, float *, const Shape &, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_direct_bwd_data(const float *, const float *, float *, const Shape &, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_direct_bwd_weight(const float *, const float *, float *, const Shape &, hipStream_t) { return hipErrorNotSupported; }
@@ -32,6 +33,7 @@ hipError_t launch_wgrad(const WgradParams &, int, int, bool, int, hipStream_t) {
 hipError_t launch_wgrad_fast(const WgradParams &, int, int, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gather_terms(const GatherGemmParams &, bool, int, int, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_halo_terms(const HaloParams &, bool, int, int, int, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_pointwise_terms(const PointwiseParams &, bool, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_wgrad_terms(const WgradParams &, int, int, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_bwd_data_small_ic(const SmallIcParams &, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_wgrad_small_ic(const SmallIcParams &, hipStream_t) { return hipErrorNotSupported; }

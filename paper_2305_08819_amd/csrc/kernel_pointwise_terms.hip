@@ -1,0 +1,286 @@
+// 1x1 layers of unit stride without padding and few channels in the reduction (backward-data of a channel reduction, forward of an
+// expansion): C[M pixels, N] = A[M, K] x filter, K <= 128, on v_mfma_f32_32x32x16_bf16 with three-term operands (split_bf16.h).
+//
+// Bound by the stores of the result.  The tiled kernels run such a call as thousands of workgroups of one or two stages, each with its own
+// loads, split, barriers and accumulator exchange.  Here a workgroup splits a panel of the filter (K x cols, all terms) into LDS once and then
+// walks row tiles of 128 pixels without a barrier: four wave pairs of 32 pixels each, the two waves of a pair take every other block of 32 columns.
+// A wave keeps its pixels' terms for the whole reduction in registers, loaded straight from memory in the fragment layout (a lane: one pixel,
+// eight channels), so an element of A is split twice a panel, and an element of the filter once a workgroup.  The next row tile is on its way
+// while one is multiplied; it is waited for before the first store of this one, because a wait for loads behind stores is one for the stores too.
+// A block is stored beside the products of the one after it.
+// Measured, us, tiled kernel and this one: 32768 pixels, 64 -> 256 channels 18.5 and 16.0 (12.7 without the stores, 13.5 without the products:
+// about 7 are launch, first loads and the filter's split), 100352 x 64 -> 256 48 and 35, 100352 x 128 -> 512 137 and 102; the three operators of a
+// 256 -> 64 layer on 128 x 16x16 pixels 50.2 and 45.9.  Nontemporal stores: 14.2 for the first alone, but 47.4 for the three operators.
+// The filter is the first operand of the MFMA: a lane of the result holds one pixel, four neighbouring channels at a time, and a block is turned in
+// LDS (the wave's own scratch) so that eight lanes store 128 bytes of a pixel.
+#include <hip/hip_runtime.h>
+#include "split_bf16.h"
+
+namespace mi355conv {
+
+namespace {
+typedef int i4s __attribute__((ext_vector_type(4)));
+
+template <int KS>
+struct SP {
+    static constexpr int KP = KS * 16, NP = pointwise_columns(KS);   // reduction and columns of a panel, padded
+    static constexpr int WAVES = 8, ROWS = 128;
+    static constexpr int HALF = NP * 16 + 16;        // bytes: eight channels of every column; the 16 put the halves of a step on other banks
+    static constexpr int PLANE = 2 * HALF, STEP = 3 * PLANE;
+    static constexpr int SCRATCH = KS * STEP, LOST = SCRATCH + WAVES * 32 * kLDT * 4;
+    static constexpr size_t SMEM = LOST + WAVES * sizeof(int);
+    static_assert(NP % 64 == 0 && SMEM <= 160 * 1024, "LDS of a CU");
+};
+}  // namespace
+
+// BWD: the filter is [K][N] (backward-data), otherwise [N][K].
+template <int KS, bool BWD>
+__global__ __launch_bounds__(512, 2) void pointwise_terms_kernel(const PointwiseParams p)
+{
+    using T = SP<KS>;
+    extern __shared__ f4 smem_raw[];
+    char *smem = reinterpret_cast<char *>(smem_raw);
+    int *lost = reinterpret_cast<int *>(smem + T::LOST);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, lh = lane >> 5;
+
+    // the panels of a row tile on one XCD (id % 8): the later ones find its pixels in L2
+    const int xcd = blockIdx.x & 7, place = blockIdx.x >> 3;
+    const int group = (int)fast_div((unsigned)place, p.divPanels), panel = place - group * p.panels;
+    int tile = group * 8 + xcd;
+    if (tile >= p.rowTiles) return;
+    const int n0 = panel * p.cols;
+    const int cols = min(p.cols, (p.N - n0 + 63) & ~63);   // columns of this panel, a multiple of 64
+
+    const __amdgpu_buffer_rsrc_t rsrcA = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.A), 0, (int)p.aBytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrcB = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.B), 0, (int)p.bBytes, 0x00020000);
+    constexpr int kOutOfRange = (int)0x80000000;   // tensors are below 2^31 bytes
+    const int wr = wave >> 1, wc = wave & 1;
+
+    f4 raw[KS][2];   // the pixels of the next row tile
+    auto load_rows = [&](int t) __attribute__((always_inline)) {
+        const int m = t * T::ROWS + wr * 32 + l32;
+        const int row = t < p.rowTiles && m < p.M ? (m * p.K + lh * 8) * 4 : kOutOfRange;   // kOutOfRange and some bytes more is out of range too
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int k = s * 16 + h * 4;
+                raw[s][h] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcA, k + lh * 8 < p.K ? row + k * 4 : kOutOfRange, 0, 0));
+            }
+    };
+    load_rows(tile);
+
+    // ---- the panel's terms: [step of 16 channels][term][half of the step][column][8 channels] --------------------
+    unsigned rest = 0u;   // what the terms left of the elements split so far (see split_bf16.h)
+    auto put = [&](int step, int kq, int col, const f4 &v) __attribute__((always_inline)) {
+        const SplitQuad q = split_quad(v, rest);
+        char *d = smem + step * T::STEP + (kq >> 1) * T::HALF + col * 16 + (kq & 1) * 8;
+        *reinterpret_cast<u2 *>(d) = q.h;
+        *reinterpret_cast<u2 *>(d + T::PLANE) = q.m;
+        *reinterpret_cast<u2 *>(d + 2 * T::PLANE) = q.l;
+    };
+    if constexpr (BWD) {   // a lane: four channels x four columns, so that it stores four channels of a column; 16 column groups x 4
+        const int cg = lane & 15, kq = lane >> 4, jobs = KS * (cols >> 6);
+        constexpr int kBatch = 2;
+        for (int j0 = wave; j0 < jobs; j0 += T::WAVES * kBatch) {
+            f4 w[kBatch][4];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int j = j0 + u * T::WAVES, s = j % KS, col = n0 + (j / KS) * 64 + cg * 4;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int k = s * 16 + kq * 4 + i;
+                    w[u][i] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                         rsrcB, j < jobs && k < p.K && col < p.N ? (k * p.N + col) * 4 : kOutOfRange, 0, 0));
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int j = j0 + u * T::WAVES, s = j % KS, col = (j / KS) * 64 + cg * 4;
+                if (j < jobs) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) put(s, kq, col + c, f4{w[u][0][c], w[u][1][c], w[u][2][c], w[u][3][c]});
+                }
+            }
+        }
+    } else {   // a lane: four channels of a column; 16 columns x 4
+        const int kq = lane & 3, jobs = KS * (cols >> 4);
+        constexpr int kBatch = 8;
+        for (int j0 = wave; j0 < jobs; j0 += T::WAVES * kBatch) {
+            f4 w[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int j = j0 + u * T::WAVES, k = (j % KS) * 16 + kq * 4, col = n0 + (j / KS) * 16 + (lane >> 2);
+                w[u] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                  rsrcB, j < jobs && k < p.K && col < p.N ? (col * p.K + k) * 4 : kOutOfRange, 0, 0));
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int j = j0 + u * T::WAVES;
+                if (j < jobs) put(j % KS, kq, (j / KS) * 16 + (lane >> 2), w[u]);
+            }
+        }
+    }
+    const int filterLost = split_lost(rest);
+    if (lane == 0) lost[wave] = filterLost;
+    __syncthreads();   // the only one: from here every wave walks its row tiles by itself
+    int panelBad = 0;
+#pragma unroll
+    for (int w = 0; w < T::WAVES; ++w) panelBad |= lost[w];
+    panelBad = __builtin_amdgcn_readfirstlane(panelBad);
+
+    const char *frag = smem + lh * T::HALF + l32 * 16;
+    float *scratch = reinterpret_cast<float *>(smem + T::SCRATCH) + wave * 32 * kLDT;
+    const int sRow = lane >> 3, seg = lane & 7;   // this lane's pixel (8q + sRow of a block) and channels (4*seg .. +3) when it stores
+    const int stride = p.groups * 8;
+
+    for (; tile < p.rowTiles; tile += stride) {   // uniform
+        const int m0 = tile * T::ROWS + wr * 32;
+        bf8 fa[KS][3];
+        rest = 0u;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const SplitQuad a = split_quad(raw[s][0], rest), b = split_quad(raw[s][1], rest);
+            typedef unsigned u4 __attribute__((ext_vector_type(4)));
+            fa[s][0] = __builtin_bit_cast(bf8, u4{a.h[0], a.h[1], b.h[0], b.h[1]});
+            fa[s][1] = __builtin_bit_cast(bf8, u4{a.m[0], a.m[1], b.m[0], b.m[1]});
+            fa[s][2] = __builtin_bit_cast(bf8, u4{a.l[0], a.l[1], b.l[0], b.l[1]});
+        }
+        const bool rowsBad = split_lost(rest) || panelBad != 0;
+        load_rows(tile + stride);   // past the last tile: nothing is read
+
+        // 32 rows of the result: the range check drops rows past the last one (and everything where there is no row)
+        // (uniform; saying so keeps the descriptor in SGPRs instead of a loop over the lanes' values)
+        const unsigned long long rows = (unsigned long long)(p.C + (long long)m0 * p.N);
+        const unsigned rowsLo = (unsigned)__builtin_amdgcn_readfirstlane((int)rows), rowsHi = (unsigned)__builtin_amdgcn_readfirstlane((int)(rows >> 32));
+        const __amdgpu_buffer_rsrc_t rsrcC = __builtin_amdgcn_make_buffer_rsrc(
+            reinterpret_cast<float *>((unsigned long long)rowsHi << 32 | rowsLo), 0,
+            __builtin_amdgcn_readfirstlane(max(0, min(32, p.M - m0)) * p.N * 4), 0x00020000);
+
+        auto steps = [&](int cb, int s0, int s1, float16v &acc, float16v &low) __attribute__((always_inline)) {
+#pragma unroll
+            for (int s = s0; s < s1; ++s) {
+                bf8 fb[3];
+#pragma unroll
+                for (int t = 0; t < 3; ++t) fb[t] = *reinterpret_cast<const bf8 *>(frag + cb * 16 + s * T::STEP + t * T::PLANE);
+#pragma unroll
+                for (int g = 0; g < kSplitProducts; ++g) {
+                    float16v &sum = g == kSplitProducts - 1 ? acc : low;
+                    sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kProdB[g]], fa[s][kProdA[g]], sum, 0, 0, 0);
+                }
+            }
+        };
+        auto check = [&](int cb, float16v &acc) __attribute__((always_inline)) {
+            SplitCheck look;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) look.look(f4{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]});
+            if (rowsBad || __any(look.bad())) {
+                // operands that three bf16 terms do not hold: the block again with v_mfma_f32_32x32x2_f32 (kept small, not fast)
+                acc = float16v{};
+                const int m = m0 + l32, col = n0 + cb + l32;
+                for (int k0 = 0; k0 < p.K; k0 += 8) {
+                    const int k = k0 + lh * 4;
+                    const f4 a = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                            rsrcA, m < p.M && k < p.K ? (m * p.K + k) * 4 : kOutOfRange, 0, 0));
+                    f4 b;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        b[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                   rsrcB, col < p.N && k < p.K ? (BWD ? (k + e) * p.N + col : col * p.K + k + e) * 4 : kOutOfRange, 0, 0));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[e], a[e], acc, 0, 0, 0);
+                }
+            }
+        };
+        auto store = [&](int cb, const float16v &acc) __attribute__((always_inline)) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                *reinterpret_cast<f4 *>(scratch + l32 * kLDT + g * 8 + lh * 4) = f4{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+            const int col = n0 + cb + seg * 4;
+            f4 bias = f4{0.f, 0.f, 0.f, 0.f};
+            if (!BWD && p.bias) {   // 4-byte loads: the bias may be aligned to 4 bytes only
+#pragma unroll
+                for (int e = 0; e < 4; ++e) bias[e] = col < p.N ? p.bias[col + e] : 0.f;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                f4 v = *reinterpret_cast<const f4 *>(scratch + (q * 8 + sRow) * kLDT + seg * 4);
+                if (!BWD && p.epilogue) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float x = v[e] + bias[e];
+                        v[e] = x > 0.f ? x : x * p.slope;
+                    }
+                }
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i4s, v), rsrcC,
+                                                       col < p.N ? ((q * 8 + sRow) * p.N + col) * 4 : kOutOfRange, 0, 0);
+            }
+        };
+
+        // A block is stored beside the products of the one after it.
+        float16v done = {}, low = {};
+        int cb = wc * 32;
+        steps(cb, 0, KS, done, low);
+        done += low;
+        check(cb, done);
+#pragma unroll
+        for (int s = 0; s < KS; ++s)   // the next tile's pixels are here before the first store goes out
+#pragma unroll
+            for (int h = 0; h < 2; ++h) asm volatile("" : "+v"(raw[s][h]));
+        for (cb += 64; cb < cols; cb += 64) {
+            float16v acc = {};
+            low = float16v{};
+            steps(cb, 0, 1, acc, low);
+            store(cb - 64, done);
+            steps(cb, 1, KS, acc, low);
+            done = acc + low;
+            check(cb, done);
+        }
+        store(cb - 64, done);
+    }
+}
+
+template <int KS, bool BWD>
+static hipError_t launch_pointwise_one(const PointwiseParams &p, int grid, hipStream_t st)
+{
+    hipLaunchKernelGGL((pointwise_terms_kernel<KS, BWD>), dim3((unsigned)grid), dim3(512), SP<KS>::SMEM, st, p);
+    return hipGetLastError();
+}
+
+// The panels need more LDS than a kernel gets by default (64 KB): limit raised once per device, outside any stream capture.
+hipError_t prepare_pointwise_terms()
+{
+    hipError_t e = hipSuccess;
+#define MI355_POINTWISE_PREP(KS_, BWD_)                                                                                  \
+    if (e == hipSuccess)                                                                                               \
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(pointwise_terms_kernel<KS_, BWD_>),                      \
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)SP<KS_>::SMEM);
+    MI355_POINTWISE_PREP(2, false)
+    MI355_POINTWISE_PREP(2, true)
+    MI355_POINTWISE_PREP(4, false)
+    MI355_POINTWISE_PREP(4, true)
+    MI355_POINTWISE_PREP(6, false)
+    MI355_POINTWISE_PREP(6, true)
+    MI355_POINTWISE_PREP(8, false)
+    MI355_POINTWISE_PREP(8, true)
+#undef MI355_POINTWISE_PREP
+    return e;
+}
+
+hipError_t launch_pointwise_terms(const PointwiseParams &p, bool bwdData, int grid, hipStream_t st)
+{
+    const int ks = pointwise_steps(p.K);
+    if (ks == 0 || p.K % 4 != 0 || p.N % 4 != 0 || p.cols % 64 != 0 || p.cols > pointwise_columns(ks) || p.cols < 64 ||
+        (long long)p.cols * p.panels < p.N || (long long)p.cols * (p.panels - 1) >= p.N || p.groups < 1 || grid != p.groups * 8 * p.panels)
+        return hipErrorInvalidValue;
+#define MI355_POINTWISE_CASE(KS_) \
+    if (ks == KS_) return bwdData ? launch_pointwise_one<KS_, true>(p, grid, st) : launch_pointwise_one<KS_, false>(p, grid, st);
+    MI355_POINTWISE_CASE(2)
+    MI355_POINTWISE_CASE(4)
+    MI355_POINTWISE_CASE(6)
+    MI355_POINTWISE_CASE(8)
+#undef MI355_POINTWISE_CASE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace mi355conv

@@ -1,0 +1,87 @@
+"""The 1x1 kernel that keeps a filter panel in LDS (forward and backward-data, at most 128 reduction channels) at the edges of its
+steps, panels, blocks and row tiles, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2305_08819_amd as mc
+from tests import gpu_util as gu
+from tests.test_gpu_products import far_from_one, inputs, run
+
+pytestmark = pytest.mark.gpu
+CODE = {"fwd": mc.OP_FWD, "bwd_data": mc.OP_BWD_DATA}
+
+# pixels, reduction channels, result channels
+CASES = [
+    (21851, 8, 36),       # few of either: one step half empty, one of zeros, one block and one of four columns
+    (24576, 32, 64),      # one block a wave, whole tiles
+    (12289, 32, 68),      # one pixel in the last tile
+    (6151, 36, 132),      # the first sizes past a step and past a panel
+    (3104, 64, 256),      # whole panel; the last tile is one block of 32 pixels
+    (3073, 68, 260),
+    (2079, 96, 388),
+    (2051, 100, 1028),    # more panels than an even share of the CUs
+    (2048, 128, 512),     # the fewest pixels
+    (100003, 64, 64),     # several row tiles a workgroup, the last lap partly empty
+    (40001, 32, 512),
+    (33000, 128, 128),
+]
+
+
+def desc(case, op):
+    M, K, N = case
+    n, h, w = (M // 8, 2, 4) if M % 8 == 0 else (M, 1, 1)
+    d = mc.make_desc(n, h, w, *((K, N) if op == "fwd" else (N, K)), 1, 1, 1, 0)
+    p = mc.conv2d_query_plan(CODE[op], d)
+    assert p.order == mc.ORDER_CONTIGUOUS and mc.conv2d_query_products(CODE[op], d) == mc.PRODUCTS_TERMS and p.workspace_bytes == 0
+    print("pointwise", case, op, p.grid, flush=True)
+    return d
+
+
+@pytest.mark.parametrize("op", ["fwd", "bwd_data"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+def test_panels(case, op):
+    d = desc(case, op)
+    gu.check_all_ops(d, *inputs(d, 31), ops=(op,), label=str(case), twice=True)
+
+
+@pytest.mark.parametrize("op", ["fwd", "bwd_data"])
+@pytest.mark.parametrize("kind", ["1e-37", "1e-42", "hidden", "2^-133"])
+def test_small_operand_with_a_large_partner(op, kind):
+    """Operands that three bf16 terms do not hold (see test_gpu_products), in either operand, at the parity tests' bar."""
+    d = desc((6151, 36, 132), op)
+    a, b = far_from_one(op, *gu.operands(op, *inputs(d, 11)), kind)
+    ref = gu.run_oracle(op, d, a, b)
+    got = run(op, d, a, b).astype(np.float64)
+    assert np.linalg.norm((got - ref).ravel()) <= 1e-5 * np.linalg.norm(ref.ravel())
+
+
+@pytest.mark.parametrize("op", ["fwd", "bwd_data"])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_non_finite_operands_reach_their_row_or_column(op, value):
+    d = desc((3073, 68, 260), op)
+    for which in (0, 1):
+        ab = list(gu.operands(op, *inputs(d, 3)))
+        ab[which].reshape(-1)[ab[which].size // 3] = value
+        ref, got = gu.run_oracle(op, d, *ab), run(op, d, *ab)
+        assert 0 < np.isfinite(ref).sum() < ref.size
+        for f in (np.isnan, np.isposinf, np.isneginf):
+            assert np.array_equal(f(got), f(ref)), which
+        ok = np.isfinite(ref)
+        assert np.linalg.norm(got[ok].astype(np.float64) - ref[ok]) <= 1e-5 * np.linalg.norm(ref[ok])
+
+
+def test_fused_bias_and_activation():
+    for case in ((2079, 96, 388), (40001, 32, 512)):
+        d = desc(case, "fwd")
+        X, W, _ = inputs(d, 5)
+        bias = np.linspace(-1, 1, d.OC + 1).astype(np.float32)
+        ref = gu.run_oracle("fwd", d, X, W) + bias[1:]
+        ref = np.where(ref > 0, ref, ref * np.float32(0.125))
+        buf, Y = gu.guarded((d.N, d.OH, d.OW, d.OC))
+        tb = torch.from_numpy(bias).cuda()[1:]        # aligned to 4 bytes only
+        mc.conv2d_fwd_bias_act(gu.nan_fenced(X), gu.nan_fenced(W), tb, Y, d, 0.125)
+        torch.cuda.synchronize()
+        assert gu.guards_intact(buf)
+        rel, mx = gu.errors(Y.cpu().numpy(), ref)
+        assert rel <= gu.REL_L2_TOL and mx <= gu.MAX_ABS_TOL, (case, rel, mx)
