@@ -114,7 +114,7 @@ __device__ __forceinline__ void gather_block_store(const P &p, float *C, bool ep
 
 // The fp32 form of a tile, for operands that three bf16 terms do not hold: v_mfma_f32_32x32x2_f32 on
 // fragments read straight from memory.  A wave redoes the blocks it finishes, on
-// its own.  Reached only through split_lost and split_suspect, so it is kept small, not fast (a launch that redoes every
+// its own.  Reached only through split_lost and SplitCheck, so it is kept small, not fast (a launch that redoes every
 // tile takes two to three times as long).
 template <class T, bool BWD, class P>
 __device__ __forceinline__ void gather_redo_fp32(const P &p, const GatherTile &tile, __amdgpu_buffer_rsrc_t rsrcA,
@@ -553,20 +553,21 @@ __global__ __launch_bounds__((SG<BM, BN, BWD, FINE>::THREADS), (FINE ? 4 : BM * 
     const int mineLost = split_lost(rest);
     if (lane == 0) lost[wave] = mineLost;
     __syncthreads();
-    bool bad = false;
+    int anyLost = 0;
 #pragma unroll
-    for (int w = 0; w < T::WAVES; ++w) bad = bad || lost[w] != 0;
+    for (int w = 0; w < T::WAVES; ++w) anyLost |= lost[w];   // eight reads at once; as a chain of || they follow one another
+    SplitCheck check;
     if (finishes) {
 #pragma unroll
         for (int o = 0; o < T::NOWN; ++o)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 own[o][r] += theirs[(o * 32 + 8 * (r / 4) + 4 * lh + r % 4) * kLDT + l32];
-                bad = bad || split_suspect(own[o][r]);
+                check.look(own[o][r]);
             }
     }
     if (!finishes) return;   // no barrier follows
-    if (__any(bad)) gather_redo_fp32<T, BWD>(p, tile, rsrcA, rsrcB, rowBase, rowY, rowX, wm, wn, kh, lane, it0, it1, own);
+    if (__any(anyLost != 0 || check.bad())) gather_redo_fp32<T, BWD>(p, tile, rsrcA, rsrcB, rowBase, rowY, rowX, wm, wn, kh, lane, it0, it1, own);
 
     float *C = p.C + (long long)slice * p.sliceStride;
     const bool epi = p.epilogue && p.split == 1;   // sliced launches leave it to the combine pass

@@ -418,9 +418,9 @@ __global__ __launch_bounds__((SH<BM, BN, BWD>::THREADS), 2) void halo_terms_kern
     const int mineLost = split_lost(rest);
     if (lane == 0) lost[wave] = mineLost;
     __syncthreads();
-    bool bad = false;
+    int anyLost = 0;
 #pragma unroll
-    for (int w = 0; w < T::WAVES; ++w) bad = bad || lost[w] != 0;
+    for (int w = 0; w < T::WAVES; ++w) anyLost |= lost[w];   // eight reads at once; as a chain of || they follow one another
     const int sRow = lane >> 3, seg = lane & 7;   // this lane's pixel (8q + sRow of a block) and channels (4*seg .. +3)
     f4 own[T::NOWN][4];
     SplitCheck check;
@@ -432,7 +432,7 @@ __global__ __launch_bounds__((SH<BM, BN, BWD>::THREADS), 2) void halo_terms_kern
             own[o][q] = *reinterpret_cast<const f4 *>(mine + at) + *reinterpret_cast<const f4 *>(theirs + at);
             check.look(own[o][q]);
         }
-    bad = bad || check.bad();
+    const bool bad = anyLost != 0 || check.bad();
     const int colBase = n0 + wn * 64 + kh * 32;   // the columns this wave finishes
     if (__any(bad)) {
         float16v redo[T::NOWN];

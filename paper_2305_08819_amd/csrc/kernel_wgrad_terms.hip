@@ -462,18 +462,19 @@ __global__ __launch_bounds__((SW<BM, BN>::THREADS), 2) void wgrad_terms_kernel(c
     const int mineLost = split_lost(rest);
     if (lane == 0) lost[wave] = mineLost;
     __syncthreads();
-    bool bad = false;
+    int anyLost = 0;
 #pragma unroll
-    for (int w = 0; w < T::WAVES; ++w) bad = bad || lost[w] != 0;
+    for (int w = 0; w < T::WAVES; ++w) anyLost |= lost[w];   // eight reads at once; as a chain of || they follow one another
+    SplitCheck check;
 #pragma unroll
     for (int o = 0; o < T::NOWN; ++o)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             own[o][r] += theirs[(o * 32 + 8 * (r / 4) + 4 * lh + r % 4) * kLDT + l32];
-            bad = bad || split_suspect(own[o][r]);
+            check.look(own[o][r]);
         }
     const int col = col0 + wn * T::WTN + kh * 32 + l32;   // this lane's column in every block it finishes
-    if (__any(bad)) {
+    if (__any(anyLost != 0 || check.bad())) {
         // operands that three bf16 terms do not hold: the tile again with v_mfma_f32_32x32x2_f32 on elements read
         // straight from memory (kept small, not fast: a launch that redoes every tile takes up to six times as long), folded as above
         const __amdgpu_buffer_rsrc_t rsrcG =

@@ -79,25 +79,22 @@ constexpr int kProdB[kSplitProducts] = {1, 0, 2, 0, 1, 0};
 // Looking at their magnitudes instead - the minimum of (bits << 1) - 1, 1.5 instructions per value - cost 2 to 6 %, and
 // v_cmp_class_f32 on the remainders more (its results go through scalar registers).
 __device__ __forceinline__ bool split_lost(unsigned rest) { return __builtin_amdgcn_ballot_w64((rest & 0xffffu) != 0u) != 0ull; }
-__device__ __forceinline__ bool split_suspect(float v)
-{
-    const unsigned u = __builtin_bit_cast(unsigned, v) & 0x7fffffffu;
-    return u >= 0x7f800000u || u - 1u < 0x17800000u - 1u;   // u = 0 wraps to the largest value
-}
 
-// The same over many sums, 2.5 instructions per value: (bits << 1) - 2 is below that of 2^-80 for the nonzero values under it and wraps for
+// The look at the sums, 2.5 instructions per value (a comparison of each by itself took four): (bits << 1) - 2 is below that of 2^-80 for the nonzero values under it and wraps for
 // zeros; 0 * v is NaN for infinities and NaN.
 struct SplitCheck {
     unsigned least = 0xffffffffu;
     float sum = 0.f;
+    __device__ __forceinline__ void look(float v)
+    {
+        const unsigned w = (__builtin_bit_cast(unsigned, v) << 1) - 2u;
+        least = w < least ? w : least;
+        sum = __builtin_fmaf(v, 0.f, sum);
+    }
     __device__ __forceinline__ void look(const f4 &v)
     {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const unsigned w = (__builtin_bit_cast(unsigned, v[e]) << 1) - 2u;
-            least = w < least ? w : least;
-            sum = __builtin_fmaf(v[e], 0.f, sum);
-        }
+        for (int e = 0; e < 4; ++e) look(v[e]);
     }
     __device__ __forceinline__ bool bad() const { return least < 2u * 0x17800000u - 2u || sum != 0.f; }   // NaN != 0
 };
