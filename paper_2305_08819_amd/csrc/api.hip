@@ -1641,6 +1641,7 @@ void fill_halo_geometry(HaloParams &h, const Shape &s, const Plan &pl, bool bwd)
     h.aBytes = (unsigned)((long long)h.M * h.SC * 4);
     h.bBytes = (unsigned)((long long)s.OC * h.taps * s.IC * 4);
     h.sliceStride = pl.sliceStride;
+    h.stream = pl.split > 1 || pl.outElems * 4 >= (32LL << 20);
     // neighbouring row tiles, which share their halo, and the column tiles and slices of one stay on one XCD
     h.xcdUnit = pl.grid >= 8 ? pl.grid / 8 : 1;
     h.xcdWhole = pl.grid / (8 * h.xcdUnit) * (8 * h.xcdUnit);

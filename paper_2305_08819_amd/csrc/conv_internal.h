@@ -228,7 +228,7 @@ struct HaloParams {
     int haloLo, span, items;   // a tile reads pixels m0 - haloLo .. + span-1, in `items` passes of 64
     // tap (0,0) reads pixel m + shift0; the next tap is shiftStep further, a new filter row shiftWrap more, a new chunk shiftChunk more
     int shift0, shiftStep, shiftWrap, shiftChunk;
-    int epilogue;
+    int epilogue, stream;   // stream: nontemporal stores (see store_result)
     float slope;
     long long sliceStride;
     FastDiv divTilesN, divSplit, divXcdUnit, divHW, divW;

@@ -17,7 +17,7 @@
 // Bound by the chip's power: a 256 x 64 stage takes 1870 cycles of the 1536 that its MFMAs need, at 1.7 to 1.8 GHz while all CUs run it
 // (0.97 us; 0.74 with half of them, at 2.3 GHz).  Around the stages of a workgroup are 0.7 us of decode, 1.3 of first loads, 1.1 of the
 // last stage and 2.4 of exchange and stores, and 2 to 3 us of launch.  Both sides in turn, us, gather_terms_kernel and here: 128 x
-// 32x32x64 -> 64 with bias and activation 62.6 and 54.1, 8x8x256 backward-data (two slices) 55.3 and 49.5, 100 x 14x14 5x5 192 -> 48
+// 32x32x64 -> 64 with bias and activation 62.6 and 54.1 (51.0 with nontemporal stores), 8x8x256 backward-data (two slices) 55.3 and 49.5, 100 x 14x14 5x5 192 -> 48
 // forward and backward-data 160 and 108.  The whole VGG-shaped step stays at 1.56 ms: it runs against the power limit, and its clock falls as its
 // kernels get denser (2.14 to 2.03 GHz).
 //
@@ -471,7 +471,7 @@ __global__ __launch_bounds__((SH<BM, BN, BWD>::THREADS), 2) void halo_terms_kern
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int m = m1 + o * 32 + q * 8;
-            if (m < p.M) *reinterpret_cast<f4 *>(C + (long long)m * p.DC + col) = own[o][q];
+            if (m < p.M) store_result(own[o][q], C + (long long)m * p.DC + col, p.stream);
         }
 }
 
