@@ -227,6 +227,10 @@ __global__ __launch_bounds__(kPatchWaves * 64, U8 ? 3 : 2) void fwd_small_ic_ker
     const __amdgpu_buffer_rsrc_t rsrcY = __builtin_amdgcn_make_buffer_rsrc(p.dX, 0, (int)((unsigned)p.M * (unsigned)p.OC * 4u), 0x00020000);
     typedef unsigned i4s __attribute__((ext_vector_type(4)));
     float *scratch = turn[wave];
+    // Nontemporal stores from 96 MB on: a result of about half the last-level cache is not found there again.  512 x 32x32x3 -> 64 (134 MB) from bytes, us:
+    // 31.7 (38.2 on some cards) and 29.0; with a reader behind it 75.5 and 69, with a ReLU in place 69.6 and 71.  Of 34 and 67 MB alone 12.3 and 10.0,
+    // 16.9 and 19.4, with a reader 25 and 27, 39 and 41, so there they are plain.
+    const bool stream = (unsigned)p.M * (unsigned)p.OC * 4u >= 96u << 20;
 
     // this lane's columns: offset of column 16*lh + e from the pixel's first one (bytes)
     int kOff[16];
@@ -434,8 +438,9 @@ __global__ __launch_bounds__(kPatchWaves * 64, U8 ? 3 : 2) void fwd_small_ic_ker
             for (int q = 0; q < 4; ++q) {
                 const int m = tile * kPatchTile + q * 8 + sRow, col = oc0 + b * 32 + seg * 4, off = (m * p.OC + col) * 4;
                 if (QUAD) {
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i4s, out[b][q]), rsrcY,
-                                                           m < p.M && col < p.OC ? off : kOutOfRange, 0, 0);
+                    const int at = m < p.M && col < p.OC ? off : kOutOfRange;
+                    if (stream) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i4s, out[b][q]), rsrcY, at, 0, 2);   // nontemporal
+                    else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i4s, out[b][q]), rsrcY, at, 0, 0);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
