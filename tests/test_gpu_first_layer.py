@@ -133,3 +133,25 @@ def test_bias_and_activation():
         assert gu.guards_intact(buf)
         rel, mx = gu.errors(Y.cpu().numpy(), ref)
         assert rel <= gu.REL_L2_TOL and mx <= gu.MAX_ABS_TOL, (shp, rel, mx)
+
+
+@pytest.mark.parametrize("n", [383, 385])
+def test_results_around_96_mb(n):
+    """Below: plain stores; from there on nontemporal ones, the last tile partial (1023 pixels an image)."""
+    d = mc.make_desc(n, 33, 31, 3, 64, 3, 3, 1, 1)
+    check_kernel("fwd", d)
+    assert (d.N * d.OH * d.OW * d.OC * 4 >= 96 << 20) == (n == 385)
+    print("first layer large", n, flush=True)
+    X, W, _ = inputs(d, 7)
+    X8 = np.rint(np.abs(X) * 60).clip(0, 255).astype(np.uint8)
+    for src in (X, X8):
+        buf, Y = gu.guarded((d.N, d.OH, d.OW, d.OC))
+        if src is X:
+            mc.conv2d_fwd(gu.nan_fenced(X), gu.nan_fenced(W), Y, d)
+        else:
+            mc.conv2d_fwd_u8(torch.from_numpy(X8).cuda(), 0.25, gu.nan_fenced(W), Y, d)
+        torch.cuda.synchronize()
+        assert gu.guards_intact(buf)
+        ref = gu.run_oracle("fwd", d, X if src is X else X8.astype(np.float32) * np.float32(0.25), W)
+        got = Y.cpu().numpy().astype(np.float64)
+        assert np.linalg.norm((got - ref).ravel()) <= gu.REL_L2_TOL * np.linalg.norm(ref.ravel())

@@ -114,3 +114,12 @@ def test_fused_bias_and_activation():
         assert gu.guards_intact(buf)
         rel, mx = gu.errors(Y.cpu().numpy(), ref)
         assert rel <= gu.REL_L2_TOL and mx <= gu.MAX_ABS_TOL, (shp, split, rel, mx)
+
+
+@pytest.mark.parametrize("n", [128, 129])
+def test_results_around_32_mb(n):
+    """Below: plain stores; from there on nontemporal ones, the last tile partial."""
+    d = mc.make_desc(n, 33, 31, 64, 64, 3, 3, 1, 1)
+    assert (d.N * d.OH * d.OW * d.OC * 4 >= 32 << 20) == (n == 129) and plan("fwd", d).split == 1
+    print("halo large", n, flush=True)
+    gu.check_all_ops(d, *inputs(d, 9), ops=("fwd",), label=str(n), twice=True)
