@@ -81,7 +81,8 @@ typedef struct conv2d_plan_info {
     int variant;        /* MI355CONV_VARIANT_*                                              */
     int tile_m, tile_n; /* workgroup output tile (GEMM rows x cols); 0 for DIRECT.  Kernels whose workgroups
                            walk over tiles (FIRST_LAYER forward, 1x1 CONTIGUOUS): one step of the walk       */
-    int split;          /* number of reduction slices (1 = no split)                        */
+    int split;          /* number of reduction slices (1 = no split); DIRECT with three-term products: the slices that the
+                           workspace has room for, though the one launch writes none                */
     int pos_major;      /* 1: GEMM rows ordered (oh,ow,n) so tiles skip padded taps         */
     int grid;           /* workgroups of the main kernel (conv2d_fwd_u8 starts more for results of 96 MB and more) */
     size_t workspace_bytes;
@@ -104,7 +105,8 @@ enum {
  * WGRAD_FAST name the loader and map, whichever way the products are formed: conv2d_query_products tells that. */
 enum {
     MI355CONV_KERNEL_DIRECT = 0,       /* kernels for any shape: one thread per element (variant DIRECT), one
-                                          32 x 32 block per workgroup (variant MFMA, short calls)   */
+                                          32 x 32 block per workgroup (variant MFMA: short calls, fp32 products; small
+                                          results with longer sums, three-term products)            */
     MI355CONV_KERNEL_GATHER = 1,       /* gather-GEMM, 16-byte loads along the channel axis     */
     MI355CONV_KERNEL_GATHER_ELEM = 2,  /* gather-GEMM, element-wise loads (any channel count)   */
     MI355CONV_KERNEL_FIRST_LAYER = 3,  /* the kernels for at most 32 patch columns / 4 channels */

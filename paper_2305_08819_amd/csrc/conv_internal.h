@@ -698,6 +698,25 @@ struct ShortParams {
 hipError_t launch_short(int op, const float *A, const float *B, float *C, const Shape &s, bool epi, const float *bias,
                         float slope, hipStream_t st);
 
+// Small results with long sums (kernel_block_terms.hip): 32 x 32 blocks of the result, one workgroup each.
+struct BlockParams {
+    const float *A, *B, *bias;
+    float *C;
+    unsigned aBytes, bBytes;   // below 2^31
+    float slope;
+    int epilogue;
+    int SH, SW, SC, DH, DW, DC;   // source and destination map
+    int FH, FW, sh, sw, ph, pw;
+    int M, chunks;                // rows; 32-channel items of a tap
+    int posMajor, rowInner;       // rows in (y, x, n) order: rowInner = N; in (n, y, x): DH * DW
+    int evenY, evenX;             // backward-data with stride 2: even rows and columns of the map, which come first
+    int colsSlow, inner;          // order of the blocks: columns or rows outermost; blocks of the inner one
+    int xcdUnit, xcdWhole;
+    int waves;                    // 8 or 16
+    FastDiv divXcdUnit, divInner, divRow, divDW, divFW, divChunks;
+};
+hipError_t launch_block_terms(const BlockParams &p, bool bwdData, int grid, hipStream_t st);
+
 // out[i] = sum_{s<split} ws[s*stride + i], combined pairwise in a fixed order.
 // With bias / slope (cols = channel count of the output's last axis, cols > 0):
 // out[i] = act(sum + bias[i % cols]).

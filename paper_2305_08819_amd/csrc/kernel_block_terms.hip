@@ -1,0 +1,286 @@
+// Forward and backward-data of small results with long sums, in one launch: v_mfma_f32_32x32x16_bf16 with three-term
+// operands (split_bf16.h), every wave by itself.
+//
+//   C[row, col] = sum over taps t, channels c of A[source pixel of row under t, c] * W(t, c, col)
+//
+// Rows are the pixels of the tensor being produced, columns its channels.  A workgroup owns one 32 x 32 block of the result;
+// its 8 or 16 waves share the reduction, cut into items of 32 channels of one tap.  A wave loads an item's rows 128 bytes at a
+// time, turns them into fragments in its own 4 KB of LDS, splits them in registers and multiplies, with the next item's loads
+// under way; no barrier is met until the partial blocks are added, in wave order and in fp64, at the end.  Only taps that some
+// row of the block has inside the image are walked, so on maps of a few pixels, with rows in (y, x, n) order, a block of one
+// position skips its padding (2x2 under a padded 3x3 filter: five of nine taps); with a stride, backward-data takes even rows
+// and columns of the map before odd ones, so that a block's rows share their taps.
+//
+// Why: the tiled kernels have 64 x 64 tiles or more, so a result of 512 x 512 is 64 workgroups, and filling the chip takes four
+// slices of the reduction, whose partial results a second kernel adds: two launches, and some 7 us around the stages in the first.  Here
+// 512 x 512 is 256 workgroups without a slice: forward 17.7 -> 15.1 us, backward-data 18.3 -> 15.3 (128 x 2x2x512, taps
+// inside the image 4 of 9), the layer's three operators 49.0 -> 41.8.
+//
+// Bound by the vector instructions of the split: 64 rows and columns are split for every 32 x 32 block, 192 instructions for
+// twelve MFMAs, two cycles each (v_sub, v_and, v_add) or four (v_cvt_pk, v_lshl, v_or3) with two waves or more on a SIMD; about 0.17 us an item
+// with every CU busy.  Around the items are 2.2 us of launch and some 2.5 of row table, first loads and addition.
+// Measured and left: loads straight into fragments, 32 bytes of a row at a time, 20.4 us for the forward call above; two
+// items in flight 16.2 (eight waves); every wave finding the rows' taps for itself 15.8; v_dot2_f32_bf16 in place of unpack and
+// subtract 29.0.
+#include <hip/hip_runtime.h>
+#include "split_bf16.h"
+
+namespace mi355conv {
+
+namespace {
+
+struct BlockItem {   // uniform: a tap of the block and the first of 32 channels
+    unsigned taps;   // taps left, this one the lowest
+    int tap, c;
+    int left;        // items of the wave from here on; none: its loads return zeros
+};
+}  // namespace
+
+template <int WAVES, bool BWD, bool RAGGED>
+__global__ __launch_bounds__(WAVES * 64) void block_terms_kernel(const BlockParams p)
+{
+    __shared__ f4 part[WAVES * 32 * 8];   // [wave][row][column / 4], the last index exchanged by row
+    __shared__ int lost[WAVES];
+    __shared__ int rowSrc[32], rowPixel[32];   // source offset in bytes under tap 0, destination pixel (-1: none)
+    __shared__ unsigned rowTaps[33];           // taps inside the image; the last one of all rows together
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int kOutOfRange = (int)0x80000000;   // tensors are below 2^31 bytes
+
+    const int bid = xcd_remap_fast(blockIdx.x, p.xcdWhole, p.xcdUnit, p.divXcdUnit);
+    const int slow = (int)fast_div((unsigned)bid, p.divInner), fast = bid - slow * p.inner;
+    const int m0 = (p.colsSlow ? fast : slow) * 32, n0 = (p.colsSlow ? slow : fast) * 32;
+    const __amdgpu_buffer_rsrc_t rsrcA =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.A), 0, (int)p.aBytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrcB =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.B), 0, (int)p.bBytes, 0x00020000);
+
+    // ---- rows: source, pixel, taps inside the image; the first wave finds them for all ------------------
+    const int lgY = p.sh - 1, lgX = p.sw - 1;   // strides of backward-data are 1 or 2
+    if (wave == 0) {
+        const int row = m0 + l32;
+        const int hi = (int)fast_div((unsigned)row, p.divRow), lo = row - hi * p.rowInner;
+        const int pos = p.posMajor ? hi : lo, n = p.posMajor ? lo : hi;
+        int y = (int)fast_div((unsigned)pos, p.divDW), x = pos - y * p.DW;
+        if (BWD && p.sh == 2) y = y < p.evenY ? 2 * y : 2 * (y - p.evenY) + 1;
+        if (BWD && p.sw == 2) x = x < p.evenX ? 2 * x : 2 * (x - p.evenX) + 1;
+        unsigned xs = 0u, mask = 0u;
+        for (int v = 0; v < p.FW; ++v) {
+            const int t = BWD ? x + p.pw - v : x * p.sw - p.pw + v;
+            const bool ok = BWD ? t >= 0 && (t & lgX) == 0 && t >> lgX < p.SW : (unsigned)t < (unsigned)p.SW;
+            xs |= (ok ? 1u : 0u) << v;
+        }
+        for (int u = 0; u < p.FH; ++u) {
+            const int t = BWD ? y + p.ph - u : y * p.sh - p.ph + u;
+            const bool ok = BWD ? t >= 0 && (t & lgY) == 0 && t >> lgY < p.SH : (unsigned)t < (unsigned)p.SH;
+            mask |= (ok ? xs : 0u) << (u * p.FW);
+        }
+        if (row >= p.M) mask = 0u;
+        unsigned all = mask;   // both halves of the wave hold the same rows
+#pragma unroll
+        for (int d = 1; d < 32; d <<= 1) all |= __shfl_xor((int)all, d);
+        const int sy = BWD ? (y + p.ph) >> lgY : y * p.sh - p.ph, sx = BWD ? (x + p.pw) >> lgX : x * p.sw - p.pw;
+        if (lane < 32) {
+            rowSrc[lane] = ((n * p.SH + sy) * p.SW + sx) * p.SC * 4;
+            rowPixel[lane] = row < p.M ? (n * p.DH + y) * p.DW + x : -1;
+            rowTaps[lane] = mask;
+            if (lane == 0) rowTaps[32] = all;
+        }
+    }
+    __syncthreads();
+    const unsigned taps = (unsigned)__builtin_amdgcn_readfirstlane((int)rowTaps[32]);
+    const int col = n0 + l32, tapsAll = p.FH * p.FW;
+    const int bBase = col >= p.DC ? kOutOfRange : (lh * 4 * tapsAll * p.DC + col) * 4;   // backward-data
+
+    // ---- the items of this wave -----------------------------------------------------------------------------
+    const int total = __builtin_popcount(taps) * p.chunks;
+    const int first = wave * total / WAVES, count = (wave + 1) * total / WAVES - first;
+    auto begin = [&]() __attribute__((always_inline)) {
+        BlockItem it;
+        const int skip = (int)fast_div((unsigned)first, p.divChunks);
+        it.taps = taps;
+        for (int i = 0; i < skip; ++i) it.taps &= it.taps - 1u;
+        it.tap = __builtin_ctz(it.taps | 0x80000000u);
+        it.c = (first - skip * p.chunks) * 32;
+        it.left = count;
+        return it;
+    };
+    auto next = [&](BlockItem &it) __attribute__((always_inline)) {
+        --it.left;
+        it.c += 32;
+        if (it.c >= p.SC) {
+            it.c = 0;
+            it.taps &= it.taps - 1u;
+            it.tap = __builtin_ctz(it.taps | 0x80000000u);
+        }
+    };
+    // A load takes eight rows of 128 bytes, eight lanes each; the wave's own part of LDS turns them (16-byte pieces exchanged by
+    // row).  The filter of backward-data, whose columns are neighbours in memory, is loaded as it is used.
+    const int lRow = lane >> 3, lSeg = lane & 7;
+    int aRow[4], bRow[4];       // the rows and columns that this lane loads
+    unsigned aMask[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int src = j * 8 + lRow, c = n0 + src;
+        aRow[j] = rowSrc[src] + lSeg * 16;
+        aMask[j] = rowTaps[src];
+        bRow[j] = c >= p.DC ? kOutOfRange : c * tapsAll * p.SC * 4 + lSeg * 16;
+    }
+    auto load = [&](const BlockItem &it, f4 (&a)[4], f4 (&b)[4]) __attribute__((always_inline)) {
+        const int fh = (int)fast_div((unsigned)it.tap, p.divFW), fw = it.tap - fh * p.FW;
+        const int shift = (BWD ? -((fh >> lgY) * p.SW + (fw >> lgX)) : fh * p.SW + fw) * p.SC * 4;
+        const int past = it.left > 0 ? 0 : kOutOfRange;
+        const bool drop = RAGGED && it.c + lSeg * 4 >= p.SC;   // channels past the last one
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int aOff = (((aMask[j] >> it.tap) & 1u) && !drop ? aRow[j] + shift : kOutOfRange) | past;
+            a[j] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcA, aOff, it.c * 4, 0));
+            if (!BWD)
+                b[j] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcB, (drop ? kOutOfRange : bRow[j]) | past,
+                                                                                    (it.tap * p.SC + it.c) * 4, 0));
+        }
+        if (BWD) {   // channels past the last one lie past the tensor
+            const int row = tapsAll * p.DC * 4;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    b[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                            rsrcB, bBase | past, (it.c + j * 8 + e) * row + it.tap * p.DC * 4, 0));
+        }
+    };
+    f4 *const mine = part + wave * (32 * 8);
+    auto turn = [&](f4 (&a)[4]) __attribute__((always_inline)) {   // rows as loaded -> quads of this lane's row or column
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mine[(j * 8 + lRow) * 8 + (lSeg ^ lRow)] = a[j];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[j] = mine[l32 * 8 + ((j * 2 + lh) ^ (l32 & 7))];
+    };
+
+    float16v acc = {}, low = {};   // sums of the h*h products and of the five smaller ones
+    unsigned rest = 0u;
+    auto multiply = [&](const f4 (&a)[4], const f4 (&b)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            bf8 fa[3], fb[3];
+            const SplitQuad a0 = split_quad(a[2 * s], rest), a1 = split_quad(a[2 * s + 1], rest);
+            const SplitQuad b0 = split_quad(b[2 * s], rest), b1 = split_quad(b[2 * s + 1], rest);
+            auto join = [](u2 lo, u2 hi) {
+                typedef unsigned u4 __attribute__((ext_vector_type(4)));
+                return __builtin_bit_cast(bf8, u4{lo[0], lo[1], hi[0], hi[1]});
+            };
+            fa[0] = join(a0.h, a1.h), fa[1] = join(a0.m, a1.m), fa[2] = join(a0.l, a1.l);
+            fb[0] = join(b0.h, b1.h), fb[1] = join(b0.m, b1.m), fb[2] = join(b0.l, b1.l);
+#pragma unroll
+            for (int g = 0; g < kSplitProducts; ++g) {   // filter first: a lane of the result holds channels of one pixel
+                float16v &sum = g == kSplitProducts - 1 ? acc : low;
+                sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[kProdB[g]], fa[kProdA[g]], sum, 0, 0, 0);
+            }
+        }
+    };
+    {
+        BlockItem it = begin();
+        f4 a[4], b[4];
+        load(it, a, b);
+        for (int i = 0; i < count; ++i) {
+            next(it);
+            turn(a);
+            if (!BWD) turn(b);
+            f4 ta[4], tb[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) ta[j] = a[j], tb[j] = b[j];
+            load(it, a, b);   // issued in any case: the compiler counts them
+            multiply(ta, tb);
+        }
+    }
+
+    // ---- the partial blocks meet ------------------------------------------------------------------------
+    auto put = [&](const float16v &v) __attribute__((always_inline)) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            part[(wave * 32 + l32) * 8 + ((2 * g + lh) ^ (l32 & 7))] = f4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+    };
+    constexpr int E = 32 * 32 / (WAVES * 64);   // elements of a thread: neighbouring columns
+    const int r = tid / (32 / E), c = tid % (32 / E) * E;
+    float out[E];
+    SplitCheck check;
+    auto join = [&]() __attribute__((always_inline)) {
+        const float *f = reinterpret_cast<const float *>(part) + (r * 8 + ((c >> 2) ^ (r & 7))) * 4 + (c & 3);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            double sum = 0.;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) sum += (double)f[w * 32 * 32 + e];
+            out[e] = (float)sum;
+        }
+    };
+    put(acc + low);
+    const int mineLost = split_lost(rest);
+    if (lane == 0) lost[wave] = mineLost;
+    __syncthreads();
+    int anyLost = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) anyLost |= lost[w];
+    join();
+#pragma unroll
+    for (int e = 0; e < E; ++e) check.look(out[e]);
+    if (__syncthreads_or(anyLost != 0 || check.bad())) {
+        // The fp32 form of the block: every item summed by itself and added only to the rows that it is inside the image
+        // for, so that infinities and NaN reach no further than their taps do.
+        BlockItem it = begin();
+        const unsigned mask = rowTaps[l32];
+        float16v sum = {};
+        for (int i = 0; i < count; ++i) {
+            f4 a[4], b[4];
+            load(it, a, b);
+            turn(a);
+            if (!BWD) turn(b);
+            float16v one = {};
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) one = __builtin_amdgcn_mfma_f32_32x32x2f32(b[j][e], a[j][e], one, 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 16; ++q) sum[q] += (mask >> it.tap) & 1u ? one[q] : 0.f;
+            next(it);
+        }
+        put(sum);
+        __syncthreads();
+        join();
+    }
+
+    const int pixel = rowPixel[r];
+    if (pixel < 0 || n0 + c >= p.DC) return;   // DC is a multiple of 4
+    float *to = p.C + (long long)pixel * p.DC + n0 + c;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        if (p.epilogue) {
+            const float v = out[e] + (p.bias ? p.bias[n0 + c + e] : 0.f);
+            out[e] = v > 0.f ? v : v * p.slope;
+        }
+        to[e] = out[e];
+    }
+}
+
+template <int WAVES>
+static void launch_block_waves(const BlockParams &p, bool bwdData, int grid, hipStream_t st)
+{
+    const bool ragged = p.SC % 32 != 0;
+    const dim3 g((unsigned)grid), b(WAVES * 64);
+    if (bwdData && ragged) hipLaunchKernelGGL((block_terms_kernel<WAVES, true, true>), g, b, 0, st, p);
+    else if (bwdData) hipLaunchKernelGGL((block_terms_kernel<WAVES, true, false>), g, b, 0, st, p);
+    else if (ragged) hipLaunchKernelGGL((block_terms_kernel<WAVES, false, true>), g, b, 0, st, p);
+    else hipLaunchKernelGGL((block_terms_kernel<WAVES, false, false>), g, b, 0, st, p);
+}
+
+hipError_t launch_block_terms(const BlockParams &p, bool bwdData, int grid, hipStream_t st)
+{
+    if (p.SC % 4 != 0 || p.DC % 4 != 0 || p.FH * p.FW > 32 || grid != ((p.M + 31) / 32) * ((p.DC + 31) / 32) ||
+        (bwdData && (p.sh > 2 || p.sw > 2)))
+        return hipErrorInvalidValue;
+    if (p.waves == 16) launch_block_waves<16>(p, bwdData, grid, st);
+    else launch_block_waves<8>(p, bwdData, grid, st);
+    return hipGetLastError();
+}
+
+}  // namespace mi355conv
