@@ -89,6 +89,8 @@ def kernel_name(layer, op, plan, desc, mc):
         return "pointwise_terms_kernel<%d, %s>" % ((src + 31) // 32 * 2, b(bwd))
     if terms and plan.order == mc.ORDER_CONTIGUOUS:
         return "halo_terms_kernel<%d, %d, %s, %s>" % (t + (b(bwd), b(src % 32 != 0)))
+    if terms and bwd and t == (64, 64) and plan.grid == -(-layer.N * layer.OH * layer.OW // 64) * -(-dst // 64) * plan.split and layer.stride == 2:
+        return "stride_terms_kernel<%s>" % b(src % 32 != 0)
     if terms:
         fine = t == (64, 64) and plan.grid <= 512
         return "gather_terms_kernel<%d, %d, %s, %s, %s, %s>" % (t + (b(bwd), b(belem), b(belem or src % 32 != 0), b(fine)))

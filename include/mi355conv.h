@@ -80,7 +80,8 @@ enum {
 typedef struct conv2d_plan_info {
     int variant;        /* MI355CONV_VARIANT_*                                              */
     int tile_m, tile_n; /* workgroup output tile (GEMM rows x cols); 0 for DIRECT.  Kernels whose workgroups
-                           walk over tiles (FIRST_LAYER forward, 1x1 CONTIGUOUS): one step of the walk       */
+                           walk over tiles (FIRST_LAYER forward, 1x1 CONTIGUOUS): one step of the walk; the kernel
+                           that forms the four phases of stride-2 backward-data together: pixels of dY       */
     int split;          /* number of reduction slices (1 = no split); DIRECT with three-term products: the slices that the
                            workspace has room for, though the one launch writes none                */
     int pos_major;      /* 1: GEMM rows ordered (oh,ow,n) so tiles skip padded taps         */

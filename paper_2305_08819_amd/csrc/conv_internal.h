@@ -258,6 +258,28 @@ inline bool halo_span(const Shape &s, int bm, int *lo, int *span, int *items)
     return *items * 64 <= halo_rows(bm) && taps <= 32 && taps >= *items + 2;
 }
 
+// ---- backward-data of 3x3 layers with stride 2 and padding 1 (kernel_stride_terms.hip) ------------------
+// dY pixel (j, i) serves the dX pixels (2j, 2i) .. (2j + 1, 2i + 1); they read dY pixels (j .. j + 1, i .. i + 1).
+struct StrideParams {
+    const float *A;       // dY [M pixels of an H x W map, SC]
+    const float *B;       // filter
+    float *C;             // dX [DH x DW map, DC], or workspace base when split > 1
+    unsigned aBytes, bBytes;
+    int M, H, W, SC, DH, DW, DC;
+    int chunks, split;    // 32-channel chunks of SC, cut into split slices
+    int tilesN, xcdUnit, xcdWhole;
+    int span;             // a tile reads pixels m0 .. m0 + span - 1
+    int stream;           // nontemporal stores (see stream_partials)
+    long long sliceStride;
+    FastDiv divTilesN, divSplit, divXcdUnit, divHW, divW;
+};
+constexpr int kStrideRows = 128;   // dY pixels that the LDS tile holds: 64 and a row and one more
+inline bool stride_accepts(const Shape &s)
+{
+    return s.sh == 2 && s.sw == 2 && s.FH == 3 && s.FW == 3 && s.ph == 1 && s.pw == 1 && s.IC % 4 == 0 && s.OC % 4 == 0 &&
+           64 + s.OW + 1 <= kStrideRows && (long long)(s.OC + kBK) * 9 * s.IC * 4 < (1LL << 31);   // a last chunk's channels past the filter
+}
+
 // ---- 1x1 layers of unit stride without padding, few reduction channels (kernel_pointwise_terms.hip) -----
 // C[M, N] = A[M, K] x filter; the filter's columns in panels, a workgroup takes one and walks 128-row tiles.
 struct PointwiseParams {
@@ -671,6 +693,7 @@ hipError_t prepare_gather_terms();
 hipError_t prepare_wgrad_terms();
 hipError_t prepare_halo_terms();
 hipError_t prepare_pointwise_terms();
+hipError_t prepare_stride_terms();
 
 hipError_t launch_direct_fwd(const float *X, const float *W, float *Y, const Shape &s, hipStream_t st);
 hipError_t launch_direct_bwd_data(const float *G, const float *W, float *dX, const Shape &s, hipStream_t st);
@@ -733,6 +756,8 @@ hipError_t launch_gather_gemm(const GatherGemmParams &p, bool bwdData, int bm, i
 hipError_t launch_gather_terms(const GatherGemmParams &p, bool bwdData, int bm, int bn, int grid, hipStream_t st);
 // unit stride, equal maps (halo_span); tiles 128x128 and 256x64
 hipError_t launch_halo_terms(const HaloParams &p, bool bwdData, int bm, int bn, int grid, hipStream_t st);
+// 3x3 filters with stride 2 and padding 1 (stride_accepts)
+hipError_t launch_stride_terms(const StrideParams &p, int grid, hipStream_t st);
 // 1x1 filters (pointwise_accepts)
 hipError_t launch_pointwise_terms(const PointwiseParams &p, bool bwdData, int grid, hipStream_t st);
 // same tiles (except 128x128), element-wise loader: any channel counts

@@ -1,0 +1,406 @@
+// Backward-data of 3x3 layers with stride 2 and padding 1 (the down-sampling layers of residual networks), on
+// v_mfma_f32_32x32x16_bf16 with three-term operands (split_bf16.h): the four stride phases of a region in one workgroup.
+//
+// dX pixel (2j + a, 2i + b) reads dY pixels (j + sy, i + sx): filter row 1 serves a = 0 with sy = 0, rows 0 and 2 serve a = 1 with sy =
+// 1 and 0, columns likewise.  So each dY pixel (j, i) has four dX pixels, one of every phase, with 1, 2, 2 and 4 taps, and the nine
+// taps read four different dY pixels.  A workgroup takes 64 consecutive dY pixels x 64 channels of dX, all four phases: the
+// dY run of a 32-channel chunk (its own pixels and OW + 1 more) is loaded, split and stored to LDS once for all nine taps; a
+// tap shifts the row of the fragment reads (a row whose pixel lies outside reads zeros), and taps with one shift share fragments.
+//
+// Why: with a tile per phase the launch lasts as long as its four-tap tiles, which hold 4 of 9 taps of a quarter of
+// dX, whatever the order of the workgroups, and dY is loaded and split once per tap.  Here all workgroups are equal.
+//
+// Eight waves: a pair (halves of the 32 channels) for 32 pixels x 32 channels of each phase.  A stage is three taps: 18 MFMAs a
+// wave, one barrier.  us, a tile per phase and here: 128 x 16x16x128 <- 256 45.6 and 34.0 (the layer's three operators 111.5 and 99.9).
+// A chunk takes 3.3 us with every CU busy and 2.3 with few: some 6000 cycles, of which the MFMAs need 3456, LDS
+// 2800 and the vector instructions 1900; 8 us of launch, first loads, exchange and stores around them.  What was tried in the
+// loop: products of one tap behind one another (a chain of five on one accumulator) the same; a filter item split between
+// two MFMAs instead of four, 3.7 us a chunk; loads three stages ahead spill.
+#include <hip/hip_runtime.h>
+#include "split_bf16.h"
+
+#include <type_traits>
+
+namespace mi355conv {
+
+namespace {
+struct SP {
+    static constexpr int BM = 64, BN = 64, WAVES = 8, THREADS = WAVES * 64;
+    static constexpr int ROWS = kStrideRows, PA = ROWS / 64;       // dY pixels in LDS, eight threads each
+    static constexpr int TAPS = 3;                                 // of a stage; three stages a chunk
+    // columns of 16 bytes as in kernel_halo_terms.hip; row ROWS is the row of zeros
+    static constexpr int A_COL = ((ROWS + 1) * 16 + 191) / 256 * 256 + 64;
+    static constexpr int A_PLANE = 4 * A_COL, A_BUF = 3 * A_PLANE;
+    static constexpr int B_PLANE = BN * kBK * 2, B_TAP = 3 * B_PLANE, B_BUF = TAPS * B_TAP;   // [tap][plane][k][64 columns]
+    static constexpr int B_BASE = 2 * A_BUF;
+    static constexpr int EXCHANGE = WAVES * 4 * 32 * kLDT * 4;
+    static constexpr int LOST = B_BASE + 2 * B_BUF > EXCHANGE ? B_BASE + 2 * B_BUF : EXCHANGE;
+    static constexpr size_t SMEM = LOST + WAVES * sizeof(int);
+    static_assert(A_COL >= (ROWS + 1) * 16 && A_COL % 256 == 64, "columns of the gathered tile");
+    static_assert(SMEM <= 160 * 1024, "LDS of a CU");
+};
+// The taps, those with one shift behind one another and no two of one phase: the products of a tap and those of the next
+// alternate, and an MFMA that adds to the result of the one before it would wait for it.
+struct StrideTap {
+    int fh, fw, phase, shift;   // phase 2a + b, shift 2sy + sx
+};
+constexpr StrideTap kStrideTaps[9] = {{0, 0, 3, 3}, {1, 0, 1, 1}, {2, 0, 3, 1}, {1, 1, 0, 0}, {2, 2, 3, 0},
+                                      {1, 2, 1, 0}, {2, 1, 2, 0}, {0, 2, 3, 2}, {0, 1, 2, 2}};
+}  // namespace
+
+// The fp32 form of the two phases that a wave finishes (see kernel_halo_terms.hip).
+__device__ __forceinline__ void stride_redo_fp32(const StrideParams &p, __amdgpu_buffer_rsrc_t rsrcA, __amdgpu_buffer_rsrc_t rsrcB,
+                                                 int pixel, unsigned mask, int phaseX, int col, int lane, int c0, int c1,
+                                                 float16v (&own)[2])
+{
+    constexpr int kOutOfRange = (int)0x80000000;
+    const int lh = lane >> 5, wRowStride = 9 * p.DC;
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) own[o][r] = 0.f;
+        // filter rows and columns of the phase: 1, or 0 and 2
+#pragma unroll 1
+        for (int fh = 1 - o; fh < 3; fh += 2)
+#pragma unroll 1
+            for (int fw = 1 - phaseX; fw < 3; fw += 2) {
+                const int sy = fh == 0, sx = fw == 0;
+                const bool inside = (mask >> (2 * sy + sx)) & 1u;
+                const int aBase = ((pixel + sy * p.W + sx) * p.SC + lh * 4) * 4, bBase = ((fh * 3 + fw) * p.DC + col) * 4;
+                float16v sum = {};
+#pragma unroll 1
+                for (int k0 = c0 * kBK; k0 < c1 * kBK; k0 += 8) {
+                    const int k = k0 + lh * 4;
+                    const f4 a = __builtin_bit_cast(
+                        f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcA, inside && k < p.SC ? aBase + k0 * 4 : kOutOfRange, 0, 0));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float b = __builtin_bit_cast(
+                            float, __builtin_amdgcn_raw_buffer_load_b32(
+                                       rsrcB, k < p.SC && col < p.DC ? (k + e) * wRowStride * 4 + bBase : kOutOfRange, 0, 0));
+                        sum = __builtin_amdgcn_mfma_f32_32x32x2f32(b, a[e], sum, 0, 0, 0);
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) own[o][r] += inside ? sum[r] : 0.f;
+            }
+    }
+}
+
+// RAGGED: the channel count of dY is a multiple of 4 but not of 32.
+template <bool RAGGED>
+__global__ __launch_bounds__(SP::THREADS, 2) void stride_terms_kernel(const StrideParams p)
+{
+    using T = SP;
+    extern __shared__ f4 smem_raw[];
+    char *smem = reinterpret_cast<char *>(smem_raw);
+    int *lost = reinterpret_cast<int *>(smem + T::LOST);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+
+    const int bid = xcd_remap_fast(blockIdx.x, p.xcdWhole, p.xcdUnit, p.divXcdUnit);
+    const int rest0 = (int)fast_div((unsigned)bid, p.divTilesN);
+    const int n0 = (bid - rest0 * p.tilesN) * T::BN;
+    const int tm = (int)fast_div((unsigned)rest0, p.divSplit);
+    const int slice = rest0 - tm * p.split;
+    const int m0 = tm * T::BM;
+    const int c0 = (int)fast_div((unsigned)(slice * p.chunks), p.divSplit);
+    const int c1 = (int)fast_div((unsigned)((slice + 1) * p.chunks), p.divSplit);
+
+    const __amdgpu_buffer_rsrc_t rsrcA =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.A), 0, (int)p.aBytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrcB =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.B), 0, (int)p.bBytes, 0x00020000);
+    constexpr int kOutOfRange = (int)0x80000000;   // tensors are below 2^31 bytes
+
+    // ---- loader state: 8 threads a pixel of 32 channels, 16 threads a filter row of 64 columns -----------------
+    const int aSeg = tid & 7, aRow = tid >> 3, bSeg = tid & 15, bRow = tid >> 4;
+    int aOff[T::PA];
+#pragma unroll
+    for (int q = 0; q < T::PA; ++q) {
+        const int row = aRow + 64 * q;
+        aOff[q] = row < p.span && m0 + row < p.M ? ((m0 + row) * p.SC + aSeg * 4) * 4 : kOutOfRange;
+    }
+    const bool aLastOk = aSeg * 4 < p.SC - (p.chunks - 1) * kBK;
+    const int wRowStride = 9 * p.DC;   // floats per channel of dY; rows past the last one lie past the filter
+    const int bOff = n0 + bSeg * 4 < p.DC ? (bRow * wRowStride + n0 + bSeg * 4) * 4 : kOutOfRange;
+
+    f4 rawA[T::PA], rawB[T::TAPS];   // loads in flight
+    auto load_a = [&](int chunk) __attribute__((always_inline)) {
+        const bool drop = RAGGED && chunk == p.chunks - 1 && !aLastOk;
+#pragma unroll
+        for (int q = 0; q < T::PA; ++q)
+            rawA[q] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcA, drop ? kOutOfRange : aOff[q], chunk * (kBK * 4), 0));
+    };
+    auto load_b = [&](auto stageTag, int chunk, int i) __attribute__((always_inline)) {
+        constexpr int T0 = decltype(stageTag)::value * T::TAPS;
+        const int tap = kStrideTaps[T0 + i].fh * 3 + kStrideTaps[T0 + i].fw;
+        rawB[i] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcB, bOff, (chunk * kBK * wRowStride + tap * p.DC) * 4, 0));
+    };
+
+    // ---- LDS tiles ----------------------------------------------------------------------------------
+    constexpr auto kSwz = [](int r) { return (r >> 1) & 1; };
+    int aStore = (aSeg >> 1) * T::A_COL + aRow * 16 + (aSeg & 1) * 8;
+    int bStore = T::B_BASE + bRow * (T::BN * 2) + (((bSeg >> 3) ^ kSwz(bRow)) << 6) + (bSeg & 7) * 8;
+    unsigned rest = 0u;   // what the terms left of the elements split so far (see split_bf16.h)
+    auto store = [&](char *d, int plane, const SplitQuad &s) __attribute__((always_inline)) {
+        *reinterpret_cast<u2 *>(d) = s.h;
+        *reinterpret_cast<u2 *>(d + plane) = s.m;
+        *reinterpret_cast<u2 *>(d + 2 * plane) = s.l;
+    };
+    SplitQuad sa, sb;
+    auto store_a = [&](int q) __attribute__((always_inline)) {
+        store(smem + aStore + q * 64 * 16, T::A_PLANE, split_quad(rawA[q], rest));
+    };
+    auto store_b = [&](int i, const f4 &x) __attribute__((always_inline)) {
+        store(smem + bStore + i * T::B_TAP, T::B_PLANE, split_quad(x, rest));
+    };
+    if (tid < 24)   // the rows of zeros of both buffers
+        *reinterpret_cast<f4 *>(smem + (tid >> 2) * T::A_PLANE + (tid & 3) * T::A_COL + T::ROWS * 16) = f4{0.f, 0.f, 0.f, 0.f};
+
+    // ---- this lane's pixel and what it reads under the four shifts ------------------------------------
+    const int kh = wave & 1, wm = wave >> 2, wn = (wave >> 1) & 1, l32 = lane & 31, lh = lane >> 5;
+    auto place = [&](int m, int *y, int *x) __attribute__((always_inline)) {   // returns the image
+        const int n = (int)fast_div((unsigned)m, p.divHW), q = m - n * (p.H * p.W);
+        *y = (int)fast_div((unsigned)q, p.divW);
+        *x = q - *y * p.W;
+        return n;
+    };
+    const int pixel = m0 + wm * 32 + l32;
+    unsigned mask = 0u;   // bit 2sy + sx: inside the image
+    int aFrag[4];
+    {
+        int y, x;
+        place(pixel, &y, &x);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const bool ok = pixel < p.M && y + (s >> 1) < p.H && x + (s & 1) < p.W;
+            mask |= (ok ? 1u : 0u) << s;
+            aFrag[s] = (kh * 2 + lh) * T::A_COL + (ok ? wm * 32 + l32 + (s >> 1) * p.W + (s & 1) : T::ROWS) * 16;
+        }
+    }
+    int bFrag;
+    {
+        const int k = kh * 16 + lh * 8 + ((lane & 15) >> 2);
+        bFrag = T::B_BASE + k * (T::BN * 2) + ((wn ^ kSwz(k)) << 6) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+    }
+
+    float16v acc[4], low[4];   // per phase: sums of the h*h products and of the five smaller ones
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[b][r] = low[b][r] = 0.f;
+
+    // A tap's six products: three beside the last three of the tap before it, three beside the first three of the next.
+    constexpr int kA[kSplitProducts] = {1, 0, 1, 2, 0, 0}, kB[kSplitProducts] = {1, 1, 0, 0, 2, 0};
+    struct Frags {
+        bf8 a[3], b[3];
+    } prev = {}, cur, next;   // the registers of planes that a tap has no more use for are the next one's
+    auto get_a = [&](int shift, int plane) __attribute__((always_inline)) {
+        return *reinterpret_cast<const bf8 *>(smem + aFrag[shift] + plane * T::A_PLANE);
+    };
+    auto get_b = [&](int tap, int plane) __attribute__((always_inline)) {
+        const char *s = smem + bFrag + tap * T::B_TAP + plane * T::B_PLANE;
+        return join_quads(lds_read_tr(s), lds_read_tr(s + 4 * T::BN * 2));
+    };
+    int aStep = T::A_BUF, bStep = T::B_BUF, bRead = T::B_BUF;   // distances to the other buffers
+    auto product = [&](const Frags &f, int phase, int g) __attribute__((always_inline)) {
+        float16v &sum = g == kSplitProducts - 1 ? acc[phase] : low[phase];
+        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[kB[g]], f.a[kA[g]], sum, 0, 0, 0);
+    };
+
+    // One stage: taps 3S .. 3S+2.  Beside the first two the wave splits and stores its share of the next stage's filter tile (loaded a
+    // stage ago; the loads of the one after follow); the barrier comes before the last, beside which the next stage's first
+    // fragments are read.  The first stage of a chunk loads the next chunk's pixels, the last one splits and stores them.
+    auto stage = [&](auto stageTag, int chunk, auto lastTag) __attribute__((always_inline)) {
+        constexpr int S = decltype(stageTag)::value;
+        constexpr bool LAST = decltype(lastTag)::value;   // the slice's last chunk: nothing of a next one
+#pragma unroll
+        for (int i = 0; i < T::TAPS; ++i) {
+            constexpr int T0 = S * T::TAPS;
+            const int shift = kStrideTaps[T0 + i].shift, phase = kStrideTaps[T0 + i].phase, phaseBefore = kStrideTaps[(T0 + i + 8) % 9].phase;
+            const int nextTap = (i + 1) % T::TAPS, nextShift = kStrideTaps[(T0 + i + 1) % 9].shift;
+            const bool turn = nextShift != shift;
+            const int after = S == 0 || LAST ? chunk : chunk + 1;   // of stage S + 2; past the slice the loads are repeated and not used
+            if (i == 2) {
+                __syncthreads();
+                bFrag += bRead;
+                bRead = -bRead;
+                if (S == 2 && !LAST) {
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) aFrag[s] -= aStep;   // turned round by the stores
+                }
+            }
+#pragma unroll
+            for (int h = 0; h < 3; ++h) {   // a product of the tap before, one of this tap, and what runs beside them
+                const int at = i * 3 + h;    // 0 .. 8
+                if (h == 0) {
+                    next.b[1] = get_b(nextTap, 1);
+                    next.b[0] = get_b(nextTap, 0);
+                }
+                if (h == 1 && turn) {
+                    next.a[1] = get_a(nextShift, 1);
+                    next.a[0] = get_a(nextShift, 0);
+                }
+                if (h == 2) {
+                    next.b[2] = get_b(nextTap, 2);
+                    if (turn) next.a[2] = get_a(nextShift, 2);
+                }
+                if (at < 6) {   // half an item of the filter
+                    split_pair(rawB[at / 2], at & 1, rest, sb);
+                    if (at & 1) {
+                        store(smem + bStore + at / 2 * T::B_TAP, T::B_PLANE, sb);
+                        load_b(std::integral_constant<int, (S + 2) % 3>(), after, at / 2);
+                    }
+                }
+                if (at == 5) {
+                    bStore += bStep;
+                    bStep = -bStep;
+                }
+                if (!LAST) {   // the next chunk's pixels: loaded by the first stage, stored from the second's end on
+                    if (S == 0 && at == 1) load_a(chunk + 1);
+                    if (S == 1 && at == 6) {
+                        aStore += aStep;
+                        aStep = -aStep;
+                    }
+                    const int half = S == 1 ? at - 6 : at + 3;
+                    if (S > 0 && half >= 0 && half < 4) {
+                        split_pair(rawA[half >> 1], half & 1, rest, sa);
+                        if (half & 1) store(smem + aStore + (half >> 1) * 64 * 16, T::A_PLANE, sa);
+                    }
+                }
+                asm volatile("" : "+v"(rest));
+                product(prev, phaseBefore, 3 + h);
+                product(cur, phase, h);
+#pragma unroll
+                for (int g = 0; g < 2; ++g) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA, then
+                    __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);   // LDS reads,
+                    __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);   // vector instructions,
+                    __builtin_amdgcn_sched_group_barrier(0x200, 2, 0);   // LDS stores,
+                    __builtin_amdgcn_sched_group_barrier(0x004, 4, 0);   // scalar instructions
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            prev = cur;
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) {
+                cur.b[pl] = next.b[pl];
+                if (turn) cur.a[pl] = next.a[pl];
+            }
+        }
+    };
+
+    // ---- main loop ------------------------------------------------------------------------------------
+#pragma unroll
+    for (int i = 0; i < T::TAPS; ++i) load_b(std::integral_constant<int, 0>(), c0, i);
+    load_a(c0);
+#pragma unroll
+    for (int i = 0; i < T::TAPS; ++i) {
+        store_b(i, rawB[i]);
+        load_b(std::integral_constant<int, 1>(), c0, i);
+    }
+    bStore += bStep;
+    bStep = -bStep;
+#pragma unroll
+    for (int q = 0; q < T::PA; ++q) store_a(q);
+    __syncthreads();
+#pragma unroll
+    for (int pl = 0; pl < 3; ++pl) {
+        cur.a[pl] = get_a(kStrideTaps[0].shift, pl);
+        cur.b[pl] = get_b(0, pl);
+    }
+    auto whole = [&](int c, auto last) __attribute__((always_inline)) {
+        stage(std::integral_constant<int, 0>(), c, last);
+        stage(std::integral_constant<int, 1>(), c, last);
+        stage(std::integral_constant<int, 2>(), c, last);
+    };
+    for (int c = c0; c + 1 < c1; ++c) whole(c, std::false_type());
+    whole(c1 - 1, std::true_type());
+#pragma unroll
+    for (int g = 3; g < kSplitProducts; ++g) product(prev, kStrideTaps[8].phase, g);
+    __syncthreads();   // every wave has used its last fragments: the buffers are free
+
+    // ---- the pair's halves meet: each wave finishes the two phases of its column parity -------------------
+    float *mine = reinterpret_cast<float *>(smem) + wave * 4 * 32 * kLDT;
+    const float *theirs = reinterpret_cast<const float *>(smem) + (wave ^ 1) * 4 * 32 * kLDT;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            f4 x;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = acc[b][g * 4 + e] + low[b][g * 4 + e];
+            *reinterpret_cast<f4 *>(mine + (b * 32 + l32) * kLDT + g * 8 + lh * 4) = x;
+        }
+    const int mineLost = split_lost(rest);
+    if (lane == 0) lost[wave] = mineLost;
+    __syncthreads();
+    int anyLost = 0;
+#pragma unroll
+    for (int w = 0; w < T::WAVES; ++w) anyLost |= lost[w];
+    const int sRow = lane >> 3, seg = lane & 7;   // this lane's pixel (8q + sRow of a block) and channels (4*seg .. +3)
+    f4 own[2][4];
+    SplitCheck check;
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int at = ((2 * o + kh) * 32 + q * 8 + sRow) * kLDT + seg * 4;
+            own[o][q] = *reinterpret_cast<const f4 *>(mine + at) + *reinterpret_cast<const f4 *>(theirs + at);
+            check.look(own[o][q]);
+        }
+    const bool bad = anyLost != 0 || check.bad();
+    const int colBase = n0 + wn * 32;
+    if (__any(bad)) {
+        float16v redo[2];
+        stride_redo_fp32(p, rsrcA, rsrcB, pixel, mask, kh, colBase + l32, lane, c0, c1, redo);
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {   // turned in the wave's own buffer of the block, which its partner does not read
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mine[((2 * o + kh) * 32 + l32) * kLDT + 8 * (r / 4) + 4 * lh + r % 4] = redo[o][r];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                own[o][q] = *reinterpret_cast<const f4 *>(mine + ((2 * o + kh) * 32 + q * 8 + sRow) * kLDT + seg * 4);
+        }
+    }
+
+    float *C = p.C + (long long)slice * p.sliceStride;
+    const int col = colBase + seg * 4;
+    if (col >= p.DC) return;   // no barrier follows
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int m = m0 + wm * 32 + q * 8 + sRow;
+        int y, x;
+        const int n = place(m, &y, &x);
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            const int dy = 2 * y + o, dx = 2 * x + kh;
+            if (m < p.M && dy < p.DH && dx < p.DW)
+                store_result(own[o][q], C + (((long long)n * p.DH + dy) * p.DW + dx) * p.DC + col, p.stream);
+        }
+    }
+}
+
+hipError_t prepare_stride_terms()
+{
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(stride_terms_kernel<false>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)SP::SMEM);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(stride_terms_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)SP::SMEM);
+    return e;
+}
+
+hipError_t launch_stride_terms(const StrideParams &p, int grid, hipStream_t st)
+{
+    if (p.span > kStrideRows || p.SC % 4 != 0 || p.DC % 4 != 0 || p.split < 1 || p.split > p.chunks ||
+        grid != ((p.M + SP::BM - 1) / SP::BM) * ((p.DC + SP::BN - 1) / SP::BN) * p.split || p.H != (p.DH + 1) / 2 || p.W != (p.DW + 1) / 2)
+        return hipErrorInvalidValue;
+    if (p.SC % kBK != 0)
+        hipLaunchKernelGGL((stride_terms_kernel<true>), dim3((unsigned)grid), dim3(SP::THREADS), SP::SMEM, st, p);
+    else
+        hipLaunchKernelGGL((stride_terms_kernel<false>), dim3((unsigned)grid), dim3(SP::THREADS), SP::SMEM, st, p);
+    return hipGetLastError();
+}
+
+}  // namespace mi355conv

@@ -1,0 +1,63 @@
+"""The kernel that forms the four stride phases of 3x3 backward-data (stride 2, padding 1) together, at the edges of its tiles, chunks,
+slices and maps, against the oracle."""
+import numpy as np
+import pytest
+
+import paper_2305_08819_amd as mc
+from tests import gpu_util as gu
+from tests.test_gpu_products import far_from_one, inputs, run
+
+pytestmark = pytest.mark.gpu
+
+# N, IH, IW, IC, OC, slices that the planner takes
+CASES = [
+    (128, 16, 16, 128, 256, 1),    # one tile a CU
+    (200, 4, 4, 256, 348, 4),      # 28 channels in the last chunk, maps of 2 x 2: every pixel lacks neighbours, slices of uneven length
+    (64, 15, 15, 40, 300, 4),      # odd maps: no odd row or column at the end; 40 of 64 columns
+    (1, 121, 126, 224, 316, 2),    # the widest rows that fit, one image
+    (32, 24, 24, 192, 44, 1),      # two chunks, the second of 12 channels
+    (28, 24, 20, 204, 136, 1),
+    (64, 14, 14, 296, 128, 1),
+    (17, 6, 24, 196, 376, 6),      # tiles that cross images
+]
+
+
+def desc(case):
+    n, h, w, ic, oc, split = case
+    d = mc.make_desc(n, h, w, ic, oc, 3, 3, 2, 1)
+    p = mc.conv2d_query_plan(mc.OP_BWD_DATA, d)
+    tiles = -(-n * d.OH * d.OW // 64) * -(-ic // 64)
+    assert (p.kernel, p.tile_m, p.tile_n, p.split, p.grid) == (mc.KERNEL_GATHER, 64, 64, split, tiles * split), (p.tile_m, p.tile_n, p.split, p.grid)
+    assert mc.conv2d_query_products(mc.OP_BWD_DATA, d) == mc.PRODUCTS_TERMS
+    print("stride", case, p.grid, flush=True)
+    return d
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+def test_phases(case):
+    gu.check_all_ops(desc(case), *inputs(desc(case), 31), ops=("bwd_data",), label=str(case), twice=True)
+
+
+@pytest.mark.parametrize("kind", ["1e-37", "1e-42", "hidden", "2^-133"])
+def test_small_operand_with_a_large_partner(kind):
+    """Operands that three bf16 terms do not hold (see test_gpu_products), in either operand, at the parity tests' bar."""
+    d = desc(CASES[4])
+    a, b = far_from_one("bwd_data", *gu.operands("bwd_data", *inputs(d, 11)), kind)
+    ref = gu.run_oracle("bwd_data", d, a, b)
+    got = run("bwd_data", d, a, b).astype(np.float64)
+    assert np.linalg.norm((got - ref).ravel()) <= 1e-5 * np.linalg.norm(ref.ravel())
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_non_finite_operands_reach_what_their_taps_reach(value):
+    for case in (CASES[4], CASES[1], CASES[7]):
+        d = desc(case)
+        for which in (0, 1):
+            ab = list(gu.operands("bwd_data", *inputs(d, 3)))
+            ab[which].reshape(-1)[ab[which].size // 3] = value
+            ref, got = gu.run_oracle("bwd_data", d, *ab), run("bwd_data", d, *ab)
+            assert 0 < np.isfinite(ref).sum() < ref.size
+            for f in (np.isnan, np.isposinf, np.isneginf):
+                assert np.array_equal(f(got), f(ref)), (case, which)
+            ok = np.isfinite(ref)
+            assert np.linalg.norm(got[ok].astype(np.float64) - ref[ok]) <= 1e-5 * np.linalg.norm(ref[ok])
