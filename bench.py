@@ -71,6 +71,12 @@ def kernel_name(layer, op, plan, desc, mc):
                 "bwd_weight": "wgrad_small_ic_kernel<%s, %s>" % (b(layer.OW % 8 == 0), fp32)}[op]
     terms = products_name(op, desc, mc) == "terms"
     if terms and op == "bwd_weight":
+        ocb, icb, reach = -(-layer.OC // 64), -(-layer.IC // 64), (layer.FH - 1) * layer.IW + layer.FW - 1
+        rows = 128 if reach <= 64 else 256
+        flat = ocb == 1 and icb > 1 and rows == 128
+        tiles = -(-layer.FH * layer.FW * (icb if flat else ocb) // 4) * (1 if flat else icb)
+        if plan.kernel == mc.KERNEL_WGRAD and t == (64, 64) and plan.grid == tiles * plan.split and not plan.pos_major and layer.stride == 1:
+            return "wring_terms_kernel<%d, %d>" % (rows, 2 if flat else ocb > 1)
         aligned = 32 % layer.OW == 0 or layer.OW % 32 == 0
         aligned = aligned and (32 % (layer.OH * layer.OW) == 0 or layer.OH * layer.OW % 32 == 0)
         mode = 1 if plan.pos_major else 3 if not aligned else 2 if layer.OW > 32 else 0

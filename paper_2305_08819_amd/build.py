@@ -18,7 +18,7 @@ LIB = os.path.join(PKG, "libmi355conv.so")
 BINDING = os.path.join(PKG, "_binding.so")      # the Python binding's fast path (host code only)
 SOURCES = ["api.hip", "kernels_direct.hip", "kernel_gather_gemm.hip", "kernel_gather_elem.hip",
            "kernel_wgrad.hip", "kernel_wgrad_fast.hip", "kernel_gather_terms.hip", "kernel_wgrad_terms.hip", "kernel_halo_terms.hip", "kernel_pointwise_terms.hip",
-           "kernel_short.hip", "kernel_block_terms.hip", "kernel_stride_terms.hip",
+           "kernel_short.hip", "kernel_block_terms.hip", "kernel_stride_terms.hip", "kernel_wring_terms.hip",
            "kernel_small_ic.hip", "probe_mfma.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall", "-Wno-unused-function",

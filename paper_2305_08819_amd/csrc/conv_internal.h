@@ -302,6 +302,40 @@ inline bool pointwise_accepts(const Shape &s, bool bwd)
            pointwise_steps(bwd ? s.OC : s.IC) != 0;
 }
 
+// ---- backward-weight of unit-stride layers with equal maps (kernel_wring_terms.hip) ----------------------
+// Units of one tap x 64 output x 64 input channels; a workgroup takes four of one block of input channels, and a slice of the pixels.
+struct WringParams {
+    const float *G, *X;
+    float *C;                  // dW, or workspace base when split > 1
+    unsigned gBytes, xBytes;
+    int M, H, W, IC, OC, FW, FH, ph, pw, taps;
+    int units, groups, tiles;  // of one block of input channels (wring_flat: of all); workgroups of it; of a slice
+    int stages, split;         // stages of 32 pixels, cut into split slices
+    int mapStep;               // 32 modulo H * W
+    int xcdUnit, xcdWhole, lds;
+    long long sliceStride;
+    FastDiv divXcdUnit, divTiles, divGroups, divSplit, divTaps, divFW, divHW, divW;
+};
+constexpr int kWringLds = 160 * 1024;
+// Rows of the ring: what all taps together reach, the stage's own 32 pixels and 32 that are being stored; 0: not taken.
+inline int wring_rows(const Shape &s)
+{
+    if (s.sh != 1 || s.sw != 1 || s.OH != s.IH || s.OW != s.IW || s.IC % 4 != 0 || s.OC % 4 != 0) return 0;
+    const long long taps = (long long)s.FH * s.FW, reach = (long long)(s.FH - 1) * s.IW + s.FW - 1, pixels = (long long)s.IH * s.IW;
+    if (taps < 3 || taps > 32 || s.FH > 32 || s.FW > 32 || reach > 192) return 0;
+    const int rows = (reach + 2 * kBK - 1) / kBK * kBK + kBK <= 128 ? 128 : 256;
+    const long long lds = 3LL * (rows + 1) * 128 + 12LL * kBK * 128 + pixels * 4;   // 128 rows: two rings and one block of dY take 122 KB
+    return lds + 128 <= kWringLds && pixels <= 8192 ? rows : 0;
+}
+// Units of four taps each run on from one block of input channels to the next: one block of output channels, and both rings fit.
+inline bool wring_flat(const Shape &s) { return s.OC <= 64 && s.IC > 64 && wring_rows(s) == 128; }
+inline int wring_groups(const Shape &s)   // workgroups of a block of input channels (all of them where the units run on)
+{
+    const long long units = (long long)s.FH * s.FW * (wring_flat(s) ? (s.IC + 63) / 64 : (s.OC + 63) / 64);
+    return (int)((units + 3) / 4);
+}
+inline int wring_tiles(const Shape &s) { return wring_groups(s) * (wring_flat(s) ? 1 : (s.IC + 63) / 64); }
+
 // ---- backward-weight ---------------------------------------------------------------------
 // dW[oc, col] = sum over rows m=(n,oh,ow): G[m, oc] * X[n, oh*sh-ph+fh(col), ow*sw-pw+fw(col), ic(col)]
 // with col = (fh*FW + fw)*IC + ic.  The row range is cut into `split` slices.
@@ -694,6 +728,7 @@ hipError_t prepare_wgrad_terms();
 hipError_t prepare_halo_terms();
 hipError_t prepare_pointwise_terms();
 hipError_t prepare_stride_terms();
+hipError_t prepare_wring_terms();
 
 hipError_t launch_direct_fwd(const float *X, const float *W, float *Y, const Shape &s, hipStream_t st);
 hipError_t launch_direct_bwd_data(const float *G, const float *W, float *dX, const Shape &s, hipStream_t st);
@@ -769,6 +804,8 @@ hipError_t launch_wgrad(const WgradParams &p, int bm, int bn, bool xElem, int gr
 hipError_t launch_wgrad_fast(const WgradParams &p, int bm, int bn, int grid, hipStream_t st);
 // same tiles, any map, products on the bf16 matrix pipe (three-term operands)
 hipError_t launch_wgrad_terms(const WgradParams &p, int bm, int bn, int grid, hipStream_t st);
+// unit stride, equal maps (wring_rows)
+hipError_t launch_wring_terms(WringParams p, int rows, int grid, hipStream_t st);
 // unit stride, FH*FW*IC <= 32, IC <= 4, OC % 32 == 0, (4+FH-1)*(32+FW-1) <= 224, tensors below 2^31 bytes
 hipError_t launch_bwd_data_small_ic(const SmallIcParams &p, hipStream_t st);
 // FH*FW*IC <= 32, any stride; grid = ceil(OC / 64) * split

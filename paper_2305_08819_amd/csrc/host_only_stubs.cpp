@@ -15,12 +15,14 @@ hipError_t prepare_gather_terms() { return hipErrorNotSupported; }
 hipError_t prepare_wgrad_terms() { return hipErrorNotSupported; }
 hipError_t prepare_halo_terms() { return hipErrorNotSupported; }
 hipError_t prepare_stride_terms() { return hipErrorNotSupported; }
+hipError_t prepare_wring_terms() { return hipErrorNotSupported; }
 hipError_t prepare_pointwise_terms() { return hipErrorNotSupported; }
 hipError_t launch_direct_fwd(const float *, const float *, float *, const Shape &, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_direct_bwd_data(const float *, const float *, float *, const Shape &, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_direct_bwd_weight(const float *, const float *, float *, const Shape &, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_block_terms(const BlockParams &, bool, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_stride_terms(const StrideParams &, int, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_wring_terms(WringParams, int, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_short(int, const float *, const float *, float *, const Shape &, bool, const float *, float, hipStream_t)
 {
     return hipErrorNotSupported;

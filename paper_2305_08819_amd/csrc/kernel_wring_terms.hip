@@ -1,0 +1,445 @@
+// Backward-weight of unit-stride layers whose two maps have the same size (3x3 with padding 1, 5x5 with padding 2, ...), on
+// v_mfma_f32_32x32x16_bf16 with three-term operands (split_bf16.h): the input is split once for the taps of a workgroup.
+//
+//   dW[oc, tap, ic] = sum over pixels m of dY[m, oc] * X[m + shift(tap), ic], shift = dy*W + dx, taps inside the image only
+//
+// A unit is one tap for 64 output and 64 input channels; a workgroup takes four consecutive ones of one block of input channels
+// (taps first, then blocks of output channels: so at most two of the latter).  It walks its slice of the pixels 32 at a time.  X
+// pixels live in a ring of LDS rows that holds what the four taps reach before and behind the stage, so each pixel is loaded,
+// split and stored once; a tap shifts the row that the fragment reads start from, and a pixel whose source lies outside
+// the image reads a row of zeros (a table of the map has one bit per pixel and tap).
+//
+// Why: the tiled kernel splits both operands once per tap, 6 to 12 vector instructions for an MFMA (64 x 64 to 128 x 64 tiles), and
+// a wave issues fewer than seven beside it; here it is three.
+//
+// Eight waves: a pair (halves of the 32 pixels) for each unit, 64 x 64.  A stage is 24 MFMAs a wave and one barrier, between the third and
+// fourth of the six products as in kernel_halo_terms.hip; half an item is split beside each product.
+//
+// Bound like that kernel (21.5 and 20.4 million busy CU cycles for the same products, the matrix pipe at work in two thirds of them, and
+// at the clock that power leaves): 1.05 us a stage with every CU busy, 3.3 us around a workgroup's stages, 5 us of combine pass.  us,
+// tiled kernel and this one: 100 x 14x14x192 -> 48 5x5 89.1 and 72.6, 128 x 8x8x256 -> 256 66.1 and 56.7, 32x32x64 -> 64
+// 77.3 and 71.7.  Measured and left: a branch for the second block inside the loop 76.6 for the first of these; selects in place
+// of masks for the rows outside, which became branches, 64.4 for the second; the splitting beside the first three products only, the same.
+#include <hip/hip_runtime.h>
+#include "split_bf16.h"
+
+namespace mi355conv {
+
+namespace {
+// What a workgroup may have two blocks of 64 channels of: neither operand, dY (units of one block of input channels), or X (units of the only block
+// of output channels, on through the blocks of input channels).
+enum { kOneEach, kTwoG, kTwoX };
+
+template <int ROWS, int BLOCKS>   // rows of the ring, a power of two
+struct WR {
+    static constexpr int WAVES = 8, THREADS = WAVES * 64;
+    static constexpr int PITCH = 128;                                  // 64 channels of one plane
+    static constexpr int X_MASK = ROWS * PITCH - 1, X_PLANE = ROWS * PITCH + PITCH, X_ZERO = ROWS * PITCH;   // and a row of zeros
+    static constexpr int X_BLOCK = 3 * X_PLANE;                                                           // [block][plane][pixel]
+    static constexpr int G_PLANE = kBK * PITCH, G_BLOCK = 3 * G_PLANE, G_BUF = (BLOCKS == kTwoG ? 2 : 1) * G_BLOCK;
+    static constexpr int G_BASE = (BLOCKS == kTwoX ? 2 : 1) * X_BLOCK, TABLE = G_BASE + 2 * G_BUF;
+    static constexpr int EXCHANGE = WAVES * 4 * 32 * kLDT * 4;
+};
+}  // namespace
+
+// The table of the map lies behind the tiles; the exchange buffers reuse all but the flags.
+template <class T>
+static int wring_lds(int pixels)
+{
+    const int tiles = (T::TABLE + pixels * 4 + 15) / 16 * 16;
+    return (tiles > T::EXCHANGE ? tiles : T::EXCHANGE) + 64;
+}
+
+// The fp32 form of the two blocks that a wave finishes: v_mfma_f32_32x32x2_f32 on elements read straight from memory, both operands 0
+// where the tap lies outside the image.
+__device__ __forceinline__ void wring_redo_fp32(const WringParams &p, __amdgpu_buffer_rsrc_t rsrcG, __amdgpu_buffer_rsrc_t rsrcX, int m0,
+                                                int m1, int dy, int dx, int oc, int ic, int lane, float16v (&own)[2])
+{
+    constexpr int kOutOfRange = (int)0x80000000;
+    const int lh = lane >> 5;
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) own[o][r] = 0.f;
+#pragma unroll 1
+    for (int m = m0 + lh; m < m1 + lh; m += 2) {
+        const int q = m - (int)fast_div((unsigned)m, p.divHW) * (p.H * p.W), y = (int)fast_div((unsigned)q, p.divW), x = q - y * p.W;
+        const bool ok = m < m1 && (unsigned)(y + dy) < (unsigned)p.H && (unsigned)(x + dx) < (unsigned)p.W;
+        const float b = __builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(rsrcX, ok && ic < p.IC ? ((m + dy * p.W + dx) * p.IC + ic) * 4 : kOutOfRange, 0, 0));
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            const float g = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(rsrcG, ok && oc + o * 32 < p.OC ? (m * p.OC + oc + o * 32) * 4 : kOutOfRange, 0, 0));
+            own[o] = __builtin_amdgcn_mfma_f32_32x32x2f32(b, g, own[o], 0, 0, 0);
+        }
+    }
+}
+
+template <int ROWS, int BLOCKS>
+__global__ __launch_bounds__((WR<ROWS, BLOCKS>::THREADS), 2) void wring_terms_kernel(const WringParams p)
+{
+    using T = WR<ROWS, BLOCKS>;
+    constexpr bool TWO = BLOCKS != kOneEach;
+    extern __shared__ f4 smem_raw[];
+    char *smem = reinterpret_cast<char *>(smem_raw);
+    int *lost = reinterpret_cast<int *>(smem + p.lds - 64);
+    unsigned *table = reinterpret_cast<unsigned *>(smem + T::TABLE);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, lh = lane >> 5;
+
+    const int bid = xcd_remap_fast(blockIdx.x, p.xcdWhole, p.xcdUnit, p.divXcdUnit);
+    const int slice = (int)fast_div((unsigned)bid, p.divTiles), tile = bid - slice * p.tiles;
+    const int icb = (int)fast_div((unsigned)tile, p.divGroups), unit0 = (tile - icb * p.groups) * 4;
+    const int s0 = (int)fast_div((unsigned)(slice * p.stages), p.divSplit), s1 = (int)fast_div((unsigned)((slice + 1) * p.stages), p.divSplit);
+    const int m0 = s0 * kBK;
+
+    // ---- units: which taps, which rows of X the stages reach ---------------------------------------------
+    auto tap_of = [&](int unit, int *block, int *dy, int *dx) __attribute__((always_inline)) {
+        *block = (int)fast_div((unsigned)unit, p.divTaps);
+        const int t = unit - *block * p.taps, u = (int)fast_div((unsigned)t, p.divFW);
+        *dy = u - p.ph;
+        *dx = t - u * p.FW - p.pw;
+        return t;
+    };
+    int low_shift = 0x7fffffff, high_shift = -0x7fffffff, block0 = 0, blockLast = 0;   // blocks of output (with kTwoX: input) channels
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        int block, dy, dx;
+        if (unit0 + j >= p.units) continue;
+        tap_of(unit0 + j, &block, &dy, &dx);
+        const int s = dy * p.W + dx;
+        low_shift = s < low_shift ? s : low_shift;
+        high_shift = s > high_shift ? s : high_shift;
+        if (j == 0) block0 = block;
+        blockLast = block;
+    }
+    const int blocks = (high_shift - low_shift + 2 * kBK - 1) >> 5;        // of 32 rows that a stage reaches
+    const int first = m0 + kBK + high_shift - blocks * kBK;                // X pixel in row 0 of the ring
+
+    const __amdgpu_buffer_rsrc_t rsrcG =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.G), 0, (int)p.gBytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrcX =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.X), 0, (int)p.xBytes, 0x00020000);
+
+    // ---- loader state: 16 threads a pixel of 64 channels ---------------------------------------------------
+    const int seg = tid & 15, row = tid >> 4;
+    // tensors are below 2^31 bytes: an offset that starts there stays past them
+    auto channel = [](bool ok, int pixel, int channels, int c) { return ok && c < channels ? (pixel * channels + c) * 4 : (int)0x80000000; };
+    const int xChannel = (BLOCKS == kTwoX ? block0 : icb) * 64 + seg * 4, gChannel = (BLOCKS == kTwoX ? 0 : block0) * 64 + seg * 4;
+    int xOff = channel(true, first + row, p.IC, xChannel), gOff = channel(true, m0 + row, p.OC, gChannel);
+    int off2 = BLOCKS == kTwoX ? channel(blockLast != block0, first + row, p.IC, xChannel + 64)
+                               : channel(blockLast != block0, m0 + row, p.OC, gChannel + 64);
+    const int xStep = kBK * p.IC * 4, gStep = kBK * p.OC * 4;
+    f4 rawX, rawG, raw2;   // loads in flight
+    auto load_x = [&]() __attribute__((always_inline)) {
+        rawX = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcX, xOff, 0, 0));
+        xOff += xStep;
+    };
+    auto load_g = [&]() __attribute__((always_inline)) {
+        rawG = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcG, gOff, 0, 0));
+        gOff += gStep;
+    };
+    auto load_2 = [&]() __attribute__((always_inline)) {   // the second block of either
+        raw2 = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(BLOCKS == kTwoX ? rsrcX : rsrcG, off2, 0, 0));
+        off2 += BLOCKS == kTwoX ? xStep : gStep;
+    };
+
+    // ---- LDS tiles: rows of 128 bytes, their 64-byte halves exchanged by row ------------------------------
+    const int inRow = row * T::PITCH + (((seg >> 3) ^ ((row >> 1) & 1)) << 6) + (seg & 7) * 8;
+    int xBlock = 0;                        // where the next 32 rows of the ring begin
+    int gStore = T::G_BASE + inRow, gStep2 = T::G_BUF;
+    unsigned rest = 0u;   // what the terms left of the elements split so far (see split_bf16.h)
+    auto store = [&](char *d, int plane, const SplitQuad &s) __attribute__((always_inline)) {
+        *reinterpret_cast<u2 *>(d) = s.h;
+        *reinterpret_cast<u2 *>(d + plane) = s.m;
+        *reinterpret_cast<u2 *>(d + 2 * plane) = s.l;
+    };
+    auto store_x = [&](const SplitQuad &s) __attribute__((always_inline)) { store(smem + xBlock + inRow, T::X_PLANE, s); };
+    auto next_x = [&]() __attribute__((always_inline)) { xBlock = (xBlock + kBK * T::PITCH) & T::X_MASK; };
+    if (tid < (BLOCKS == kTwoX ? 48 : 24))
+        *reinterpret_cast<f4 *>(smem + (tid >> 3) * T::X_PLANE + T::X_ZERO + (tid & 7) * 16) = f4{0.f, 0.f, 0.f, 0.f};
+    for (int q = tid; q < p.H * p.W; q += T::THREADS) {   // taps inside the image
+        const int y = (int)fast_div((unsigned)q, p.divW), x = q - y * p.W;
+        unsigned xs = 0u, m = 0u;
+        for (int v = 0; v < p.FW; ++v) xs |= ((unsigned)(x + v - p.pw) < (unsigned)p.W ? 1u : 0u) << v;
+        for (int u = 0; u < p.FH; ++u) m |= ((unsigned)(y + u - p.ph) < (unsigned)p.H ? xs : 0u) << (u * p.FW);
+        table[q] = m;
+    }
+
+    // ---- this wave's unit ------------------------------------------------------------------------------------
+    const int kh = wave & 1, unit = unit0 + (wave >> 1);
+    const bool active = unit < p.units;   // uniform; a pair without a unit repeats the first one and keeps nothing
+    int block, dy, dx;
+    const int tap = tap_of(active ? unit : unit0, &block, &dy, &dx);
+    const int second = block - block0;   // of the workgroup's two blocks
+    const int shift = dy * p.W + dx;
+    const int k = kh * 16 + lh * 8 + ((lane & 15) >> 2);   // the transposing reads: this lane's pixel of a stage, and the fourth behind it
+    const int inFrag = ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+    int gFrag = T::G_BASE + (BLOCKS == kTwoG ? second * T::G_BLOCK : 0) + k * T::PITCH + (((k >> 1) & 1) << 6) + inFrag, gRead = T::G_BUF;
+    const int xBase = BLOCKS == kTwoX ? second * T::X_BLOCK : 0;
+    int ring[2], in[2], pixel[2], place[2], xFrag[2];   // in bytes of the ring; of the row; in the map; of all pixels
+    unsigned mask[2];
+    const int hw = p.H * p.W;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int r = m0 + k + 4 * h + shift - first;
+        ring[h] = r * T::PITCH;
+        in[h] = (((r >> 1) & 1) << 6) + inFrag;
+        place[h] = m0 + k + 4 * h;
+        pixel[h] = place[h] - (int)fast_div((unsigned)place[h], p.divHW) * hw;
+    }
+    auto look = [&]() __attribute__((always_inline)) {   // the masks of this lane's pixels, then on to the next stage
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            mask[h] = table[pixel[h]];
+            const unsigned n = (unsigned)(pixel[h] + p.mapStep), w = n - (unsigned)hw;
+            pixel[h] = (int)(n < w ? n : w);
+        }
+    };
+    auto place_x = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int at = (ring[h] & T::X_MASK) | in[h];
+            const int inside = __builtin_amdgcn_sbfe((int)mask[h], tap, 1) & ((place[h] - p.M) >> 31);   // -1 or 0
+            xFrag[h] = xBase + ((inside & at) | (~inside & (T::X_ZERO + inFrag)));
+            ring[h] += kBK * T::PITCH;
+            place[h] += kBK;
+        }
+    };
+
+    float16v acc[4], low[4];   // [block of output channels][block of input channels]
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[b][r] = low[b][r] = 0.f;
+    bf8 fg[3][2], fx[3][2];
+    auto read_g = [&](int plane) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const char *s = smem + (gFrag ^ (i << 6)) + plane * T::G_PLANE;
+            fg[plane][i] = join_quads(lds_read_tr(s), lds_read_tr(s + 4 * T::PITCH));
+        }
+    };
+    auto read_x = [&](int plane) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            fx[plane][j] = join_quads(lds_read_tr(smem + (xFrag[0] ^ (j << 6)) + plane * T::X_PLANE),
+                                      lds_read_tr(smem + (xFrag[1] ^ (j << 6)) + plane * T::X_PLANE));
+    };
+    auto multiply = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                float16v &sum = g == kSplitProducts - 1 ? acc[i * 2 + j] : low[i * 2 + j];
+                sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[kProdB[g]][j], fg[kProdA[g]][i], sum, 0, 0, 0);
+            }
+    };
+
+    // ---- main loop ------------------------------------------------------------------------------------------
+    load_g();
+    constexpr int MOST = ROWS / kBK - 1;
+    f4 reach[MOST], reach2[BLOCKS == kTwoX ? MOST : 1];
+#pragma unroll
+    for (int b = 0; b < MOST; ++b)
+        if (b < blocks) {
+            load_x();
+            reach[b] = rawX;
+            if (BLOCKS == kTwoX) {
+                load_2();
+                reach2[b] = raw2;
+            }
+        }
+    if (BLOCKS == kTwoG) {
+        load_2();
+        reach2[0] = raw2;
+    }
+    load_x();
+    if (TWO) load_2();
+#pragma unroll
+    for (int b = 0; b < MOST; ++b)
+        if (b < blocks) {
+            store_x(split_quad(reach[b], rest));
+            if (BLOCKS == kTwoX) store(smem + xBlock + inRow + T::X_BLOCK, T::X_PLANE, split_quad(reach2[b], rest));
+            next_x();
+        }
+    store(smem + gStore, T::G_PLANE, split_quad(rawG, rest));
+    load_g();
+    if (BLOCKS == kTwoG) store(smem + gStore + T::G_BLOCK, T::G_PLANE, split_quad(reach2[0], rest));
+    gStore += gStep2;
+    gStep2 = -gStep2;
+    if (BLOCKS == kTwoG) {   // the second block a stage ahead of the first one
+        store(smem + gStore + T::G_BLOCK, T::G_PLANE, split_quad(raw2, rest));
+        load_2();
+    }
+    SplitQuad sx;
+    split_pair(rawX, 0, rest, sx);
+    __syncthreads();
+    look();
+    place_x();
+#pragma unroll
+    for (int pl = 2; pl >= 0; --pl) {   // in the order in which a stage reads them: the compiler counts what is under way
+        read_g(pl);
+        read_x(pl);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    constexpr int kBarrier = 3;   // every plane of both operands has been used by the first three groups
+    for (int s = s0; s + 1 < s1; ++s) {
+        SplitQuad sg, s2;
+#pragma unroll
+        for (int g = 0; g < kSplitProducts; ++g) {   // half an item each
+            if (g == 0) {
+                look();
+                split_pair(rawX, 1, rest, sx);
+                store_x(sx);
+                load_x();
+            }
+            if (g == 1) {
+                split_pair(rawG, 0, rest, sg);
+                if (BLOCKS == kTwoX) split_pair(raw2, 0, rest, s2);
+            }
+            if (g == 2) {
+                split_pair(rawG, 1, rest, sg);
+                store(smem + gStore, T::G_PLANE, sg);
+                load_g();
+                gStore += gStep2;
+                gStep2 = -gStep2;
+                if (BLOCKS == kTwoX) {
+                    split_pair(raw2, 1, rest, s2);
+                    store(smem + xBlock + inRow + T::X_BLOCK, T::X_PLANE, s2);
+                    load_2();
+                }
+                next_x();
+                place_x();
+                gFrag += gRead;
+                gRead = -gRead;
+            }
+            if (g == kBarrier) {
+                __syncthreads();   // the tile of this stage is free: of the next but one, the second block is stored at once
+                read_g(2);
+                read_x(2);
+                if (BLOCKS == kTwoG) split_pair(raw2, 0, rest, s2);
+            }
+            if (g == kBarrier + 1) {
+                read_g(1);
+                if (BLOCKS == kTwoG) {
+                    split_pair(raw2, 1, rest, s2);
+                    store(smem + gStore + T::G_BLOCK, T::G_PLANE, s2);
+                    load_2();
+                }
+            }
+            if (g == kBarrier + 2) {
+                read_x(1);
+                split_pair(rawX, 0, rest, sx);
+            }
+            asm volatile("" : "+v"(rest));
+            multiply(g);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                              // one MFMA, then
+                if (g >= kBarrier) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);           // LDS reads,
+                __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);                              // vector instructions,
+                __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);                              // an LDS store,
+                __builtin_amdgcn_sched_group_barrier(0x004, 4, 0);                              // scalar instructions
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        read_x(0);
+        read_g(0);
+    }
+#pragma unroll
+    for (int g = 0; g < kSplitProducts; ++g) {   // the last stage: nothing left to store or to read
+        if (g == kBarrier) __syncthreads();       // every wave has used its last fragments: the buffers are free
+        multiply(g);
+    }
+
+    // ---- the pair's halves meet: each wave finishes the two blocks of its input channels --------------------
+    float *mine = reinterpret_cast<float *>(smem) + wave * 4 * 32 * kLDT;
+    const float *theirs = reinterpret_cast<const float *>(smem) + (wave ^ 1) * 4 * 32 * kLDT;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            f4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = acc[b][g * 4 + e] + low[b][g * 4 + e];
+            *reinterpret_cast<f4 *>(mine + (b * 32 + l32) * kLDT + g * 8 + lh * 4) = v;
+        }
+    const int mineLost = split_lost(rest);
+    if (lane == 0) lost[wave] = mineLost;
+    __syncthreads();
+    if (!active) return;   // no barrier follows
+    int anyLost = 0;
+#pragma unroll
+    for (int w = 0; w < T::WAVES; ++w) anyLost |= lost[w];
+    const int sRow = lane >> 3, sSeg = lane & 7;   // this lane's output channel (8q + sRow of a block) and input channels (4*sSeg .. +3)
+    f4 own[2][4];
+    SplitCheck check;
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int at = ((2 * o + kh) * 32 + q * 8 + sRow) * kLDT + sSeg * 4;
+            own[o][q] = *reinterpret_cast<const f4 *>(mine + at) + *reinterpret_cast<const f4 *>(theirs + at);
+            check.look(own[o][q]);
+        }
+    const bool bad = anyLost != 0 || check.bad();
+    const int ic0 = (BLOCKS == kTwoX ? block : icb) * 64 + kh * 32, oc0 = BLOCKS == kTwoX ? 0 : block * 64;
+    if (__any(bad)) {
+        float16v redo[2];
+        const int end = s1 * kBK < p.M ? s1 * kBK : p.M;
+        wring_redo_fp32(p, rsrcG, rsrcX, m0, end, dy, dx, oc0 + l32, ic0 + l32, lane, redo);
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {   // turned in the wave's own buffer of the block, which its partner does not read
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mine[((2 * o + kh) * 32 + l32) * kLDT + 8 * (r / 4) + 4 * lh + r % 4] = redo[o][r];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                own[o][q] = *reinterpret_cast<const f4 *>(mine + ((2 * o + kh) * 32 + q * 8 + sRow) * kLDT + sSeg * 4);
+        }
+    }
+    float *C = p.C + (long long)slice * p.sliceStride;
+    const int ic = ic0 + sSeg * 4;
+    if (ic >= p.IC) return;
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int oc = oc0 + o * 32 + q * 8 + sRow;
+            if (oc < p.OC) *reinterpret_cast<f4 *>(C + ((long long)oc * p.taps + tap) * p.IC + ic) = own[o][q];
+        }
+}
+
+template <int ROWS, int BLOCKS>
+static hipError_t launch_wring_one(WringParams &p, int grid, hipStream_t st)
+{
+    using T = WR<ROWS, BLOCKS>;
+    p.lds = wring_lds<T>(p.H * p.W);
+    if (p.lds > kWringLds) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((wring_terms_kernel<ROWS, BLOCKS>), dim3((unsigned)grid), dim3(T::THREADS), (size_t)p.lds, st, p);
+    return hipGetLastError();
+}
+
+hipError_t prepare_wring_terms()
+{
+    hipError_t e = hipSuccess;
+    for (const void *k : {reinterpret_cast<const void *>(wring_terms_kernel<128, kOneEach>), reinterpret_cast<const void *>(wring_terms_kernel<128, kTwoG>),
+                          reinterpret_cast<const void *>(wring_terms_kernel<128, kTwoX>), reinterpret_cast<const void *>(wring_terms_kernel<256, kOneEach>),
+                          reinterpret_cast<const void *>(wring_terms_kernel<256, kTwoG>)})
+        if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kWringLds);
+    return e;
+}
+
+hipError_t launch_wring_terms(WringParams p, int rows, int grid, hipStream_t st)
+{
+    if (p.taps > 32 || p.taps < 3 || p.IC % 4 != 0 || p.OC % 4 != 0 || p.split < 1 || p.split > p.stages || grid != p.tiles * p.split)
+        return hipErrorInvalidValue;
+    const bool twoX = p.groups == p.tiles && p.IC > 64, twoG = p.OC > 64;   // wring_flat: units on through the blocks of input channels
+    if (rows == 128 && twoX) return twoG ? hipErrorInvalidValue : launch_wring_one<128, kTwoX>(p, grid, st);
+    if (rows == 128 && twoG) return launch_wring_one<128, kTwoG>(p, grid, st);
+    if (rows == 128) return launch_wring_one<128, kOneEach>(p, grid, st);
+    if (rows != 256 || twoX) return hipErrorInvalidValue;
+    return twoG ? launch_wring_one<256, kTwoG>(p, grid, st) : launch_wring_one<256, kOneEach>(p, grid, st);
+}
+
+}  // namespace mi355conv

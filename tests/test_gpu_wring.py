@@ -1,0 +1,67 @@
+"""The backward-weight kernel that splits the input once for a workgroup's four taps, at the edges of its units, rings, slices and maps,
+against the oracle."""
+import numpy as np
+import pytest
+
+import paper_2305_08819_amd as mc
+from tests import gpu_util as gu
+from tests.test_gpu_products import far_from_one, inputs, run
+
+pytestmark = pytest.mark.gpu
+
+# N, IH, IW, IC, OC, F, slices, workgroups of a slice
+CASES = [
+    (3, 12, 27, 412, 148, 3, 5, 49),     # three blocks of output channels: workgroups of one and of two; 28 and 20 channels in the last ones
+    (3, 13, 13, 452, 272, 3, 2, 96),     # maps whose pixels are no multiple of a stage; the last pair of the last workgroup idle
+    (200, 6, 6, 176, 44, 3, 36, 7),      # one block of output channels: units run on through the input channels
+    (200, 3, 3, 320, 48, 5, 8, 32),      # maps of fewer pixels than a stage, filters wider than the map
+    (34, 7, 7, 380, 36, 5, 6, 38),
+    (3, 37, 41, 300, 48, 3, 17, 15),     # the long ring
+    (3, 42, 24, 188, 52, 5, 12, 21),
+    (1, 24, 24, 360, 100, 5, 3, 78),     # one image: the last stage of the last slice ends with the tensor
+    (3, 6, 60, 136, 404, 3, 5, 48),
+    (1, 31, 31, 280, 80, 5, 3, 65),
+    (128, 8, 8, 256, 256, 3, 7, 36),     # a layer in earnest
+]
+
+
+def desc(case):
+    n, h, w, ic, oc, f, split, tiles = case
+    d = mc.make_desc(n, h, w, ic, oc, f, f, 1, f // 2)
+    p = mc.conv2d_query_plan(mc.OP_BWD_WEIGHT, d)
+    assert (p.kernel, p.tile_m, p.tile_n, p.pos_major, p.split, p.grid) == (mc.KERNEL_WGRAD, 64, 64, 0, split, split * tiles), (p.split, p.grid)
+    assert mc.conv2d_query_products(mc.OP_BWD_WEIGHT, d) == mc.PRODUCTS_TERMS
+    print("wring", case, flush=True)
+    return d
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+def test_units(case):
+    gu.check_all_ops(desc(case), *inputs(desc(case), 31), ops=("bwd_weight",), label=str(case), twice=True)
+
+
+@pytest.mark.parametrize("case", [CASES[2], CASES[7]], ids=["two blocks of X", "two blocks of dY"])
+@pytest.mark.parametrize("kind", ["1e-37", "1e-42", "hidden", "2^-133"])
+def test_small_operand_with_a_large_partner(kind, case):
+    """Operands that three bf16 terms do not hold (see test_gpu_products), in either operand, at the parity tests' bar."""
+    d = desc(case)
+    a, b = far_from_one("bwd_weight", *gu.operands("bwd_weight", *inputs(d, 11)), kind)
+    ref = gu.run_oracle("bwd_weight", d, a, b)
+    got = run("bwd_weight", d, a, b).astype(np.float64)
+    assert np.linalg.norm((got - ref).ravel()) <= 1e-5 * np.linalg.norm(ref.ravel())
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("at", [0, -1, None], ids=["first", "last", "inside"])
+def test_non_finite_operands_reach_what_their_taps_reach(value, at):
+    for case in (CASES[2], CASES[7]):
+        d = desc(case)
+        for which in (0, 1):
+            ab = list(gu.operands("bwd_weight", *inputs(d, 3)))
+            ab[which].reshape(-1)[ab[which].size // 3 if at is None else at] = value
+            ref, got = gu.run_oracle("bwd_weight", d, *ab), run("bwd_weight", d, *ab)
+            assert 0 < np.isfinite(ref).sum() < ref.size
+            for f in (np.isnan, np.isposinf, np.isneginf):
+                assert np.array_equal(f(got), f(ref)), (case, which)
+            ok = np.isfinite(ref)
+            assert np.linalg.norm(got[ok].astype(np.float64) - ref[ok]) <= 1e-5 * np.linalg.norm(ref[ok])
