@@ -47,6 +47,9 @@ def kernel_name(layer, op, plan, desc, mc):
     """Name of the main kernel a plan launches, spelled as rocprofv3 prints it."""
     b = lambda v: "true" if v else "false"   # noqa: E731
     t = (plan.tile_m, plan.tile_n)
+    if plan.kernel == mc.KERNEL_DIRECT and op == "bwd_data" and plan.tile_m > 32 and products_name(op, desc, mc) == "terms":
+        halo = (plan.tile_m // 32 + layer.FH - 1) * (31 + layer.FW)
+        return "bwd_data_small_ic_kernel<false, %d, 2>" % (3 if halo > 256 else 2)
     if plan.kernel == mc.KERNEL_DIRECT and products_name(op, desc, mc) == "terms":
         bwd, st = op == "bwd_data", layer.stride
         most = [max(sum(0 <= t and t % (st if bwd else 1) == 0 and t // (st if bwd else 1) < n_src for t in
@@ -67,7 +70,7 @@ def kernel_name(layer, op, plan, desc, mc):
         fp32 = b(products_name(op, desc, mc) == "fp32")
         halo = (plan.tile_m // 32 + layer.FH - 1) * (31 + layer.FW)
         return {"fwd": "fwd_small_ic_kernel<false, false, %s, %s, false>" % (b(layer.OC % 4 == 0), fp32),
-                "bwd_data": "bwd_data_small_ic_kernel<%s, %d, %s>" % (fp32, 3 if halo > 256 else 2, b(layer.OC % 64 != 0)),
+                "bwd_data": "bwd_data_small_ic_kernel<%s, %d, %d>" % (fp32, 3 if halo > 256 else 2, layer.OC % 64 != 0),
                 "bwd_weight": "wgrad_small_ic_kernel<%s, %s>" % (b(layer.OW % 8 == 0), fp32)}[op]
     terms = products_name(op, desc, mc) == "terms"
     if terms and op == "bwd_weight":

@@ -714,7 +714,7 @@ inline int small_ic_fwd_grid(int M, int OC, bool stream)
 }
 inline bool bwd_data_small_ic_accepts(int IC, int OC, int FH, int FW, int sh, int sw)
 {
-    return sh == 1 && sw == 1 && IC <= 4 && FH * FW * IC <= 32 && OC % kBK == 0 && (4 + FH - 1) * (32 + FW - 1) <= 224;
+    return sh == 1 && sw == 1 && IC <= 4 && FH * FW * IC <= 32 && OC % 4 == 0 && (4 + FH - 1) * (32 + FW - 1) <= 224;
 }
 inline bool patch_small_ic_accepts(int IC, int FH, int FW) { return FH * FW * IC <= 32; }   // forward, backward-weight
 
@@ -806,7 +806,7 @@ hipError_t launch_wgrad_fast(const WgradParams &p, int bm, int bn, int grid, hip
 hipError_t launch_wgrad_terms(const WgradParams &p, int bm, int bn, int grid, hipStream_t st);
 // unit stride, equal maps (wring_rows)
 hipError_t launch_wring_terms(WringParams p, int rows, int grid, hipStream_t st);
-// unit stride, FH*FW*IC <= 32, IC <= 4, OC % 32 == 0, (4+FH-1)*(32+FW-1) <= 224, tensors below 2^31 bytes
+// unit stride, FH*FW*IC <= 32, IC <= 4, OC % 4 == 0, (4+FH-1)*(32+FW-1) <= 224, tensors below 2^31 bytes
 hipError_t launch_bwd_data_small_ic(const SmallIcParams &p, hipStream_t st);
 // FH*FW*IC <= 32, any stride; grid = ceil(OC / 64) * split
 hipError_t launch_wgrad_small_ic(const SmallIcParams &p, hipStream_t st);

@@ -29,8 +29,9 @@ constexpr int kPChunk = 64;                        // channels of dY whose filte
 }  // namespace
 
 // FP32: products on v_mfma_f32_32x32x2_f32 (conv2d_set_products), the same loads and steps.  BLOCKS: of 32 halo pixels
-// a wave.  HALF: OC is an odd multiple of 32, so the last chunk has half its steps.
-template <bool FP32, int BLOCKS, bool HALF>
+// a wave.  LAST: what the last 64 channels are: all there, half of them (OC an odd multiple of 32), or any multiple of 4.
+enum { kWholeChunk, kHalfChunk, kAnyChunk };
+template <bool FP32, int BLOCKS, int LAST>
 __global__ __launch_bounds__(kThreads, 2) void bwd_data_small_ic_kernel(const SmallIcParams p)
 {
     typedef unsigned u4 __attribute__((ext_vector_type(4)));
@@ -71,7 +72,8 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_data_small_ic_kernel(const Sm
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const int ch = c0 + 16 * (q >> 1);   // uniform; a lane's 8 channels lie in the same half of 32
-            raw[set][q] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcG, ch < p.OC ? gOff[b] : kOutOfRange,
+            const bool there = LAST == kAnyChunk ? ch + 8 * lh + 4 * (q & 1) < p.OC : ch < p.OC;
+            raw[set][q] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcG, there ? gOff[b] : kOutOfRange,
                                                                                        (ch < p.OC ? ch : 0) * 4 + (q & 1) * 16, 0));
         }
     };
@@ -111,7 +113,8 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_data_small_ic_kernel(const Sm
             if (b + 1 < BLOCKS) load((b + 1) & 1, b + 1, c0);
 #pragma unroll
             for (int s = 0; s < kPChunk / 16; ++s) {
-                if (HALF && s == 2 && c0 + 32 >= p.OC) break;   // uniform
+                if (LAST == kHalfChunk && s == 2 && c0 + 32 >= p.OC) break;   // uniform
+                if (LAST == kAnyChunk && s > 0 && c0 + 16 * s >= p.OC) break;   // uniform
                 if constexpr (FP32) {
 #pragma unroll
                     for (int e = 0; e < 8; ++e)
@@ -166,7 +169,9 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_data_small_ic_kernel(const Sm
                 sum = __builtin_amdgcn_mfma_f32_32x32x2f32(w, g, sum, 0, 0, 0);
             }
 #pragma unroll
-            for (int r = 0; r < 16; ++r) Ps[((wave + 4 * b) * 32 + l32) * kLDP + 8 * (r / 4) + 4 * lh + r % 4] = sum[r];
+            for (int r = 0; r < 16; ++r)   // padding has no part, an infinite filter element's neither (whole and half chunks multiply it as 0)
+                Ps[((wave + 4 * b) * 32 + l32) * kLDP + 8 * (r / 4) + 4 * lh + r % 4] =
+                    LAST == kAnyChunk && off == kOutOfRange ? 0.f : sum[r];
         }
     } else {
 #pragma unroll
@@ -204,18 +209,22 @@ hipError_t launch_bwd_data_small_ic(const SmallIcParams &p, hipStream_t st)
     static_assert(kTC == 32 && kThreads == 8 * kTC, "small_ic_tile_rows() and small_ic_bwd_grid() state these tile sizes");
     static_assert(sizeof(float) * kPRows * kLDP + 3 * kPChunk * 32 * 2 <= 64 * 1024, "within the LDS a kernel gets");
     const int grid = small_ic_bwd_grid(p.N, p.IH, p.IW, p.FH, p.FW);
-    const bool three = (p.rows + p.FH - 1) * (kTC + p.FW - 1) > 256, half = p.OC % kPChunk != 0;
-#define MI355_FIRST_BWD(FP32_, BLOCKS_, HALF_)                                                     \
-    if ((p.fp32 != 0) == FP32_ && three == (BLOCKS_ == 3) && half == HALF_)                        \
-        hipLaunchKernelGGL((bwd_data_small_ic_kernel<FP32_, BLOCKS_, HALF_>), dim3((unsigned)grid), dim3(kThreads), 0, st, p);
-    MI355_FIRST_BWD(false, 2, false)
-    MI355_FIRST_BWD(false, 2, true)
-    MI355_FIRST_BWD(false, 3, false)
-    MI355_FIRST_BWD(false, 3, true)
-    MI355_FIRST_BWD(true, 2, false)
-    MI355_FIRST_BWD(true, 2, true)
-    MI355_FIRST_BWD(true, 3, false)
-    MI355_FIRST_BWD(true, 3, true)
+    const bool three = (p.rows + p.FH - 1) * (kTC + p.FW - 1) > 256;
+    const int last = p.OC % kPChunk == 0 ? kWholeChunk : p.OC % (kPChunk / 2) == 0 ? kHalfChunk : kAnyChunk;
+#define MI355_FIRST_BWD(FP32_, BLOCKS_, LAST_)                                                     \
+    if ((p.fp32 != 0) == FP32_ && three == (BLOCKS_ == 3) && last == LAST_)                        \
+        hipLaunchKernelGGL((bwd_data_small_ic_kernel<FP32_, BLOCKS_, LAST_>), dim3((unsigned)grid), dim3(kThreads), 0, st, p);
+    if (p.fp32 && last == kAnyChunk) return hipErrorNotSupported;   // fp32 products of such channel counts stay with the tiled kernel
+    MI355_FIRST_BWD(false, 2, kWholeChunk)
+    MI355_FIRST_BWD(false, 2, kHalfChunk)
+    MI355_FIRST_BWD(false, 2, kAnyChunk)
+    MI355_FIRST_BWD(false, 3, kWholeChunk)
+    MI355_FIRST_BWD(false, 3, kHalfChunk)
+    MI355_FIRST_BWD(false, 3, kAnyChunk)
+    MI355_FIRST_BWD(true, 2, kWholeChunk)
+    MI355_FIRST_BWD(true, 2, kHalfChunk)
+    MI355_FIRST_BWD(true, 3, kWholeChunk)
+    MI355_FIRST_BWD(true, 3, kHalfChunk)
 #undef MI355_FIRST_BWD
     return hipGetLastError();
 }
