@@ -57,8 +57,8 @@ def kernel_name(layer, op, plan, desc, mc):
                 for f, n_src, n_dst in ((layer.FH, layer.OH if bwd else layer.IH, layer.IH if bwd else layer.OH),
                                         (layer.FW, layer.OW if bwd else layer.IW, layer.IW if bwd else layer.OW))]
         src = layer.OC if bwd else layer.IC        # items of a block of one position: taps inside the image x 32 channels
-        waves = 16 if plan.grid <= 256 and most[0] * most[1] * -(-src // 32) >= 10 else 8
-        return "block_terms_kernel<%d, %s, %s>" % (waves, b(bwd), b(src % 32 != 0))
+        waves = 16 if plan.grid <= 256 and most[0] * most[1] * -(-src // 32) >= 10 and not (bwd and src % 4) else 8
+        return "block_terms_kernel<%d, %s, %d>" % (waves, b(bwd), 2 if src % 4 else src % 32 != 0)
     if plan.kernel == mc.KERNEL_DIRECT and plan.variant == mc.VARIANT_MFMA:
         quad = (layer.IC if op == "fwd" else layer.OC) % 4 == 0 and op != "bwd_weight"
         depth = layer.N * layer.OH * layer.OW if op == "bwd_weight" else layer.FH * layer.FW * (layer.IC if op == "fwd" else layer.OC)

@@ -16,6 +16,10 @@
 // 512 x 512 is 256 workgroups without a slice: forward 17.7 -> 15.1 us, backward-data 18.3 -> 15.3 (128 x 2x2x512, taps
 // inside the image 4 of 9), the layer's three operators 49.0 -> 41.8.
 //
+// Source channels off the grid of four: rows start at any 4 bytes (the loads need no more), and a tap's last quad is the last four channels,
+// those that it shares with the quad before zeroed on the way to LDS: no load passes the pixel's end, and the items keep 16-byte
+// loads where the tiled kernel takes elements (32 x 33x33x78 -> 80 119 us and 73 here, backward-data 96 x 14x14x94 <- 248 with stride 2 268 and 38).
+//
 // Bound by the vector instructions of the split: 64 rows and columns are split for every 32 x 32 block, 192 instructions for
 // twelve MFMAs, two cycles each (v_sub, v_and, v_add) or four (v_cvt_pk, v_lshl, v_or3) with two waves or more on a SIMD; about 0.17 us an item
 // with every CU busy.  Around the items are 2.2 us of launch and some 2.5 of row table, first loads and addition.
@@ -34,9 +38,12 @@ struct BlockItem {   // uniform: a tap of the block and the first of 32 channels
     int tap, c;
     int left;        // items of the wave from here on; none: its loads return zeros
 };
+// What a tap's last item of 32 channels holds: all of them, a number of quads, or (source channels off the grid of quads) a last quad that
+// starts at the fourth channel from the end: the channels that the quad before it has are 0 in A.
+enum { kWhole, kQuads, kChannels };
 }  // namespace
 
-template <int WAVES, bool BWD, bool RAGGED>
+template <int WAVES, bool BWD, int LAST>
 __global__ __launch_bounds__(WAVES * 64) void block_terms_kernel(const BlockParams p)
 {
     __shared__ f4 part[WAVES * 32 * 8];   // [wave][row][column / 4], the last index exchanged by row
@@ -91,6 +98,7 @@ __global__ __launch_bounds__(WAVES * 64) void block_terms_kernel(const BlockPara
     const unsigned taps = (unsigned)__builtin_amdgcn_readfirstlane((int)rowTaps[32]);
     const int col = n0 + l32, tapsAll = p.FH * p.FW;
     const int bBase = col >= p.DC ? kOutOfRange : (lh * 4 * tapsAll * p.DC + col) * 4;   // backward-data
+    const int twice = LAST == kChannels ? (4 - p.SC % 4) % 4 : 0;   // channels that a last quad has twice, at its front
 
     // ---- the items of this wave -----------------------------------------------------------------------------
     const int total = __builtin_popcount(taps) * p.chunks;
@@ -124,30 +132,55 @@ __global__ __launch_bounds__(WAVES * 64) void block_terms_kernel(const BlockPara
         const int src = j * 8 + lRow, c = n0 + src;
         aRow[j] = rowSrc[src] + lSeg * 16;
         aMask[j] = rowTaps[src];
-        bRow[j] = c >= p.DC ? kOutOfRange : c * tapsAll * p.SC * 4 + lSeg * 16;
+        bRow[j] = c >= p.DC ? kOutOfRange + 16 : c * tapsAll * p.SC * 4 + lSeg * 16;
     }
+    auto lastQuad = [&](const BlockItem &it, int quad) __attribute__((always_inline)) {   // of a tap, some of its channels there
+        const int c = it.c + quad * 4;
+        return LAST == kChannels && c < p.SC && c + 4 > p.SC;
+    };
+    unsigned keep = ~0u;   // kChannels: 0 where the loaded quads of A are a tap's last ones
     auto load = [&](const BlockItem &it, f4 (&a)[4], f4 (&b)[4]) __attribute__((always_inline)) {
         const int fh = (int)fast_div((unsigned)it.tap, p.divFW), fw = it.tap - fh * p.FW;
-        const int shift = (BWD ? -((fh >> lgY) * p.SW + (fw >> lgX)) : fh * p.SW + fw) * p.SC * 4;
+        int shift = (BWD ? -((fh >> lgY) * p.SW + (fw >> lgX)) : fh * p.SW + fw) * p.SC * 4;
+        int aC = it.c * 4, bC = (it.tap * p.SC + it.c) * 4, bShift = 0;
+        if (LAST == kChannels) {   // the lane's offset steps back, so it holds all of the address
+            const int back = lastQuad(it, lSeg) ? twice * 4 : 0;
+            keep = back ? 0u : ~0u;
+            shift += aC - back, bShift = bC - back;
+            aC = bC = 0;
+        }
         const int past = it.left > 0 ? 0 : kOutOfRange;
-        const bool drop = RAGGED && it.c + lSeg * 4 >= p.SC;   // channels past the last one
+        const bool drop = LAST != kWhole && it.c + lSeg * 4 >= p.SC;   // channels past the last one
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int aOff = (((aMask[j] >> it.tap) & 1u) && !drop ? aRow[j] + shift : kOutOfRange) | past;
-            a[j] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcA, aOff, it.c * 4, 0));
+            a[j] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcA, aOff, aC, 0));
             if (!BWD)
-                b[j] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrcB, (drop ? kOutOfRange : bRow[j]) | past,
-                                                                                    (it.tap * p.SC + it.c) * 4, 0));
+                b[j] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                   rsrcB, (drop ? kOutOfRange : bRow[j] + bShift) | past, bC, 0));
         }
         if (BWD) {   // channels past the last one lie past the tensor
             const int row = tapsAll * p.DC * 4;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < 4; ++j) {
+                int from = bBase, c = it.c + j * 8;
+                if (LAST == kChannels) {
+                    from = col >= p.DC ? kOutOfRange : from + (c - (lastQuad(it, 2 * j + lh) ? twice : 0)) * row;
+                    c = 0;
+                }
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     b[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                                            rsrcB, bBase | past, (it.c + j * 8 + e) * row + it.tap * p.DC * 4, 0));
+                                                            rsrcB, from | past, (c + e) * row + it.tap * p.DC * 4, 0));
+            }
         }
+    };
+    auto once = [&](f4 (&a)[4], unsigned there) __attribute__((always_inline)) {   // every channel of a tap in one quad only
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        if (LAST != kChannels) return;
+        const u4 mask = {twice > 0 ? there : ~0u, twice > 1 ? there : ~0u, twice > 2 ? there : ~0u, ~0u};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[j] = __builtin_bit_cast(f4, __builtin_bit_cast(u4, a[j]) & mask);
     };
     f4 *const mine = part + wave * (32 * 8);
     auto turn = [&](f4 (&a)[4]) __attribute__((always_inline)) {   // rows as loaded -> quads of this lane's row or column
@@ -184,6 +217,7 @@ __global__ __launch_bounds__(WAVES * 64) void block_terms_kernel(const BlockPara
         load(it, a, b);
         for (int i = 0; i < count; ++i) {
             next(it);
+            once(a, keep);
             turn(a);
             if (!BWD) turn(b);
             f4 ta[4], tb[4];
@@ -233,8 +267,16 @@ __global__ __launch_bounds__(WAVES * 64) void block_terms_kernel(const BlockPara
         for (int i = 0; i < count; ++i) {
             f4 a[4], b[4];
             load(it, a, b);
+            once(a, keep);   // and the filter's, which may hold infinities
+            if (!BWD) once(b, keep);
             turn(a);
             if (!BWD) turn(b);
+            if (BWD && LAST == kChannels)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int e = 0; e < 3; ++e)
+                        if (lastQuad(it, 2 * j + lh) && e < twice) b[j][e] = 0.f;
             float16v one = {};
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -250,10 +292,11 @@ __global__ __launch_bounds__(WAVES * 64) void block_terms_kernel(const BlockPara
     }
 
     const int pixel = rowPixel[r];
-    if (pixel < 0 || n0 + c >= p.DC) return;   // DC is a multiple of 4
+    if (pixel < 0) return;
     float *to = p.C + (long long)pixel * p.DC + n0 + c;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
+        if (n0 + c + e >= p.DC) return;
         if (p.epilogue) {
             const float v = out[e] + (p.bias ? p.bias[n0 + c + e] : 0.f);
             out[e] = v > 0.f ? v : v * p.slope;
@@ -265,17 +308,19 @@ __global__ __launch_bounds__(WAVES * 64) void block_terms_kernel(const BlockPara
 template <int WAVES>
 static void launch_block_waves(const BlockParams &p, bool bwdData, int grid, hipStream_t st)
 {
-    const bool ragged = p.SC % 32 != 0;
+    const int last = p.SC % 32 == 0 ? kWhole : p.SC % 4 == 0 ? kQuads : kChannels;
     const dim3 g((unsigned)grid), b(WAVES * 64);
-    if (bwdData && ragged) hipLaunchKernelGGL((block_terms_kernel<WAVES, true, true>), g, b, 0, st, p);
-    else if (bwdData) hipLaunchKernelGGL((block_terms_kernel<WAVES, true, false>), g, b, 0, st, p);
-    else if (ragged) hipLaunchKernelGGL((block_terms_kernel<WAVES, false, true>), g, b, 0, st, p);
-    else hipLaunchKernelGGL((block_terms_kernel<WAVES, false, false>), g, b, 0, st, p);
+    if (bwdData && last == kChannels) hipLaunchKernelGGL((block_terms_kernel<8, true, kChannels>), g, dim3(8 * 64), 0, st, p);   // 16 waves spill
+    else if (bwdData && last == kQuads) hipLaunchKernelGGL((block_terms_kernel<WAVES, true, kQuads>), g, b, 0, st, p);
+    else if (bwdData) hipLaunchKernelGGL((block_terms_kernel<WAVES, true, kWhole>), g, b, 0, st, p);
+    else if (last == kChannels) hipLaunchKernelGGL((block_terms_kernel<WAVES, false, kChannels>), g, b, 0, st, p);
+    else if (last == kQuads) hipLaunchKernelGGL((block_terms_kernel<WAVES, false, kQuads>), g, b, 0, st, p);
+    else hipLaunchKernelGGL((block_terms_kernel<WAVES, false, kWhole>), g, b, 0, st, p);
 }
 
 hipError_t launch_block_terms(const BlockParams &p, bool bwdData, int grid, hipStream_t st)
 {
-    if (p.SC % 4 != 0 || p.DC % 4 != 0 || p.FH * p.FW > 32 || grid != ((p.M + 31) / 32) * ((p.DC + 31) / 32) ||
+    if (p.SC < 4 || p.FH * p.FW > 32 || grid != ((p.M + 31) / 32) * ((p.DC + 31) / 32) ||
         (bwdData && (p.sh > 2 || p.sw > 2)))
         return hipErrorInvalidValue;
     if (p.waves == 16) launch_block_waves<16>(p, bwdData, grid, st);
