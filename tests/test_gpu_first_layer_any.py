@@ -40,6 +40,15 @@ def test_any_quads(case):
     gu.check_all_ops(desc(case), *inputs(desc(case), 41), ops=("bwd_data",), label=str(case), twice=True)
 
 
+@pytest.mark.parametrize("shape", [(18, 16, 16, 3, 36, 3, 1), (4, 32, 32, 3, 44, 3, 1), (160, 7, 7, 3, 36, 3, 0)])
+def test_former_short_calls_need_no_workspace(shape):
+    n, h, w, ic, oc, f, pad = shape
+    d = mc.make_desc(n, h, w, ic, oc, f, f, 1, pad)
+    p = mc.conv2d_query_plan(mc.OP_BWD_DATA, d)
+    assert (p.tile_m, p.split) == (128, 1) and mc.conv2d_workspace_bytes(mc.OP_BWD_DATA, d) == 0
+    gu.check_all_ops(d, *inputs(d, 43), ops=("bwd_data",), label=str(shape))
+
+
 @pytest.mark.parametrize("kind", ["1e-37", "1e-42", "hidden", "2^-133"])
 def test_small_operand_with_a_large_partner(kind):
     """Operands that three bf16 terms do not hold (see test_gpu_products), in either operand, at the parity tests' bar."""
