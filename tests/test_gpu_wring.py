@@ -11,16 +11,16 @@ pytestmark = pytest.mark.gpu
 
 # N, IH, IW, IC, OC, F, slices, workgroups of a slice
 CASES = [
-    (3, 12, 27, 412, 148, 3, 5, 49),     # three blocks of output channels: workgroups of one and of two; 28 and 20 channels in the last ones
-    (3, 13, 13, 452, 272, 3, 2, 96),     # maps whose pixels are no multiple of a stage; the last pair of the last workgroup idle
-    (200, 6, 6, 176, 44, 3, 36, 7),      # one block of output channels: units run on through the input channels
-    (200, 3, 3, 320, 48, 5, 8, 32),      # maps of fewer pixels than a stage, filters wider than the map
-    (34, 7, 7, 380, 36, 5, 6, 38),
+    (3, 12, 27, 412, 148, 3, 4, 49),     # three blocks of output channels: workgroups of one and of two; 28 and 20 channels in the last ones
+    (5, 15, 15, 452, 336, 3, 2, 112),     # maps whose pixels are no multiple of a stage; the last pair of the last workgroup idle
+    (200, 6, 6, 176, 44, 3, 30, 7),      # one block of output channels: units run on through the input channels
+    (200, 3, 3, 320, 48, 5, 6, 32),      # maps of fewer pixels than a stage, filters wider than the map
+    (34, 7, 7, 380, 36, 5, 5, 38),
     (3, 37, 41, 300, 48, 3, 17, 15),     # the long ring
-    (3, 42, 24, 188, 52, 5, 12, 21),
+    (3, 42, 24, 188, 52, 5, 10, 21),
     (1, 24, 24, 360, 100, 5, 3, 78),     # one image: the last stage of the last slice ends with the tensor
     (3, 6, 60, 136, 404, 3, 5, 48),
-    (1, 31, 31, 280, 80, 5, 3, 65),
+    (1, 29, 25, 344, 72, 5, 3, 78),
     (128, 8, 8, 256, 256, 3, 7, 36),     # a layer in earnest
 ]
 
