@@ -107,8 +107,9 @@ enum {
 enum {
     MI355CONV_KERNEL_DIRECT = 0,       /* kernels for any shape: one thread per element (variant DIRECT), one
                                           32 x 32 block per workgroup (variant MFMA: short calls, fp32 products; small
-                                          results with longer sums, three-term products), and first-layer
-                                          backward-data with channel counts off the 32-grid         */
+                                          results with longer sums and channel counts off the grid of four,
+                                          three-term products), and first-layer backward-data with channel
+                                          counts off the 32-grid                                    */
     MI355CONV_KERNEL_GATHER = 1,       /* gather-GEMM, 16-byte loads along the channel axis     */
     MI355CONV_KERNEL_GATHER_ELEM = 2,  /* gather-GEMM, element-wise loads (any channel count)   */
     MI355CONV_KERNEL_FIRST_LAYER = 3,  /* the kernels for at most 32 patch columns / 4 channels */
